@@ -28,7 +28,9 @@ FLAGS = [
 # per-file extras: the quantizer's code decisions are individually rounded binary32 operations
 # quantize.hip: no contraction (its operations are separately rounded by definition); inputs are finite by contract, so
 # the packed fp16 min / max need no NaN canonicalisation (-fno-honor-nans drops one instruction of three there)
-EXTRA = {"quantize.hip": ["-ffp-contract=off", "-fno-honor-nans"], "pt.hip": ["-ffp-contract=off"]}
+EXTRA = {"quantize.hip": ["-ffp-contract=off", "-fno-honor-nans"], "pt.hip": ["-ffp-contract=off"],
+         # finite inputs by contract: the running maximum needs no NaN canonicalisation (an instruction per score)
+         "prefill_attn.hip": ["-fno-honor-nans"]}
 
 
 def hipcc():

@@ -189,7 +189,7 @@ int minikv_decode_step(const minikv_shape *s, const minikv_f16 *q, const minikv_
 size_t selective_flash_attn_workspace_bytes(int32_t B, int32_t Hkv, int64_t L)
 {
     if (B <= 0 || Hkv <= 0 || L < 1) return 0;
-    return (size_t)B * Hkv * kD * (size_t)((L + 63) / 64 * 64) * sizeof(minikv_f16);     // V transposed, keys padded to 64
+    return (size_t)B * Hkv * kD * (size_t)((L + 63) / 64 * 64) * sizeof(minikv_f16);     // reserved: the kernels use none of it
 }
 
 int selective_flash_attn(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f16 *Q, const minikv_f16 *K,
@@ -203,7 +203,7 @@ int selective_flash_attn(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const mi
     if (!(sm_scale > 0.0f) || sm_scale - sm_scale != 0.0f) return MINIKV_EINVAL;       // positive and finite
     if ((int64_t)B * Hq * ((L + 127) / 128) > 0x7fffffff || (int64_t)B * Hkv > 65535) return MINIKV_EINVAL;
     if (workspace_bytes < selective_flash_attn_workspace_bytes(B, Hkv, L)) return MINIKV_EWORKSPACE;
-    return launch_prefill(B, Hq, Hkv, L, Q, K, V, sm_scale, X_O, lse, A_cumul, workspace, (hipStream_t)stream);
+    return launch_prefill(B, Hq, Hkv, L, Q, K, V, sm_scale, X_O, lse, A_cumul, (hipStream_t)stream);
 }
 
 size_t kv_select_workspace_bytes(int32_t units, int32_t rep, int64_t L)

@@ -71,6 +71,40 @@ def test_random_shapes(g):
         check(g, int(rng.integers(1, 3)), Hkv * rep, Hkv, L, seed=300 + case, gain=float(rng.choice([0.5, 1.0, 1.7])))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(64, 16, 4, 1), (64, 16, 4, 65), (32, 16, 16, 257), (32, 16, 2, 320), (32, 16, 4, 447)])
+def test_launches_with_256_queries_per_workgroup(g, B, Hq, Hkv, L):
+    """Launches of at least 1024 blocks of 256 queries: tile and block edges; the oracle recomputes the first and the
+    last sequence."""
+    from oracle import ref
+    assert B * Hq * ((L + 255) // 256) >= 1024
+    sm = 1.0 / math.sqrt(128)
+    Q, K, V = W.make_prefill_inputs(B, Hq, Hkv, L, 900 + L, device="cuda")
+    xo, lse, acc = run_gpu(Q, K, V, sm)
+    assert torch.isfinite(xo).all() and torch.isfinite(lse).all()
+    assert torch.allclose(acc.double().sum(-1), torch.full((B, Hq), float(L), dtype=torch.float64, device="cuda"), rtol=1e-4)
+    sel = [0, B - 1]
+    _, xo64, lse64, acc64 = ref.selective_flash_attn(g.to_np(Q[sel]), g.to_np(K[sel]), g.to_np(V[sel]), sm)
+    assert np.max(np.abs(g.to_np(xo[sel]).astype(np.float64) - xo64)) <= TOL_O
+    assert np.max(np.abs(g.to_np(lse[sel]).astype(np.float64) - lse64)) <= TOL_LSE
+    assert np.all(np.abs(g.to_np(acc[sel]) - acc64) <= RTOL_A * np.abs(acc64) + ATOL_A)
+
+
+@pytest.mark.parametrize("per_tile", [-3.0, 0.02, 0.7, 3.0, 30.0])
+def test_scores_that_rise_or_fall_along_the_keys(g, per_tile):
+    """The reference of the softmax weights lags behind the running maximum by a bounded amount: scores whose level moves
+    by `per_tile` (in powers of e) every 64 keys, so that it never, seldom or always follows."""
+    from oracle import ref
+    B, Hq, Hkv, L = 1, 4, 2, 700
+    Q, K, V = W.make_prefill_inputs(B, Hq, Hkv, L, 41, device="cuda", gain=0.3)
+    Q[..., 0] = 8.0
+    K[..., 0] = (torch.arange(L, device="cuda") * (per_tile / 64.0 / 8.0 * math.sqrt(128))).to(torch.float16)
+    xo, lse, acc = run_gpu(Q, K, V, 1.0 / math.sqrt(128))
+    _, xo64, lse64, acc64 = ref.selective_flash_attn(g.to_np(Q), g.to_np(K), g.to_np(V), 1.0 / math.sqrt(128))
+    assert np.max(np.abs(g.to_np(xo).astype(np.float64) - xo64)) <= TOL_O
+    assert np.max(np.abs(g.to_np(lse).astype(np.float64) - lse64)) <= TOL_LSE
+    assert np.all(np.abs(g.to_np(acc) - acc64) <= RTOL_A * np.abs(acc64) + ATOL_A)
+
+
 def test_first_pass_alone(g):
     from oracle import ref
     Q, K, V = W.make_prefill_inputs(1, 2, 1, 200, 5, device="cuda")
