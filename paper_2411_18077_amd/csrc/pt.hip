@@ -15,7 +15,7 @@
 namespace minikv {
 
 constexpr int kPtBlockTok = 64;      // tokens one workgroup of the quantizer takes
-constexpr int kPtSB = 256;           // tokens per inner block of the decode kernel (= threads)
+constexpr int kPtMinChunk = 256;     // least tokens of a decode workgroup
 constexpr int kPtMaxRep = 8;
 
 struct PtQuantArgs {
@@ -154,304 +154,312 @@ struct PtDecArgs {
     const uint16_t *Ks, *Kz, *Vs, *Vz;
     const int32_t *q_len;
     uint16_t *out;
-    float *ws;                    // partials [B*Hq][nchunk][kPartialStride]: m, l, 2 pad, o[128]
+    float *ws;                    // partials (nchunk > 1) [B*Hq][nchunk][kPartialStride]: m, l, 2 pad, o[128]
     float c1;                     // sm_scale * log2(e)
     int Hq, Hkv, rep, Tcap, chunk, nchunk;
 };
 
-__device__ inline float pt_wave_max(float v)
-{
-    for (int o = 32; o; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ inline float pt_wave_sum(float v)
-{
-    for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-// A 16-bit half of a packed word holds NF = 16 / BITS codes.  A code field that lies inside bits 0..9 of its
-// half is, masked in place, an fp16 SUBNORMAL: code * 2^(BITS*pos) * 2^-24 -- so one v_and_b32 "converts" two
-// codes (one per half) and one v_dot2_f32_f16 multiplies them with two fp16 operands and adds both products
-// in binary32 (fp16 subnormals are honoured by that instruction).  Fields at positions 0 .. PMAX-1 are taken
-// from the word as it is, the others from the word shifted right by SH2 bits, which brings them to positions
-// NF-PMAX .. PMAX-1 ... of a field j: pt_field_pos().  Sums are kept per position and scaled once at the end.
+// A 16-bit half of a packed word holds NF = 16 / BITS codes.  A code field inside bits 0..9 of its half is, masked in
+// place, an fp16 SUBNORMAL, code * 2^(bit - 24), so one v_and_b32 "converts" two codes, one per half, and the matrix
+// instructions multiply them as they are.  The lower fields are taken from the word shifted left by 2, the upper ones
+// from the word shifted right by 6: both land at bits 2 + BITS*p, p = 0 .. P-1, the highest places that two shifts
+// reach.  The place matters: a matrix instruction aligns its sum by the exponent field, 2^-14 for a subnormal, and cuts
+// what is 24 bits below, so that next to a weight of 1 a code at bit 0 loses the weight's bits below 2^-14, always
+// downwards (1.7e-4 of the result on 6592 tokens of 2 bits; at bit 2 a quarter of that).
+typedef _Float16 pt_half8 __attribute__((ext_vector_type(8)));
+typedef float pt_float4 __attribute__((ext_vector_type(4)));
 template <int BITS> struct PtFields {
-    static constexpr int NF = 16 / BITS;                 // fields per half-word
-    static constexpr int PMAX = 10 / BITS;               // positions whose field fits into the fp16 mantissa
-    static constexpr int SH2 = BITS * (NF - PMAX);       // shift that brings the upper fields down
-    static constexpr uint32_t M0 = ((1u << BITS) - 1u) * 0x00010001u;
-    static_assert(NF <= 2 * PMAX, "two looks at a word reach every field");
-    __device__ static constexpr int pos(int j) { return j < PMAX ? j : j - (NF - PMAX); }
-    // 2^(24 - BITS*pos): what a sum over position pos is multiplied by
-    __device__ static constexpr float unscale(int p) { return 16777216.0f / (float)(1u << (BITS * p)); }
+    static constexpr int CPW = 32 / BITS, NF = 16 / BITS, P = NF / 2;
+    // 2^(22 - BITS*p): what a sum over place p is multiplied by
+    __device__ static constexpr float unscale(int p) { return 4194304.0f / (float)(1u << (BITS * p)); }
+    // operand of place p from two words: codes p, NF+p, P+p, NF+P+p of each, in this order
+    __device__ static pt_half8 operand(uint32_t w0, uint32_t w1, int p)
+    {
+        const uint32_t m = ((((1u << BITS) - 1u) << 2) * 0x00010001u) << (BITS * p);
+        return __builtin_bit_cast(pt_half8, make_uint4((w0 << 2) & m, (w0 >> 6) & m, (w1 << 2) & m, (w1 >> 6) & m));
+    }
+    // code index (0 .. CPW-1) of half i (0..3) of a word's share of the operand
+    __device__ static constexpr int code_at(int p, int i) { return p + (i & 1) * NF + (i >> 1) * P; }
 };
-typedef _Float16 pt_h2 __attribute__((ext_vector_type(2)));
 
-// One workgroup = one (unit, chunk of tokens), all query heads of the unit.  Per inner block of 256 tokens:
-// score phase, one token per thread -- sum_c q_c * (code * Ks + Kz) = sum_g Ks_g * (sum_{c in g} q_c code_c)
-// + Kz_g * (sum_{c in g} q_c), so the codes meet the query before any scale does; the query sits in LDS as
-// the fp16 pairs (channel c0 + j, channel c0 + NF + j) that the two halves of a word's field j hold --;
-// block-wide online softmax; value phase, one channel per thread, the weights times the token's V scale in LDS
-// as fp16 pairs (token t0 + j, token t0 + NF + j) in the same way; the zero-point term kept per token thread
-// and reduced once at the end.
+// One workgroup = one (unit, chunk of tokens), all query heads of the unit; its four waves take blocks of TB tokens in
+// turn, each with an online softmax of its own, and meet once at the end.  Both products run on 16x16x32 matrix
+// instructions: scores with 16 tokens as rows and the query heads as columns, outputs with 16 channels as rows, the
+// heads as columns and the tokens in between.  The order of the tokens inside a block is chosen so that the lane that
+// gets a score is the lane that needs its weight as an operand, and the order of channels so that codes are loaded
+// 128 bits at a time.  Column n of a score product holds head n % REPT and, where a token has several channel groups,
+// only group (n / REPT) % NG of it (the query is zero elsewhere), so that every group meets its own scale; the groups
+// are added across lanes afterwards.
+// What bounds it: memory (136 bytes per token at 4 bits with one group); a form with one dot2 per pair of codes and
+// head was bound by its vector instructions.  128 units x 13088 tokens, 4 heads each, G = 128: 4 bits 79 -> 45 us
+// (5.1 TB/s; a plain copy reaches 5.0), 2 bits 81 -> 50, 8 bits 109 -> 81; 32 units x 8 heads x 8192 tokens 41 -> 16 us.
 template <int BITS, int G, int REPT>
 __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
 {
     typedef PtFields<BITS> F;
-    constexpr int CPW = 32 / BITS, NG = kD / G, W = kD / CPW, NF = F::NF, NP = F::PMAX;
-    constexpr int NPAIR = kPtSB / 2;                                     // weight pairs of a block
-    __shared__ float qsum[REPT][NG];                                     // sums of q over the channel groups
-    __shared__ __attribute__((aligned(16))) pt_h2 qp[kD / 2][REPT];      // query pairs, by (word, field)
-    __shared__ __attribute__((aligned(16))) pt_h2 wp[NG][NPAIR][REPT];   // weight * V scale pairs, by (word, field)
-    __shared__ float red[4][REPT];
-    __shared__ float comb[REPT][kD];
-    __shared__ float zsum[REPT][NG];
+    constexpr int CPW = F::CPW, P = F::P, NG = kD / G, W = kD / CPW;
+    constexpr int KW = W / 4;                            // key words of one lane and token: 32 channels
+    constexpr int TB = 8 * CPW, NT = TB / 16;            // tokens of a block, score tiles of a block
+    constexpr int NS = NG * REPT > 16 ? 2 : 1;           // column sets of a score product
+    constexpr int NB = NG == 1 ? 1 : 2;                  // weight operands: the channel halves may differ in scale
+    constexpr int E = TB * NG / 64 ? TB * NG / 64 : 1;   // scales of a block and array that one lane loads
+    __shared__ __align__(16) _Float16 meta[4][4][NG][TB];                  // wave; Ks, Kz, Vs, Vz; group; token
+    __shared__ float part_o[4][REPT][kD], part_m[4][REPT], part_l[4][REPT], zsum[4][NG][REPT];
 
-    const int u = blockIdx.y, ch = blockIdx.x, tid = threadIdx.x, rep = a.rep;
+    const int u = blockIdx.y, ch = blockIdx.x, tid = threadIdx.x, lane = tid & 63, rep = a.rep;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, kg = lane >> 4, h = col % REPT;
     const int b = u / a.Hkv, kvh = u % a.Hkv;
     const int bq0 = b * a.Hq + kvh * rep;
     const int T = min(max(a.q_len[u], 0), a.Tcap);
     const int t_begin = ch * a.chunk, t_end = min(T, t_begin + a.chunk);
-    if (t_begin >= t_end) return;                       // the merge kernel skips this slot
-
-    // heads beyond rep read the unit's last head and are never written out
-    for (int i = tid; i < (kD / 2) * REPT; i += 256) {
-        const int h = i % REPT, pi = i / REPT, w = pi / NF, j = pi % NF;
-        const uint16_t *qr = a.q + (size_t)(bq0 + min(h, rep - 1)) * kD + w * CPW + j;
-        pt_h2 v;
-        v[0] = __builtin_bit_cast(_Float16, qr[0]);
-        v[1] = __builtin_bit_cast(_Float16, qr[NF]);
-        qp[pi][h] = v;
-    }
-    if (tid < REPT * NG) {
-        const int h = tid / NG, g = tid % NG;
-        float s = 0.f;
-        for (int c = 0; c < G; c++) s += pt_h2f(a.q[(size_t)(bq0 + min(h, rep - 1)) * kD + g * G + c]);
-        qsum[h][g] = s;
-    }
-    __syncthreads();
+    if (t_begin >= t_end && a.nchunk > 1) return;       // the merge kernel skips this slot
 
     const uint32_t *Kc = a.Kc + (size_t)u * a.Tcap * W;
     const uint32_t *Vc = a.Vc + (size_t)u * (size_t)(a.Tcap / CPW) * kD;
-    const uint16_t *Ks = a.Ks + (size_t)u * a.Tcap * NG, *Kz = a.Kz + (size_t)u * a.Tcap * NG;
-    const uint16_t *Vs = a.Vs + (size_t)u * a.Tcap * NG, *Vz = a.Vz + (size_t)u * a.Tcap * NG;
+    const uint16_t *mt[4] = {a.Ks + (size_t)u * a.Tcap * NG, a.Kz + (size_t)u * a.Tcap * NG,
+                             a.Vs + (size_t)u * a.Tcap * NG, a.Vz + (size_t)u * a.Tcap * NG};
 
-    float m[REPT], l[REPT], o[REPT], pz[REPT][NG];
+    // requests of a block, made one block ahead (addresses stay inside the buffers; what lies past t_end is masked)
+    uint32_t kw[NT][KW];
+    uint4 vw[2][2];                                     // [half of the channels][s]: words of tokens CPW (kg + 4 s) ..
+    uint16_t mr[4][E];
+    auto request = [&](int t0) {
 #pragma unroll
-    for (int h = 0; h < REPT; h++) {
-        m[h] = -1e30f; l[h] = 0.f; o[h] = 0.f;
+        for (int tau = 0; tau < NT; tau++) {
+            const int s = tau / (CPW / 4), q4 = tau % (CPW / 4);
+            const int t = min(t0 + CPW * (col >> 2) + 4 * CPW * s + 4 * q4 + (col & 3), a.Tcap - 1);
+            const uint32_t *src = Kc + (size_t)t * W + kg * KW;
+            if constexpr (KW == 2) {
+                const uint2 v = *reinterpret_cast<const uint2 *>(src);
+                kw[tau][0] = v.x, kw[tau][1] = v.y;
+            } else {
 #pragma unroll
-        for (int g = 0; g < NG; g++) pz[h][g] = 0.f;
-    }
-    const int c = tid & (kD - 1), half = tid >> 7, cg = c / G;
-    // where this thread's token puts its weight: pair (tid / CPW) * NF + (tid % CPW) % NF, component (tid % CPW) / NF
-    const int my_pair = (tid / CPW) * NF + (tid % CPW) % NF, my_comp = (tid % CPW) / NF;
-
-    // The words of a block are requested well before they are used: the key words, scales and zero-points
-    // of the NEXT block right after the score phase has consumed this block's, the value words of this
-    // block before its score phase.  (A load that waits for its predecessor's data costs a full memory
-    // round trip; sixteen of those per block is what bounds a version without this.)
-    constexpr int NVW = 128 / CPW;                      // value words of one thread and block
-    uint4 kq[W / 4];
-    uint16_t ksr[NG], kzr[NG], vsr[NG], vzr[NG];
-    auto request_k = [&](int ts_) {
-        const int tc_ = min(ts_ + tid, t_end - 1);
-        const uint4 *kw4 = reinterpret_cast<const uint4 *>(Kc + (size_t)tc_ * W);
-#pragma unroll
-        for (int i = 0; i < W / 4; i++) kq[i] = kw4[i];
-#pragma unroll
-        for (int g = 0; g < NG; g++) {
-            ksr[g] = Ks[(size_t)tc_ * NG + g]; kzr[g] = Kz[(size_t)tc_ * NG + g];
-            vsr[g] = Vs[(size_t)tc_ * NG + g]; vzr[g] = Vz[(size_t)tc_ * NG + g];
+                for (int i = 0; i < KW / 4; i++) {
+                    const uint4 v = reinterpret_cast<const uint4 *>(src)[i];
+                    kw[tau][4 * i] = v.x, kw[tau][4 * i + 1] = v.y, kw[tau][4 * i + 2] = v.z, kw[tau][4 * i + 3] = v.w;
+                }
+            }
         }
-    };
-    request_k(t_begin);
-    const int vrow_last = a.Tcap / CPW - 1;
-
-    // sums over the field positions, each with its power of two
-    auto fold = [&](const float (&acc)[NP]) -> float {
-        float r = 0.f;
 #pragma unroll
-        for (int p = 0; p < NP; p++) r = __builtin_fmaf(acc[p], F::unscale(p), r);
-        return r;
+        for (int s = 0; s < 2; s++) {
+            const int row = min(t0 / CPW + kg + 4 * s, a.Tcap / CPW - 1);
+#pragma unroll
+            for (int half = 0; half < 2; half++)
+                vw[half][s] = *reinterpret_cast<const uint4 *>(Vc + (size_t)row * kD + half * 64 + col * 4);
+        }
+        const int e0 = min(t0 * NG + lane * E, a.Tcap * NG - E);
+#pragma unroll
+        for (int k = 0; k < 4; k++) __builtin_memcpy(mr[k], __builtin_assume_aligned(mt[k] + e0, 2 * E), 2 * E);
     };
 
-    for (int ts = t_begin; ts < t_end; ts += kPtSB) {
-        const bool valid = ts + tid < t_end;
-        // (an index the compiler cannot see through: without it the reads of the query pairs, which no iteration
-        // changes, are all moved in front of the loop and held in 64 x REPT registers)
-        int iter0 = 0;
-        asm volatile("" : "+v"(iter0));
-        uint32_t vw[NVW];                               // rows past the cache's end repeat its last row: their weights are 0
+    const int t_first = t_begin + wave * TB;
+    if (t_first < t_end) request(t_first);
+
+    // the query as operand: [column set][pair of words][position]; heads beyond rep repeat the last one, unused
+    pt_half8 qb[NS][KW / 2][P];
+    float qz[NS];                                       // sum of the query over the column's group
+    {
+        const _Float16 *qr = reinterpret_cast<const _Float16 *>(a.q) + (size_t)(bq0 + min(h, rep - 1)) * kD + kg * 32;
+        pt_half8 qv[4];
 #pragma unroll
-        for (int i = 0; i < NVW; i++) vw[i] = Vc[(size_t)min((ts + half * 128) / CPW + i, vrow_last) * kD + c];
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- scores of token ts + tid
-        float s[REPT];
+        for (int i = 0; i < 4; i++) qv[i] = reinterpret_cast<const pt_half8 *>(qr)[i];
+        float sum = 0.f;
 #pragma unroll
-        for (int h = 0; h < REPT; h++) s[h] = 0.f;
-        float vs[NG], vz[NG];
-        {
-            // the query pairs of one word at a time (scheduling barriers keep it so: left alone, the compiler
-            // requests all 64 x REPT pairs at once and spills); the other waves of the SIMD cover the LDS latency
-            // The query pairs of word wi + 1 are read from LDS while the products of word wi run.  Left alone, the
-            // compiler requests the pairs of all 64 words first and spills what comes back (scheduling barriers and
-            // plain memory barriers do not stop it: the products have no side effects and sink below them); so each
-            // word ends with empty asm statements that take its sums as operands AND clobber memory: the next
-            // reads cannot pass them, and they cannot pass the products.
-            pt_h2 qa[NF][REPT], qb[NF][REPT];
-            auto read_q = [&](pt_h2 (&dst)[NF][REPT], int wi) {
+        for (int c = 0; c < 32; c++) sum += (float)qv[c >> 3][c & 7];
 #pragma unroll
-                for (int j = 0; j < NF; j++)
+        for (int ns = 0; ns < NS; ns++) {
+            const bool mine = kg * 32 / G == ((ns * 16 + col) / REPT) % NG;
 #pragma unroll
-                    for (int h = 0; h < REPT; h++) dst[j][h] = qp[iter0 + wi * NF + j][h];
-            };
-            read_q(qa, 0);
-            float dot[REPT][NP];
+            for (int wp = 0; wp < KW / 2; wp++)
 #pragma unroll
-            for (int wi = 0; wi < W; wi++) {
-                constexpr int WG_ = G / CPW;                                   // words of one channel group
-                const int g = wi / WG_;
-                if (wi % WG_ == 0) {
+                for (int p = 0; p < P; p++)
 #pragma unroll
-                    for (int h = 0; h < REPT; h++)
-#pragma unroll
-                        for (int p = 0; p < NP; p++) dot[h][p] = 0.f;
-                }
-                if (wi + 1 < W) read_q(qb, wi + 1);
-                const uint4 q4 = kq[wi / 4];
-                const uint32_t word = (wi & 3) == 0 ? q4.x : (wi & 3) == 1 ? q4.y : (wi & 3) == 2 ? q4.z : q4.w;
-                const uint32_t upper = word >> F::SH2;
-#pragma unroll
-                for (int j = 0; j < NF; j++) {
-                    const int p = F::pos(j);
-                    const uint32_t fld = (j < F::PMAX ? word : upper) & (F::M0 << (BITS * p));
-                    const pt_h2 kk = __builtin_bit_cast(pt_h2, fld);
-#pragma unroll
-                    for (int h = 0; h < REPT; h++) dot[h][p] = __builtin_amdgcn_fdot2(kk, qa[j][h], dot[h][p], false);
-                }
-#pragma unroll
-                for (int h = 0; h < REPT; h++)
-#pragma unroll
-                    for (int p = 0; p < NP; p++) asm volatile("" : "+v"(dot[h][p])::"memory");
-                if (wi % WG_ == WG_ - 1) {                                     // the group's last word: its scale and zero-point
-                    const float ks = pt_h2f(ksr[g]), kz = pt_h2f(kzr[g]);
-                    vs[g] = pt_h2f(vsr[g]); vz[g] = pt_h2f(vzr[g]);
-#pragma unroll
-                    for (int h = 0; h < REPT; h++) s[h] += ks * fold(dot[h]) + kz * qsum[h][g];
-                }
-#pragma unroll
-                for (int j = 0; j < NF; j++)
-#pragma unroll
-                    for (int h = 0; h < REPT; h++) qa[j][h] = qb[j][h];
-            }
+                    for (int i = 0; i < 8; i++) {
+                        const int c = (2 * wp + (i >> 2)) * CPW + F::code_at(p, i & 3);
+                        qb[ns][wp][p][i] = mine ? qv[c >> 3][c & 7] : (_Float16)0;
+                    }
+            qz[ns] = mine ? sum : 0.f;
+            qz[ns] += __shfl_xor(qz[ns], 16);
+            qz[ns] += __shfl_xor(qz[ns], 32);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if (ts + kPtSB < t_end) request_k(ts + kPtSB);
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- block max, weights, block sum
-#pragma unroll
-        for (int h = 0; h < REPT; h++) {
-            s[h] = valid ? s[h] * a.c1 : -INFINITY;       // base-2 domain
-            const float wm = pt_wave_max(s[h]);
-            if ((tid & 63) == 0) red[tid >> 6][h] = wm;
-        }
-        __syncthreads();
-        float scale[REPT], p[REPT];
-#pragma unroll
-        for (int h = 0; h < REPT; h++) {
-            const float bm = fmaxf(fmaxf(red[0][h], red[1][h]), fmaxf(red[2][h], red[3][h]));
-            const float mn = fmaxf(m[h], bm);
-            scale[h] = exp2f(m[h] - mn);
-            m[h] = mn;
-            p[h] = exp2f(s[h] - mn);                    // exp2(-inf) = 0 for the masked tail
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < REPT; h++) {
-            // (the value phase sees p * Vs rounded to fp16; the sum of weights keeps the binary32 p)
-            const float ws = pt_wave_sum(p[h]);
-            if ((tid & 63) == 0) red[tid >> 6][h] = ws;
-#pragma unroll
-            for (int g = 0; g < NG; g++) {
-                reinterpret_cast<_Float16 *>(&wp[g][my_pair][h])[my_comp] = (_Float16)(p[h] * vs[g]);
-                pz[h][g] = pz[h][g] * scale[h] + p[h] * vz[g];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < REPT; h++) {
-            l[h] = l[h] * scale[h] + (red[0][h] + red[1][h] + red[2][h] + red[3][h]);
-            o[h] *= scale[h];
-        }
-        // ---- weighted values: thread (c, half) takes tokens [half*128, half*128 + 128) of the block
-        float oacc[REPT][NP];
-#pragma unroll
-        for (int h = 0; h < REPT; h++)
-#pragma unroll
-            for (int pp = 0; pp < NP; pp++) oacc[h][pp] = 0.f;
-        {
-            pt_h2 wa[NF][REPT], wb[NF][REPT];                                   // weight pairs of word i, word i + 1
-            auto read_w = [&](pt_h2 (&dst)[NF][REPT], int i) {
-#pragma unroll
-                for (int j = 0; j < NF; j++)
-#pragma unroll
-                    for (int h = 0; h < REPT; h++) dst[j][h] = wp[cg][iter0 + ((half * 128) / CPW + i) * NF + j][h];
-            };
-            read_w(wa, 0);
-#pragma unroll
-            for (int i = 0; i < NVW; i++) {
-                // (words past the block's last token meet weights that are 0: no branch)
-                if (i + 1 < NVW) read_w(wb, i + 1);
-                const uint32_t word = vw[i], upper = word >> F::SH2;
-#pragma unroll
-                for (int j = 0; j < NF; j++) {
-                    const int pp = F::pos(j);
-                    const uint32_t fld = (j < F::PMAX ? word : upper) & (F::M0 << (BITS * pp));
-                    const pt_h2 vv = __builtin_bit_cast(pt_h2, fld);
-#pragma unroll
-                    for (int h = 0; h < REPT; h++) oacc[h][pp] = __builtin_amdgcn_fdot2(vv, wa[j][h], oacc[h][pp], false);
-                }
-#pragma unroll
-                for (int h = 0; h < REPT; h++)
-#pragma unroll
-                    for (int pp = 0; pp < NP; pp++) asm volatile("" : "+v"(oacc[h][pp])::"memory");
-#pragma unroll
-                for (int j = 0; j < NF; j++)
-#pragma unroll
-                    for (int h = 0; h < REPT; h++) wa[j][h] = wb[j][h];
-            }
-        }
-#pragma unroll
-        for (int h = 0; h < REPT; h++) o[h] += fold(oacc[h]);
-        __syncthreads();
     }
 
-    // ---- zero-point term: sum over the token threads, per (head, channel group)
-    if (tid < REPT * NG) zsum[tid / NG][tid % NG] = 0.f;
-    __syncthreads();
+    float m = -1e30f, l = 0.f, pz[NS];
+    pt_float4 o[2][4];                                  // o[half][i][j]: channel 64 half + 4 (4 kg + j) + i of head h
 #pragma unroll
-    for (int h = 0; h < REPT; h++) {
+    for (int ns = 0; ns < NS; ns++) pz[ns] = 0.f;
 #pragma unroll
-        for (int g = 0; g < NG; g++) {
-            const float wsum = pt_wave_sum(pz[h][g]);
-            if ((tid & 63) == 0) atomicAdd(&zsum[h][g], wsum);
-        }
-    }
-    if (half == 1) {
+    for (int i = 0; i < 8; i++) o[i >> 2][i & 3] = pt_float4{0.f, 0.f, 0.f, 0.f};
+
+    for (int t0 = t_first; t0 < t_end; t0 += 4 * TB) {
+        // ---- scales and zero-points to LDS by (group, token); zero past the end
+        if (TB * NG >= 64 || lane < TB * NG) {
 #pragma unroll
-        for (int h = 0; h < REPT; h++) comb[h][c] = o[h];
-    }
-    __syncthreads();
-    if (half == 0) {
+            for (int e = 0; e < E; e++) {
+                const int t = (lane * E + e) / NG, g = (lane * E + e) % NG;
+                const bool in = t0 + t < t_end;
 #pragma unroll
-        for (int h = 0; h < REPT; h++) {
-            if (h < rep) {
-                float *pp = a.ws + ((size_t)(bq0 + h) * a.nchunk + ch) * kPartialStride;
-                pp[4 + c] = o[h] + comb[h][c] + zsum[h][cg];
-                if (c == 0) { pp[0] = m[h]; pp[1] = l[h]; }
+                for (int k = 0; k < 4; k++) meta[wave][k][g][t] = __builtin_bit_cast(_Float16, in ? mr[k][e] : (uint16_t)0);
             }
+        }
+        asm volatile("" ::: "memory");                  // (one wave: LDS operations stay in order)
+        __builtin_amdgcn_wave_barrier();
+        // the four tokens of lane kg in tile tau start here
+        auto at = [&](int tau) { return CPW * kg + 4 * CPW * (tau / (CPW / 4)) + 4 * (tau % (CPW / 4)); };
+        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+
+        // ---- scores
+        float s[NT][4];
+#pragma unroll
+        for (int tau = 0; tau < NT; tau++) {
+#pragma unroll
+            for (int j = 0; j < 4; j++) s[tau][j] = 0.f;
+#pragma unroll
+            for (int ns = 0; ns < NS; ns++) {
+                pt_float4 acc[P];
+#pragma unroll
+                for (int p = 0; p < P; p++) {
+                    acc[p] = pt_float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int wp = 0; wp < KW / 2; wp++)
+                        acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::operand(kw[tau][2 * wp], kw[tau][2 * wp + 1], p),
+                                                                        qb[ns][wp][p], acc[p], 0, 0, 0);
+                }
+                const int g = ((ns * 16 + col) / REPT) % NG;
+                const h4 ks = *reinterpret_cast<const h4 *>(&meta[wave][0][g][at(tau)]);
+                const h4 kz = *reinterpret_cast<const h4 *>(&meta[wave][1][g][at(tau)]);
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    float d = 0.f;
+#pragma unroll
+                    for (int p = 0; p < P; p++) d = __builtin_fmaf(acc[p][j], F::unscale(p), d);
+                    s[tau][j] += __builtin_fmaf((float)ks[j], d, (float)kz[j] * qz[ns]);
+                }
+            }
+#pragma unroll
+            for (int d = REPT; d < (NG * REPT > 16 ? 16 : NG * REPT); d <<= 1)       // the other groups of the token
+#pragma unroll
+                for (int j = 0; j < 4; j++) s[tau][j] += __shfl_xor(s[tau][j], d);
+            if (NT == 8)                                 // (all tiles' operands at once do not fit the registers)
+                asm volatile("" : "+v"(s[tau][0]), "+v"(s[tau][1]), "+v"(s[tau][2]), "+v"(s[tau][3])::"memory");
+        }
+        uint4 vc[2][2];
+#pragma unroll
+        for (int i = 0; i < 4; i++) vc[i >> 1][i & 1] = vw[i >> 1][i & 1];
+        if (t0 + 4 * TB < t_end) request(t0 + 4 * TB);
+        // ---- online softmax over the block (base-2 domain)
+        const bool whole = t0 + TB <= t_end;
+        float bm = m;
+#pragma unroll
+        for (int tau = 0; tau < NT; tau++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                s[tau][j] *= a.c1;
+                if (!whole && t0 + at(tau) + j >= t_end) s[tau][j] = -INFINITY;
+                bm = fmaxf(bm, s[tau][j]);
+            }
+        bm = fmaxf(bm, __shfl_xor(bm, 16));
+        bm = fmaxf(bm, __shfl_xor(bm, 32));
+        const float alpha = __builtin_amdgcn_exp2f(m - bm);
+        m = bm;
+        if (__any(alpha != 1.0f)) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) o[i >> 2][i & 3] *= alpha;
+        }
+        float sum = 0.f;
+        pt_half8 wb[NB][P];                              // weights times V scale, in the order of the value operands
+#pragma unroll
+        for (int ns = 0; ns < NS; ns++) pz[ns] *= alpha;
+#pragma unroll
+        for (int tau = 0; tau < NT; tau++) {
+            const h4 vsA = *reinterpret_cast<const h4 *>(&meta[wave][2][NG == 4 ? (col / REPT) & 1 : 0][at(tau)]);
+            h4 vsB = vsA;
+            if constexpr (NB == 2)
+                vsB = *reinterpret_cast<const h4 *>(&meta[wave][2][NG == 4 ? 2 + ((col / REPT) & 1) : 1][at(tau)]);
+            float w[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) sum += w[j] = __builtin_amdgcn_exp2f(s[tau][j] - m);
+#pragma unroll
+            for (int ns = 0; ns < NS; ns++) {
+                const h4 vz = *reinterpret_cast<const h4 *>(&meta[wave][3][((ns * 16 + col) / REPT) % NG][at(tau)]);
+#pragma unroll
+                for (int j = 0; j < 4; j++) pz[ns] = __builtin_fmaf(w[j], (float)vz[j], pz[ns]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int sw = tau / (CPW / 4), e = 4 * (tau % (CPW / 4)) + j;       // code e of word sw
+                const int hi = e / F::NF, up = (e % F::NF) / P, p = e % P;
+                const int at_op = sw * 4 + up * 2 + hi;
+                // (the place's power of two goes with the weight, so that one sum takes all places)
+                const float wp = p ? w[j] * (1.0f / (float)(1u << (BITS * p))) : w[j];
+                const float wa = wp * (float)vsA[j];
+                wb[0][p][at_op] = (_Float16)wa;
+                if constexpr (NB == 2) {
+                    const float wz = wp * (float)vsB[j];
+                    wb[NB - 1][p][at_op] = (_Float16)wz;
+                    }
+            }
+        }
+        l = __builtin_fmaf(l, alpha, sum);
+        // ---- weighted values: 16 channels a tile
+#pragma unroll
+        for (int half = 0; half < 2; half++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint4 q0 = vc[half][0], q1 = vc[half][1];
+                const uint32_t w0 = i == 0 ? q0.x : i == 1 ? q0.y : i == 2 ? q0.z : q0.w;
+                const uint32_t w1 = i == 0 ? q1.x : i == 1 ? q1.y : i == 2 ? q1.z : q1.w;
+                pt_float4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int p = 0; p < P; p++)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::operand(w0, w1, p), wb[NB == 2 ? half : 0][p], acc, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 4; j++) o[half][i][j] = __builtin_fmaf(acc[j], F::unscale(0), o[half][i][j]);
+                if (NT == 8) asm volatile("" : "+v"(o[half][i])::"memory");
+            }
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+    }
+
+    // ---- the four waves' parts meet
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+#pragma unroll
+    for (int ns = 0; ns < NS; ns++) {
+        pz[ns] += __shfl_xor(pz[ns], 16);
+        pz[ns] += __shfl_xor(pz[ns], 32);
+        if (kg == 0) zsum[wave][((ns * 16 + col) / REPT) % NG][h] = pz[ns];          // (equal columns write equal values)
+    }
+    // with four groups a column of the value product is right for the channels of its own group parity only
+    if (NG == 4 ? (col < 2 * REPT && col / REPT == kg >> 1) : col < REPT) {
+#pragma unroll
+        for (int half = 0; half < 2; half++)
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) part_o[wave][h][64 * half + 4 * (4 * kg + j) + i] = o[half][i][j];
+    }
+    if (lane < REPT) part_m[wave][lane] = m, part_l[wave][lane] = l;
+    __syncthreads();
+    const int c = tid & (kD - 1);
+    for (int hh = tid >> 7; hh < rep; hh += 2) {
+        float M = part_m[0][hh];
+#pragma unroll
+        for (int w = 1; w < 4; w++) M = fmaxf(M, part_m[w][hh]);
+        float Ls = 0.f, O = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; w++) {
+            const float e = __builtin_amdgcn_exp2f(part_m[w][hh] - M);
+            Ls = __builtin_fmaf(part_l[w][hh], e, Ls);
+            O = __builtin_fmaf(part_o[w][hh][c] + zsum[w][c / G][hh], e, O);
+        }
+        if (a.nchunk == 1) {
+            a.out[(size_t)(bq0 + hh) * kD + c] = __half_as_ushort(__float2half_rn(Ls > 0.f ? O / Ls : 0.f));
+        } else {
+            float *pp = a.ws + ((size_t)(bq0 + hh) * a.nchunk + ch) * kPartialStride;
+            pp[4 + c] = O;
+            if (c == 0) pp[0] = M, pp[1] = Ls;
         }
     }
 }
@@ -520,15 +528,26 @@ static int pt_validate_cache(const minikv_pt_cache *c)
     return MINIKV_OK;
 }
 
-// token chunk of one decode workgroup: a multiple of the 256-token block, as long as the launch keeps more
-// than a thousand workgroups (a workgroup sets up the query pairs once, so chunks of several blocks pay;
-// chunks of one block measured 5-20 % slower on the batch-32 configuration)
+// Chunks per unit the workspace is sized for.
+static int pt_ws_chunks(const minikv_pt_shape &s)
+{
+    const long units = (long)s.B * s.Hkv;
+    int chunk = kPtMinChunk;
+    while (chunk < 8192 && units * ((s.Tcap + 2 * chunk - 1) / (2 * chunk)) >= 1024) chunk *= 2;
+    return (s.Tcap + chunk - 1) / chunk;
+}
+
+// Token chunk of one decode workgroup: a multiple of 256 tokens, as few chunks as keep kPtTargetWgs workgroups in the
+// launch -- the two per compute unit that the registers allow, so that all run at once and each sets up its query operands
+// once (1024: 49.7 instead of 44.7 us on 128 units x 13088 tokens, 38 instead of 32 on 16 x 65536) -- and never more
+// chunks than the workspace holds (a unit's share of 1024 workgroups).
+constexpr int kPtTargetWgs = 512;
 static int pt_chunk(const minikv_pt_shape &s)
 {
     const long units = (long)s.B * s.Hkv;
-    int chunk = kPtSB;
-    while (chunk < 8192 && units * ((s.Tcap + 2 * chunk - 1) / (2 * chunk)) >= 1024) chunk *= 2;
-    return chunk;
+    const long most = kPtTargetWgs / units > 1 ? kPtTargetWgs / units : 1;
+    const long blocks = ((long)s.Tcap + kPtMinChunk - 1) / kPtMinChunk;
+    return (int)((blocks + most - 1) / most) * kPtMinChunk;
 }
 
 template <int BITS>
@@ -591,9 +610,7 @@ size_t minikv_pt_cache_bytes(const minikv_pt_shape *s, int which)
 size_t minikv_pt_workspace_bytes(const minikv_pt_shape *s)
 {
     if (pt_validate_shape(s) != MINIKV_OK) return 0;
-    const int chunk = pt_chunk(*s);
-    const size_t nchunk = (size_t)(s->Tcap + chunk - 1) / chunk;
-    return (size_t)s->B * s->Hq * nchunk * kPartialStride * sizeof(float);
+    return (size_t)s->B * s->Hq * (size_t)pt_ws_chunks(*s) * kPartialStride * sizeof(float);
 }
 
 int kv_quantize_pack_pt(const minikv_pt_shape *s, const minikv_f16 *K, const minikv_f16 *V, int64_t L,
@@ -645,7 +662,7 @@ int minikv_decode_attn_pt(const minikv_pt_shape *s, const minikv_f16 *q, const m
     case 8: rc = pt_launch_decode<8>(a, s->G, grid, (hipStream_t)stream); break;
     default: return MINIKV_EUNSUPPORTED;
     }
-    if (rc) return rc;
+    if (rc || a.nchunk == 1) return rc;                 // (a single chunk is the result)
     hipLaunchKernelGGL(merge_pt_kernel, dim3(s->B * s->Hq), dim3(128), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }

@@ -84,6 +84,37 @@ def test_head_counts_empty_units_and_many_chunks(Hq, Hkv, B):
     assert not got.reshape(B * Hkv, Hq // Hkv, 128)[0].any()          # unit 0 holds nothing -> zeros
 
 
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("G,rep", [(32, 1), (32, 4), (32, 8), (64, 3), (64, 8), (128, 2), (128, 5)])
+def test_block_and_chunk_edges_with_poisoned_tails(bits, G, rep):
+    """Lengths around a wave's token block (32, 64 or 128 tokens), a workgroup's four of them and its chunk, in a cache
+    whose capacity is no multiple of the block; everything past a unit's tokens is NaN (scales) or all ones (codes)."""
+    from oracle import ref
+    from paper_2411_18077_amd import api
+    lengths = [0, 16, 32, 48, 112, 128, 144, 256, 272, 576, 720, 832]
+    Hkv = len(lengths)
+    w, inp = _inputs(1, rep * Hkv, Hkv, 832, seed=600 + bits + G + rep, keep=1.0)
+    inp.n_tok.copy_(torch.tensor(lengths, dtype=torch.int32))
+    s = api.make_pt_shape(1, rep * Hkv, Hkv, 128, G, bits, 832)
+    gc = api.PtCache(s)
+    for name in ("Ks", "Kz", "Vs", "Vz"):
+        gc.t[name].fill_(float("nan"))
+    gc.Kc.fill_(-1), gc.Vc.fill_(-1)
+    gc.workspace.fill_(0xFF)
+    api.kv_quantize_pack_pt(s, inp.K, inp.V, w.L, inp.idx, inp.idx.shape[1], inp.n_tok, 832, gc)
+    rc = ref.RefPtCache(ref.RefPtShape(1, rep * Hkv, Hkv, 128, G, bits, 832))
+    assert ref.quantize_pack_pt(rc, inp.K.cpu().numpy(), inp.V.cpu().numpy(), inp.n_tok.cpu().numpy(), inp.idx.cpu().numpy()) == 0
+    out = torch.full((1, rep * Hkv, 128), float("nan"), dtype=torch.float16, device="cuda")
+    sm = 1.0 / math.sqrt(128)
+    api.minikv_decode_attn_pt(s, inp.q, gc, sm, out)
+    torch.cuda.synchronize()
+    want, _ = ref.decode_attn_pt(rc, inp.q.cpu().numpy(), sm)
+    got = out.float().cpu().numpy()
+    assert np.isfinite(got).all()
+    # one fp16 step of a result above 2 is more than the bar
+    assert np.all(np.abs(got - want.astype(np.float32)) <= np.maximum(TOL, np.abs(want) * 2.0 ** -10))
+
+
 @pytest.mark.parametrize("bits,G", [(2, 32), (8, 32), (2, 128), (8, 64)])
 @pytest.mark.parametrize("rep", [2, 8])
 def test_two_and_eight_heads_per_kv_head(rep, bits, G):
