@@ -138,3 +138,38 @@ def test_decode_loop_append_and_flush_bit_exact(g):
     api.kv_append_residual(s, k + 1, v, gc)
     torch.cuda.synchronize()
     assert gc.r_len.cpu().tolist() == [w.Rcap] * w.units and torch.equal(before, gc.Rk)
+
+
+@pytest.mark.parametrize("G,Rcap", [(16, 16), (16, 64), (16, 80), (16, 192), (16, 272), (32, 128), (32, 256), (64, 64),
+                                    (64, 192), (128, 128), (128, 256), (128, 384)])
+def test_flush_of_one_to_five_blocks(g, G, Rcap):
+    """Residuals that one workgroup quantizes and counts by itself (up to 256 tokens) and longer ones: units that are
+    full, that are not, and that have no room left."""
+    from paper_2411_18077_amd import api
+    from oracle import ref
+    w = small(G, B=3, L=512, keep=0.5, Rcap=Rcap)
+    inp = W.make_inputs(w, "cuda")
+    s, rs = g.shapes_for(w, inp.Tcap)
+    r = np.full(w.units, Rcap, np.int32)
+    r[1], r[4] = Rcap - 1, 0
+    gc, rc = g.gpu_build_cache(inp, s), g.ref_build_cache(inp, rs)
+    for c in (gc, rc):
+        c.q_len[5] = inp.Tcap - Rcap + G                 # no room for the residual
+    gc.Rk.view(w.units, Rcap, w.D).copy_(inp.Rk), gc.Rv.view(w.units, Rcap, w.D).copy_(inp.Rv)
+    gc.r_len.copy_(torch.from_numpy(r))
+    rc.Rk[:], rc.Rv[:], rc.r_len[:] = g.to_np(inp.Rk), g.to_np(inp.Rv), r
+    api.kv_flush_residual(s, gc)
+    torch.cuda.synchronize()
+    assert ref.flush_residual(rc) == 0
+    assert gc.r_len.cpu().tolist() == rc.r_len.tolist() == [0, Rcap - 1, 0, 0, 0, Rcap]
+    g.assert_cache_bit_exact(gc, rc)
+
+
+@pytest.mark.parametrize("G", [16, 128])
+def test_short_calls_with_lengths_up_to_the_bound(g, G):
+    """kv_quantize_pack with a host bound of at most 256 tokens: every length below it, gathered."""
+    w = small(G, B=2, Hkv=4, Hq=4, L=300, keep=256 / 300)
+    inp = W.make_inputs(w, "cuda")
+    inp.n_tok.copy_(torch.tensor([0, G, 2 * G, 128, 256, 256 - G, 128 + G if G < 128 else 256, 128], dtype=torch.int32))
+    s, rs = g.shapes_for(w, inp.Tcap)
+    g.assert_cache_bit_exact(g.gpu_build_cache(inp, s), g.ref_build_cache(inp, rs))
