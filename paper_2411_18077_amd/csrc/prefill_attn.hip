@@ -93,14 +93,22 @@ __device__ __forceinline__ half4 read_transposed(const _Float16 *p)
     return (half4)__builtin_amdgcn_ds_read_tr16_b64_v4f16((__attribute__((address_space(3))) fp16x4 *)p);
 }
 
-template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 2) void prefill_fwd_kernel(PrefillArgs a)
+// SPLIT == 2: two sets of WAVES waves take the even and the odd tiles of the same queries, each through LDS buffers of
+// its own, and meet at the end; for launches that leave a compute unit a single set.  (The second launch bound keeps
+// every instance in 256 registers: with more the accumulators go to the registers only matrix instructions reach.  Two
+// sets of two waves never have two waves on a SIMD, about which the compiler would warn.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wpass-failed"
+template <int WAVES, int SPLIT>
+__global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(PrefillArgs a)
 {
     constexpr int kRows = kPfN / WAVES, kLoads = kRows / 4;     // rows of a tile one wave loads, four per instruction
-    __shared__ __align__(16) _Float16 Ks[2 * kPfTile], Vs[2 * kPfTile];
+    __shared__ __align__(16) _Float16 tiles[SPLIT][4 * kPfTile];
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WAVES;
+    const int set = SPLIT == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WAVES;
+    _Float16 *Ks = tiles[set], *Vs = tiles[set] + 2 * kPfTile;
     // heaviest row blocks (the last ones: they see the most keys) first
     const int nbh = (int)gridDim.x / a.nblk, head = (int)blockIdx.x % nbh;
     const int qb = a.nblk - 1 - (int)blockIdx.x / nbh;
@@ -116,9 +124,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_fwd_kernel(PrefillArgs 
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const half8 *)(qp + ks * 16);
     }
-    const int ntiles = (min((qb + 1) * (32 * WAVES), L) + kPfN - 1) / kPfN;   // tiles some query of the block sees
-    const int mytiles = min((q0 + 31) / kPfN + 1, ntiles);                    // tiles some query of this wave sees
-    const int nfull = min((q0 + 1) / kPfN, mytiles);                          // tiles every query of this wave sees whole
+    // Tile n of this set is tile n * SPLIT + set of the prompt.  Steps of the workgroup (every wave meets each barrier),
+    // this set's tiles some query of this wave sees, and those every query of the wave sees whole:
+    auto of_set = [&](int n) { return max((n - set + SPLIT - 1) / SPLIT, 0); };
+    const int all = (min((qb + 1) * (32 * WAVES), L) + kPfN - 1) / kPfN;
+    const int ntiles = (all + SPLIT - 1) / SPLIT;
+    const int mytiles = of_set(min((q0 + 31) / kPfN + 1, all)), nfull = min(of_set((q0 + 1) / kPfN), mytiles);
 
     // tile loads
     unsigned k_off[kLoads];
@@ -132,7 +143,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_fwd_kernel(PrefillArgs 
     // last repeats that one into a buffer nobody reads any more.)
     const int last_tile = (L - 1) / kPfN;
     auto request = [&](const _Float16 *base, int n, bool is_v) {
-        const int t = min(n, last_tile), row0 = t * kPfN + wave * kRows;
+        const int row0 = min(n * SPLIT + set, last_tile) * kPfN + wave * kRows;
         const char *tile = (const char *)(base + (long)min(row0, L - 1) * kPfD);
         const unsigned lds = (is_v ? v_lds : k_lds) + (n & 1) * (kPfTile * 2u);
         const int end = max(L - 1 - row0, 0) * 256 + 240;
@@ -188,7 +199,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_fwd_kernel(PrefillArgs 
     };
     // keys after the query do not count: their scores become -inf
     auto mask = [&](float16v (&s)[2], int n) {
-        const int rel = query - n * kPfN - 4 * g;
+        const int rel = query - (n * SPLIT + set) * kPfN - 4 * g;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -261,47 +272,67 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_fwd_kernel(PrefillArgs 
     request(Vh, 0, true);
     hand_over();                                       // (the Q rows have arrived as well)
     float16v sa[2], sb[2];
+    if (SPLIT == 1 || mytiles > 0) {                   // (the second set may have nothing for the first rows)
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sa[t][i] = 0.0f;
+            for (int i = 0; i < 16; ++i) sa[t][i] = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) sa[j & 1] = mfma32(read_k(j, 0), qf[j >> 1], sa[j & 1]);
-    if (nfull < 1) mask(sa, 0);
-    {
+        for (int j = 0; j < 16; ++j) sa[j & 1] = mfma32(read_k(j, 0), qf[j >> 1], sa[j & 1]);
+        if (nfull < 1) mask(sa, 0);
         float mx = -INFINITY;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sa[t][i]);
         settle(mx);
-    }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) kf[j] = read_k(j, 1);  // (with a single tile: unused)
+        for (int j = 0; j < 4; ++j) kf[j] = read_k(j, 1);      // (with a single tile: unused)
+    }
     hand_over();
     request(Kh, 2, false);
 
     const std::true_type yes{};
     const std::false_type no{};
-    int n = 0;
-    for (; n + 2 < nfull; n += 2) {
-        step(sa, sb, n, yes, no);
-        step(sb, sa, n + 1, yes, no);
+    if (SPLIT == 1 || mytiles > 0) {
+        int n = 0;
+        for (; n + 2 < nfull; n += 2) {
+            step(sa, sb, n, yes, no);
+            step(sb, sa, n + 1, yes, no);
+        }
+        for (; n + 2 < mytiles; n += 2) {
+            step(sa, sb, n, yes, yes);
+            step(sb, sa, n + 1, yes, yes);
+        }
+        if (n + 1 < mytiles) {
+            step(sa, sb, n, yes, yes);
+            step(sb, sa, n + 1, no, no);
+        } else {
+            step(sa, sb, n, no, no);
+        }
     }
-    for (; n + 2 < mytiles; n += 2) {
-        step(sa, sb, n, yes, yes);
-        step(sb, sa, n + 1, yes, yes);
-    }
-    if (n + 1 < mytiles) {
-        step(sa, sb, n, yes, yes);
-        step(sb, sa, n + 1, no, no);
-    } else {
-        step(sa, sb, n, no, no);
-    }
-    for (n = mytiles; n < ntiles; ++n) {               // tiles only later waves see: this one still loads its share
+    for (int n = mytiles; n < ntiles; ++n) {           // tiles only other waves see: this one still loads its share
         hand_over();
         request(Vh, n + 1, true);
         request(Kh, n + 3, false);
+    }
+    if constexpr (SPLIT == 2) {
+        // the second set's state goes to the first through LDS (every tile has been read, every load has landed)
+        float *xch = (float *)&tiles[0][0] + wave * (66 * 64) + lane;
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        if (set == 1) {
+            xch[0] = m, xch[64] = l;
+#pragma unroll
+            for (int i = 0; i < 64; ++i) xch[(2 + i) * 64] = o[i >> 4][i & 15];
+        }
+        __syncthreads();
+        if (set == 1) return;
+        const float m1 = xch[0], top = fmaxf(m, m1);   // (m is finite: the first set has the prompt's first tile)
+        const float f0 = __builtin_amdgcn_exp2f((m - top) * c), f1 = __builtin_amdgcn_exp2f((m1 - top) * c);
+        l = l * f0 + xch[64] * f1;
+#pragma unroll
+        for (int i = 0; i < 64; ++i) o[i >> 4][i & 15] = o[i >> 4][i & 15] * f0 + xch[(2 + i) * 64] * f1;
+        m = top;
     }
 
     l += __shfl_xor(l, 32, 64);
@@ -320,6 +351,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_fwd_kernel(PrefillArgs 
             }
     }
 }
+
+#pragma clang diagnostic pop
 
 // A workgroup owns 128 keys and walks the queries from the diagonal down in tiles of 64 through LDS.  Wave (kw, qw)
 // holds the K rows of 64 of the keys as B operands and takes 32 of a tile's queries, so that every Q fragment read
@@ -500,16 +533,27 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
     a.Q = (const _Float16 *)Q, a.K = (const _Float16 *)K, a.V = (const _Float16 *)V;
     a.XO = (_Float16 *)XO, a.lse = lse, a.A_cumul = A_cumul;
     a.Hq = Hq, a.rep = Hq / Hkv, a.L = L, a.scale_log2 = sm_scale * kLog2e;
-    // 256 queries per workgroup halve what a tile costs to load (32 heads x 32768: 8.11 -> 7.81 ms); blocks of 128 keep
-    // more workgroups in flight where 256 would leave fewer than four per compute unit (32 x 2048: 51 against 58 us).
+    // Queries per workgroup and whether two sets of waves share them.  256 queries halve what a tile costs to load
+    // (32 heads x 32768: 8.11 -> 7.81 ms) while they leave four workgroups per compute unit; else 128 (32 x 2048: 51
+    // against 58 us).  A launch of at most one workgroup per compute unit lasts as long as its longest row block: two sets
+    // of waves halve that (32 x 1024: 25.0 -> 23.3 us; with more workgroups the halves only compete, 64 x 777 26 -> 30),
+    // and where even blocks of 64 queries leave one per compute unit those are shorter still (32 x 500 15.1 -> 13.2 us,
+    // 32 x 200 11.6 -> 9.5; 32 x 777, 416 of them, 20 -> 22).
     // In the second pass eight waves per workgroup lose (4.36 -> 4.62 ms): they wait for each other at every tile.
-    const bool wide = (int64_t)B * Hq * ((L + 255) / 256) >= 1024;
     const int64_t heads = (int64_t)B * Hq;
-    a.nblk = (int)((L + (wide ? 255 : 127)) / (wide ? 256 : 128));
-    if (wide)
-        hipLaunchKernelGGL(prefill_fwd_kernel<8>, dim3((unsigned)(heads * a.nblk)), dim3(512), 0, st, a);
+    auto blocks = [&](int queries) { return heads * ((L + queries - 1) / queries); };
+    constexpr int64_t kComputeUnits = 256;
+    const int queries = blocks(256) >= 4 * kComputeUnits ? 256 : blocks(64) <= kComputeUnits ? 64 : 128;
+    a.nblk = (int)((L + queries - 1) / queries);
+    const dim3 grid((unsigned)(heads * a.nblk));
+    if (queries == 256)
+        hipLaunchKernelGGL((prefill_fwd_kernel<8, 1>), grid, dim3(512), 0, st, a);
+    else if (queries == 64)
+        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2>), grid, dim3(256), 0, st, a);
+    else if (blocks(128) <= kComputeUnits)
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 2>), grid, dim3(512), 0, st, a);
     else
-        hipLaunchKernelGGL(prefill_fwd_kernel<4>, dim3((unsigned)(heads * a.nblk)), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 1>), grid, dim3(256), 0, st, a);
     if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     if (A_cumul) {
         a.nblk = (int)((L + 127) / 128);

@@ -89,6 +89,23 @@ def test_launches_with_256_queries_per_workgroup(g, B, Hq, Hkv, L):
     assert np.all(np.abs(g.to_np(acc[sel]) - acc64) <= RTOL_A * np.abs(acc64) + ATOL_A)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv", [(1, 2, 1), (4, 16, 4), (4, 32, 8), (5, 32, 16)])
+@pytest.mark.parametrize("L", [1, 63, 64, 127, 129, 192, 321])
+def test_every_division_of_a_launch(g, B, Hq, Hkv, L):
+    """2 to 160 heads at lengths around a tile, a pair of tiles (two sets of waves take every other one) and a block:
+    launches with 64 and 128 queries per workgroup, split and not."""
+    from oracle import ref
+    sm = 1.0 / math.sqrt(128)
+    Q, K, V = W.make_prefill_inputs(B, Hq, Hkv, L, 950 + L, device="cuda")
+    xo, lse, acc = run_gpu(Q, K, V, sm)
+    assert torch.isfinite(xo).all() and torch.isfinite(lse).all() and torch.isfinite(acc).all()
+    sel = [B - 1]
+    _, xo64, lse64, acc64 = ref.selective_flash_attn(g.to_np(Q[sel]), g.to_np(K[sel]), g.to_np(V[sel]), sm)
+    assert np.max(np.abs(g.to_np(xo[sel]).astype(np.float64) - xo64)) <= TOL_O
+    assert np.max(np.abs(g.to_np(lse[sel]).astype(np.float64) - lse64)) <= TOL_LSE
+    assert np.all(np.abs(g.to_np(acc[sel]) - acc64) <= RTOL_A * np.abs(acc64) + ATOL_A)
+
+
 @pytest.mark.parametrize("per_tile", [-3.0, 0.02, 0.7, 3.0, 30.0])
 def test_scores_that_rise_or_fall_along_the_keys(g, per_tile):
     """The reference of the softmax weights lags behind the running maximum by a bounded amount: scores whose level moves
