@@ -142,8 +142,16 @@ __device__ inline float *slot_ptr(const DecArgs &a, int slot, int h)
 // waves of 4 to 6 items each, 16 us of which 7 are items worked off one after the other.  When the whole
 // launch cannot hold more items than half the waves the device holds, balance does not matter and
 // parallelism does: with unit weights every item gets a wave of its own.
-template <int G, bool LO, bool PAIRED, bool FUSED, bool FLAT>
-__global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecArgs a)
+//
+// UNIT: a workgroup of kUnitWaves waves IS one unit; they divide its items, and their partials meet in local memory.
+// What a small launch spends its time on is round trips -- lengths to work line, partial to ticket, ticket to merge --,
+// and this form has one of them, the unit's own two lengths: see launch_stream() for where it is taken.
+template <int G> constexpr int kUnitWaves = G == 16 ? 4 : 8;     // (two per SIMD, one at G = 16)
+template <int G> constexpr size_t kWaveLds =                     // local memory of one wave, bytes
+    (size_t)(kD / G) * kPsG * 2 > (size_t)kNH * kD * 2 + (size_t)64 * kKRowH * 2
+        ? (size_t)(kD / G) * kPsG * 2 : (size_t)kNH * kD * 2 + (size_t)64 * kKRowH * 2;
+template <int G, bool LO, bool PAIRED, bool FUSED, bool FLAT, bool UNIT>
+__global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) void decode_stream_kernel(DecArgs a)
 {
     constexpr int kWQ = FLAT ? 1 : kPassWeight, kWR = FLAT ? 1 : kResidualWeight;
     const bool APPEND = FUSED && a.append;
@@ -160,10 +168,17 @@ __global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecA
     typedef KData<NKW> KD;
     typedef VData<NCG> VD;
 
-    extern __shared__ __attribute__((aligned(16))) _Float16 lds[];
+    extern __shared__ __attribute__((aligned(16))) _Float16 lds_launch[];
+    _Float16 *lds_all = lds_launch;
+    if constexpr (UNIT) {                                  // (the size is known here: no launch attribute to set)
+        __shared__ __attribute__((aligned(16))) _Float16 lds_unit[kUnitWaves<G> * kWaveLds<G> / 2];
+        lds_all = lds_unit;
+    }
+    const int wave = UNIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    _Float16 *lds = lds_all + wave * (kWaveLds<G> / 2);
     _Float16 *ps = lds;                                    // [NCG][kNH][kPsH] halfs (quantized passes)
 
-    const int lane = threadIdx.x;
+    const int lane = UNIT ? threadIdx.x & 63 : threadIdx.x;
     const int NU = a.units * a.hsets;
 
     // ---------------- the work list: total weight P, this wave's range, the unit that holds its start.
@@ -211,13 +226,29 @@ __global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecA
     // form it took there, the item's local-memory reads and its loads lost their overlap.)
     uint4 new_piece = {0u, 0u, 0u, 0u};
     int new_row = -1;
-    const bool files_new = APPEND && (int)blockIdx.x < a.units && lane < 32;
+    const int file_unit = UNIT ? (int)blockIdx.x >> a.hs_shift : (int)blockIdx.x;
+    const bool files_new = APPEND && lane < 32 && (UNIT ? wave == 0 && ((int)blockIdx.x & (a.hsets - 1)) == 0
+                                                        : (int)blockIdx.x < a.units);
     auto new_src = [&](int u) { return reinterpret_cast<const uint4 *>((lane < 16 ? a.k_new : a.v_new) + (size_t)u * kD) + (lane & 15); };
     auto new_dst = [&](int u, int r) { return reinterpret_cast<uint4 *>(const_cast<uint16_t *>(lane < 16 ? a.Rk : a.Rv) + ((size_t)u * a.Rcap + r) * kD) + (lane & 15); };
     if (files_new) {
-        new_row = a.r_len[blockIdx.x];
-        new_piece = *new_src(blockIdx.x);
+        new_row = a.r_len[file_unit];
+        new_piece = *new_src(file_unit);
     }
+    int up = -1, w = 0, nw_log = 0, skew16 = 8;
+    long ib = 0, start = 0, end = 1;                       // position of the unit's first item; this wave's range
+    float inv_p = 0.0f;
+    int T_first = 0, R_first = 0;                          // lengths of the wave's first unit
+    if constexpr (UNIT) {
+        up = blockIdx.x;
+        T_first = clampi(load_const_i32(a.q_len + file_unit), 0, a.Tcap);
+        R_first = res_len(APPEND, a, load_const_i32(a.r_len + file_unit));
+        if (files_new && new_row >= 0 && new_row < a.Rcap) *new_dst(file_unit, new_row) = new_piece;
+        if (weight_of(T_first, R_first) == 0) {            // (uniform in the workgroup)
+            if (wave == 0) zero_fill(up);
+            return;
+        }
+    } else {
     for (int base = 0; base < NU; base += 256) {
         lengths4(base, Tl, Rl);
 #pragma unroll
@@ -246,7 +277,8 @@ __global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecA
     // that the cuts need no division.
     if (P == 0) return;
     const int nw_cap = max(1, min((int)gridDim.x, P / kWR));
-    const int nw_log = 31 - __builtin_clz(nw_cap), NW = 1 << nw_log;
+    nw_log = 31 - __builtin_clz(nw_cap);
+    const int NW = 1 << nw_log;
     if ((int)blockIdx.x >= NW) return;
     // Wave numbers.  The hardware serves the older of the two waves on a SIMD first, so the workgroups
     // that were dispatched first (they fill the first wave slot of every SIMD, a.first_slot of them) get
@@ -254,20 +286,17 @@ __global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecA
     // and workgroup b + a.first_slot take the neighbouring numbers 2b and 2b + 1, so that every unit is
     // served by both kinds in equal parts and all units finish together.
     const bool paired = NW == 2 * a.first_slot;
-    const int w = !paired ? (int)blockIdx.x
+    w = !paired ? (int)blockIdx.x
                 : (int)blockIdx.x < a.first_slot ? 2 * (int)blockIdx.x : 2 * ((int)blockIdx.x - a.first_slot) + 1;
     // (the wave in the first slot of a SIMD runs faster; both parts of a pair range must stay longer than one
     // item, so that every wave between the first and the last of a unit owns an item of it)
     const int want16 = min(max(a.skew16, 4), 12);
-    const int skew16 = paired && ((((2L * P) >> nw_log) * min(want16, 16 - want16)) >> 4) >= kWR ? want16 : 8;
-    const long start = range_start(w, P, nw_log, skew16), end = range_start(w + 1, P, nw_log, skew16);
+    skew16 = paired && ((((2L * P) >> nw_log) * min(want16, 16 - want16)) >> 4) >= kWR ? want16 : 8;
+    start = range_start(w, P, nw_log, skew16), end = range_start(w + 1, P, nw_log, skew16);
     // (NW / P as a wave-uniform value in a scalar register)
-    const float inv_p = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)NW / (float)P)));
+    inv_p = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)NW / (float)P)));
 
     // ---------------- the unit whose weight span holds position `start`
-    int up = -1;
-    long ib = 0;                                           // position of the unit's first item
-    int T_first = 0, R_first = 0;                          // its lengths
     {
         long running = 0;
         for (int base = 0; base < NU && up < 0; base += 256) {
@@ -295,6 +324,7 @@ __global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecA
             }
         }
     }
+    }   // (not UNIT)
     const int up_first = up;
 
     const int blk4 = lane >> 2, row = lane & 3;            // block of 4 lanes; row = query head this lane
@@ -322,18 +352,27 @@ __global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecA
         const int span = wt + kWR;
         const int ds = (int)min((long)span, max(0L, start - ib)), de = (int)min((long)span, max(0L, end - ib));
         const int dq = kWR * nf, db = dq + kWQ * it.nq;
-        const int f0 = min(nf, (ds + kWR - 1) / kWR), f1 = min(nf, (de + kWR - 1) / kWR);
-        const int j0 = min(it.nq, (max(0, ds - dq) + kWQ - 1) / kWQ), j1 = min(it.nq, (max(0, de - dq) + kWQ - 1) / kWQ);
-        const int b0 = min(nb, (max(0, ds - db) + kWR - 1) / kWR), b1 = min(nb, (max(0, de - db) + kWR - 1) / kWR);
-        if (f0 >= f1 && j0 >= j1 && b0 >= b1) { ib = ib_next; continue; }
+        int f0 = min(nf, (ds + kWR - 1) / kWR), f1 = min(nf, (de + kWR - 1) / kWR);
+        int j0 = min(it.nq, (max(0, ds - dq) + kWQ - 1) / kWQ), j1 = min(it.nq, (max(0, de - dq) + kWQ - 1) / kWQ);
+        int b0 = min(nb, (max(0, ds - db) + kWR - 1) / kWR), b1 = min(nb, (max(0, de - db) + kWR - 1) / kWR);
+        if constexpr (UNIT) {
+            // passes from the first wave on, residual items (even ones in front, odd ones at the back) from the last
+            constexpr int NWV = kUnitWaves<G>, HW = NWV / 2;
+            auto share = [](int n, int k, int of) { return (n * k + of - 1) / of; };
+            const int back = NWV - 1 - wave, k = back >> 1;
+            j0 = share(it.nq, wave, NWV), j1 = share(it.nq, wave + 1, NWV);
+            f0 = f1 = b0 = b1 = 0;
+            if (back & 1) b0 = share(nb, k, HW), b1 = share(nb, k + 1, HW);
+            else f0 = share(nf, k, HW), f1 = share(nf, k + 1, HW);
+        } else if (f0 >= f1 && j0 >= j1 && b0 >= b1) { ib = ib_next; continue; }
         const int u = up >> a.hs_shift, hs = up & (a.hsets - 1);
         const int bi = (int)fast_div((uint32_t)u, a.hkv_magic, a.hkv_shift);
         const int bq0 = bi * a.Hq + (u - bi * a.Hkv) * a.rep + hs * kNH;
         const int nheads = min(kNH, a.rep - hs * kNH);
         const int t_end = it.T;
         // the waves that own items of this unit: from the owner of the first item to the owner of the last
-        const int wf = wave_of(ib, P, nw_log, inv_p, skew16);
-        const int wl = wave_of(ib_next - (nb ? kWR : it.nq ? kWQ : kWR), P, nw_log, inv_p, skew16);
+        const int wf = UNIT ? 0 : wave_of(ib, P, nw_log, inv_p, skew16);
+        const int wl = UNIT ? 0 : wave_of(ib_next - (nb ? kWR : it.nq ? kWQ : kWR), P, nw_log, inv_p, skew16);
         const int expected = wl - wf + 1;
         const uint32_t *Kc = a.Kc + (size_t)u * kc_words(a.Tcap);
         const uint32_t *Vc = a.Vc + (size_t)u * vc_words(a.Tcap);
@@ -850,7 +889,37 @@ __global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecA
         auto write_next_len = [&]() {
             if (APPEND && lane == 0) a.r_len_out[u] = it.rn >= 0 ? it.rn + 1 : a.r_len[u];
         };
-        if (expected == 1) {
+        if constexpr (UNIT) {
+            // every wave's state goes to its own part of the local memory; then a thread per (head, channel) merges them
+            // in wave order (a wave without items left m = -1e30, weight 0)
+            constexpr int NWV = kUnitWaves<G>;
+            float *mine = reinterpret_cast<float *>(lds);
+            asm volatile("" ::: "memory");                 // (the same bytes held weights and rows, as other types)
+#pragma unroll
+            for (int h = 0; h < kNH; h++) {
+                mine[h * kPartialStride + 4 + lane] = oa[h];
+                mine[h * kPartialStride + 4 + lane + 64] = ob[h];
+                if (lane == 0) mine[h * kPartialStride] = m[h], mine[h * kPartialStride + 1] = lsum[h];
+            }
+            __syncthreads();
+            if (wave == 0) write_next_len();
+            for (int i = wave * 64 + lane_p; i < nheads * kD; i += 64 * NWV) {
+                const int h = i / kD, c = i % kD;
+                const float *part = reinterpret_cast<const float *>(lds_all) + h * kPartialStride;
+                constexpr size_t step = kWaveLds<G> / 4;
+                float M = part[0];
+#pragma unroll
+                for (int k = 1; k < NWV; k++) M = fmaxf(M, part[k * step]);
+                float L = 0.f, O = 0.f;
+#pragma unroll
+                for (int k = 0; k < NWV; k++) {
+                    const float e = fast_exp2(part[k * step] - M);
+                    L = __builtin_fmaf(part[k * step + 1], e, L);
+                    O = __builtin_fmaf(part[k * step + 4 + c], e, O);
+                }
+                a.out[(size_t)(bq0 + h) * kD + c] = __half_as_ushort(__float2half_rn(L > 0.f ? O / L : 0.f));
+            }
+        } else if (expected == 1) {
             // the only partial of its unit: normalise and write the result directly
             write_next_len();
 #pragma unroll
@@ -1010,12 +1079,40 @@ __global__ __launch_bounds__(64, G == 16 ? 1 : 2) void decode_stream_kernel(DecA
     }
 }
 
+template <int G, bool LO, bool PAIRED, bool APPEND>
+static int launch_units(const DecArgs &a, hipStream_t st)
+{
+    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, true, true>), dim3((unsigned)(a.units * a.hsets)),
+                       dim3(64 * kUnitWaves<G>), 0, st, a);
+    return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
+}
+
+// Whether a workgroup per unit serves the call, from the capacities (the lengths are on the device).  It needs a compute
+// unit per unit, and few enough items that the eight waves of a unit (four at G = 16) are done before the work line, which
+// spreads the items over the whole device, has paid for its round trips -- also when the lengths are ragged and the line
+// has the better balance.  Measured with all lengths at the capacity / ragged (5 .. 100 % of it), line against unit, us:
+//   32/8 heads, G = 32:    8 units x 11 items 12.1 / 11.5 against 11.5, 15 items 12.0 against 14.1
+//                         64 units x 11 items 13.3 against 12.0 / 16.3 against 11.8, 15 items 13.5 against 14.9
+//                        128 units x 19 items 19.9 against 15.2, 27 items 17.9 against 17.9, 35 items 19.6 against 20.8
+//                        256 units x 11 items 17.6 against 13.5 / 21.6 against 12.8, 27 items 25.9 against 21.4 / 22.1
+//                            against 18.7, 50 items 40.2 against 34.8 / 27.8 against 28.4
+//   32/8 heads, G = 16:   16 units x 11 items 13.9 against 14.6; 128 units x 19 items 24.6 against 20.0, 27 items 22.7
+//                            against 24.2; 256 units x 19 items 28.8 against 21.2
+static bool unit_per_workgroup(const DecArgs &a, int G)
+{
+    const long units = (long)a.units * a.hsets;
+    const int items = (a.Tcap + kPass - 1) / kPass + (a.Rcap + 63) / 64;
+    if (units > 256) return false;                         // compute units of the device
+    if (G == 16) return items <= (units >= 96 ? 20 : units >= 32 ? 12 : 0);
+    return items <= (units >= 192 ? 28 : units >= 96 ? 24 : 12);
+}
+
 template <int G, bool LO, bool PAIRED, bool APPEND, bool FLAT>
 static int launch_stream_w(DecArgs a, long nw, int resident, size_t lds_bytes, hipStream_t st)
 {
     a.first_slot = resident / 2;
     a.skew16 = kSkew16;
-    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT>), dim3((unsigned)nw), dim3(64), lds_bytes, st, a);
+    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT, false>), dim3((unsigned)nw), dim3(64), lds_bytes, st, a);
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
 
@@ -1030,11 +1127,8 @@ bool set_decode_weights(int mode)
 template <int G, bool LO, bool PAIRED, bool APPEND>
 static int launch_stream(DecArgs a, hipStream_t st)
 {
-    constexpr int NCG = kD / G;
-    constexpr size_t q_bytes = (size_t)NCG * kPsG * 2;
-    constexpr size_t r_bytes = (size_t)kNH * kD * 2 + (size_t)64 * kKRowH * 2;
-    constexpr size_t lds_bytes = q_bytes > r_bytes ? q_bytes : r_bytes;
-    auto kern = decode_stream_kernel<G, LO, PAIRED, APPEND, false>;
+    constexpr size_t lds_bytes = kWaveLds<G>;
+    auto kern = decode_stream_kernel<G, LO, PAIRED, APPEND, false, false>;
     static int resident = 0;                               // single-wave workgroups the device holds at once
     if (resident == 0) {
         int dev = 0, cus = 0, per_cu = 0;
@@ -1053,6 +1147,7 @@ static int launch_stream(DecArgs a, hipStream_t st)
     // shapes of 80 to 2240 items, they win up to 608 items -- 13.3 against 16.7 us -- tie at 560 and lose from
     // 1120 on -- 19.8 against 17.7 us)
     const int mode = g_decode_weights.load();
+    if (mode == 0 && unit_per_workgroup(a, G)) return launch_units<G, LO, PAIRED, APPEND>(a, st);
     return (mode == 0 ? cap_items * 2 <= (long)resident : mode == 2) ? launch_stream_w<G, LO, PAIRED, APPEND, true>(a, nw, resident, lds_bytes, st)
                                  : launch_stream_w<G, LO, PAIRED, APPEND, false>(a, nw, resident, lds_bytes, st);
 }

@@ -100,6 +100,26 @@ def test_ragged_units_including_empty_ones(g, variant):
     assert not got.reshape(3, 2, 2, 128)[2, 0].any()          # unit 4: no tokens at all -> zeros
 
 
+@pytest.mark.parametrize("G", [16, 32, 64, 128])
+@pytest.mark.parametrize("Hq,Hkv,B,L,Rcap", [(4, 4, 9, 128, 128), (8, 2, 17, 1024, 128), (16, 2, 8, 1000, 384),
+                                             (3, 3, 32, 2048, 256), (12, 12, 20, 300, 768), (8, 1, 1, 900, 128)])
+def test_a_workgroup_per_unit(g, G, Hq, Hkv, B, L, Rcap):
+    """Calls that a workgroup per unit serves (few items per unit; with 32 of them only from 32 units on at G = 16): one to
+    twenty-odd items over eight or four waves, more residual items than passes, units of every length down to none."""
+    w = tiny(G, B=B, Hq=Hq, Hkv=Hkv, L=L, Rcap=Rcap, keep=None, keep_range=(0.02, 1.0))
+    rng = np.random.default_rng(L + G)
+    r = rng.integers(0, Rcap + 1, w.units)
+    r[: min(6, w.units)] = np.array([0, 1, 64, 65, Rcap - 1, Rcap])[: min(6, w.units)]
+
+    def mutate(inp):
+        if w.units > 2:
+            inp.n_tok[0] = 0                               # unit 0 holds nothing at all
+            inp.n_tok[2] = 0
+    got, want = run_both(g, w, r, 3, mutate=mutate)
+    assert np.all(np.abs(got - want) <= np.maximum(TOL, fp16_step(want)))
+    assert w.units <= 2 or not got.reshape(w.units, -1)[0].any()
+
+
 @pytest.mark.parametrize("variant", VARIANTS)
 def test_peaked_attention_with_outlier_channels(g, variant):
     """Few tokens, the query aligned with one key, x10 outlier channels: the case that stresses 2e-3."""
