@@ -23,7 +23,7 @@ int minikv_stream_read_probe(const void *src, size_t bytes, uint32_t *sums, void
 int minikv_diag_redo_count(const minikv_shape *shape, const void *workspace, int32_t *count);
 
 /* How minikv_decode_attn / minikv_decode_step cut the work into waves (process-wide): 0 = chosen by shape
- * (default), 1 = a residual item of 64 tokens weighs 3.5 quantized passes of 128, as measured (what large launches
+ * (default; calls of few items per unit take a workgroup per unit instead), 1 = a residual item of 64 tokens weighs 3.5 quantized passes of 128, as measured (what large launches
  * use), 2 = every item weighs the same (what launches of few items use, so that every item gets a wave).  Both
  * give the same result up to the order of the merge; the parity tests run each.  MINIKV_EINVAL otherwise. */
 int         minikv_diag_decode_weights(int mode);
