@@ -151,8 +151,9 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
         for (int i = 0; i < kLoads; ++i)
             load_to_lds(tile, (unsigned)min((int)(is_v ? v_off : k_off[i]) + i * 1024, end), lds + i * 1024u);
     };
-    // all loads of this wave have landed; then the barrier that hands every wave's share over
-    auto hand_over = [&]() { asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // all loads of this wave have landed and its fragment reads have returned (their buffer is about to be refilled); then
+    // the barrier that hands every wave's share over
+    auto hand_over = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     // fragment reads
     int k_place[8], v_place[4];
@@ -319,7 +320,7 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
     if constexpr (SPLIT == 2) {
         // the second set's state goes to the first through LDS (every tile has been read, every load has landed)
         float *xch = (float *)&tiles[0][0] + wave * (66 * 64) + lane;
-        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        hand_over();
         if (set == 1) {
             xch[0] = m, xch[64] = l;
 #pragma unroll
