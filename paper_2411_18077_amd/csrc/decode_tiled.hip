@@ -227,29 +227,28 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
     uint4 new_piece = {0u, 0u, 0u, 0u};
     int new_row = -1;
     const int file_unit = UNIT ? (int)blockIdx.x >> a.hs_shift : (int)blockIdx.x;
-    const bool files_new = APPEND && lane < 32 && (UNIT ? wave == 0 && ((int)blockIdx.x & (a.hsets - 1)) == 0
-                                                        : (int)blockIdx.x < a.units);
+    const bool files_new = UNIT ? APPEND && wave == 0 && ((int)blockIdx.x & (a.hsets - 1)) == 0 && lane < 32
+                                : APPEND && (int)blockIdx.x < a.units && lane < 32;
     auto new_src = [&](int u) { return reinterpret_cast<const uint4 *>((lane < 16 ? a.k_new : a.v_new) + (size_t)u * kD) + (lane & 15); };
     auto new_dst = [&](int u, int r) { return reinterpret_cast<uint4 *>(const_cast<uint16_t *>(lane < 16 ? a.Rk : a.Rv) + ((size_t)u * a.Rcap + r) * kD) + (lane & 15); };
     if (files_new) {
         new_row = a.r_len[file_unit];
         new_piece = *new_src(file_unit);
     }
-    int up = -1, w = 0, nw_log = 0, skew16 = 8;
-    long ib = 0, start = 0, end = 1;                       // position of the unit's first item; this wave's range
-    float inv_p = 0.0f;
-    int T_first = 0, R_first = 0;                          // lengths of the wave's first unit
+    // (UNIT: only this unit's two lengths are read; the work line below does not exist.  It is guarded statement by
+    // statement, not enclosed, so that the line instances are compiled from unchanged code: other arrangements of the same
+    // statements ran up to 3 % slower there.)
+    int unit_T = 0, unit_R = 0;
     if constexpr (UNIT) {
-        up = blockIdx.x;
-        T_first = clampi(load_const_i32(a.q_len + file_unit), 0, a.Tcap);
-        R_first = res_len(APPEND, a, load_const_i32(a.r_len + file_unit));
+        unit_T = clampi(load_const_i32(a.q_len + file_unit), 0, a.Tcap);
+        unit_R = res_len(APPEND, a, load_const_i32(a.r_len + file_unit));
         if (files_new && new_row >= 0 && new_row < a.Rcap) *new_dst(file_unit, new_row) = new_piece;
-        if (weight_of(T_first, R_first) == 0) {            // (uniform in the workgroup)
-            if (wave == 0) zero_fill(up);
+        if (weight_of(unit_T, unit_R) == 0) {              // (uniform in the workgroup)
+            if (wave == 0) zero_fill(blockIdx.x);
             return;
         }
-    } else {
-    for (int base = 0; base < NU; base += 256) {
+    }
+    for (int base = 0; !UNIT && base < NU; base += 256) {
         lengths4(base, Tl, Rl);
 #pragma unroll
         for (int k = 0; k < 4; k++) {
@@ -260,14 +259,14 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             P += __builtin_amdgcn_readlane(incl4[k], 63);
         }
     }
-    if (files_new) {
+    if (!UNIT && files_new) {
         if (new_row >= 0 && new_row < a.Rcap) *new_dst(blockIdx.x, new_row) = new_piece;
         for (int u = blockIdx.x + gridDim.x; u < a.units; u += gridDim.x) {     // (more units than workgroups)
             const int r = a.r_len[u];
             if (r >= 0 && r < a.Rcap) *new_dst(u, r) = *new_src(u);
         }
     }
-    if (__ballot(empties)) {                               // rare: look again, one unit at a time
+    if (!UNIT && __ballot(empties)) {                               // rare: look again, one unit at a time
         for (int uu = blockIdx.x; uu < NU; uu += gridDim.x) {
             const UnitItems it = unit_items(APPEND, a, uu);
             if (it.nq + it.nr == 0) zero_fill(uu);
@@ -275,29 +274,31 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
     }
     // The weight line is cut into NW ranges, each at least one residual item long.  NW is a power of two so
     // that the cuts need no division.
-    if (P == 0) return;
+    if (!UNIT && P == 0) return;
     const int nw_cap = max(1, min((int)gridDim.x, P / kWR));
-    nw_log = 31 - __builtin_clz(nw_cap);
-    const int NW = 1 << nw_log;
-    if ((int)blockIdx.x >= NW) return;
+    const int nw_log = 31 - __builtin_clz(nw_cap), NW = 1 << nw_log;
+    if (!UNIT && (int)blockIdx.x >= NW) return;
     // Wave numbers.  The hardware serves the older of the two waves on a SIMD first, so the workgroups
     // that were dispatched first (they fill the first wave slot of every SIMD, a.first_slot of them) get
     // through their passes measurably faster than the rest.  When the launch fills both slots, workgroup b
     // and workgroup b + a.first_slot take the neighbouring numbers 2b and 2b + 1, so that every unit is
     // served by both kinds in equal parts and all units finish together.
     const bool paired = NW == 2 * a.first_slot;
-    w = !paired ? (int)blockIdx.x
+    const int w = !paired ? (int)blockIdx.x
                 : (int)blockIdx.x < a.first_slot ? 2 * (int)blockIdx.x : 2 * ((int)blockIdx.x - a.first_slot) + 1;
     // (the wave in the first slot of a SIMD runs faster; both parts of a pair range must stay longer than one
     // item, so that every wave between the first and the last of a unit owns an item of it)
     const int want16 = min(max(a.skew16, 4), 12);
-    skew16 = paired && ((((2L * P) >> nw_log) * min(want16, 16 - want16)) >> 4) >= kWR ? want16 : 8;
-    start = range_start(w, P, nw_log, skew16), end = range_start(w + 1, P, nw_log, skew16);
+    const int skew16 = paired && ((((2L * P) >> nw_log) * min(want16, 16 - want16)) >> 4) >= kWR ? want16 : 8;
+    const long start = UNIT ? 0 : range_start(w, P, nw_log, skew16), end = UNIT ? 1 : range_start(w + 1, P, nw_log, skew16);
     // (NW / P as a wave-uniform value in a scalar register)
-    inv_p = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)NW / (float)P)));
+    const float inv_p = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)NW / (float)P)));
 
     // ---------------- the unit whose weight span holds position `start`
-    {
+    int up = UNIT ? (int)blockIdx.x : -1;
+    long ib = 0;                                           // position of the unit's first item
+    int T_first = unit_T, R_first = unit_R;                // its lengths
+    if (!UNIT) {
         long running = 0;
         for (int base = 0; base < NU && up < 0; base += 256) {
             if (!small) {
@@ -324,7 +325,6 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             }
         }
     }
-    }   // (not UNIT)
     const int up_first = up;
 
     const int blk4 = lane >> 2, row = lane & 3;            // block of 4 lanes; row = query head this lane
@@ -352,19 +352,15 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
         const int span = wt + kWR;
         const int ds = (int)min((long)span, max(0L, start - ib)), de = (int)min((long)span, max(0L, end - ib));
         const int dq = kWR * nf, db = dq + kWQ * it.nq;
-        int f0 = min(nf, (ds + kWR - 1) / kWR), f1 = min(nf, (de + kWR - 1) / kWR);
-        int j0 = min(it.nq, (max(0, ds - dq) + kWQ - 1) / kWQ), j1 = min(it.nq, (max(0, de - dq) + kWQ - 1) / kWQ);
-        int b0 = min(nb, (max(0, ds - db) + kWR - 1) / kWR), b1 = min(nb, (max(0, de - db) + kWR - 1) / kWR);
-        if constexpr (UNIT) {
-            // passes from the first wave on, residual items (even ones in front, odd ones at the back) from the last
-            constexpr int NWV = kUnitWaves<G>, HW = NWV / 2;
-            auto share = [](int n, int k, int of) { return (n * k + of - 1) / of; };
-            const int back = NWV - 1 - wave, k = back >> 1;
-            j0 = share(it.nq, wave, NWV), j1 = share(it.nq, wave + 1, NWV);
-            f0 = f1 = b0 = b1 = 0;
-            if (back & 1) b0 = share(nb, k, HW), b1 = share(nb, k + 1, HW);
-            else f0 = share(nf, k, HW), f1 = share(nf, k + 1, HW);
-        } else if (f0 >= f1 && j0 >= j1 && b0 >= b1) { ib = ib_next; continue; }
+        // (UNIT: passes from the first wave on, residual items -- even ones in front, odd ones at the back -- from the last)
+        constexpr int NWV = kUnitWaves<G>, HW = NWV / 2;
+        auto share = [](int n, int k, int of) { return (n * k + of - 1) / of; };
+        const int from_last = NWV - 1 - wave, kf = UNIT && !(from_last & 1) ? from_last >> 1 : 0, kb = UNIT && (from_last & 1) ? from_last >> 1 : 0;
+        const int on_f = UNIT && !(from_last & 1), on_b = UNIT && (from_last & 1);
+        const int f0 = UNIT ? share(nf, kf, HW) : min(nf, (ds + kWR - 1) / kWR), f1 = UNIT ? (on_f ? share(nf, kf + 1, HW) : 0) : min(nf, (de + kWR - 1) / kWR);
+        const int j0 = UNIT ? share(it.nq, wave, NWV) : min(it.nq, (max(0, ds - dq) + kWQ - 1) / kWQ), j1 = UNIT ? share(it.nq, wave + 1, NWV) : min(it.nq, (max(0, de - dq) + kWQ - 1) / kWQ);
+        const int b0 = UNIT ? share(nb, kb, HW) : min(nb, (max(0, ds - db) + kWR - 1) / kWR), b1 = UNIT ? (on_b ? share(nb, kb + 1, HW) : 0) : min(nb, (max(0, de - db) + kWR - 1) / kWR);
+        if (!UNIT && f0 >= f1 && j0 >= j1 && b0 >= b1) { ib = ib_next; continue; }
         const int u = up >> a.hs_shift, hs = up & (a.hsets - 1);
         const int bi = (int)fast_div((uint32_t)u, a.hkv_magic, a.hkv_shift);
         const int bq0 = bi * a.Hq + (u - bi * a.Hkv) * a.rep + hs * kNH;
