@@ -159,24 +159,29 @@ struct PtDecArgs {
     int Hq, Hkv, rep, Tcap, chunk, nchunk;
 };
 
-// A 16-bit half of a packed word holds NF = 16 / BITS codes.  A code field inside bits 0..9 of its half is, masked in
-// place, an fp16 SUBNORMAL, code * 2^(bit - 24), so one v_and_b32 "converts" two codes, one per half, and the matrix
-// instructions multiply them as they are.  The lower fields are taken from the word shifted left by 2, the upper ones
-// from the word shifted right by 6: both land at bits 2 + BITS*p, p = 0 .. P-1, the highest places that two shifts
-// reach.  The place matters: a matrix instruction aligns its sum by the exponent field, 2^-14 for a subnormal, and cuts
-// what is 24 bits below, so that next to a weight of 1 a code at bit 0 loses the weight's bits below 2^-14, always
-// downwards (1.7e-4 of the result on 6592 tokens of 2 bits; at bit 2 a quarter of that).
+// A 16-bit half of a packed word holds NF = 16 / BITS codes.  A code field moved to the top of its half's ten mantissa bits
+// under the exponent of 1 is the fp16 number 1 + code / 2^BITS: a shift and one v_and_or_b32 "convert" two codes, one per
+// half, exactly, and the same way for every field, so that one accumulator takes all of them and the other operand is used
+// as it is.  The ones are taken out by what the accumulator starts from: minus the sum of the other operand.  (Masked in
+// place, without the exponent, the fields are fp16 subnormals, a shift less per pair.  But a matrix instruction aligns its
+// sum by the exponent field, 2^-14 for a subnormal, and cuts what is 24 bits below, always downwards; and the power of two
+// that then belongs to a field's place has to go somewhere: with the weights it pushed those of small values below what
+// fp16 holds, error 5e-4 -> 1.8e-3 at 4 bits on values of deviation 1/64.)
 typedef _Float16 pt_half8 __attribute__((ext_vector_type(8)));
 typedef float pt_float4 __attribute__((ext_vector_type(4)));
 template <int BITS> struct PtFields {
     static constexpr int CPW = 32 / BITS, NF = 16 / BITS, P = NF / 2;
-    // 2^(22 - BITS*p): what a sum over place p is multiplied by
-    __device__ static constexpr float unscale(int p) { return 4194304.0f / (float)(1u << (BITS * p)); }
-    // operand of place p from two words: codes p, NF+p, P+p, NF+P+p of each, in this order
+    static constexpr float steps = (float)(1 << BITS);   // code = steps * (operand - 1)
+    __device__ static uint32_t pair(uint32_t w, int f)   // 1 + code / steps of fields f of both halves
+    {
+        const int up = 10 - BITS - BITS * f;
+        const uint32_t m = (((1u << BITS) - 1u) << (10 - BITS)) * 0x00010001u;
+        return ((up >= 0 ? w << up : w >> -up) & m) | 0x3C003C00u;
+    }
+    // operand p (0 .. P-1) from two words: codes p, NF+p, P+p, NF+P+p of each, in this order
     __device__ static pt_half8 operand(uint32_t w0, uint32_t w1, int p)
     {
-        const uint32_t m = ((((1u << BITS) - 1u) << 2) * 0x00010001u) << (BITS * p);
-        return __builtin_bit_cast(pt_half8, make_uint4((w0 << 2) & m, (w0 >> 6) & m, (w1 << 2) & m, (w1 >> 6) & m));
+        return __builtin_bit_cast(pt_half8, make_uint4(pair(w0, p), pair(w0, P + p), pair(w1, p), pair(w1, P + p)));
     }
     // code index (0 .. CPW-1) of half i (0..3) of a word's share of the operand
     __device__ static constexpr int code_at(int p, int i) { return p + (i & 1) * NF + (i >> 1) * P; }
@@ -317,25 +322,19 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
             for (int j = 0; j < 4; j++) s[tau][j] = 0.f;
 #pragma unroll
             for (int ns = 0; ns < NS; ns++) {
-                pt_float4 acc[P];
+                pt_float4 acc = {-qz[ns], -qz[ns], -qz[ns], -qz[ns]};
 #pragma unroll
-                for (int p = 0; p < P; p++) {
-                    acc[p] = pt_float4{0.f, 0.f, 0.f, 0.f};
+                for (int p = 0; p < P; p++)
 #pragma unroll
                     for (int wp = 0; wp < KW / 2; wp++)
-                        acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::operand(kw[tau][2 * wp], kw[tau][2 * wp + 1], p),
-                                                                        qb[ns][wp][p], acc[p], 0, 0, 0);
-                }
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::operand(kw[tau][2 * wp], kw[tau][2 * wp + 1], p),
+                                                                     qb[ns][wp][p], acc, 0, 0, 0);
                 const int g = ((ns * 16 + col) / REPT) % NG;
                 const h4 ks = *reinterpret_cast<const h4 *>(&meta[wave][0][g][at(tau)]);
                 const h4 kz = *reinterpret_cast<const h4 *>(&meta[wave][1][g][at(tau)]);
 #pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    float d = 0.f;
-#pragma unroll
-                    for (int p = 0; p < P; p++) d = __builtin_fmaf(acc[p][j], F::unscale(p), d);
-                    s[tau][j] += __builtin_fmaf((float)ks[j], d, (float)kz[j] * qz[ns]);
-                }
+                for (int j = 0; j < 4; j++)
+                    s[tau][j] += __builtin_fmaf((float)ks[j], acc[j] * F::steps, (float)kz[j] * qz[ns]);
             }
 #pragma unroll
             for (int d = REPT; d < (NG * REPT > 16 ? 16 : NG * REPT); d <<= 1)       // the other groups of the token
@@ -391,18 +390,21 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
                 const int sw = tau / (CPW / 4), e = 4 * (tau % (CPW / 4)) + j;       // code e of word sw
                 const int hi = e / F::NF, up = (e % F::NF) / P, p = e % P;
                 const int at_op = sw * 4 + up * 2 + hi;
-                // (the place's power of two goes with the weight, so that one sum takes all places)
-                const float wp = p ? w[j] * (1.0f / (float)(1u << (BITS * p))) : w[j];
-                const float wa = wp * (float)vsA[j];
-                wb[0][p][at_op] = (_Float16)wa;
-                if constexpr (NB == 2) {
-                    const float wz = wp * (float)vsB[j];
-                    wb[NB - 1][p][at_op] = (_Float16)wz;
-                    }
+                wb[0][p][at_op] = (_Float16)(w[j] * (float)vsA[j]);
+                if constexpr (NB == 2) wb[NB - 1][p][at_op] = (_Float16)(w[j] * (float)vsB[j]);
             }
         }
         l = __builtin_fmaf(l, alpha, sum);
-        // ---- weighted values: 16 channels a tile
+        // ---- weighted values: 16 channels a tile, from minus the sum of the weights as they were rounded
+        pt_float4 minus[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++) {
+            const _Float16 n1 = (_Float16)-1.0f;
+            minus[nb] = pt_float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int p = 0; p < P; p++)
+                minus[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pt_half8{n1, n1, n1, n1, n1, n1, n1, n1}, wb[nb][p], minus[nb], 0, 0, 0);
+        }
 #pragma unroll
         for (int half = 0; half < 2; half++)
 #pragma unroll
@@ -410,12 +412,12 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
                 const uint4 q0 = vc[half][0], q1 = vc[half][1];
                 const uint32_t w0 = i == 0 ? q0.x : i == 1 ? q0.y : i == 2 ? q0.z : q0.w;
                 const uint32_t w1 = i == 0 ? q1.x : i == 1 ? q1.y : i == 2 ? q1.z : q1.w;
-                pt_float4 acc = {0.f, 0.f, 0.f, 0.f};
+                pt_float4 acc = minus[NB == 2 ? half : 0];
 #pragma unroll
                 for (int p = 0; p < P; p++)
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::operand(w0, w1, p), wb[NB == 2 ? half : 0][p], acc, 0, 0, 0);
 #pragma unroll
-                for (int j = 0; j < 4; j++) o[half][i][j] = __builtin_fmaf(acc[j], F::unscale(0), o[half][i][j]);
+                for (int j = 0; j < 4; j++) o[half][i][j] = __builtin_fmaf(acc[j], F::steps, o[half][i][j]);
                 if (NT == 8) asm volatile("" : "+v"(o[half][i])::"memory");
             }
         __builtin_amdgcn_wave_barrier();

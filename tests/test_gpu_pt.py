@@ -157,6 +157,58 @@ def test_large_and_small_magnitudes(bits, kscale, vscale, qscale):
     assert np.max(np.abs(got - want.astype(np.float32))) <= bar
 
 
+def _quantized(x, G, bits):
+    """Codes, scales and zero-points of fp16 rows x [T, 128], per token and group of G, as [T, 128] float64 each."""
+    levels = np.float32((1 << bits) - 1)
+    g = x.reshape(x.shape[0], 128 // G, G)
+    zero = g.min(2, keepdims=True)
+    scale = ((g.max(2, keepdims=True).astype(np.float32) - zero.astype(np.float32)) / levels).astype(np.float16)
+    inv = np.where(scale > 0, np.float32(1.0) / np.maximum(scale, np.float16(6e-8)).astype(np.float32), np.float32(0.0))
+    code = np.clip(np.rint((g.astype(np.float32) - zero.astype(np.float32)) * inv), 0, levels)
+    return [np.broadcast_to(a, g.shape).reshape(x.shape).astype(np.float64) for a in (code, scale, zero)]
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("G", [32, 128])
+@pytest.mark.parametrize("vstd,qstd,outliers", [(1.0, 1.0, False), (1.0, 1.0, True), (1.0 / 32, 1.0, False), (1.0 / 64, 1.57, False),
+                                                (1.0 / 256, 1.57, False), (0.1, 3.0, False)])
+def test_error_is_that_of_one_rounding_of_the_weights(bits, G, vstd, qstd, outliers):
+    """Values of small deviation, peaked scores and outlier query channels, judged relative to the result.  The only
+    roundings to 16 bits are those of weight x V scale and of the result, so the bar is the error that these two make in
+    64-bit arithmetic, and half of it for the other rounding that the kernel's own running maximum gives the weights."""
+    from paper_2411_18077_amd import api
+    T, Hkv, rep = 4096, 2, 4
+    rng = np.random.default_rng(bits + G)
+    K, V = (rng.standard_normal((Hkv, T, 128)).astype(np.float16) for _ in range(2))
+    q = (rng.standard_normal((Hkv, rep, 128)) * qstd).astype(np.float16)
+    if outliers:                                           # a few large query channels that meet small keys
+        q[..., :4] *= np.float16(64.0)
+        K[..., :4] *= np.float16(1.0 / 64)
+    V *= np.float16(vstd)
+    sm = 1.0 / math.sqrt(128)
+    want, bar = [], []
+    for u in range(Hkv):
+        (kc, ks, kz), (vc, vs, vz) = _quantized(K[u], G, bits), _quantized(V[u], G, bits)
+        s = q[u].astype(np.float64) @ (kc * ks + kz).T * sm
+        p = np.exp(s - s.max(1, keepdims=True))
+        total = p.sum(1, keepdims=True)
+        want.append(p @ (vc * vs + vz) / total)
+        once = np.stack([((ph[:, None] * vs).astype(np.float16).astype(np.float64) * vc).sum(0) for ph in p])
+        bar.append(((once + p @ vz) / total).astype(np.float16).astype(np.float64))
+    want, bar = np.stack(want), np.stack(bar)
+    shape = api.make_pt_shape(1, Hkv * rep, Hkv, 128, G, bits, T)
+    c = api.PtCache(shape)
+    n_tok = torch.full((Hkv,), T, dtype=torch.int32, device="cuda")
+    api.kv_quantize_pack_pt(shape, torch.from_numpy(K).cuda(), torch.from_numpy(V).cuda(), T, None, 0, n_tok, T, c)
+    out = torch.full((1, Hkv * rep, 128), float("nan"), dtype=torch.float16, device="cuda")
+    api.minikv_decode_attn_pt(shape, torch.from_numpy(q.reshape(1, Hkv * rep, 128)).cuda(), c, sm, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.float64).reshape(Hkv, rep, 128)
+    norm = np.linalg.norm(want)
+    err, limit = np.linalg.norm(got - want) / norm, 1.5 * np.linalg.norm(bar - want) / norm
+    assert err <= limit, (err, limit)
+
+
 def test_benchmarked_shape_on_sampled_units():
     """The shape bench.py times (batch 16, 32 query / 8 KV heads, 13088 of 32768 tokens kept, 4 bits, one group
     per head): the oracle takes eight sampled units as a problem of its own (units are independent), the GPU
