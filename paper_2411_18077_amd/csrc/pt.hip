@@ -160,23 +160,27 @@ struct PtDecArgs {
 };
 
 // A 16-bit half of a packed word holds NF = 16 / BITS codes.  A code field moved to the top of its half's ten mantissa bits
-// under the exponent of 1 is the fp16 number 1 + code / 2^BITS: a shift and one v_and_or_b32 "convert" two codes, one per
-// half, exactly, and the same way for every field, so that one accumulator takes all of them and the other operand is used
-// as it is.  The ones are taken out by what the accumulator starts from: minus the sum of the other operand.  (Masked in
-// place, without the exponent, the fields are fp16 subnormals, a shift less per pair.  But a matrix instruction aligns its
-// sum by the exponent field, 2^-14 for a subnormal, and cuts what is 24 bits below, always downwards; and the power of two
-// that then belongs to a field's place has to go somewhere: with the weights it pushed those of small values below what
-// fp16 holds, error 5e-4 -> 1.8e-3 at 4 bits on values of deviation 1/64.)
+// under the exponent of 2^BITS is the fp16 number 2^BITS + code: a shift and one v_and_or_b32 "convert" two codes, one per
+// half, exactly, and every field's place counts the same, so that one accumulator takes them all and the other operand is
+// used as it is.  (Two bits: neighbouring fields share a shift, the lower one is 16 + code.)  The constant is taken out by
+// what the accumulator starts from: minus the sum of the other operand times it.  Masked in place, without the exponent,
+// the fields are fp16 subnormals, at 4 bits half the shifts.  But a matrix instruction aligns its sum by the exponent field,
+// 2^-14 for a subnormal, and cuts what is 24 bits below, always downwards; and the power of two that then belongs to a
+// field's place has to go somewhere: with the weights it pushed those of small values below what fp16 holds, error
+// 5e-4 -> 1.8e-3 at 4 bits on values of deviation 1/64.
 typedef _Float16 pt_half8 __attribute__((ext_vector_type(8)));
 typedef float pt_float4 __attribute__((ext_vector_type(4)));
 template <int BITS> struct PtFields {
     static constexpr int CPW = 32 / BITS, NF = 16 / BITS, P = NF / 2;
-    static constexpr float steps = (float)(1 << BITS);   // code = steps * (operand - 1)
-    __device__ static uint32_t pair(uint32_t w, int f)   // 1 + code / steps of fields f of both halves
+    __device__ static constexpr int bit(int f) { return BITS == 2 && !(f & 1) ? 6 : 10 - BITS; }   // where field f goes
+    // the fields of operand p are this + code
+    __device__ static constexpr float base(int p) { return (float)(1 << (10 - bit(p))); }
+    __device__ static uint32_t pair(uint32_t w, int f)   // field f of both halves
     {
-        const int up = 10 - BITS - BITS * f;
-        const uint32_t m = (((1u << BITS) - 1u) << (10 - BITS)) * 0x00010001u;
-        return ((up >= 0 ? w << up : w >> -up) & m) | 0x3C003C00u;
+        const int up = bit(f) - BITS * f;
+        const uint32_t m = (((1u << BITS) - 1u) << bit(f)) * 0x00010001u;
+        const uint32_t e = (uint32_t)(15 + 10 - bit(f)) * 0x04000400u;
+        return ((up >= 0 ? w << up : w >> -up) & m) | e;
     }
     // operand p (0 .. P-1) from two words: codes p, NF+p, P+p, NF+P+p of each, in this order
     __device__ static pt_half8 operand(uint32_t w0, uint32_t w1, int p)
@@ -195,9 +199,10 @@ template <int BITS> struct PtFields {
 // 128 bits at a time.  Column n of a score product holds head n % REPT and, where a token has several channel groups,
 // only group (n / REPT) % NG of it (the query is zero elsewhere), so that every group meets its own scale; the groups
 // are added across lanes afterwards.
-// What bounds it: memory (136 bytes per token at 4 bits with one group); a form with one dot2 per pair of codes and
-// head was bound by its vector instructions.  128 units x 13088 tokens, 4 heads each, G = 128: 4 bits 79 -> 45 us
-// (5.1 TB/s; a plain copy reaches 5.0), 2 bits 81 -> 50, 8 bits 109 -> 81; 32 units x 8 heads x 8192 tokens 41 -> 16 us.
+// What bounds it: memory (136 bytes per token at 4 bits with one group) and, nearly as much, the vector instructions that
+// make operands of codes and weights; a form with one dot2 per pair of codes and head was bound by those alone.  Calls of
+// 128 units x 13088 tokens, 4 heads each, G = 128: 4 bits 79 -> 52 us (4.4 TB/s; a plain copy reaches 5.0), 2 bits
+// 82 -> 46.5, 8 bits 110 -> 83; 16 units 23 -> 16 us; G = 32, 128 units x 8192 tokens 63 -> 41 us.
 template <int BITS, int G, int REPT>
 __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
 {
@@ -263,15 +268,18 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
 
     // the query as operand: [column set][pair of words][position]; heads beyond rep repeat the last one, unused
     pt_half8 qb[NS][KW / 2][P];
-    float qz[NS];                                       // sum of the query over the column's group
+    float qz[NS], minus_q[NS];                          // sum of the query over the column's group; minus that of its bases
     {
         const _Float16 *qr = reinterpret_cast<const _Float16 *>(a.q) + (size_t)(bq0 + min(h, rep - 1)) * kD + kg * 32;
         pt_half8 qv[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) qv[i] = reinterpret_cast<const pt_half8 *>(qr)[i];
-        float sum = 0.f;
+        float sum = 0.f, based = 0.f;
 #pragma unroll
-        for (int c = 0; c < 32; c++) sum += (float)qv[c >> 3][c & 7];
+        for (int c = 0; c < 32; c++) {
+            sum += (float)qv[c >> 3][c & 7];
+            based = __builtin_fmaf((float)qv[c >> 3][c & 7], F::base(c % CPW % P), based);
+        }
 #pragma unroll
         for (int ns = 0; ns < NS; ns++) {
             const bool mine = kg * 32 / G == ((ns * 16 + col) / REPT) % NG;
@@ -287,6 +295,9 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
             qz[ns] = mine ? sum : 0.f;
             qz[ns] += __shfl_xor(qz[ns], 16);
             qz[ns] += __shfl_xor(qz[ns], 32);
+            minus_q[ns] = mine ? -based : 0.f;
+            minus_q[ns] += __shfl_xor(minus_q[ns], 16);
+            minus_q[ns] += __shfl_xor(minus_q[ns], 32);
         }
     }
 
@@ -322,7 +333,7 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
             for (int j = 0; j < 4; j++) s[tau][j] = 0.f;
 #pragma unroll
             for (int ns = 0; ns < NS; ns++) {
-                pt_float4 acc = {-qz[ns], -qz[ns], -qz[ns], -qz[ns]};
+                pt_float4 acc = {minus_q[ns], minus_q[ns], minus_q[ns], minus_q[ns]};
 #pragma unroll
                 for (int p = 0; p < P; p++)
 #pragma unroll
@@ -334,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
                 const h4 kz = *reinterpret_cast<const h4 *>(&meta[wave][1][g][at(tau)]);
 #pragma unroll
                 for (int j = 0; j < 4; j++)
-                    s[tau][j] += __builtin_fmaf((float)ks[j], acc[j] * F::steps, (float)kz[j] * qz[ns]);
+                    s[tau][j] += __builtin_fmaf((float)ks[j], acc[j], (float)kz[j] * qz[ns]);
             }
 #pragma unroll
             for (int d = REPT; d < (NG * REPT > 16 ? 16 : NG * REPT); d <<= 1)       // the other groups of the token
@@ -395,15 +406,16 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
             }
         }
         l = __builtin_fmaf(l, alpha, sum);
-        // ---- weighted values: 16 channels a tile, from minus the sum of the weights as they were rounded
+        // ---- weighted values: 16 channels a tile, from minus the sum of the (rounded) weights times the codes' bases
         pt_float4 minus[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; nb++) {
-            const _Float16 n1 = (_Float16)-1.0f;
             minus[nb] = pt_float4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int p = 0; p < P; p++)
-                minus[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pt_half8{n1, n1, n1, n1, n1, n1, n1, n1}, wb[nb][p], minus[nb], 0, 0, 0);
+            for (int p = 0; p < P; p++) {
+                const _Float16 n = (_Float16)-F::base(p);
+                minus[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pt_half8{n, n, n, n, n, n, n, n}, wb[nb][p], minus[nb], 0, 0, 0);
+            }
         }
 #pragma unroll
         for (int half = 0; half < 2; half++)
@@ -417,7 +429,7 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
                 for (int p = 0; p < P; p++)
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::operand(w0, w1, p), wb[NB == 2 ? half : 0][p], acc, 0, 0, 0);
 #pragma unroll
-                for (int j = 0; j < 4; j++) o[half][i][j] = __builtin_fmaf(acc[j], F::steps, o[half][i][j]);
+                for (int j = 0; j < 4; j++) o[half][i][j] += acc[j];
                 if (NT == 8) asm volatile("" : "+v"(o[half][i])::"memory");
             }
         __builtin_amdgcn_wave_barrier();
