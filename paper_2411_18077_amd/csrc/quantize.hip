@@ -7,8 +7,8 @@
 // One workgroup of 256 threads takes a block of BT = max(64, G) consecutive retained tokens of one unit:
 // the fp16 rows are gathered (Algorithm 1 line 3: only retained rows are read) into LDS with 128-bit
 // loads, group statistics are taken from LDS, and each thread then builds whole 32-bit words so that
-// every store is a full word and consecutive threads write consecutive addresses.  Where a unit's tokens fit into at
-// most four blocks (every flush of a residual of up to 256 tokens), one workgroup of 256 threads per block takes the
+// every store is a full word and consecutive threads write consecutive addresses.  Where a unit's tokens fit into a few
+// blocks and the units are few (a flush of the residual, as a rule), one workgroup of 256 threads per block takes the
 // whole unit and writes its lengths as well: no second launch.
 #include "common.h"
 
@@ -123,9 +123,10 @@ struct WordAcc {
 };
 
 // NSUB == 0: a workgroup is one block of a unit of any length (update_lengths_kernel follows).  NSUB > 0: a workgroup is a
-// whole unit of at most NSUB blocks, 256 threads each, and leaves the new lengths when it is done.
+// whole unit of at most NSUB blocks, 256 threads each, and leaves the new lengths when it is done.  (The second launch bound
+// keeps G = 64 in 64 registers, eight waves per SIMD, where the compiler would take 67: 1024 units x 256 tokens 45.5 -> 43.3 us.)
 template <int G, int NSUB>
-__global__ __launch_bounds__(256 * (NSUB ? NSUB : 1)) void quantize_pack_kernel(QuantArgs a)
+__global__ __launch_bounds__(256 * (NSUB ? NSUB : 1), G == 64 && NSUB == 0 ? 8 : 1) void quantize_pack_kernel(QuantArgs a)
 {
     constexpr bool kWholeUnit = NSUB > 0;
     constexpr int kSub = kWholeUnit ? NSUB : 1;
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(256 * (NSUB ? NSUB : 1)) void quantize_pack_kernel(
     __shared__ __attribute__((aligned(16))) float2 pars[kSub][NPAR];   // (-zero, 1/scale) of every group
 
     const int u = blockIdx.y;
-    const int tid = threadIdx.x & 255, sub = kWholeUnit ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+    const int tid = kWholeUnit ? threadIdx.x & 255 : threadIdx.x, sub = kWholeUnit ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
     uint16_t *tile = tiles[sub];
     float2 *par = pars[sub];
     float one = 1.0f;
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(256 * (NSUB ? NSUB : 1)) void quantize_pack_kernel(
     const int n = tokens_to_append<G>(a, u, q0);
     const int i0 = (kWholeUnit ? sub : (int)blockIdx.x) * BT;
     if (kWholeUnit ? n == 0 : i0 >= n) return;         // (uniform in the workgroup)
-    const int nt = max(min(n - i0, BT), 0);            // multiple of G; 0: a block the unit does not reach
+    const int nt = kWholeUnit ? max(min(n - i0, BT), 0) : n - i0 < BT ? n - i0 : BT;            // multiple of G; 0: a block the unit does not reach
     const int t0 = q0 + i0;                            // first destination token, multiple of G
 
     // ---------------- K: groups of G tokens per channel.  Statistics: one thread per (group, channel pair),
@@ -303,15 +304,23 @@ static int launch_quantize_g(const QuantArgs &a, int units, int max_tok, hipStre
 {
     constexpr int BT = G > 64 ? G : 64;
     const int nblk = (max_tok + BT - 1) / BT;
-    // One workgroup per unit up to four blocks of 64 tokens: no launch of update_lengths_kernel behind this one (append +
-    // flush + attend, 256 units, 128 residual rows: 40.2 -> 38.9 us).
-    if (nblk * BT <= 256) {
+    // One workgroup per unit, and no launch of update_lengths_kernel behind this one, where a unit is a single block, or up
+    // to four blocks of 64 tokens as long as the launch holds no more than four blocks per compute unit: then all of them
+    // run at once in either form (256 units x 128 rows, the call: 17.1 -> 13.9 us; 256 x 256 17.1 -> 17.0; 512 x 128
+    // 17.0 -> 14.4).  Beyond that a workgroup of two or four blocks stops for each of its barriers as one, and four take
+    // the local memory of half a compute unit (320 x 256 17.7 -> 27.2 us, 1024 x 256 42.9 -> 64.0, 1024 x 128
+    // 23.5 -> 25.6).  Two blocks of 128 tokens in one workgroup gain nothing at any count (64 x 256 17.4 -> 20.0 us).
+    constexpr int kComputeUnits = 256;
+    const int sub = nblk <= 2 ? nblk : 4;
+    if (nblk == 1 || (BT == 64 && nblk <= 4 && (int64_t)units * sub <= 4 * kComputeUnits)) {
         if (nblk == 1)
             hipLaunchKernelGGL((quantize_pack_kernel<G, 1>), dim3(1, units), dim3(256), 0, st, a);
-        else if (nblk == 2)
-            hipLaunchKernelGGL((quantize_pack_kernel<G, 2>), dim3(1, units), dim3(512), 0, st, a);
-        else if constexpr (BT == 64)
-            hipLaunchKernelGGL((quantize_pack_kernel<G, 4>), dim3(1, units), dim3(1024), 0, st, a);
+        else if constexpr (BT == 64) {
+            if (nblk == 2)
+                hipLaunchKernelGGL((quantize_pack_kernel<G, 2>), dim3(1, units), dim3(512), 0, st, a);
+            else
+                hipLaunchKernelGGL((quantize_pack_kernel<G, 4>), dim3(1, units), dim3(1024), 0, st, a);
+        }
         return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
     }
     hipLaunchKernelGGL((quantize_pack_kernel<G, 0>), dim3(nblk, units), dim3(256), 0, st, a);

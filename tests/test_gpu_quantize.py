@@ -173,3 +173,21 @@ def test_short_calls_with_lengths_up_to_the_bound(g, G):
     inp.n_tok.copy_(torch.tensor([0, G, 2 * G, 128, 256, 256 - G, 128 + G if G < 128 else 256, 128], dtype=torch.int32))
     s, rs = g.shapes_for(w, inp.Tcap)
     g.assert_cache_bit_exact(g.gpu_build_cache(inp, s), g.ref_build_cache(inp, rs))
+
+
+@pytest.mark.parametrize("G,T,B", [(16, 256, 64), (16, 192, 65), (32, 256, 65), (64, 192, 64), (32, 128, 128), (16, 128, 129),
+                                   (64, 128, 129), (32, 64, 260), (128, 256, 8), (128, 128, 65)])
+def test_short_calls_of_many_units(g, G, T, B):
+    """Up to four blocks per unit at the unit counts where a unit stops being one workgroup (256 of four blocks, 512 of two)
+    and beyond, with lengths of every kind; the oracle takes sampled units."""
+    w = small(G, B=B, Hkv=4, Hq=4, L=T, keep=1.0)
+    inp = W.make_inputs(w, "cuda")
+    n = torch.tensor([T, 0, G, T - G, T // 2 // G * G], dtype=torch.int32, device="cuda")
+    inp.n_tok.copy_(n.repeat(w.units // 5 + 1)[: w.units])
+    s, rs = g.shapes_for(w, inp.Tcap)
+    units = sorted(set([0, 1, 2, 3, 4, w.units // 2] + list(range(w.units - 6, w.units))))
+    one = small(G, B=len(units), Hkv=1, Hq=1, L=T, keep=1.0)
+    _, rs = g.shapes_for(one, inp.Tcap)
+    gc = g.gpu_build_cache(inp, s)
+    assert gc.q_len.cpu().tolist() == inp.n_tok.cpu().tolist()
+    g.assert_cache_bit_exact(gc, g.ref_build_cache(inp, rs, units=units), unit_map=units)
