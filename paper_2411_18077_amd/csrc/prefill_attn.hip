@@ -94,13 +94,11 @@ __device__ __forceinline__ half4 read_transposed(const _Float16 *p)
 }
 
 // SPLIT == 2: two sets of WAVES waves take the even and the odd tiles of the same queries, each through LDS buffers of
-// its own, and meet at the end; for launches that leave a compute unit a single set.  (The second launch bound keeps
-// every instance in 256 registers: with more the accumulators go to the registers only matrix instructions reach.  Two
-// sets of two waves never have two waves on a SIMD, about which the compiler would warn.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Wpass-failed"
+// its own, and meet at the end; for launches that leave a compute unit a single set.  (The second launch bound keeps the
+// accumulators out of the registers only matrix instructions reach.  Two sets of two waves never have two waves on a SIMD:
+// they use the registers of both, the second half as accumulation registers.)  No instance has a private segment.
 template <int WAVES, int SPLIT>
-__global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(PrefillArgs a)
+__global__ __launch_bounds__(64 * WAVES * SPLIT, SPLIT == 2 && WAVES == 2 ? 1 : 2) void prefill_fwd_kernel(PrefillArgs a)
 {
     constexpr int kRows = kPfN / WAVES, kLoads = kRows / 4;     // rows of a tile one wave loads, four per instruction
     __shared__ __align__(16) _Float16 tiles[SPLIT][4 * kPfTile];
@@ -139,14 +137,13 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
         k_off[i] = (lane >> 4) * 256u + (((lane & 15) ^ ((wave * kRows + i * 4 + (lane >> 4)) & 15)) << 4);
     const unsigned k_lds = lds_offset(Ks) + wave * (kRows * 256u), v_lds = lds_offset(Vs) + wave * (kRows * 256u);
     // (no branch: code motion across one would take the interleaving below apart.  Lanes whose row lies past the
-    // prompt load the last chunk of its last row, any finite value will do: their weights are 0.  A tile past the
-    // last repeats that one into a buffer nobody reads any more.)
-    const int last_tile = (L - 1) / kPfN;
+    // prompt load the last chunk of its last row, any finite value will do: their weights are 0.  For a tile past the
+    // last one that counts every lane loads the same bytes, into a buffer nobody reads any more: nearly nothing moves.)
     auto request = [&](const _Float16 *base, int n, bool is_v) {
-        const int row0 = min(n * SPLIT + set, last_tile) * kPfN + wave * kRows;
+        const int t = n * SPLIT + set, row0 = min(t, all - 1) * kPfN + wave * kRows;
         const char *tile = (const char *)(base + (long)min(row0, L - 1) * kPfD);
         const unsigned lds = (is_v ? v_lds : k_lds) + (n & 1) * (kPfTile * 2u);
-        const int end = max(L - 1 - row0, 0) * 256 + 240;
+        const int end = t < all ? max(L - 1 - row0, 0) * 256 + 240 : 0;
 #pragma unroll
         for (int i = 0; i < kLoads; ++i)
             load_to_lds(tile, (unsigned)min((int)(is_v ? v_off : k_off[i]) + i * 1024, end), lds + i * 1024u);
@@ -165,11 +162,11 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
         for (int db = 0; db < 4; ++db)
             v_place[db] = row * kPfD + (((4 * db + c0) ^ v_swizzle(row)) << 3) + (i & 1) * 4;
     }
-    auto read_k = [&](int j, int n) -> half8 {         // fragment j of tile n: keys 32 (j & 1) .., channels 16 (j >> 1) ..
-        return *(const half8 *)(Ks + (n & 1) * kPfTile + (j & 1) * 32 * kPfD + k_place[j >> 1]);
+    auto read_k = [&](int j, int odd) -> half8 {       // fragment j of an even / odd tile: keys 32 (j & 1) .., channels 16 (j >> 1) ..
+        return *(const half8 *)(Ks + odd * kPfTile + (j & 1) * 32 * kPfD + k_place[j >> 1]);
     };
-    auto read_v = [&](int j, int n) -> half8 {         // fragment j: keys 16 (j >> 2) + 4 g + {0..3, 8..11}, channels 32 (j & 3) + r
-        const _Float16 *p = Vs + (n & 1) * kPfTile + (j >> 2) * 16 * kPfD + v_place[j & 3];
+    auto read_v = [&](int j, int odd) -> half8 {         // fragment j: keys 16 (j >> 2) + 4 g + {0..3, 8..11}, channels 32 (j & 3) + r
+        const _Float16 *p = Vs + odd * kPfTile + (j >> 2) * 16 * kPfD + v_place[j & 3];
         const half4 lo = read_transposed(p), hi = read_transposed(p + 8 * kPfD);
         return half8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     };
@@ -209,8 +206,9 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
     };
 
     // tile n: scores in cur, their maximum settled, K fragments 0-3 of tile n+1 in kf.  `multiply`: there is a tile n+1
-    // for this wave; `masked`: it may reach past a query.
-    auto step = [&](float16v (&cur)[2], float16v (&next)[2], int n, auto multiply, auto masked) {
+    // for this wave.
+    auto step = [&](float16v (&cur)[2], float16v (&next)[2], int n, auto multiply, auto parity, auto masked) {
+        constexpr int odd = decltype(parity)::value;
         half8 pb[4];                                   // B operands of the output product: the weights as fp16
         float x[2], y[2], sum[2] = {0.0f, 0.0f};
         // weights 2e, 2e+1 of this lane pass through three stages (exponent, power, sum) in three consecutive slots
@@ -218,6 +216,7 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
             if (e >= 2 && e <= 17) {
                 const int w = 2 * (e - 2);
                 sum[0] += y[0], sum[1] += y[1];
+                asm volatile("" : "+v"(sum[0]), "+v"(sum[1]));      // (else the sums of the last step sink to where they are used, and every weight lives until then)
                 pb[w >> 3][w & 7] = (_Float16)y[0], pb[w >> 3][(w & 7) + 1] = (_Float16)y[1];
             }
             if (e >= 1 && e <= 16) y[0] = __builtin_amdgcn_exp2f(x[0]), y[1] = __builtin_amdgcn_exp2f(x[1]);
@@ -238,14 +237,14 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
         for (int j = 0; j < 16; ++j) {
             if (decltype(multiply)::value) {
                 next[j & 1] = mfma32(kf[j & 3], qf[j >> 1], next[j & 1]);
-                if (j < 12) kf[j & 3] = read_k(j + 4, n + 1);
+                if (j < 12) kf[j & 3] = read_k(j + 4, !odd);
             }
             if (j < 13) slot(j + 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         hand_over();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) vf[j] = read_v(j, n);
+        for (int j = 0; j < 4; ++j) vf[j] = read_v(j, odd);
         request(Vh, n + 1, true);
         request(Kh, n + 3, false);
         float mx[4];
@@ -254,8 +253,8 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             o[j & 3] = mfma32(vf[j & 3], pb[j >> 2], o[j & 3]);
-            if (j < 12) vf[j & 3] = read_v(j + 4, n);
-            if (decltype(multiply)::value && j >= 12) kf[j & 3] = read_k(j & 3, n + 2);   // (past the last tile: unused)
+            if (j < 12) vf[j & 3] = read_v(j + 4, odd);
+            if (decltype(multiply)::value && j >= 12) kf[j & 3] = read_k(j & 3, odd);   // (past the last tile: unused)
             if (j < 4) slot(j + 14);
             if (decltype(multiply)::value && j >= 4 && j < 12) {
                 const int e = 4 * (j - 4), t = e >> 4, i = e & 15, k = j & 3;
@@ -298,19 +297,20 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
     if (SPLIT == 1 || mytiles > 0) {
         int n = 0;
         for (; n + 2 < nfull; n += 2) {
-            step(sa, sb, n, yes, no);
-            step(sb, sa, n + 1, yes, no);
+            step(sa, sb, n, yes, no, no);
+            step(sb, sa, n + 1, yes, yes, no);
         }
         for (; n + 2 < mytiles; n += 2) {
-            step(sa, sb, n, yes, yes);
-            step(sb, sa, n + 1, yes, yes);
+            step(sa, sb, n, yes, no, yes);
+            step(sb, sa, n + 1, yes, yes, yes);
         }
+        // (one copy of the last step: with one for either parity the compiler keeps state of both and spills)
         if (n + 1 < mytiles) {
-            step(sa, sb, n, yes, yes);
-            step(sb, sa, n + 1, no, no);
-        } else {
-            step(sa, sb, n, no, no);
+            step(sa, sb, n, yes, no, yes);
+            sa[0] = sb[0], sa[1] = sb[1];
+            Vs += kPfTile, ++n;
         }
+        step(sa, sb, n, no, no, no);
     }
     for (int n = mytiles; n < ntiles; ++n) {           // tiles only other waves see: this one still loads its share
         hand_over();
@@ -353,8 +353,6 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
     }
 }
 
-#pragma clang diagnostic pop
-
 // A workgroup owns 128 keys and walks the queries from the diagonal down in tiles of 64 through LDS.  Wave (kw, qw)
 // holds the K rows of 64 of the keys as B operands and takes 32 of a tile's queries, so that every Q fragment read
 // from LDS feeds two products.  The products of tile n+1 and the exponentials of tile n stand side by side in one
@@ -364,9 +362,10 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
 // counts is energy as well as issue slots.  Q tiles therefore go straight to LDS: staging them through registers cost
 // 12 % of the cycles (the LDS stores stall the stream).  32 heads x 32768 tokens 4.85 -> 4.47 ms (980 TFLOP/s),
 // 32 x 2048 32 -> 25 us, 32 x 777 15.6 -> 12.3 us.  Three LDS buffers instead of two: the same.
-__global__ __launch_bounds__(256, 2) void prefill_colsum_kernel(PrefillArgs a)
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves, 2) void prefill_colsum_kernel(PrefillArgs a)
 {
-    constexpr int kWaves = 4, kKeyWaves = kWaves / 2, kKeys = 64 * kKeyWaves;
+    constexpr int kKeyWaves = kWaves / 2, kKeys = 64 * kKeyWaves;
     constexpr int kRows = kPfN / kWaves, kLoads = kRows / 4;    // rows of a tile one wave loads, four per instruction
     __shared__ __align__(16) _Float16 Qs[2 * kPfN * kPfD];
     __shared__ __align__(16) float lse2[4 * kPfN];     // LSE of a tile's queries in powers of two; read one iteration
@@ -394,24 +393,19 @@ __global__ __launch_bounds__(256, 2) void prefill_colsum_kernel(PrefillArgs a)
 
     const float c = a.scale_log2;
     const int tile0 = kb * kKeyWaves, ntiles = (L + kPfN - 1) / kPfN;
-    // A wave loads kRows consecutive rows of a tile; rows past the prompt repeat its last one
-    // (their weights are masked), tiles past the last repeat that one and are never used.
+    // A wave loads kRows consecutive rows of a tile; lanes whose row lies past the prompt load the last chunk of its last
+    // row (their weights are masked), and for a tile past the last every lane loads the same bytes: nearly nothing moves.
     const unsigned q_lds = lds_offset(Qs) + wave * (kRows * 256u);
-    unsigned q_off[kLoads], q_end[kLoads];
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-        const int row = wave * kRows + i * 4 + (lane >> 4), chunk = (lane & 15) ^ (row & 15);
-        q_off[i] = row * 256u + chunk * 16u;
-        q_end[i] = (unsigned)(L - 1) * 256u + chunk * 16u;
-    }
-    float lr = 0.0f;
-    auto request = [&](int n) {
+    const unsigned q_off = (wave * kRows + (lane >> 4)) * 256u + (((lane & 15) ^ (lane >> 4)) << 4);    // of the first load
+    auto request = [&](int n) -> float {               // returns the LSE of query `lane` of the tile
         const unsigned tile = (unsigned)min(n, ntiles - 1) * (kPfN * 256u);
+        const unsigned end = n < ntiles ? (unsigned)(L - 1) * 256u + 240u : 0u;
 #pragma unroll
         for (int i = 0; i < kLoads; ++i)
-            load_to_lds(Qh, min(q_off[i] + tile, q_end[i]), q_lds + (n & 1) * (kPfN * 256u) + i * 1024u);
-        lr = lseh[min(n * kPfN + lane, L - 1)];        // (each wave the same 64: no branch in the stream)
+            load_to_lds(Qh, min((q_off ^ ((i & 3) << 6)) + i * 1024u + tile, end), q_lds + (n & 1) * (kPfN * 256u) + i * 1024u);
+        return lseh[min(n * kPfN + lane, L - 1)];      // (each wave the same 64: no branch in the stream)
     };
+    float lr = 0.0f;
     auto settle = [&](int n) {                         // tile n is in LDS (this wave's share): then a barrier
         lse2[(n & 3) * kPfN + lane] = lr * kLog2e;
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
@@ -466,7 +460,7 @@ __global__ __launch_bounds__(256, 2) void prefill_colsum_kernel(PrefillArgs a)
             }
             if (m) cs[(m - 1) >> 3] += y[1];
             y[0] = y0, y[1] = y1;
-            if (m == 0) request(n + 3);
+            if (m == 0) lr = request(n + 3);
             if (m == 15) settle(n + 3);
             if (m >= 8 && !(m & 1)) read_lse((m - 8) >> 1, n + 1);
             __builtin_amdgcn_sched_barrier(0);
@@ -482,24 +476,24 @@ __global__ __launch_bounds__(256, 2) void prefill_colsum_kernel(PrefillArgs a)
             for (int i = 0; i < 16; ++i) cs[t] += __builtin_amdgcn_exp2f(__builtin_fmaf(cur[t][i], c, -ls[i]));
     };
 
-    request(tile0);
-    settle(tile0);
-    request(tile0 + 1);
-    settle(tile0 + 1);                                 // (the K rows have arrived as well)
+    lr = request(tile0);
+    const float lr1 = request(tile0 + 1);
+    lse2[((tile0 + 1) & 3) * kPfN + lane] = lr1 * kLog2e;
+    settle(tile0);                                     // (the second tile and the K rows have arrived as well)
     __syncthreads();
     float16v sa[2], sb[2];
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) read_q(ks, tile0);
+#pragma unroll
+    for (int iq = 0; iq < 4; ++iq) read_lse(iq, tile0);
+    __syncthreads();
+    lr = request(tile0 + 2);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 16; ++i) sa[t][i] = 0.0f;
 #pragma unroll
     for (int m = 0; m < 16; ++m) sa[m & 1] = mfma32(qf[m >> 1], kf[m & 1][m >> 1], sa[m & 1]);
-#pragma unroll
-    for (int iq = 0; iq < 4; ++iq) read_lse(iq, tile0);
-    __syncthreads();
-    request(tile0 + 2);
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) read_q(ks, tile0 + 1);
     settle(tile0 + 2);
@@ -534,31 +528,38 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
     a.Q = (const _Float16 *)Q, a.K = (const _Float16 *)K, a.V = (const _Float16 *)V;
     a.XO = (_Float16 *)XO, a.lse = lse, a.A_cumul = A_cumul;
     a.Hq = Hq, a.rep = Hq / Hkv, a.L = L, a.scale_log2 = sm_scale * kLog2e;
-    // Queries per workgroup and whether two sets of waves share them.  256 queries halve what a tile costs to load
-    // (32 heads x 32768: 8.11 -> 7.81 ms) while they leave four workgroups per compute unit; else 128 (32 x 2048: 51
-    // against 58 us).  A launch of at most one workgroup per compute unit lasts as long as its longest row block: two sets
-    // of waves halve that (32 x 1024: 25.0 -> 23.3 us; with more workgroups the halves only compete, 64 x 777 26 -> 30),
-    // and where even blocks of 64 queries leave one per compute unit those are shorter still (32 x 500 15.1 -> 13.2 us,
-    // 32 x 200 11.6 -> 9.5; 32 x 777, 416 of them, 20 -> 22).
-    // In the second pass eight waves per workgroup lose (4.36 -> 4.62 ms): they wait for each other at every tile.
+    // Queries per workgroup and whether two sets of waves share them.  256 queries halve what a tile costs to load; on long
+    // prompts, while they leave four workgroups per compute unit, that is 1-3 % (64 heads x 16384: 4.32 -> 4.25 ms), on
+    // shorter ones the waves that are done wait for the others (512 heads x 257: 47 -> 59 us).  Else 128.  A launch of at
+    // most one workgroup per compute unit lasts as long as its longest row block: two sets of waves halve that, less what
+    // their meeting costs (8 heads x 4096: 71.8 -> 64.7 us, 32 x 1024 23.0 -> 22.7, but 32 x 512 14.5 -> 15.2), and where
+    // even blocks of 64 queries leave one per compute unit those are shorter still (8 x 2048 37.6 -> 31.9 us, 32 x 512
+    // 14.5 -> 13.3, 32 x 400 12.4 -> 12.1, but 32 x 200 9.0 -> 9.5).
+    // In the second pass eight waves per workgroup lose (4.36 -> 4.62 ms): they wait for each other at every tile.  Two
+    // waves (64 keys) are for prompts of one such block, where two of the four would have no key, once the workgroups no
+    // longer all run at once (1024 heads x 48: first and second pass 26.7 -> 24.0 us).
     const int64_t heads = (int64_t)B * Hq;
     auto blocks = [&](int queries) { return heads * ((L + queries - 1) / queries); };
     constexpr int64_t kComputeUnits = 256;
-    const int queries = blocks(256) >= 4 * kComputeUnits ? 256 : blocks(64) <= kComputeUnits ? 64 : 128;
+    const int queries = L >= 4096 && blocks(256) >= 4 * kComputeUnits ? 256 : L > 384 && blocks(64) <= kComputeUnits ? 64 : 128;
     a.nblk = (int)((L + queries - 1) / queries);
     const dim3 grid((unsigned)(heads * a.nblk));
     if (queries == 256)
         hipLaunchKernelGGL((prefill_fwd_kernel<8, 1>), grid, dim3(512), 0, st, a);
     else if (queries == 64)
         hipLaunchKernelGGL((prefill_fwd_kernel<2, 2>), grid, dim3(256), 0, st, a);
-    else if (blocks(128) <= kComputeUnits)
+    else if (L >= 1024 && blocks(128) <= kComputeUnits)
         hipLaunchKernelGGL((prefill_fwd_kernel<4, 2>), grid, dim3(512), 0, st, a);
     else
         hipLaunchKernelGGL((prefill_fwd_kernel<4, 1>), grid, dim3(256), 0, st, a);
     if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     if (A_cumul) {
-        a.nblk = (int)((L + 127) / 128);
-        hipLaunchKernelGGL(prefill_colsum_kernel, dim3((unsigned)(heads * a.nblk)), dim3(256), 0, st, a);
+        const int keys = L <= 64 && heads > 2 * kComputeUnits ? 64 : 128;
+        a.nblk = (int)((L + keys - 1) / keys);
+        if (keys == 64)
+            hipLaunchKernelGGL(prefill_colsum_kernel<2>, dim3((unsigned)(heads * a.nblk)), dim3(128), 0, st, a);
+        else
+            hipLaunchKernelGGL(prefill_colsum_kernel<4>, dim3((unsigned)(heads * a.nblk)), dim3(256), 0, st, a);
         if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     }
     return MINIKV_OK;

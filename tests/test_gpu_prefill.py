@@ -73,8 +73,8 @@ def test_random_shapes(g):
 
 @pytest.mark.parametrize("B,Hq,Hkv,L", [(64, 16, 4, 1), (64, 16, 4, 65), (32, 16, 16, 257), (32, 16, 2, 320), (32, 16, 4, 447)])
 def test_launches_with_256_queries_per_workgroup(g, B, Hq, Hkv, L):
-    """Launches of at least 1024 blocks of 256 queries: tile and block edges; the oracle recomputes the first and the
-    last sequence."""
+    """Many heads and short prompts, at least 1024 blocks of 256 queries (which serve long prompts only, below): tile and
+    block edges; the oracle recomputes the first and the last sequence."""
     from oracle import ref
     assert B * Hq * ((L + 255) // 256) >= 1024
     sm = 1.0 / math.sqrt(128)
@@ -92,8 +92,8 @@ def test_launches_with_256_queries_per_workgroup(g, B, Hq, Hkv, L):
 @pytest.mark.parametrize("B,Hq,Hkv", [(1, 2, 1), (4, 16, 4), (4, 32, 8), (5, 32, 16)])
 @pytest.mark.parametrize("L", [1, 63, 64, 127, 129, 192, 321])
 def test_every_division_of_a_launch(g, B, Hq, Hkv, L):
-    """2 to 160 heads at lengths around a tile, a pair of tiles (two sets of waves take every other one) and a block:
-    launches with 64 and 128 queries per workgroup, split and not."""
+    """2 to 160 heads at lengths around a tile, a pair of tiles and a block (two sets of waves share a block on longer
+    prompts, below)."""
     from oracle import ref
     sm = 1.0 / math.sqrt(128)
     Q, K, V = W.make_prefill_inputs(B, Hq, Hkv, L, 950 + L, device="cuda")
@@ -106,10 +106,50 @@ def test_every_division_of_a_launch(g, B, Hq, Hkv, L):
     assert np.all(np.abs(g.to_np(acc[sel]) - acc64) <= RTOL_A * np.abs(acc64) + ATOL_A)
 
 
+def check_last(g, B, Hq, Hkv, L, seed):
+    """Everything finite, every column sum's total right; the last sequence against the oracle."""
+    from oracle import ref
+    sm = 1.0 / math.sqrt(128)
+    Q, K, V = W.make_prefill_inputs(B, Hq, Hkv, L, seed, device="cuda")
+    xo, lse, acc = run_gpu(Q, K, V, sm)
+    assert torch.isfinite(xo).all() and torch.isfinite(lse).all()
+    assert torch.allclose(acc.double().sum(-1), torch.full((B, Hq), float(L), dtype=torch.float64, device="cuda"), rtol=1e-4)
+    sel = [B - 1]
+    _, xo64, lse64, acc64 = ref.selective_flash_attn(g.to_np(Q[sel]), g.to_np(K[sel]), g.to_np(V[sel]), sm)
+    assert np.max(np.abs(g.to_np(xo[sel]).astype(np.float64) - xo64)) <= TOL_O
+    assert np.max(np.abs(g.to_np(lse[sel]).astype(np.float64) - lse64)) <= TOL_LSE
+    assert np.all(np.abs(g.to_np(acc[sel]) - acc64) <= RTOL_A * np.abs(acc64) + ATOL_A)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(1, 2, 1, 385), (1, 2, 2, 447), (1, 2, 1, 448), (2, 4, 1, 449), (8, 4, 2, 512), (1, 2, 1, 577), (1, 1, 1, 1000)])
+def test_two_sets_of_waves_on_64_queries(g, B, Hq, Hkv, L):
+    """More than 384 tokens and at most 256 blocks of 64 queries: an odd and an even number of tiles, ragged ends."""
+    check_last(g, B, Hq, Hkv, L, 1100 + L)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(16, 1, 1, 1024), (8, 2, 1, 1025), (15, 1, 1, 1151), (14, 1, 1, 1217)])
+def test_two_sets_of_waves_on_128_queries(g, B, Hq, Hkv, L):
+    """From 1024 tokens on, more than 256 blocks of 64 queries (or just as many) and at most 256 of 128."""
+    check_last(g, B, Hq, Hkv, L, 1200 + L)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(64, 1, 1, 4096), (61, 1, 1, 4223)])
+def test_256_queries_per_workgroup_on_long_prompts(g, B, Hq, Hkv, L):
+    """From 4096 tokens and 1024 blocks of 256 queries on."""
+    assert B * Hq * ((L + 255) // 256) >= 1024
+    check_last(g, B, Hq, Hkv, L, 1300 + L)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(33, 16, 4, 1), (33, 16, 16, 31), (33, 16, 8, 63), (33, 16, 4, 64), (33, 16, 4, 65), (32, 16, 4, 64)])
+def test_column_sums_of_64_keys_per_workgroup(g, B, Hq, Hkv, L):
+    """Prompts of up to 64 tokens on more than 512 heads, and the calls next to them."""
+    check_last(g, B, Hq, Hkv, L, 1400 + L)
+
+
 @pytest.mark.parametrize("per_tile", [-3.0, 0.02, 0.7, 3.0, 30.0])
 def test_scores_that_rise_or_fall_along_the_keys(g, per_tile):
-    """The reference of the softmax weights lags behind the running maximum by a bounded amount: scores whose level moves
-    by `per_tile` (in powers of e) every 64 keys, so that it never, seldom or always follows."""
+    """Scores whose level moves by `per_tile` (in powers of e) every 64 keys, so that the running maximum is raised, and the
+    output rescaled, on the first tile only, now and then, or on every tile."""
     from oracle import ref
     B, Hq, Hkv, L = 1, 4, 2, 700
     Q, K, V = W.make_prefill_inputs(B, Hq, Hkv, L, 41, device="cuda", gain=0.3)
