@@ -49,7 +49,8 @@ __device__ __forceinline__ int acc_row(int i, int g) { return (i >> 2) * 8 + g *
 
 // 64 lanes x 16 bytes from base + off (per lane) straight to LDS at lds + 16 * lane: no registers and no LDS store
 // instructions in between.  The compiler does not count this load: wait with s_waitcnt vmcnt before the barrier that
-// hands the data over.
+// hands the data over.  (m0, which it sets, is a register the compiler reserves and holds no value in from one statement to
+// the next -- it refuses it as a clobber --, and nothing else in this file reads it.)
 __device__ __forceinline__ void load_to_lds(const void *base, unsigned off, unsigned lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"

@@ -19,6 +19,16 @@ def g():
     return gpu_common
 
 
+@pytest.fixture(params=[0, 1, 2], ids=["by-shape", "measured-weights", "unit-weights"])
+def weights(request):
+    """The work cut as the library chooses (a workgroup per unit at most of these sizes), then along the work line with
+    either weights, as larger calls have it."""
+    from paper_2411_18077_amd import api
+    api.minikv_diag_decode_weights(request.param)
+    yield request.param
+    api.minikv_diag_decode_weights(0)
+
+
 def both_ways(g, w, r_len, seed_offset=0, mutate=None):
     """Two identical caches; one takes append + attend, the other the fused step.  Returns the caches, the
     outputs and the length array the fused step wrote."""
@@ -66,6 +76,7 @@ def tiny(G=32, **kw):
     return W.Workload(**base)
 
 
+@pytest.mark.usefixtures("weights")
 @pytest.mark.parametrize("r", [0, 1, 31, 62, 63, 64])
 def test_every_fill_of_the_residual(g, r):
     """Empty, one row, the last free row (the append fills the buffer), and a full buffer (nothing is appended:
@@ -76,6 +87,7 @@ def test_every_fill_of_the_residual(g, r):
     assert nxt.cpu().tolist() == [min(r + 1, 64)] * w.units
 
 
+@pytest.mark.usefixtures("weights")
 @pytest.mark.parametrize("G,Hq,Hkv,B", [(32, 8, 8, 1), (16, 4, 2, 2), (64, 16, 2, 1), (128, 12, 3, 1), (32, 5, 5, 2),
                                         (32, 14, 2, 1)])
 def test_head_layouts_and_ragged_lengths(g, G, Hq, Hkv, B):
@@ -95,6 +107,26 @@ def test_head_layouts_and_ragged_lengths(g, G, Hq, Hkv, B):
     assert np.isfinite(ob.float().cpu().numpy()).all()
 
 
+@pytest.mark.parametrize("G,Hq,Hkv,B", [(16, 2, 2, 16), (16, 16, 2, 16), (16, 5, 1, 40), (128, 8, 2, 2), (128, 16, 2, 1), (64, 8, 1, 3),
+                                        (32, 16, 2, 50), (32, 2, 1, 100)])
+def test_a_workgroup_per_unit_appends(g, G, Hq, Hkv, B):
+    """Calls of few items per unit (at G = 16 from 32 units on), one and two sets of heads: residuals of every length, full
+    ones among them, and units without any quantized token."""
+    w = tiny(G, Hq=Hq, Hkv=Hkv, B=B, L=1000, Rcap=max(G, 64), keep=None, keep_range=(0.05, 0.8))
+    rng = np.random.default_rng(7 + G + Hq)
+    r = rng.integers(0, w.Rcap + 1, w.units)
+    r[0], r[1 % w.units] = w.Rcap, 0
+
+    def mutate(inp):
+        inp.n_tok[0] = 0                       # unit 0: a full residual and nothing else
+        inp.n_tok[1 % w.units] = 0             # unit 1: the appended token alone
+
+    s, inp, ca, cb, oa, ob, nxt, rb = both_ways(g, w, r, mutate=mutate)
+    assert_same(w, ca, cb, oa, ob, nxt, rb)
+    assert torch.isfinite(ob).all()
+
+
+@pytest.mark.usefixtures("weights")
 def test_against_the_oracle(g):
     """The fused step against Algorithm 1 as the oracle runs it (append, then attention in fp64)."""
     from oracle import ref
@@ -117,6 +149,7 @@ def test_against_the_oracle(g):
     assert nxt.cpu().tolist() == [41] * w.units
 
 
+@pytest.mark.usefixtures("weights")
 def test_many_steps_with_flushes(g):
     """70 fused steps on one cache, the two length arrays swapped from step to step, a flush whenever the residual
     is full; next to it the same steps as separate calls.  Outputs and the whole cache state agree at the end."""
@@ -164,6 +197,7 @@ def test_arguments_are_checked_on_the_host(g):
         api.minikv_decode_step(s, inp.q, None, k, c, torch.zeros_like(c.r_len), g.sm_scale(), out)
 
 
+@pytest.mark.usefixtures("weights")
 def test_two_fused_steps_captured_in_a_graph_and_replayed(g):
     """The length arrays alternate from step to step, so a HIP graph holds TWO steps (lengths A -> B, then B -> A),
     each with the flush in front.  The graph is replayed with new inputs in its static buffers, with eager work

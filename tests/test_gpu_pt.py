@@ -136,7 +136,7 @@ def test_two_and_eight_heads_per_kv_head(rep, bits, G):
 @pytest.mark.parametrize("kscale,vscale,qscale", [(40.0, 500.0, 3.0), (0.02, 3e4, 0.05), (600.0, 0.01, 60.0)])
 def test_large_and_small_magnitudes(bits, kscale, vscale, qscale):
     """Keys, values and queries far from unit scale (up to the edge of fp16 for the values): the value-side
-    operands are fp16 (weight x V scale), so the bar is 2e-3 of the value scale."""
+    operands are fp16 (weight x V scale), so the bar is 2e-3 of the value scale, or one fp16 step of the result."""
     from oracle import ref
     from paper_2411_18077_amd import api
     w, inp = _inputs(1, 8, 2, 2048, seed=580 + bits, keep=0.5)
@@ -153,7 +153,7 @@ def test_large_and_small_magnitudes(bits, kscale, vscale, qscale):
     want, _ = ref.decode_attn_pt(rc, inp.q.cpu().numpy(), sm)
     got = out.float().cpu().numpy()
     assert np.isfinite(got).all()
-    bar = max(TOL * vscale, TOL, float(np.max(np.abs(want))) * 2.0 ** -10)     # ... or one fp16 step of the result
+    bar = max(TOL * vscale, float(np.max(np.abs(want))) * 2.0 ** -10)
     assert np.max(np.abs(got - want.astype(np.float32))) <= bar
 
 
