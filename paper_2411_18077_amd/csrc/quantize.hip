@@ -123,10 +123,9 @@ struct WordAcc {
 };
 
 // NSUB == 0: a workgroup is one block of a unit of any length (update_lengths_kernel follows).  NSUB > 0: a workgroup is a
-// whole unit of at most NSUB blocks, 256 threads each, and leaves the new lengths when it is done.  (The second launch bound
-// keeps G = 64 in 64 registers, eight waves per SIMD, where the compiler would take 67: 1024 units x 256 tokens 45.5 -> 43.3 us.)
+// whole unit of at most NSUB blocks, 256 threads each, and leaves the new lengths when it is done.
 template <int G, int NSUB>
-__global__ __launch_bounds__(256 * (NSUB ? NSUB : 1), G == 64 && NSUB == 0 ? 8 : 1) void quantize_pack_kernel(QuantArgs a)
+__global__ __launch_bounds__(256 * (NSUB ? NSUB : 1)) void quantize_pack_kernel(QuantArgs a)
 {
     constexpr bool kWholeUnit = NSUB > 0;
     constexpr int kSub = kWholeUnit ? NSUB : 1;
@@ -139,8 +138,8 @@ __global__ __launch_bounds__(256 * (NSUB ? NSUB : 1), G == 64 && NSUB == 0 ? 8 :
 
     const int u = blockIdx.y;
     const int tid = kWholeUnit ? threadIdx.x & 255 : threadIdx.x, sub = kWholeUnit ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
-    uint16_t *tile = tiles[sub];
-    float2 *par = pars[sub];
+    auto &tile = tiles[sub];                           // (references: with pointers G = 64 takes 67 registers, a wave per SIMD less)
+    auto &par = pars[sub];
     float one = 1.0f;
     asm volatile("" : "+v"(one));                       // (see quant_codef)
     int q0;
@@ -180,7 +179,7 @@ __global__ __launch_bounds__(256 * (NSUB ? NSUB : 1), G == 64 && NSUB == 0 ? 8 :
     __syncthreads();
     // (the two word-building passes exist twice: for a full block of BT tokens, where every index split below is a
     // shift, and for the ragged last block of a unit, where they are divisions by run-time values)
-    auto k_words = [&a, tid, u, t0, one, tile, par](auto ntc) {
+    auto k_words = [&, tid, u, t0, one](auto ntc) {
         // one thread per (token, word): the word's 16 channels are contiguous in the tile row and in par
         const int nt = ntc;
         uint32_t *Kc = a.Kc + (size_t)u * kc_words(a.Tcap);
@@ -237,7 +236,7 @@ __global__ __launch_bounds__(256 * (NSUB ? NSUB : 1), G == 64 && NSUB == 0 ? 8 :
         par[gi] = float2{-zf, inv};
     }
     __syncthreads();
-    auto v_words = [&a, tid, u, t0, one, tile, par](auto ntc) {
+    auto v_words = [&, tid, u, t0, one](auto ntc) {
         // one thread per (block of 16 tokens, channel pair): two words
         const int nt = ntc;
         uint32_t *Vc = a.Vc + (size_t)u * vc_words(a.Tcap);
@@ -304,15 +303,18 @@ static int launch_quantize_g(const QuantArgs &a, int units, int max_tok, hipStre
 {
     constexpr int BT = G > 64 ? G : 64;
     const int nblk = (max_tok + BT - 1) / BT;
-    // One workgroup per unit, and no launch of update_lengths_kernel behind this one, where a unit is a single block, or up
-    // to four blocks of 64 tokens as long as the launch holds no more than four blocks per compute unit: then all of them
-    // run at once in either form (256 units x 128 rows, the call: 17.1 -> 13.9 us; 256 x 256 17.1 -> 17.0; 512 x 128
-    // 17.0 -> 14.4).  Beyond that a workgroup of two or four blocks stops for each of its barriers as one, and four take
-    // the local memory of half a compute unit (320 x 256 17.7 -> 27.2 us, 1024 x 256 42.9 -> 64.0, 1024 x 128
-    // 23.5 -> 25.6).  Two blocks of 128 tokens in one workgroup gain nothing at any count (64 x 256 17.4 -> 20.0 us).
+    // One workgroup per unit, and no launch of update_lengths_kernel behind this one, where a unit is a single block, or two
+    // or three blocks of 64 tokens while the launch holds no more than four (counted as 2 or 4 each) per compute unit: then
+    // all of them run at once in either form.  Append + flush + attend, G = 32: 64 units x 128 rows 38.4 -> 35.6 us, x 192
+    // 38.3 -> 35.6, 256 units x 128 49.6 -> 47.9, 512 x 128 54.5 -> 52.9.  Beyond that a workgroup of several blocks stops
+    // for each of its barriers as one, and four take the local memory of half a compute unit (the call: 320 units x 192
+    // 17.2 -> 21.4 us, 1024 x 256 42.9 -> 64.0, 1024 x 128 23.5 -> 25.6).  Four blocks gain while launches are what a step
+    // waits for (64 units x 256: 38.5 -> 36.7; 128 units 38.7 -> 39.4; G = 16, with the most groups, 38.9 -> 40.8); two
+    // blocks of 128 tokens never (64 x 256, the call: 17.4 -> 20.0 us).
     constexpr int kComputeUnits = 256;
     const int sub = nblk <= 2 ? nblk : 4;
-    if (nblk == 1 || (BT == 64 && nblk <= 4 && (int64_t)units * sub <= 4 * kComputeUnits)) {
+    const bool few = nblk <= 3 ? (int64_t)units * sub <= 4 * kComputeUnits : nblk == 4 && G > 16 && units <= kComputeUnits / 4;
+    if (nblk == 1 || (BT == 64 && few)) {
         if (nblk == 1)
             hipLaunchKernelGGL((quantize_pack_kernel<G, 1>), dim3(1, units), dim3(256), 0, st, a);
         else if constexpr (BT == 64) {
