@@ -303,18 +303,18 @@ static int launch_quantize_g(const QuantArgs &a, int units, int max_tok, hipStre
 {
     constexpr int BT = G > 64 ? G : 64;
     const int nblk = (max_tok + BT - 1) / BT;
-    // One workgroup per unit, and no launch of update_lengths_kernel behind this one, where a unit is a single block, or two
-    // or three blocks of 64 tokens while the launch holds no more than four (counted as 2 or 4 each) per compute unit: then
+    // One workgroup per unit, and no launch of update_lengths_kernel behind this one, where a unit is a single block, or up
+    // to four blocks of 64 tokens while the launch holds no more than four (counted as 2 or 4 each) per compute unit: then
     // all of them run at once in either form.  Append + flush + attend, G = 32: 64 units x 128 rows 38.4 -> 35.6 us, x 192
     // 38.3 -> 35.6, 256 units x 128 49.6 -> 47.9, 512 x 128 54.5 -> 52.9.  Beyond that a workgroup of several blocks stops
     // for each of its barriers as one, and four take the local memory of half a compute unit (the call: 320 units x 192
-    // 17.2 -> 21.4 us, 1024 x 256 42.9 -> 64.0, 1024 x 128 23.5 -> 25.6).  Four blocks gain while launches are what a step
-    // waits for (64 units x 256: 38.5 -> 36.7; 128 units 38.7 -> 39.4; G = 16, with the most groups, 38.9 -> 40.8); two
-    // blocks of 128 tokens never (64 x 256, the call: 17.4 -> 20.0 us).
+    // 17.2 -> 21.4 us, 1024 x 256 42.9 -> 64.0, 1024 x 128 23.5 -> 25.6).  Four blocks in one cost up to a microsecond more
+    // on the device than two launches (256 units x 256: 52.8 -> 53.6 us) and five less where the launches are what a step
+    // waits for (216 units x 256 rows, 672 tokens behind them: 39.2 -> 33.5 us).  Two blocks of 128 tokens gain at no
+    // count (64 x 256, the call: 17.4 -> 20.0 us).
     constexpr int kComputeUnits = 256;
     const int sub = nblk <= 2 ? nblk : 4;
-    const bool few = nblk <= 3 ? (int64_t)units * sub <= 4 * kComputeUnits : nblk == 4 && G > 16 && units <= kComputeUnits / 4;
-    if (nblk == 1 || (BT == 64 && few)) {
+    if (nblk == 1 || (BT == 64 && nblk <= 4 && (int64_t)units * sub <= 4 * kComputeUnits)) {
         if (nblk == 1)
             hipLaunchKernelGGL((quantize_pack_kernel<G, 1>), dim3(1, units), dim3(256), 0, st, a);
         else if constexpr (BT == 64) {
