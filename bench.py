@@ -435,7 +435,7 @@ def main():
             return {"B": Bp, "Hq": Hq, "Hkv": Hkv, "L": Lp, "ms": round(ms, 3), "TFLOP/s": round(fl / ms / 1e9, 1),
                     "frac_of_fp16_mfma_peak": round(fl / ms / 1e9 / 2500.0, 3)}
         result["selective_flash_attn"] = {
-            "what": "selective_flash_attn (X_O, LSE and A_cumul: transpose of V + row-block pass + column-block pass); "
+            "what": "selective_flash_attn (X_O, LSE and A_cumul: row-block pass + column-block pass); "
                     "flops = 6*D per causal (query, key) pair; peak 2500 TFLOP/s (dense fp16 matrix instructions)",
             "this_shape": time_prefill(1, w.Hq, w.Hkv, w.L, 3),
             "paper_table_longest": time_prefill(1, 32, 32, 8192, 10),

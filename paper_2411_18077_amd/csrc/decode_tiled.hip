@@ -1086,7 +1086,9 @@ static int launch_units(const DecArgs &a, hipStream_t st)
 // Whether a workgroup per unit serves the call, from the capacities (the lengths are on the device).  It needs a compute
 // unit per unit, and few enough items that the eight waves of a unit (four at G = 16) are done before the work line, which
 // spreads the items over the whole device, has paid for its round trips -- also when the lengths are ragged and the line
-// has the better balance.  Measured with all lengths at the capacity / ragged (5 .. 100 % of it), line against unit, us:
+// has the better balance.  The limits lie on the safe side of that: inside them the line never won (1.0-2.9 times over 564
+// shapes), a little outside the unit form often still does (with one head per KV head 256 units x 35 items 1.2 times).
+// Measured with all lengths at the capacity / ragged (5 .. 100 % of it), line against unit, us:
 //   32/8 heads, G = 32:    8 units x 11 items 12.1 / 11.5 against 11.5, 15 items 12.0 against 14.1
 //                         64 units x 11 items 13.3 against 12.0 / 16.3 against 11.8, 15 items 13.5 against 14.9
 //                        128 units x 19 items 19.9 against 15.2, 27 items 17.9 against 17.9, 35 items 19.6 against 20.8

@@ -76,10 +76,10 @@ __device__ __forceinline__ int tile_place(int row, int chunk) { return row * kPf
 // barrier per step, between the halves: there tile n's V and tile n+2's K are in place, tile n+1's K has been read.
 // K and V tiles go straight to LDS from their own row-major layout; the output product's A operand V^T is read with
 // the transposing LDS read.
-// What bounds it: the energy of the products (the clock falls to 1.55 GHz on N(0,1) data with the matrix unit 63 % busy;
+// What bounds it: the energy of the products (the clock falls to 1.55-1.8 GHz on N(0,1) data with the matrix unit 60 % busy;
 // 2.4 GHz on zeros).  So what moves data was taken out: no staging of tiles through registers and LDS stores, no
-// transposed copy of V in memory.  32 heads x 32768 tokens 9.25 -> 8.1 ms (1.08 PFLOP/s; a plain library product of
-// 16384^3 reaches 1.29 on this card), 2 x 32 x 4096 368 -> 305 us, 32 x 777 28 -> 20 us.  Letting the reference of the
+// transposed copy of V in memory.  32 heads x 32768 tokens 9.7 -> 8.4 ms (1.05 PFLOP/s; a plain library product of
+// 16384^3 reaches 1.29 on this card), 2 x 32 x 4096 364 -> 320 us, 32 x 777 26.7 -> 19.9 us.  Letting the reference of the
 // weights lag behind the running maximum (fewer rescales) is another 2-3 %, but then the key that dominates a row no
 // longer has the weight 1 that fp16 holds exactly, and the error grows by 1 %.
 constexpr int kPfTile = kPfN * kPfD;                    // halves of one unpadded tile in LDS
