@@ -191,3 +191,25 @@ def test_short_calls_of_many_units(g, G, T, B):
     gc = g.gpu_build_cache(inp, s)
     assert gc.q_len.cpu().tolist() == inp.n_tok.cpu().tolist()
     g.assert_cache_bit_exact(gc, g.ref_build_cache(inp, rs, units=units), unit_map=units)
+
+
+@pytest.mark.parametrize("G,first,second", [(16, 16, 32), (16, 48, 16), (16, 80, 96), (16, 32, 304), (32, 32, 32), (32, 96, 64), (32, 32, 352),
+                                            (64, 64, 64), (64, 192, 320), (128, 128, 128), (128, 384, 512)])
+def test_append_behind_every_offset(g, G, first, second):
+    """A second call writes behind a first one whose length is no multiple of a block or a code tile; an odd number of units
+    (the last has no partner where two short ones share a wave), units of every length, rows gathered and not."""
+    from paper_2411_18077_amd import api
+    from oracle import ref
+    w = small(G, B=5, Hkv=1, Hq=1, L=600, keep=1.0)
+    inp = W.make_inputs(w, "cuda")
+    s, rs = g.shapes_for(w, 1024)
+    n1 = torch.tensor([first, 0, first, G, first], dtype=torch.int32, device="cuda")
+    n2 = torch.tensor([second, second, 0, second - G, second], dtype=torch.int32, device="cuda")
+    idx = torch.arange(w.L - second, w.L, dtype=torch.int32, device="cuda").repeat(w.units, 1).contiguous()
+    gc, rc = api.Cache(s), ref.RefCache(rs)
+    api.kv_quantize_pack(s, inp.K, inp.V, w.L, None, 0, n1, first, gc)
+    api.kv_quantize_pack(s, inp.K, inp.V, w.L, idx, second, n2, second, gc)
+    torch.cuda.synchronize()
+    assert ref.quantize_pack(rc, g.to_np(inp.K), g.to_np(inp.V), g.to_np(n1), None) == 0
+    assert ref.quantize_pack(rc, g.to_np(inp.K), g.to_np(inp.V), g.to_np(n2), g.to_np(idx)) == 0
+    g.assert_cache_bit_exact(gc, rc, what=("Kc", "Ks", "Kz", "Vc", "Vs", "Vz", "q_len"))
