@@ -146,11 +146,14 @@ __device__ inline float *slot_ptr(const DecArgs &a, int slot, int h)
 // UNIT: a workgroup of kUnitWaves waves IS one unit; they divide its items, and their partials meet in local memory.
 // What a small launch spends its time on is round trips -- lengths to work line, partial to ticket, ticket to merge --,
 // and this form has one of them, the unit's own two lengths: see launch_stream() for where it is taken.
+//
+// STREAM: the code words are loaded with the streaming hint.  They are read once per call; without the hint they push each
+// other through the caches, and the read rate is what suffers: see launch_stream() for where and how much.
 template <int G> constexpr int kUnitWaves = G == 16 ? 4 : 8;     // (two per SIMD, one at G = 16)
 template <int G> constexpr size_t kWaveLds =                     // local memory of one wave, bytes
     (size_t)(kD / G) * kPsG * 2 > (size_t)kNH * kD * 2 + (size_t)64 * kKRowH * 2
         ? (size_t)(kD / G) * kPsG * 2 : (size_t)kNH * kD * 2 + (size_t)64 * kKRowH * 2;
-template <int G, bool LO, bool PAIRED, bool FUSED, bool FLAT, bool UNIT>
+template <int G, bool LO, bool PAIRED, bool FUSED, bool FLAT, bool UNIT, bool STREAM>
 __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) void decode_stream_kernel(DecArgs a)
 {
     constexpr int kWQ = FLAT ? 1 : kPassWeight, kWR = FLAT ? 1 : kResidualWeight;
@@ -389,10 +392,14 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             d.ks = load_words<NKW>(Ks + go);
             d.kz = load_words<NKW>(Kz + go);
         };
+        auto words = [](const u4 *p) -> u4 {
+            if constexpr (STREAM) return __builtin_nontemporal_load(p);
+            return *p;
+        };
         auto load_k_codes = [&](KD &d, int tp, int half) {       // half 0: words 0..3 of both tokens, 1: words 4..7
             const u4 *ktile = reinterpret_cast<const u4 *>(Kc + (size_t)(tp >> 7) * 1024);
-            d.kw[half] = ktile[half * 64 + lane_u];
-            d.kw[2 + half] = ktile[(2 + half) * 64 + lane_u];
+            d.kw[half] = words(ktile + half * 64 + lane_u);
+            d.kw[2 + half] = words(ktile + (2 + half) * 64 + lane_u);
         };
         auto load_v_meta = [&](VD &d, int tp) {
             // past the end the (clamped) load still happens (the weights of those tokens are zero), so that the
@@ -404,8 +411,8 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
         };
         auto load_v_codes = [&](VD &d, int tp, int tl) {         // tl: 64-token tile of the pass
             const u4 *vtile = reinterpret_cast<const u4 *>(Vc + (size_t)(tp >> 6) * (4 * kD));
-            d.vw[0][tl] = vtile[tl * kD + lane_u];
-            d.vw[1][tl] = vtile[tl * kD + lane_u + 64];
+            d.vw[0][tl] = words(vtile + tl * kD + lane_u);
+            d.vw[1][tl] = words(vtile + tl * kD + lane_u + 64);
         };
         auto load_k = [&](int tp) -> KD {
             KD d;
@@ -1078,7 +1085,7 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
 template <int G, bool LO, bool PAIRED, bool APPEND>
 static int launch_units(const DecArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, true, true>), dim3((unsigned)(a.units * a.hsets)),
+    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, true, true, false>), dim3((unsigned)(a.units * a.hsets)),
                        dim3(64 * kUnitWaves<G>), 0, st, a);
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
@@ -1105,12 +1112,12 @@ static bool unit_per_workgroup(const DecArgs &a, int G)
     return items <= (units >= 192 ? 28 : units >= 96 ? 24 : 12);
 }
 
-template <int G, bool LO, bool PAIRED, bool APPEND, bool FLAT>
+template <int G, bool LO, bool PAIRED, bool APPEND, bool FLAT, bool STREAM>
 static int launch_stream_w(DecArgs a, long nw, int resident, size_t lds_bytes, hipStream_t st)
 {
     a.first_slot = resident / 2;
     a.skew16 = kSkew16;
-    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT, false>), dim3((unsigned)nw), dim3(64), lds_bytes, st, a);
+    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT, false, STREAM>), dim3((unsigned)nw), dim3(64), lds_bytes, st, a);
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
 
@@ -1126,7 +1133,7 @@ template <int G, bool LO, bool PAIRED, bool APPEND>
 static int launch_stream(DecArgs a, hipStream_t st)
 {
     constexpr size_t lds_bytes = kWaveLds<G>;
-    auto kern = decode_stream_kernel<G, LO, PAIRED, APPEND, false, false>;
+    auto kern = decode_stream_kernel<G, LO, PAIRED, APPEND, false, false, false>;
     static int resident = 0;                               // single-wave workgroups the device holds at once
     if (resident == 0) {
         int dev = 0, cus = 0, per_cu = 0;
@@ -1146,8 +1153,15 @@ static int launch_stream(DecArgs a, hipStream_t st)
     // 1120 on -- 19.8 against 17.7 us)
     const int mode = g_decode_weights.load();
     if (mode == 0 && unit_per_workgroup(a, G)) return launch_units<G, LO, PAIRED, APPEND>(a, st);
-    return (mode == 0 ? cap_items * 2 <= (long)resident : mode == 2) ? launch_stream_w<G, LO, PAIRED, APPEND, true>(a, nw, resident, lds_bytes, st)
-                                 : launch_stream_w<G, LO, PAIRED, APPEND, false>(a, nw, resident, lds_bytes, st);
+    if (mode == 0 ? cap_items * 2 <= (long)resident : mode == 2) return launch_stream_w<G, LO, PAIRED, APPEND, true, false>(a, nw, resident, lds_bytes, st);
+    // Streaming loads where the packed cache (by its capacity) is larger than a third of the 256 MB memory-side cache: 4.0 ->
+    // 4.3 TB/s on 169 MB (42.7 -> 39.9 us), 107 -> 98.8 us on 510 MB, 34.7 -> 31.1 on 116 MB.  A smaller one may still be
+    // there from the call before, and is then read faster with ordinary loads (three caches in turn: 74 MB 24.8 against
+    // 25.6 us, 50 MB 19.8 against 20.2; at 82 MB 28.3 against 27.8).
+    constexpr long kStreamBytes = 80L << 20;
+    const long packed = (long)a.units * a.Tcap * (64 + 8 * kD / G);
+    return packed > kStreamBytes ? launch_stream_w<G, LO, PAIRED, APPEND, false, true>(a, nw, resident, lds_bytes, st)
+                                 : launch_stream_w<G, LO, PAIRED, APPEND, false, false>(a, nw, resident, lds_bytes, st);
 }
 
 template <bool LO, bool PAIRED>
