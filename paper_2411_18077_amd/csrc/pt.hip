@@ -203,7 +203,15 @@ template <int BITS> struct PtFields {
 // make operands of codes and weights; a form with one dot2 per pair of codes and head was bound by those alone.  Calls of
 // 128 units x 13088 tokens, 4 heads each, G = 128: 4 bits 79 -> 52 us (4.4 TB/s; a plain copy reaches 5.0), 2 bits
 // 82 -> 46.5, 8 bits 110 -> 83; 16 units 23 -> 16 us; G = 32, 128 units x 8192 tokens 63 -> 41 us.
-template <int BITS, int G, int REPT>
+// STREAM: the code words, read once per call, are loaded with the streaming hint (see pt_streams()).
+typedef uint32_t pt_word2 __attribute__((ext_vector_type(2)));
+typedef uint32_t pt_word4 __attribute__((ext_vector_type(4)));
+template <bool STREAM, class T> __device__ __forceinline__ T pt_load(const T *p)
+{
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    return *p;
+}
+template <int BITS, int G, int REPT, bool STREAM>
 __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
 {
     typedef PtFields<BITS> F;
@@ -232,7 +240,7 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
 
     // requests of a block, made one block ahead (addresses stay inside the buffers; what lies past t_end is masked)
     uint32_t kw[NT][KW];
-    uint4 vw[2][2];                                     // [half of the channels][s]: words of tokens CPW (kg + 4 s) ..
+    pt_word4 vw[2][2];                                     // [half of the channels][s]: words of tokens CPW (kg + 4 s) ..
     uint16_t mr[4][E];
     auto request = [&](int t0) {
 #pragma unroll
@@ -241,12 +249,12 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
             const int t = min(t0 + CPW * (col >> 2) + 4 * CPW * s + 4 * q4 + (col & 3), a.Tcap - 1);
             const uint32_t *src = Kc + (size_t)t * W + kg * KW;
             if constexpr (KW == 2) {
-                const uint2 v = *reinterpret_cast<const uint2 *>(src);
+                const pt_word2 v = pt_load<STREAM>(reinterpret_cast<const pt_word2 *>(src));
                 kw[tau][0] = v.x, kw[tau][1] = v.y;
             } else {
 #pragma unroll
                 for (int i = 0; i < KW / 4; i++) {
-                    const uint4 v = reinterpret_cast<const uint4 *>(src)[i];
+                    const pt_word4 v = pt_load<STREAM>(reinterpret_cast<const pt_word4 *>(src) + i);
                     kw[tau][4 * i] = v.x, kw[tau][4 * i + 1] = v.y, kw[tau][4 * i + 2] = v.z, kw[tau][4 * i + 3] = v.w;
                 }
             }
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
             const int row = min(t0 / CPW + kg + 4 * s, a.Tcap / CPW - 1);
 #pragma unroll
             for (int half = 0; half < 2; half++)
-                vw[half][s] = *reinterpret_cast<const uint4 *>(Vc + (size_t)row * kD + half * 64 + col * 4);
+                vw[half][s] = pt_load<STREAM>(reinterpret_cast<const pt_word4 *>(Vc + (size_t)row * kD + half * 64 + col * 4));
         }
         const int e0 = min(t0 * NG + lane * E, a.Tcap * NG - E);
 #pragma unroll
@@ -354,7 +362,7 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
             if (NT == 8)                                 // (all tiles' operands at once do not fit the registers)
                 asm volatile("" : "+v"(s[tau][0]), "+v"(s[tau][1]), "+v"(s[tau][2]), "+v"(s[tau][3])::"memory");
         }
-        uint4 vc[2][2];
+        pt_word4 vc[2][2];
 #pragma unroll
         for (int i = 0; i < 4; i++) vc[i >> 1][i & 1] = vw[i >> 1][i & 1];
         if (t0 + 4 * TB < t_end) request(t0 + 4 * TB);
@@ -421,7 +429,7 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
         for (int half = 0; half < 2; half++)
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                const uint4 q0 = vc[half][0], q1 = vc[half][1];
+                const pt_word4 q0 = vc[half][0], q1 = vc[half][1];
                 const uint32_t w0 = i == 0 ? q0.x : i == 1 ? q0.y : i == 2 ? q0.z : q0.w;
                 const uint32_t w1 = i == 0 ? q1.x : i == 1 ? q1.y : i == 2 ? q1.z : q1.w;
                 pt_float4 acc = minus[NB == 2 ? half : 0];
@@ -577,26 +585,40 @@ static int pt_launch_quantize(const PtQuantArgs &a, int G, dim3 grid, int units,
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
 
-template <int BITS, int REPT>
+// Whether a call loads its codes with the streaming hint: where the packed cache (by its capacity) is larger than three
+// eighths of the 256 MB memory-side cache.  128 units x 13088 tokens at 4 bits (228 MB) 51.7 -> 49.9 us, 8 bits x 8192
+// (272 MB) 55.6 -> 50.7, 104 MB 28.7 -> 28.0; what is smaller may still be cached from the call before (three caches in
+// turn, 84 MB 21.8 against 22.3, 36 .. 80 MB a tie).
+static bool pt_streams(const PtDecArgs &a, int bits, int G, unsigned units)
+{
+    return (long)units * a.Tcap * (2 * (kD * bits / 8 + 4 * kD / G)) > (96L << 20);
+}
+
+template <int BITS, int REPT, bool STREAM>
 static int pt_launch_decode_g(const PtDecArgs &a, int G, dim3 grid, hipStream_t st)
 {
     switch (G) {
-    case 32: hipLaunchKernelGGL((decode_pt_kernel<BITS, 32, REPT>), grid, dim3(256), 0, st, a); break;
-    case 64: hipLaunchKernelGGL((decode_pt_kernel<BITS, 64, REPT>), grid, dim3(256), 0, st, a); break;
-    case 128: hipLaunchKernelGGL((decode_pt_kernel<BITS, 128, REPT>), grid, dim3(256), 0, st, a); break;
+    case 32: hipLaunchKernelGGL((decode_pt_kernel<BITS, 32, REPT, STREAM>), grid, dim3(256), 0, st, a); break;
+    case 64: hipLaunchKernelGGL((decode_pt_kernel<BITS, 64, REPT, STREAM>), grid, dim3(256), 0, st, a); break;
+    case 128: hipLaunchKernelGGL((decode_pt_kernel<BITS, 128, REPT, STREAM>), grid, dim3(256), 0, st, a); break;
     default: return MINIKV_EUNSUPPORTED;
     }
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
 
 // heads per unit rounded up to 1, 2, 4 or 8 (the spare ones repeat the last head and are not written)
+template <int BITS, bool STREAM>
+static int pt_launch_decode_s(const PtDecArgs &a, int G, dim3 grid, hipStream_t st)
+{
+    if (a.rep <= 1) return pt_launch_decode_g<BITS, 1, STREAM>(a, G, grid, st);
+    if (a.rep <= 2) return pt_launch_decode_g<BITS, 2, STREAM>(a, G, grid, st);
+    if (a.rep <= 4) return pt_launch_decode_g<BITS, 4, STREAM>(a, G, grid, st);
+    return pt_launch_decode_g<BITS, 8, STREAM>(a, G, grid, st);
+}
 template <int BITS>
 static int pt_launch_decode(const PtDecArgs &a, int G, dim3 grid, hipStream_t st)
 {
-    if (a.rep <= 1) return pt_launch_decode_g<BITS, 1>(a, G, grid, st);
-    if (a.rep <= 2) return pt_launch_decode_g<BITS, 2>(a, G, grid, st);
-    if (a.rep <= 4) return pt_launch_decode_g<BITS, 4>(a, G, grid, st);
-    return pt_launch_decode_g<BITS, 8>(a, G, grid, st);
+    return pt_streams(a, BITS, G, grid.y) ? pt_launch_decode_s<BITS, true>(a, G, grid, st) : pt_launch_decode_s<BITS, false>(a, G, grid, st);
 }
 
 }  // namespace minikv
