@@ -18,6 +18,7 @@
 #include "common.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace minikv {
 
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
     int *hist = (int *)smem;                         // [kSelBins]
     int *sub_tot = hist + kSelBins;                  // [2][16]
     int *scan_tot = sub_tot + 2 * 16;                // [16]
-    int *found = scan_tot + 16;                      // [3] digit, kept count below it, keys in the digit's bin
+    int *digit_found = scan_tot + 16;                // [3][4] digit, kept count below it, keys in the digit's bin
     uint32_t *ck = smem + kSelFixedWords;            // [L] when cached
 
     const long u = blockIdx.x;
@@ -171,9 +172,13 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
     uint32_t prefix = 0;
     int rem = k, in_bin = 0;                             // (in_bin: after the last digit, the keys equal to T)
     int hi = 32;
-    // bins from the top down, two per thread; the thread whose pair crosses `rem` owns the digit
+    // bins from the top down, two per thread; the thread whose pair crosses `rem` owns the digit.  Every thread clears its
+    // bins for the next digit as it reads them, and every digit has a result of its own: two barriers, not five (a barrier
+    // of 16 waves is 0.1-0.2 us, and a short call does little else).
     auto settle_digit = [&](int lo) {
         const int c0 = hist[kSelBins - 1 - 2 * tid], c1 = hist[kSelBins - 2 - 2 * tid];
+        hist[kSelBins - 1 - 2 * tid] = 0, hist[kSelBins - 2 - 2 * tid] = 0;
+        int *found = digit_found + (lo >= 21 ? 0 : lo ? 4 : 8);
         int incl = wave_scan_incl(c0 + c1);
         if (lane == 63) scan_tot[wave] = incl;
         __syncthreads();
@@ -194,7 +199,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
         rem = found[1];
         in_bin = found[2];
         hi = lo;
-        __syncthreads();
     };
     for (int b = tid; b < kSelBins; b += kSelThreads) hist[b] = 0;
     __syncthreads();
@@ -237,8 +241,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
     while (hi > 0 && !(cached && in_bin == rem)) {
         const int lo = max(hi - 11, 0);
         const uint32_t dm = (1u << (hi - lo)) - 1u;
-        for (int b = tid; b < kSelBins; b += kSelThreads) hist[b] = 0;
-        __syncthreads();
         for (int base = 0; base < N; base += kSelThreads * kSelLoads) {
             // slot e of this thread holds token tok(e): from LDS two runs of 4 consecutive tokens (128-bit
             // reads), from memory consecutive lanes take consecutive tokens (coalesced); any order will do here
@@ -302,24 +304,28 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
         // When every key of T's bin is kept (the usual case: no tie across the cut), "kept" is just key >= T and
         // the bookkeeping of the equal ones falls away (3.7 instead of 5.9 us on 32768 tokens).
         const bool all_equal_kept = in_bin == rem;     // (uniform)
+        // (whole steps, all but the last, compare without asking whether the token is a candidate)
+        auto count = [&](int start, auto whole) -> uint32_t {
+            uint32_t key[4], tot = 0;
+            load4(start, key);
+            if (all_equal_kept) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) tot += (uint32_t)((whole || start + j < N) && key[j] >= T);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t g = (whole || start + j < N) && key[j] > T, e = (whole || start + j < N) && key[j] == T;
+                    tot += g | e << 16;
+                }
+            }
+            return tot;
+        };
 #pragma unroll
         for (int st = 0; st < NS; ++st) {
             before[st] = 0;
             if (st < nsteps) {                         // (uniform)
                 const int start = st * kSelThreads * 4 + tid * 4;
-                uint32_t key[4];
-                load4(start, key);
-                uint32_t tot = 0;
-                if (all_equal_kept) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) tot += (uint32_t)(start + j < N && key[j] >= T);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const uint32_t g = start + j < N && key[j] > T, e = start + j < N && key[j] == T;
-                        tot += g | e << 16;
-                    }
-                }
+                const uint32_t tot = (st + 1) * kSelThreads * 4 <= N ? count(start, std::true_type()) : count(start, std::false_type());
                 const uint32_t incl = (uint32_t)wave_scan_incl((int)tot);
                 before[st] = incl - tot;
                 if (lane == 63) tots[st * 16 + wave] = incl;
@@ -340,11 +346,21 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
             uint32_t key[4];
             load4(start, key);
             if (all_equal_kept) {
+                // (excl < k always holds for a kept token; the test keeps a write in its row)
+                if ((st + 1) * kSelThreads * 4 <= N) { // (uniform)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bool g = start + j < N && key[j] >= T;
-                    if (g && (int)excl < k) row[excl] = start + j;   // (excl < k always holds; the test keeps a write in its row)
-                    excl += (uint32_t)g;
+                    for (int j = 0; j < 4; ++j) {
+                        const bool g = key[j] >= T;
+                        if (g && (int)excl < k) row[excl] = start + j;
+                        excl += (uint32_t)g;
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const bool g = start + j < N && key[j] >= T;
+                        if (g && (int)excl < k) row[excl] = start + j;
+                        excl += (uint32_t)g;
+                    }
                 }
                 continue;
             }
@@ -398,32 +414,31 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
 }
 
 // ------------------------------------------------------------------------------------------------------
-// The same selection with SEVERAL workgroups per unit (prompts of up to kChMaxChunks * 4096 tokens): launches
-// over (unit, 4096-token chunk), no atomics in memory, no waiting between workgroups.  Every kernel requests
-// all it reads from memory at its start (addresses clamped with launch parameters, validity applied when the
-// values are used), so that a workgroup pays one memory round trip, not one per step.
-//   sel_hist_kernel       streams the score rows once: summed-score keys to the workspace (several heads only)
-//                         and, per chunk, a histogram of the keys' top 11 bits over the candidates.
-//   sel_unit_hist_kernel  (more than kChDirect chunks per unit) adds a unit's chunk histograms up.
-//   sel_cand_kernel       every workgroup takes its unit's histogram, finds the bin b1 the weakest kept heavy
-//                         hitter falls into, counts its chunk's keys above that bin and copies those inside it
-//                         (the "bin candidates") to the unit's list, behind those of the chunks before it.
-//   sel_write_kernel      every workgroup settles the remaining 21 bits on the unit's bin candidates (two
-//                         histogram passes over registers), counts what precedes its chunk, and compacts its
-//                         chunk in order to the slots that follow.
-// Workspace, in 32-bit words: keys [units][Lp] (several heads only; Lp = L rounded up to 4), bin candidates
-// [units][nchunk*4096], chunk histograms [units][nchunk][1024] (two 16-bit counts per word), unit histograms
-// [units][2048], per chunk four counts [units][nchunk][4] (bin candidates of the unit, keys above the bin in
-// this chunk, the bin, bin candidates of the chunks before this one).
+// The same selection with SEVERAL workgroups per unit (prompts of up to kChMaxChunks * 4096 tokens): two launches over
+// (unit, 4096-token chunk), 16 waves each, no atomics in memory, no waiting between workgroups.
+//   sel_sort_kernel       streams the score rows once.  Per chunk: the candidates' keys in descending order of their top 11
+//                         bits (a counting sort in LDS; inside a bin any order), and for every bin how many of them lie in
+//                         it or above ("cumulative counts"); with several heads also the summed-score keys in token order.
+//   sel_unit_hist_kernel  (only where adding a unit's cumulative counts in every workgroup would cost more than a launch)
+//                         adds them up once.
+//   sel_pick_kernel       every workgroup adds up its unit's cumulative counts -- the bin b1 of the weakest kept heavy hitter
+//                         is where the sum falls below the budget, no scan --, fetches the unit's keys inside that bin, one
+//                         contiguous piece per chunk, settles the remaining 21 bits on them in LDS, counts what precedes its
+//                         chunk, and compacts its chunk in order to the slots that follow.
+// A launch whose workgroups do a few dependent steps costs 4 to 9 us however small the input, so what counts is their number
+// and the round trips inside.  An earlier form (histograms, a unit sum, a candidate list, the rest: four launches of 4
+// waves per chunk) took 26.9 us on 8 units x 4 heads x 131072 where this takes 20.4.
+// Workspace, in 32-bit words: keys [units][Lp] (several heads only; Lp = L rounded up to 4), sorted keys
+// [units][nchunk][4096], cumulative counts [units][nchunk][1024] (two 16-bit counts per word), sums of those
+// [units][2048], four spare words per chunk.
 constexpr int kCh = 4096;              // tokens per chunk
-constexpr int kChThreads = 256;        // 4 waves
+constexpr int kChThreads = 1024;       // 16 waves, four tokens each thread
 constexpr int kChMaxChunks = 1024;     // most chunks of one unit
-constexpr int kChDirect = 8;           // up to this many chunks sel_cand_kernel adds the chunk histograms itself
-constexpr int kChCandRegs = 20;        // bin candidates per thread that sel_write_kernel holds in registers
+constexpr int kChList = 12288;         // keys of the cut's bin that sel_pick_kernel holds in LDS (more are read again in every pass)
 
 struct SelWs {
-    uint32_t *keys, *cand, *hist;
-    int *uhist, *cnt;
+    uint32_t *keys, *sorted, *cum;
+    int *ucum;
     long Lp;
     int nchunk, units;
 };
@@ -460,10 +475,9 @@ static SelWs sel_ws_carve(void *workspace, long units, int rep, long L)
     w.units = (int)units;
     w.Lp = (L + 3) & ~3L;
     w.keys = (uint32_t *)workspace;
-    w.cand = w.keys + (rep > 1 ? units * w.Lp : 0);
-    w.hist = w.cand + units * (long)w.nchunk * kCh;
-    w.uhist = (int *)(w.hist + units * (long)w.nchunk * (kSelBins / 2));
-    w.cnt = w.uhist + units * (long)kSelBins;
+    w.sorted = w.keys + (rep > 1 ? units * w.Lp : 0);
+    w.cum = w.sorted + units * (long)w.nchunk * kCh;
+    w.ucum = (int *)(w.cum + units * (long)w.nchunk * (kSelBins / 2));
     return w;
 }
 
@@ -475,117 +489,102 @@ __device__ __forceinline__ bool sel_budgets(long r, long h, long L, long idx_str
     return true;
 }
 
-// Inclusive prefix sum over the 256 threads of a workgroup (tot[4] in LDS; one barrier); also the grand total.
+// Inclusive prefix sum over the 1024 threads of a workgroup (tot[16] in LDS; one barrier); also the grand total.
 __device__ __forceinline__ int block_scan_incl(int v, int *tot, int lane, int wv, int &total)
 {
     int incl = wave_scan_incl(v);
     if (lane == 63) tot[wv] = incl;
     __syncthreads();
-    const int t0 = tot[0], t1 = tot[1], t2 = tot[2], t3 = tot[3];
-    incl += (wv > 0 ? t0 : 0) + (wv > 1 ? t1 : 0) + (wv > 2 ? t2 : 0);
-    total = t0 + t1 + t2 + t3;
+    const int t = lane < 16 ? tot[lane] : 0, ti = wave_scan_incl(t);
+    incl += __builtin_amdgcn_readlane(ti, wv) - __builtin_amdgcn_readlane(t, wv);      // waves before this one
+    total = __builtin_amdgcn_readlane(ti, 15);
     return incl;
 }
 
-// Walk the 2048 bins c[.] (thread t holds bins 8t .. 8t+7) from the top: the bin in which the running count
-// reaches `want` (1 <= want <= total) and how many of that bin are wanted.  The owning thread writes out[0..1]
-// and returns the bin's place in its c[.]; the others return -1.
-__device__ __forceinline__ int find_from_top(const int c[8], int want, int *tot, int *out, int tid, int lane, int wv)
+// hist_add that also returns this lane's place among the keys of its digit (in the order they arrive).
+__device__ __forceinline__ int hist_place(int *hist, bool match, int d, int lane)
 {
-    int mine = 0, total, own = -1;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) mine += c[j];
-    const int incl = block_scan_incl(mine, tot, lane, wv, total);
-    int run = total - incl;                                // count in the bins above this thread's
-#pragma unroll
-    for (int j = 7; j >= 0; --j) {
-        if (run < want && want <= run + c[j]) {
-            out[0] = 8 * tid + j;
-            out[1] = want - run;
-            own = j;
-        }
-        run += c[j];
-    }
-    return own;
+    const unsigned long long m = __ballot(match);
+    if (m == 0) return 0;
+    const int first = __ffsll((long long)m) - 1;
+    const int d0 = __shfl(d, first, 64);
+    const unsigned long long same = __ballot(match && d == d0);
+    int at = 0;
+    if (lane == first)
+        at = atomicAdd(&hist[d0], (int)__popcll(same));
+    else if (match && d != d0)
+        at = atomicAdd(&hist[d], 1);
+    const int base = __builtin_amdgcn_readlane(at, first);
+    return match && d == d0 ? base + (int)__popcll(same & ((1ull << lane) - 1ull)) : at;
 }
 
-__device__ __forceinline__ void unpack_counts(const uint4 &v, int c[8])
-{
-    c[0] = v.x & 0xFFFF, c[1] = v.x >> 16, c[2] = v.y & 0xFFFF, c[3] = v.y >> 16;
-    c[4] = v.z & 0xFFFF, c[5] = v.z >> 16, c[6] = v.w & 0xFFFF, c[7] = v.w >> 16;
-}
-
-template <int REP, bool FROM_FLOAT>
-__global__ __launch_bounds__(kChThreads) void sel_hist_kernel(const float *__restrict__ A, SelWs w, int rep_rt, long L,
+template <int REP>
+__global__ __launch_bounds__(kChThreads) void sel_sort_kernel(const float *__restrict__ A, SelWs w, int rep_rt, long L,
                                                               const int *__restrict__ n_hh,
                                                               const int *__restrict__ n_rw, long idx_stride)
 {
-    __shared__ int hist[kSelBins];
+    __shared__ int hist[kSelBins], tot[16];
+    __shared__ uint32_t sorted[kCh];
     const int rep = REP ? REP : rep_rt;
     long unit;
     int chunk;
     if (!sel_map(blockIdx.x, w.nchunk, w.units, unit, chunk)) return;
     const long base = (long)chunk * kCh;
     const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long r_ = n_rw[unit], h_ = n_hh[unit];
     const float *rows = A + unit * rep * L;
-    for (int b = tid; b < kSelBins; b += kChThreads) hist[b] = 0;
-    int N = 0, k = 0, rw;
-    bool live = false;
-    for (int e0 = 0; e0 < 16; e0 += 4) {
-        float s[4];
+    float x[4][REP ? REP : 1], s[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const long i = min(base + e * kChThreads + (long)tid, L - 1);       // clamped: no branch at the loads
+#pragma unroll
+        for (int h = 0; h < (REP ? REP : 1); ++h) x[e][h] = rows[h * L + i];
+    }
+    hist[tid] = 0, hist[tid + kChThreads] = 0;
+    int N = 0, k = 0, rw;                                  // the loads are on their way: now look at the budgets
+    const bool live = sel_budgets(r_, h_, L, idx_stride, N, k, rw) && k != 0 && k != N && base < N;
+    if (!live) return;                                     // nothing is selected by score here / no candidate in this chunk
+    __syncthreads();
+    int place[4];
+    uint32_t key[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const long i = base + e * kChThreads + tid;
+        s[e] = x[e][0];
         if (REP) {
-            float x[4][REP ? REP : 1];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const long i = min(base + (e0 + e) * kChThreads + (long)tid, L - 1);   // clamped: no branch at the loads
-#pragma unroll
-                for (int h = 0; h < REP; ++h) x[e][h] = rows[h * L + i];
-            }
-            if (e0 == 0) {                                 // the first loads are on their way: now look at the budgets
-                live = sel_budgets(r_, h_, L, idx_stride, N, k, rw) && k != 0 && k != N && base < N;
-                __syncthreads();                           // (the cleared histogram)
-                if (!live) return;                         // nothing is selected by score here / no candidate in this chunk
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                s[e] = x[e][0];
-#pragma unroll
-                for (int h = 1; h < REP; ++h) s[e] = s[e] + x[e][h];                    // head order, one rounding per add
-            }
+            for (int h = 1; h < REP; ++h) s[e] = s[e] + x[e][h];                    // head order, one rounding per add
         } else {
-            if (e0 == 0) {
-                live = sel_budgets(r_, h_, L, idx_stride, N, k, rw) && k != 0 && k != N && base < N;
-                __syncthreads();
-                if (!live) return;
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const long i = min(base + (e0 + e) * kChThreads + (long)tid, L - 1);
-                s[e] = rows[i];
-                for (int h = 1; h < rep; ++h) s[e] = s[e] + rows[h * L + i];
-            }
+            for (int h = 1; h < rep; ++h) s[e] = s[e] + rows[h * L + min(i, L - 1)];
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const long i = base + (e0 + e) * kChThreads + tid;
-            const uint32_t key = score_key(s[e]);
-            if (!FROM_FLOAT && i < N) w.keys[unit * w.Lp + i] = key;
-            hist_add(hist, i < N, (int)(key >> 21), lane);
-        }
+        key[e] = score_key(s[e]);
+        if (REP != 1 && i < N) w.keys[unit * w.Lp + i] = key[e];
+        place[e] = hist_place(hist, i < N, (int)(key[e] >> 21), lane);
     }
     __syncthreads();
-    uint4 o;                                               // (a chunk holds 4096 tokens: a count fits 16 bits)
-    o.x = (uint32_t)hist[8 * tid + 0] | ((uint32_t)hist[8 * tid + 1] << 16);
-    o.y = (uint32_t)hist[8 * tid + 2] | ((uint32_t)hist[8 * tid + 3] << 16);
-    o.z = (uint32_t)hist[8 * tid + 4] | ((uint32_t)hist[8 * tid + 5] << 16);
-    o.w = (uint32_t)hist[8 * tid + 6] | ((uint32_t)hist[8 * tid + 7] << 16);
-    reinterpret_cast<uint4 *>(w.hist + (unit * w.nchunk + chunk) * (long)(kSelBins / 2))[tid] = o;
+    const int c0 = hist[2 * tid], c1 = hist[2 * tid + 1];
+    int total;
+    const int incl = block_scan_incl(c0 + c1, tot, lane, wv, total);
+    const int ge1 = total - incl + c1, ge0 = ge1 + c0;     // keys in bin 2 tid + 1, 2 tid or above (at most 4096)
+    w.cum[(unit * w.nchunk + chunk) * (long)(kSelBins / 2) + tid] = (uint32_t)ge0 | (uint32_t)ge1 << 16;
+    hist[2 * tid] = ge1, hist[2 * tid + 1] = ge1 - c1;     // where the bin's keys start
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (base + e * kChThreads + tid < N) sorted[hist[key[e] >> 21] + place[e]] = key[e];
+    __syncthreads();
+    uint32_t *dst = w.sorted + (unit * w.nchunk + chunk) * (long)kCh;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = e * kChThreads + tid;
+        if (i < total) dst[i] = sorted[i];
+    }
 }
 
 // grid (units, 8): workgroup j of a unit adds bins 256j .. 256j+255 of the chunks that hold candidates
-__global__ __launch_bounds__(kChThreads) void sel_unit_hist_kernel(SelWs w, long L, const int *__restrict__ n_hh,
-                                                                   const int *__restrict__ n_rw, long idx_stride)
+__global__ __launch_bounds__(256) void sel_unit_hist_kernel(SelWs w, long L, const int *__restrict__ n_hh,
+                                                            const int *__restrict__ n_rw, long idx_stride)
 {
     long unit;
     int part;
@@ -594,7 +593,7 @@ __global__ __launch_bounds__(kChThreads) void sel_unit_hist_kernel(SelWs w, long
     int N, k, rw;
     if (!sel_budgets(n_rw[unit], n_hh[unit], L, idx_stride, N, k, rw) || k == 0 || k == N) return;
     const int nc = (N + kCh - 1) / kCh;
-    const uint16_t *hp = reinterpret_cast<const uint16_t *>(w.hist + unit * w.nchunk * (long)(kSelBins / 2)) + bin;
+    const uint16_t *hp = reinterpret_cast<const uint16_t *>(w.cum + unit * w.nchunk * (long)(kSelBins / 2)) + bin;
     int sum = 0;
     for (int q0 = 0; q0 < nc; q0 += 8) {
         int v[8];
@@ -603,176 +602,46 @@ __global__ __launch_bounds__(kChThreads) void sel_unit_hist_kernel(SelWs w, long
 #pragma unroll
         for (int j = 0; j < 8; ++j) sum += q0 + j < nc ? v[j] : 0;
     }
-    w.uhist[unit * kSelBins + bin] = sum;
+    w.ucum[unit * kSelBins + bin] = sum;
 }
 
-template <bool FROM_FLOAT, bool DIRECT>
-__global__ __launch_bounds__(kChThreads) void sel_cand_kernel(const float *__restrict__ A, SelWs w, long L,
+// DIRECT: the unit's cumulative counts are added up here, else sel_unit_hist_kernel has done it.  A workgroup compacts NCH
+// consecutive chunks ("chunk" is the first).
+template <bool FROM_FLOAT, bool DIRECT, int NCH>
+__global__ __launch_bounds__(kChThreads) void sel_pick_kernel(const float *__restrict__ A, SelWs w, long L,
                                                               const int *__restrict__ n_hh,
-                                                              const int *__restrict__ n_rw, long idx_stride)
+                                                              const int *__restrict__ n_rw,
+                                                              int *__restrict__ idx, long idx_stride,
+                                                              int *__restrict__ n_tok)
 {
-    __shared__ int tot[4], found[4], fill[2];
+    __shared__ int hist[kSelBins];                         // (first: piece ends and starts of the chunks)
+    __shared__ uint32_t list[kChList];
+    __shared__ int tot[16], tot2[16], found[2], acc[4];
     long unit;
     int chunk;
-    if (!sel_map(blockIdx.x, w.nchunk, w.units, unit, chunk)) return;
-    const long base = (long)chunk * kCh;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // ---- everything this workgroup reads, requested at once
-    const long r_ = n_rw[unit], h_ = n_hh[unit];
-    uint32_t kk[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const long i = min(base + e * kChThreads + (long)tid, L - 1);
-        kk[e] = FROM_FLOAT ? __float_as_uint(A[unit * L + i]) : w.keys[unit * w.Lp + i];
-    }
-    const uint32_t *hrow = w.hist + unit * w.nchunk * (long)(kSelBins / 2);
-    uint4 hv[DIRECT ? kChDirect : 2];
-    if (DIRECT) {
-#pragma unroll
-        for (int q = 0; q < kChDirect; ++q)
-            hv[q] = reinterpret_cast<const uint4 *>(hrow + (long)min(q, w.nchunk - 1) * (kSelBins / 2))[tid];
-    } else {
-        hv[0] = reinterpret_cast<const uint4 *>(w.uhist + unit * kSelBins)[2 * tid];
-        hv[1] = reinterpret_cast<const uint4 *>(w.uhist + unit * kSelBins)[2 * tid + 1];
-    }
-    if (tid < 2) fill[tid] = 0;
-    int N, k, rw;
-    if (!sel_budgets(r_, h_, L, idx_stride, N, k, rw)) return;
-    if (k == 0 || k == N || base >= N) return;
-    const int nc = (N + kCh - 1) / kCh;
-    // ---- the unit's histogram and the bin b1 where the count from the top reaches k
-    int c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (DIRECT) {
-#pragma unroll
-        for (int q = 0; q < kChDirect; ++q) {
-            int cq[8];
-            unpack_counts(hv[q], cq);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) c[j] += q < nc ? cq[j] : 0;
-        }
-    } else {
-        c[0] = hv[0].x, c[1] = hv[0].y, c[2] = hv[0].z, c[3] = hv[0].w;
-        c[4] = hv[1].x, c[5] = hv[1].y, c[6] = hv[1].z, c[7] = hv[1].w;
-    }
-    const int own = find_from_top(c, k, tot, found, tid, lane, wv);
-    // bin candidates of the unit (M) and of the chunks before this one
-    if (DIRECT) {
-        if (own >= 0) {
-            int all = 0, before = 0;
-#pragma unroll
-            for (int q = 0; q < kChDirect; ++q) {
-                int cq[8];
-                unpack_counts(hv[q], cq);
-                int x = 0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) x = own == j ? cq[j] : x;
-                all += q < nc ? x : 0;
-                before += q < chunk ? x : 0;
-            }
-            found[2] = all;
-            found[3] = before;
-        }
-        __syncthreads();
-    } else {
-        __syncthreads();
-        const uint16_t *hb = reinterpret_cast<const uint16_t *>(hrow) + found[0];
-        int mine = 0, bef = 0;
-#pragma unroll
-        for (int j = 0; j < kChMaxChunks / kChThreads; ++j) {
-            const int q = tid + j * kChThreads;
-            const int x = q < nc ? (int)hb[(long)q * kSelBins] : 0;
-            mine += x;
-            bef += q < chunk ? x : 0;
-        }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            mine += __shfl_xor(mine, d, 64);
-            bef += __shfl_xor(bef, d, 64);
-        }
-        if (tid < 2) found[2 + tid] = 0;
-        __syncthreads();
-        if (lane == 0) {
-            atomicAdd(&found[2], mine);
-            atomicAdd(&found[3], bef);
-        }
-        __syncthreads();
-    }
-    const uint32_t b1 = (uint32_t)found[0];
-    const int M = found[2], m_before = found[3];
-    uint32_t *seg = w.cand + unit * w.nchunk * (long)kCh + m_before;
-    int above = 0;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const bool in = base + e * kChThreads + tid < N;
-        const uint32_t key = FROM_FLOAT ? score_key(__uint_as_float(kk[e])) : kk[e];
-        const uint32_t d = key >> 21;
-        above += (int)(in && d > b1);
-        const bool is_c = in && d == b1;
-        const unsigned long long m = __ballot(is_c);
-        if (m) {                                            // the wave's bin candidates take consecutive places
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&fill[0], (int)__popcll(m));
-            at = __builtin_amdgcn_readfirstlane(at);
-            if (is_c) seg[at + (int)__popcll(m & ((1ull << lane) - 1ull))] = key;
-        }
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) above += __shfl_xor(above, d, 64);
-    if (lane == 0) atomicAdd(&fill[1], above);
-    __syncthreads();
-    if (tid == 0) {
-        int4 o;
-        o.x = M, o.y = fill[1], o.z = (int)b1, o.w = m_before;
-        reinterpret_cast<int4 *>(w.cnt)[unit * w.nchunk + chunk] = o;
-    }
-}
-
-template <bool FROM_FLOAT>
-__global__ __launch_bounds__(kChThreads, 4) void sel_write_kernel(const float *__restrict__ A, SelWs w, long L,
-                                                               const int *__restrict__ n_hh,
-                                                               const int *__restrict__ n_rw,
-                                                               int *__restrict__ idx, long idx_stride,
-                                                               int *__restrict__ n_tok)
-{
-    __shared__ int hist[kSelBins];
-    __shared__ int tot[4], found[2], acc[4], sub_tot[2][4];
-    long unit;
-    int chunk;
-    if (!sel_map(blockIdx.x, w.nchunk, w.units, unit, chunk)) return;
+    if (!sel_map(blockIdx.x, (w.nchunk + NCH - 1) / NCH, w.units, unit, chunk)) return;
+    chunk *= NCH;
     const int base = chunk * kCh;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // ---- everything this workgroup reads, requested at once
     const long r_ = n_rw[unit], h_ = n_hh[unit];
-    const int4 own = reinterpret_cast<const int4 *>(w.cnt)[unit * w.nchunk + chunk];
-    int ab[kChMaxChunks / kChThreads];                     // keys above the bin, chunk tid + 256 j
+    // the chunks' keys for the compaction: tokens base + 4096 r + 4 tid .. + 3 (requested now, used last)
+    uint32_t key[NCH][4];
 #pragma unroll
-    for (int j = 0; j < kChMaxChunks / kChThreads; ++j)
-        ab[j] = w.cnt[(unit * w.nchunk + min(tid + j * kChThreads, w.nchunk - 1)) * 4 + 1];
-    // this chunk's keys for the compaction: round r, thread t holds tokens base + r*1024 + 4t .. + 3
-    uint32_t key[4][4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < NCH; ++r)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const long i = min((long)base + r * 1024 + 4 * tid + j, L - 1);
+            const long i = min((long)base + r * kCh + 4 * tid + j, L - 1);
             key[r][j] = FROM_FLOAT ? __float_as_uint(A[unit * L + i]) : w.keys[unit * w.Lp + i];
         }
-    const uint32_t *cand = w.cand + unit * w.nchunk * (long)kCh;
-    const int cap = w.nchunk * kCh;
-    uint32_t cd[kChCandRegs];                              // the unit's first 6144 bin candidates (usually all)
-#pragma unroll
-    for (int e = 0; e < kChCandRegs; ++e) cd[e] = cand[min(tid + e * kChThreads, cap - 1)];
-    if (tid < 4) acc[tid] = 0;
-
+    const uint32_t *crow = w.cum + unit * w.nchunk * (long)(kSelBins / 2);
     int N, k, rw;
     if (!sel_budgets(r_, h_, L, idx_stride, N, k, rw)) {
         if (chunk == 0 && tid == 0) n_tok[unit] = 0;
         return;
     }
     int *row = idx + unit * idx_stride;
-    const int end = (int)min((long)base + kCh, L);
+    const int end = (int)min((long)base + NCH * kCh, L);
     for (int i = max(base, N) + tid; i < end; i += kChThreads) row[k + (i - N)] = i;       // the recent window
     if (chunk == 0 && tid == 0) n_tok[unit] = k + rw;
     if (k == 0 || base >= N) return;
@@ -781,87 +650,156 @@ __global__ __launch_bounds__(kChThreads, 4) void sel_write_kernel(const float *_
         return;
     }
     const int nc = (N + kCh - 1) / kCh;
-    const int M = own.x, m_before = own.w;
-    const uint32_t b1 = (uint32_t)own.z;
-    int above_all, above_before;
-    {
-        int all = 0, bef = 0;
+    // ---- keys of the unit in bin 2 tid / 2 tid + 1 or above; b1 = the last bin where at least k are
+    int ge0 = 0, ge1 = 0;
+    if (DIRECT) {
+        for (int q0 = 0; q0 < nc; q0 += 32) {              // (32 loads in flight: one round trip up to 131072 tokens)
+            uint32_t v[32];
 #pragma unroll
-        for (int j = 0; j < kChMaxChunks / kChThreads; ++j) {
-            const int q = tid + j * kChThreads;
-            all += q < nc ? ab[j] : 0;
-            bef += q < chunk ? ab[j] : 0;
-        }
+            for (int j = 0; j < 32; ++j) v[j] = crow[(long)min(q0 + j, nc - 1) * (kSelBins / 2) + tid];
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            all += __shfl_xor(all, d, 64);
-            bef += __shfl_xor(bef, d, 64);
+            for (int j = 0; j < 32; ++j)
+                if (q0 + j < nc) ge0 += (int)(v[j] & 0xFFFFu), ge1 += (int)(v[j] >> 16);
         }
-        __syncthreads();                                   // (acc cleared)
-        if (lane == 0) {
-            atomicAdd(&acc[0], all);
-            atomicAdd(&acc[1], bef);
-        }
-        __syncthreads();
-        above_all = acc[0], above_before = acc[1];
+    } else {
+        const int2 v = reinterpret_cast<const int2 *>(w.ucum + unit * kSelBins)[tid];
+        ge0 = v.x, ge1 = v.y;
     }
-    // f(key, before): every bin candidate of the unit once; before = it belongs to a chunk before this one
-    auto for_each_cand = [&](auto f) {
-#pragma unroll
-        for (int e = 0; e < kChCandRegs; ++e) {
-            const int i = tid + e * kChThreads;
-            if (i < M) f(cd[e], i < m_before);
-        }
-        for (int i = tid + kChCandRegs * kChThreads; i < M; i += kChThreads) f(cand[i], i < m_before);
-    };
-    // the 21 bits below the bin's: 11, then 10
-    int rem = k - above_all;
-    uint32_t T = 0;
-#pragma unroll 1
-    for (int level = 0; level < 2; ++level) {
-        const int lo = level ? 0 : 10;
-        const uint32_t dm = level ? 0x3FFu : 0x7FFu;
-        for (int b = tid; b < kSelBins; b += kChThreads) hist[b] = 0;
-        __syncthreads();
-        for_each_cand([&](uint32_t x, bool) {
-            const bool match = level == 0 || ((x >> 10) & 0x7FFu) == (T >> 10);
-            if (match) atomicAdd(&hist[(x >> lo) & dm], 1);
-        });
-        __syncthreads();
-        int c[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) c[j] = hist[8 * tid + j];
-        find_from_top(c, rem, tot, found, tid, lane, wv);
-        __syncthreads();
-        T |= (uint32_t)found[0] << lo;
-        rem = found[1];
-        __syncthreads();
-    }
-    const uint32_t Tfull = (b1 << 21) | T;                 // key of the weakest kept heavy hitter; `rem` of its equals are kept
-    // larger / equal keys among the bin candidates of the chunks before this one
+    if (lane == 0) tot[wv] = ge0;
+    if (tid < 4) acc[tid] = 0;
+    __syncthreads();
     {
-        int g = 0, e = 0;
-        for_each_cand([&](uint32_t x, bool before) {
-            g += (int)(before && x > Tfull);
-            e += (int)(before && x == Tfull);
-        });
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            g += __shfl_xor(g, d, 64);
-            e += __shfl_xor(e, d, 64);
-        }
-        if (lane == 0) {
-            atomicAdd(&acc[2], g);
-            atomicAdd(&acc[3], e);
-        }
+        const int below = __shfl_down(ge0, 1, 64);         // of the bin after this thread's two
+        const int next = lane < 63 ? below : wv < 15 ? tot[(wv + 1) & 15] : 0;
+        if (ge0 >= k && ge1 < k) found[0] = 2 * tid;
+        if (ge1 >= k && next < k) found[0] = 2 * tid + 1;
     }
     __syncthreads();
-    int gt_run = above_before + acc[2], eq_run = acc[3];
-    // ---- ordered compaction of this chunk: four rounds of 1024 tokens, 4 consecutive tokens per thread
+    const uint32_t b1 = (uint32_t)found[0];
+    // ---- chunk q = tid: where its keys of bin b1 start in its sorted list (= how many lie above), and how many there are
+    int gt = 0, cnt = 0;
+    if (tid < nc) {
+        const uint16_t *cq = reinterpret_cast<const uint16_t *>(crow + (long)tid * (kSelBins / 2)) + b1;
+        gt = b1 + 1 < (uint32_t)kSelBins ? cq[1] : 0;
+        cnt = cq[0] - gt;
+    }
+    int M, above_all;
+    const int cnt_end = block_scan_incl(cnt, tot2, lane, wv, M);
+    const int gt_end = block_scan_incl(gt, tot, lane, wv, above_all);
+    int *piece_at = hist, *piece_end = hist + kChMaxChunks;          // start in the chunk's list; end among the unit's bin keys
+    piece_at[tid] = gt, piece_end[tid] = cnt_end;
+    if (tid == chunk) acc[2] = gt_end - gt, acc[3] = cnt_end - cnt;  // keys above the bin / in it, in the chunks before this one
+    __syncthreads();
+    const int above_before = acc[2], m_before = acc[3];
+    const uint32_t *sorted = w.sorted + unit * w.nchunk * (long)kCh;
+    // f(key, index): the unit's bin keys, from their pieces in memory (wave v takes chunks v, v + 16, ...)
+    auto from_pieces = [&](auto f) {
+        for (int q = wv; q < nc; q += 16) {
+            const int e = piece_end[q], b = q ? piece_end[q - 1] : 0;
+            const uint32_t *src = sorted + (long)q * kCh + piece_at[q] - b;
+            for (int i = b + lane; i < e; i += 64) f(src[i], i);
+        }
+    };
+    const bool listed = M <= kChList;                      // (uniform)
+    int rem = k - above_all;
+    uint32_t T = 0;
+    int g = 0, eq = 0;
+    if (listed) {
+        // as from_pieces, but 256 keys of each of two pieces are requested before the first is stored
+        for (int q0 = wv; q0 < nc; q0 += 32) {
+            int at[2], b[2], e[2];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int start = base + r * 1024 + 4 * tid;
-        if (base + r * 1024 >= N) break;                   // (uniform)
+            for (int p = 0; p < 2; ++p) {
+                const int q = min(q0 + 16 * p, nc - 1);
+                e[p] = q0 + 16 * p < nc ? piece_end[q] : 0, b[p] = q ? piece_end[q - 1] : 0;
+                at[p] = q * kCh + piece_at[q] - b[p];
+            }
+            uint32_t x[2][4];
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[p][j] = sorted[at[p] + max(min(b[p] + 64 * j + lane, e[p] - 1), b[p])];
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (b[p] + 64 * j + lane < e[p]) list[b[p] + 64 * j + lane] = x[p][j];
+                for (int i = b[p] + 256 + lane; i < e[p]; i += 64) list[i] = sorted[at[p] + i];
+            }
+        }
+        __syncthreads();
+        // the 21 bits below the bin's: 11, then 10
+#pragma unroll 1
+        for (int level = 0; level < 2; ++level) {
+            const int lo = level ? 0 : 10;
+            const uint32_t dm = level ? 0x3FFu : 0x7FFu;
+            hist[tid] = 0, hist[tid + kChThreads] = 0;
+            __syncthreads();
+            for (int i = tid; i < M; i += kChThreads) {
+                const uint32_t x = list[i];
+                if (level == 0 || ((x >> 10) & 0x7FFu) == (T >> 10)) atomicAdd(&hist[(x >> lo) & dm], 1);
+            }
+            __syncthreads();
+            const int c0 = hist[2 * tid], c1 = hist[2 * tid + 1];
+            int total;
+            const int incl = block_scan_incl(c0 + c1, level ? tot2 : tot, lane, wv, total);
+            const int run = total - incl;                  // count in the bins above this thread's
+            if (run < rem && rem <= run + c1) found[0] = 2 * tid + 1, found[1] = rem - run;
+            if (run + c1 < rem && rem <= run + c1 + c0) found[0] = 2 * tid, found[1] = rem - run - c1;
+            __syncthreads();
+            T |= (uint32_t)found[0] << lo;
+            rem = found[1];
+        }
+        for (int i = tid; i < m_before; i += kChThreads) {
+            const uint32_t x = list[i] & 0x1FFFFFu;
+            g += (int)(x > T), eq += (int)(x == T);
+        }
+    } else {
+        // ties or a narrow range of scores: most keys share the bin, and many of them a digit.  The counts cannot use the
+        // bytes that describe the pieces: they take the list's.
+        int *count = (int *)list;
+#pragma unroll 1
+        for (int level = 0; level < 2; ++level) {
+            const int lo = level ? 0 : 10;
+            const uint32_t dm = level ? 0x3FFu : 0x7FFu;
+            count[tid] = 0, count[tid + kChThreads] = 0;
+            __syncthreads();
+            from_pieces([&](uint32_t x, int) {
+                hist_add(count, level == 0 || ((x >> 10) & 0x7FFu) == (T >> 10), (int)((x >> lo) & dm), lane);
+            });
+            __syncthreads();
+            const int c0 = count[2 * tid], c1 = count[2 * tid + 1];
+            int total;
+            const int incl = block_scan_incl(c0 + c1, level ? tot2 : tot, lane, wv, total);
+            const int run = total - incl;
+            if (run < rem && rem <= run + c1) found[0] = 2 * tid + 1, found[1] = rem - run;
+            if (run + c1 < rem && rem <= run + c1 + c0) found[0] = 2 * tid, found[1] = rem - run - c1;
+            __syncthreads();
+            T |= (uint32_t)found[0] << lo;
+            rem = found[1];
+        }
+        from_pieces([&](uint32_t x, int i) {
+            g += (int)(i < m_before && (x & 0x1FFFFFu) > T), eq += (int)(i < m_before && (x & 0x1FFFFFu) == T);
+        });
+    }
+    const uint32_t Tfull = (b1 << 21) | T;                 // key of the weakest kept heavy hitter; `rem` of its equals are kept
+    // larger / equal keys among the bin keys of the chunks before this one
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        g += __shfl_xor(g, d, 64);
+        eq += __shfl_xor(eq, d, 64);
+    }
+    if (lane == 0 && (g | eq)) {
+        atomicAdd(&acc[0], g);
+        atomicAdd(&acc[1], eq);
+    }
+    __syncthreads();
+    int gt_run = above_before + acc[0], eq_run = acc[1];
+    // ---- ordered compaction of the chunks: 4 consecutive tokens per thread
+#pragma unroll
+    for (int r = 0; r < NCH; ++r) {
+        const int start = base + r * kCh + 4 * tid;
+        if (base + r * kCh >= N) break;                    // (uniform)
         int f[4], sum = 0;                                 // packed counts: larger | equal << 16
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -869,12 +807,8 @@ __global__ __launch_bounds__(kChThreads, 4) void sel_write_kernel(const float *_
             f[j] = start + j < N ? (int)(x > Tfull) | ((int)(x == Tfull) << 16) : 0;
             sum += f[j];
         }
-        const int incl = wave_scan_incl(sum);
-        if (lane == 63) sub_tot[r & 1][wv] = incl;
-        __syncthreads();
-        const int t0 = sub_tot[r & 1][0], t1 = sub_tot[r & 1][1], t2 = sub_tot[r & 1][2], t3 = sub_tot[r & 1][3];
-        int excl = incl - sum + (wv > 0 ? t0 : 0) + (wv > 1 ? t1 : 0) + (wv > 2 ? t2 : 0);
-        const int run = t0 + t1 + t2 + t3;
+        int total;
+        int excl = block_scan_incl(sum, r & 1 ? tot2 : tot, lane, wv, total) - sum;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int g_before = gt_run + (excl & 0xFFFF), e_before = eq_run + (excl >> 16);
@@ -886,8 +820,8 @@ __global__ __launch_bounds__(kChThreads, 4) void sel_write_kernel(const float *_
             if (slot >= 0 && slot < k) row[slot] = start + j;   // slot < k always holds; the test keeps a write in its row
             excl += f[j];
         }
-        gt_run += run & 0xFFFF;
-        eq_run += run >> 16;
+        gt_run += total & 0xFFFF;
+        eq_run += total >> 16;
     }
 }
 
@@ -900,7 +834,7 @@ bool set_select_path(int path)
     return true;
 }
 
-// Several workgroups per unit pay three to four dependent launches and read the keys three times; they win when
+// Several workgroups per unit pay two dependent launches and read the keys twice; they win when
 // one workgroup per unit would leave most of the chip idle.
 static bool select_chunked(int32_t units, int64_t L)
 {
@@ -908,7 +842,10 @@ static bool select_chunked(int32_t units, int64_t L)
     if (L <= 0 || nchunk > kChMaxChunks || ((long)units + 7) * nchunk > 0x7FFFFFFFL) return false;
     const int path = g_select_path.load();
     if (path) return path == 2;
-    return nchunk > 8 && units <= 128;                  // (prompts whose keys one workgroup cannot hold in LDS; measured)
+    // Prompts whose keys one workgroup cannot hold in LDS, and of those it can the long ones of few units (one workgroup against
+    // several, 4 heads: 4 units x 32768 20.4 -> 15.3 us, 32 x 32768 22.5 -> 18.5, but 64 x 32768 22.8 -> 27.0, 44 x 22289 17.1
+    // -> 22.3, 8 x 20000 12.9 -> 14.7).
+    return nchunk > 8 ? units <= 128 : nchunk > 6 && units * nchunk <= 256;
 }
 
 size_t select_workspace_bytes(int32_t units, int32_t rep, int64_t L)
@@ -919,23 +856,23 @@ size_t select_workspace_bytes(int32_t units, int32_t rep, int64_t L)
     return (size_t)sel_ws_words(units, rep, L) * sizeof(uint32_t);
 }
 
-template <bool FROM_FLOAT>
-static void launch_chunked_tail(const float *A, const SelWs &w, int32_t units, int64_t L, const int32_t *n_hh,
-                                const int32_t *n_rw, int32_t *idx, int64_t idx_stride, int32_t *n_tok, hipStream_t st)
+template <bool FROM_FLOAT, int NCH>
+static void launch_pick(const float *A, const SelWs &w, int32_t units, int64_t L, const int32_t *n_hh, const int32_t *n_rw,
+                        int32_t *idx, int64_t idx_stride, int32_t *n_tok, hipStream_t st)
 {
-    const long units8 = sel_grid_units(units);
-    const dim3 grid((unsigned)(units8 * w.nchunk));
-    if (w.nchunk <= kChDirect) {
-        hipLaunchKernelGGL((sel_cand_kernel<FROM_FLOAT, true>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh, n_rw,
-                           (long)idx_stride);
+    const long units8 = sel_grid_units(units), parts = (w.nchunk + NCH - 1) / NCH;
+    const dim3 grid((unsigned)(units8 * parts));
+    // Every workgroup reads 4 KB of counts per chunk of its unit from its die's L2: units / 8 * parts * nchunk * 4 KB per die
+    // at 2 KB a cycle.  Up to 3 us of that are less than the launch that adds them once costs.
+    if (w.nchunk <= 64 && units * parts * w.nchunk <= 24576) {
+        hipLaunchKernelGGL((sel_pick_kernel<FROM_FLOAT, true, NCH>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh, n_rw, idx,
+                           (long)idx_stride, n_tok);
     } else {
-        hipLaunchKernelGGL(sel_unit_hist_kernel, dim3((unsigned)(units8 * 8)), dim3(kChThreads), 0, st, w, (long)L, n_hh,
-                           n_rw, (long)idx_stride);
-        hipLaunchKernelGGL((sel_cand_kernel<FROM_FLOAT, false>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh,
-                           n_rw, (long)idx_stride);
+        hipLaunchKernelGGL(sel_unit_hist_kernel, dim3((unsigned)(units8 * 8)), dim3(256), 0, st, w, (long)L, n_hh, n_rw,
+                           (long)idx_stride);
+        hipLaunchKernelGGL((sel_pick_kernel<FROM_FLOAT, false, NCH>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh, n_rw, idx,
+                           (long)idx_stride, n_tok);
     }
-    hipLaunchKernelGGL((sel_write_kernel<FROM_FLOAT>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh, n_rw, idx,
-                       (long)idx_stride, n_tok);
 }
 
 int launch_select(int32_t units, int32_t rep, int64_t L, const float *A, const int32_t *n_hh,
@@ -946,16 +883,16 @@ int launch_select(int32_t units, int32_t rep, int64_t L, const float *A, const i
     if (select_chunked(units, L)) {
         const SelWs w = sel_ws_carve(workspace, units, rep, L);
         const dim3 grid((unsigned)(sel_grid_units(units) * w.nchunk));
-        auto k1 = rep == 1   ? sel_hist_kernel<1, true>
-                  : rep == 2 ? sel_hist_kernel<2, false>
-                  : rep == 4 ? sel_hist_kernel<4, false>
-                  : rep == 8 ? sel_hist_kernel<8, false>
-                             : sel_hist_kernel<0, false>;
+        auto k1 = rep == 1   ? sel_sort_kernel<1>
+                  : rep == 2 ? sel_sort_kernel<2>
+                  : rep == 4 ? sel_sort_kernel<4>
+                  : rep == 8 ? sel_sort_kernel<8>
+                             : sel_sort_kernel<0>;
         hipLaunchKernelGGL(k1, grid, dim3(kChThreads), 0, st, A, w, rep, (long)L, n_hh, n_rw, (long)idx_stride);
-        if (rep == 1)
-            launch_chunked_tail<true>(A, w, units, L, n_hh, n_rw, idx, idx_stride, n_tok, st);
-        else
-            launch_chunked_tail<false>(A, w, units, L, n_hh, n_rw, idx, idx_stride, n_tok, st);
+        // One chunk per workgroup while all of them run at once; beyond that every further round repeats the work on the cut.
+        const bool few = (long)units * w.nchunk <= 512;
+        const auto pick = rep == 1 ? (few ? launch_pick<true, 1> : launch_pick<true, 4>) : few ? launch_pick<false, 1> : launch_pick<false, 4>;
+        pick(A, w, units, L, n_hh, n_rw, idx, idx_stride, n_tok, st);
         return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
     }
     // keys stay in LDS when the whole prompt fits beside the fixed part

@@ -214,3 +214,15 @@ def test_selected_tokens_through_quantize_and_decode(g):
     g.assert_cache_bit_exact(gc, rc, what=("Kc", "Ks", "Kz", "Vc", "Vs", "Vz", "q_len", "r_len"))
     want, _, _ = ref.decode_attn(rc, g.to_np(inp.q), g.sm_scale())
     assert np.max(np.abs(g.to_np(out).astype(np.float64) - want)) <= TOL
+
+
+@pytest.mark.parametrize("U,rep,L,kind", [(52, 1, 36865, "attention"), (64, 2, 32769, "ties"), (51, 1, 40960, "signed"), (129, 2, 13000, "attention"),
+                                          (7, 1, 36864, "ties"), (3, 4, 262145, "attention")])
+def test_four_chunks_per_workgroup_and_who_adds_the_counts(g, U, rep, L, kind):
+    """Chunk counts on both sides of where a workgroup takes four chunks (more than 512 in the launch; the last workgroup of
+    a unit has one to four), and of where a launch of its own adds the chunks' counts; windows that end inside a chunk."""
+    rng = np.random.default_rng(U + L)
+    A = W.make_scores(U * rep, L, seed=900 + U, device="cuda", kind=kind)
+    n_rw = rng.integers(0, L // 2, U)
+    n_hh = np.array([rng.integers(1, L - w) for w in n_rw])
+    check(g, A, n_hh.astype(np.int32), n_rw.astype(np.int32), rep=rep)
