@@ -95,19 +95,23 @@ __device__ __forceinline__ half4 read_transposed(const _Float16 *p)
 }
 
 // SPLIT == 2: two sets of WAVES waves take the even and the odd tiles of the same queries, each through LDS buffers of
-// its own, and meet at the end; for launches that leave a compute unit a single set.  (The second launch bound keeps the
-// accumulators out of the registers only matrix instructions reach.  Two sets of two waves never have two waves on a SIMD:
-// they use the registers of both, the second half as accumulation registers.)  No instance has a private segment.
+// its own, and meet at the end; for launches that leave a compute unit a single set.  The launch gives the LDS: where the
+// compiler knows that 128 KB leave room for one workgroup, it spreads two sets of two waves over the registers of two
+// waves per SIMD, half of them reachable for matrix instructions only, and moves 160 registers per tile (3700 cycles a
+// tile, 2400 without; 8 heads x 2048 32.2 -> 26.3 us).  With the second launch bound no instance has a register of that
+// kind, nor a private segment.
+constexpr unsigned fwd_lds_bytes(int split) { return split * 4 * kPfTile * sizeof(_Float16); }
+
 template <int WAVES, int SPLIT>
-__global__ __launch_bounds__(64 * WAVES * SPLIT, SPLIT == 2 && WAVES == 2 ? 1 : 2) void prefill_fwd_kernel(PrefillArgs a)
+__global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(PrefillArgs a)
 {
     constexpr int kRows = kPfN / WAVES, kLoads = kRows / 4;     // rows of a tile one wave loads, four per instruction
-    __shared__ __align__(16) _Float16 tiles[SPLIT][4 * kPfTile];
+    extern __shared__ __align__(16) _Float16 tiles[];
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WAVES;
     const int set = SPLIT == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WAVES;
-    _Float16 *Ks = tiles[set], *Vs = tiles[set] + 2 * kPfTile;
+    _Float16 *Ks = tiles + set * 4 * kPfTile, *Vs = Ks + 2 * kPfTile;
     // heaviest row blocks (the last ones: they see the most keys) first
     const int nbh = (int)gridDim.x / a.nblk, head = (int)blockIdx.x % nbh;
     const int qb = a.nblk - 1 - (int)blockIdx.x / nbh;
@@ -131,11 +135,9 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, SPLIT == 2 && WAVES == 2 ? 1 : 
     const int mytiles = of_set(min((q0 + 31) / kPfN + 1, all)), nfull = min(of_set((q0 + 1) / kPfN), mytiles);
 
     // tile loads
-    unsigned k_off[kLoads];
     const unsigned v_off = (lane >> 4) * 256u + (((lane & 15) ^ v_swizzle(lane >> 4)) << 4);
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i)
-        k_off[i] = (lane >> 4) * 256u + (((lane & 15) ^ ((wave * kRows + i * 4 + (lane >> 4)) & 15)) << 4);
+    // (of the first load; the i-th one is four rows further for each i, which flips bits 2 and 3 of the chunk)
+    const unsigned k_off = (lane >> 4) * 256u + (((lane & 15) ^ ((wave * kRows + (lane >> 4)) & 15)) << 4);
     const unsigned k_lds = lds_offset(Ks) + wave * (kRows * 256u), v_lds = lds_offset(Vs) + wave * (kRows * 256u);
     // (no branch: code motion across one would take the interleaving below apart.  Lanes whose row lies past the
     // prompt load the last chunk of its last row, any finite value will do: their weights are 0.  For a tile past the
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, SPLIT == 2 && WAVES == 2 ? 1 : 
         const int end = t < all ? max(L - 1 - row0, 0) * 256 + 240 : 0;
 #pragma unroll
         for (int i = 0; i < kLoads; ++i)
-            load_to_lds(tile, (unsigned)min((int)(is_v ? v_off : k_off[i]) + i * 1024, end), lds + i * 1024u);
+            load_to_lds(tile, (unsigned)min((int)(is_v ? v_off : k_off ^ ((i & 3) << 6)) + i * 1024, end), lds + i * 1024u);
     };
     // all loads of this wave have landed and its fragment reads have returned (their buffer is about to be refilled); then
     // the barrier that hands every wave's share over
@@ -320,7 +322,7 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, SPLIT == 2 && WAVES == 2 ? 1 : 
     }
     if constexpr (SPLIT == 2) {
         // the second set's state goes to the first through LDS (every tile has been read, every load has landed)
-        float *xch = (float *)&tiles[0][0] + wave * (66 * 64) + lane;
+        float *xch = (float *)tiles + wave * (66 * 64) + lane;
         hand_over();
         if (set == 1) {
             xch[0] = m, xch[64] = l;
@@ -531,28 +533,33 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
     a.Hq = Hq, a.rep = Hq / Hkv, a.L = L, a.scale_log2 = sm_scale * kLog2e;
     // Queries per workgroup and whether two sets of waves share them.  256 queries halve what a tile costs to load; on long
     // prompts, while they leave four workgroups per compute unit, that is 1-3 % (64 heads x 16384: 4.32 -> 4.25 ms), on
-    // shorter ones the waves that are done wait for the others (512 heads x 257: 47 -> 59 us).  Else 128.  A launch of at
-    // most one workgroup per compute unit lasts as long as its longest row block: two sets of waves halve that, less what
-    // their meeting costs (8 heads x 4096: 71.8 -> 64.7 us, 32 x 1024 23.0 -> 22.7, but 32 x 512 14.5 -> 15.2), and where
-    // even blocks of 64 queries leave one per compute unit those are shorter still (8 x 2048 37.6 -> 31.9 us, 32 x 512
-    // 14.5 -> 13.3, 32 x 400 12.4 -> 12.1, but 32 x 200 9.0 -> 9.5).
+    // shorter ones the waves that are done wait for the others (512 heads x 257: 47 -> 59 us).  Else 128, but a launch of
+    // few workgroups lasts as long as its longest row block, and that is shorter
+    //   with 64 queries shared by two sets, if there is one workgroup per compute unit (LDS holds no second one; 8 heads x
+    //   2048: 37.4 -> 27.2 us, 32 x 512 14.7 -> 11.9, 64 x 200 9.7 -> 9.2, 32 x 128 8.0 -> 7.4; but 64 x 257 10.9 -> 14.6 and
+    //   8 x 65 6.8 -> 7.3), or two and few heads: the second ones are then blocks that see a short part of the prompt
+    //   (16 x 2048 38.8 -> 34.7, 8 x 4096 69.6 -> 58.2, but 24 x 1200 25.5 -> 25.7, 32 x 1000 23.0 -> 23.8),
+    //   with 128 shared by two sets, if there are up to two per compute unit and the prompt is long (8 x 6000: 110.8 -> 98.5,
+    //   16 x 3000 59.8 -> 53.8; 32 x 2048 51.4 -> 52.5), at one per compute unit from 1024 tokens on (32 x 1024 23.0 -> 22.7).
     // In the second pass eight waves per workgroup lose (4.36 -> 4.62 ms): they wait for each other at every tile.  Two
     // waves (64 keys) are for prompts of one such block, where two of the four would have no key, once the workgroups no
     // longer all run at once (1024 heads x 48: first and second pass 26.7 -> 24.0 us).
     const int64_t heads = (int64_t)B * Hq;
     auto blocks = [&](int queries) { return heads * ((L + queries - 1) / queries); };
     constexpr int64_t kComputeUnits = 256;
-    const int queries = L >= 4096 && blocks(256) >= 4 * kComputeUnits ? 256 : L > 384 && blocks(64) <= kComputeUnits ? 64 : 128;
+    const bool two_sets_64 = L > 96 && blocks(64) <= (heads <= 20 ? 2 : 1) * kComputeUnits;
+    const bool two_sets_128 = L >= 1024 && blocks(128) <= (L > 2048 ? 2 : 1) * kComputeUnits;
+    const int queries = L >= 4096 && blocks(256) >= 4 * kComputeUnits ? 256 : two_sets_64 ? 64 : 128;
     a.nblk = (int)((L + queries - 1) / queries);
     const dim3 grid((unsigned)(heads * a.nblk));
     if (queries == 256)
-        hipLaunchKernelGGL((prefill_fwd_kernel<8, 1>), grid, dim3(512), 0, st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<8, 1>), grid, dim3(512), fwd_lds_bytes(1), st, a);
     else if (queries == 64)
-        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2>), grid, dim3(256), 0, st, a);
-    else if (L >= 1024 && blocks(128) <= kComputeUnits)
-        hipLaunchKernelGGL((prefill_fwd_kernel<4, 2>), grid, dim3(512), 0, st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2>), grid, dim3(256), fwd_lds_bytes(2), st, a);
+    else if (two_sets_128)
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 2>), grid, dim3(512), fwd_lds_bytes(2), st, a);
     else
-        hipLaunchKernelGGL((prefill_fwd_kernel<4, 1>), grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 1>), grid, dim3(256), fwd_lds_bytes(1), st, a);
     if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     if (A_cumul) {
         const int keys = L <= 64 && heads > 2 * kComputeUnits ? 64 : 128;

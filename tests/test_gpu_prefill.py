@@ -123,7 +123,7 @@ def check_last(g, B, Hq, Hkv, L, seed):
 
 @pytest.mark.parametrize("B,Hq,Hkv,L", [(1, 2, 1, 385), (1, 2, 2, 447), (1, 2, 1, 448), (2, 4, 1, 449), (8, 4, 2, 512), (1, 2, 1, 577), (1, 1, 1, 1000)])
 def test_two_sets_of_waves_on_64_queries(g, B, Hq, Hkv, L):
-    """More than 384 tokens and at most 256 blocks of 64 queries: an odd and an even number of tiles, ragged ends."""
+    """More than 96 tokens and at most 256 blocks of 64 queries: an odd and an even number of tiles, ragged ends."""
     check_last(g, B, Hq, Hkv, L, 1100 + L)
 
 
@@ -131,6 +131,12 @@ def test_two_sets_of_waves_on_64_queries(g, B, Hq, Hkv, L):
 def test_two_sets_of_waves_on_128_queries(g, B, Hq, Hkv, L):
     """From 1024 tokens on, more than 256 blocks of 64 queries (or just as many) and at most 256 of 128."""
     check_last(g, B, Hq, Hkv, L, 1200 + L)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(4, 32, 8, 65), (2, 32, 8, 256), (5, 32, 8, 128), (8, 1, 1, 2049), (2, 8, 2, 2048), (3, 4, 4, 2689), (11, 1, 1, 3009), (8, 1, 1, 8191)])
+def test_launches_of_up_to_two_long_row_blocks_per_compute_unit(g, B, Hq, Hkv, L):
+    """Either side of the lines between 64 queries and two sets of waves, 128 and two sets, and 128 alone."""
+    check_last(g, B, Hq, Hkv, L, 1250 + L)
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,L", [(64, 1, 1, 4096), (61, 1, 1, 4223)])
