@@ -364,7 +364,10 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
 // What bounds it: on N(0,1) data the clock falls to 1.8 GHz under this load (2.4 GHz on zeros, same cycles), so what
 // counts is energy as well as issue slots.  Q tiles therefore go straight to LDS: staging them through registers cost
 // 12 % of the cycles (the LDS stores stall the stream).  32 heads x 32768 tokens 4.85 -> 4.47 ms (980 TFLOP/s),
-// 32 x 2048 32 -> 25 us, 32 x 777 15.6 -> 12.3 us.  Three LDS buffers instead of two: the same.
+// 32 x 2048 32 -> 25 us, 32 x 777 15.6 -> 12.3 us.  Three LDS buffers instead of two: the same.  The sums are pinned where
+// they are formed: without that the weights of every other step stood after its products, in front of the next ones (32
+// heads x 16384 1.185 -> 1.156 ms, 32 x 777 12.7 -> 12.1 us, 8 x 2048 21.6 -> 20.2).  Two sets of waves on the even and the
+// odd tiles, as in the first pass, gain from 4096 tokens on only (8 x 4096 37.5 -> 35.3, but 32 x 777 12.3 -> 14.0).
 template <int kWaves>
 __global__ __launch_bounds__(64 * kWaves, 2) void prefill_colsum_kernel(PrefillArgs a)
 {
@@ -461,7 +464,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_colsum_kernel(PrefillA
                 const int t = (2 * m + 2) >> 4, i = (2 * m + 2) & 15;
                 x[0] = __builtin_fmaf(cur[t][i], c, -ls[i]), x[1] = __builtin_fmaf(cur[t][i + 1], c, -ls[i + 1]);
             }
-            if (m) cs[(m - 1) >> 3] += y[1];
+            if (m) {
+                cs[(m - 1) >> 3] += y[1];
+                asm volatile("" : "+v"(cs[(m - 1) >> 3]));    // (else every other step's weights sink behind the next one's mask test)
+            }
             y[0] = y0, y[1] = y1;
             if (m == 0) lr = request(n + 3);
             if (m == 15) settle(n + 3);
