@@ -100,9 +100,13 @@ __device__ __forceinline__ half4 read_transposed(const _Float16 *p)
 // waves per SIMD, half of them reachable for matrix instructions only, and moves 160 registers per tile (3700 cycles a
 // tile, 2400 without; 8 heads x 2048 32.2 -> 26.3 us).  With the second launch bound no instance has a register of that
 // kind, nor a private segment.
-constexpr unsigned fwd_lds_bytes(int split) { return split * 4 * kPfTile * sizeof(_Float16); }
+//
+// BUF == 1: one K and one V buffer per set instead of two, so that a compute unit has room for two workgroups of two sets.
+// K tile n+2 is requested between the halves and V tile n+1 at the end of step n, each into the buffer that has just been
+// read, at a second barrier; what a wave then waits the other workgroup's wave of its SIMD fills.
+constexpr unsigned fwd_lds_bytes(int split, int buffers) { return split * 2 * buffers * kPfTile * sizeof(_Float16); }
 
-template <int WAVES, int SPLIT>
+template <int WAVES, int SPLIT, int BUF>
 __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(PrefillArgs a)
 {
     constexpr int kRows = kPfN / WAVES, kLoads = kRows / 4;     // rows of a tile one wave loads, four per instruction
@@ -111,7 +115,7 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WAVES;
     const int set = SPLIT == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WAVES;
-    _Float16 *Ks = tiles + set * 4 * kPfTile, *Vs = Ks + 2 * kPfTile;
+    _Float16 *Ks = tiles + set * 2 * BUF * kPfTile, *Vs = Ks + BUF * kPfTile;
     // heaviest row blocks (the last ones: they see the most keys) first
     const int nbh = (int)gridDim.x / a.nblk, head = (int)blockIdx.x % nbh;
     const int qb = a.nblk - 1 - (int)blockIdx.x / nbh;
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
     auto request = [&](const _Float16 *base, int n, bool is_v) {
         const int t = n * SPLIT + set, row0 = min(t, all - 1) * kPfN + wave * kRows;
         const char *tile = (const char *)(base + (long)min(row0, L - 1) * kPfD);
-        const unsigned lds = (is_v ? v_lds : k_lds) + (n & 1) * (kPfTile * 2u);
+        const unsigned lds = (is_v ? v_lds : k_lds) + (BUF == 2 ? (n & 1) * (kPfTile * 2u) : 0u);
         const int end = t < all ? max(L - 1 - row0, 0) * 256 + 240 : 0;
 #pragma unroll
         for (int i = 0; i < kLoads; ++i)
@@ -166,10 +170,10 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
             v_place[db] = row * kPfD + (((4 * db + c0) ^ v_swizzle(row)) << 3) + (i & 1) * 4;
     }
     auto read_k = [&](int j, int odd) -> half8 {       // fragment j of an even / odd tile: keys 32 (j & 1) .., channels 16 (j >> 1) ..
-        return *(const half8 *)(Ks + odd * kPfTile + (j & 1) * 32 * kPfD + k_place[j >> 1]);
+        return *(const half8 *)(Ks + (BUF == 2 ? odd * kPfTile : 0) + (j & 1) * 32 * kPfD + k_place[j >> 1]);
     };
     auto read_v = [&](int j, int odd) -> half8 {         // fragment j: keys 16 (j >> 2) + 4 g + {0..3, 8..11}, channels 32 (j & 3) + r
-        const _Float16 *p = Vs + odd * kPfTile + (j >> 2) * 16 * kPfD + v_place[j & 3];
+        const _Float16 *p = Vs + (BUF == 2 ? odd * kPfTile : 0) + (j >> 2) * 16 * kPfD + v_place[j & 3];
         const half4 lo = read_transposed(p), hi = read_transposed(p + 8 * kPfD);
         return half8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     };
@@ -248,8 +252,8 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
         hand_over();
 #pragma unroll
         for (int j = 0; j < 4; ++j) vf[j] = read_v(j, odd);
-        request(Vh, n + 1, true);
-        request(Kh, n + 3, false);
+        if (BUF == 2) request(Vh, n + 1, true);
+        request(Kh, n + BUF + 1, false);
         float mx[4];
         if (decltype(multiply)::value && decltype(masked)::value) mask(next, n + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
         for (int j = 0; j < 16; ++j) {
             o[j & 3] = mfma32(vf[j & 3], pb[j >> 2], o[j & 3]);
             if (j < 12) vf[j & 3] = read_v(j + 4, odd);
-            if (decltype(multiply)::value && j >= 12) kf[j & 3] = read_k(j & 3, odd);   // (past the last tile: unused)
+            if (BUF == 2 && decltype(multiply)::value && j >= 12) kf[j & 3] = read_k(j & 3, odd);   // (past the last tile: unused)
             if (j < 4) slot(j + 14);
             if (decltype(multiply)::value && j >= 4 && j < 12) {
                 const int e = 4 * (j - 4), t = e >> 4, i = e & 15, k = j & 3;
@@ -267,11 +271,19 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
             __builtin_amdgcn_sched_barrier(0);
         }
         l += sum[0] + sum[1];
+        if (BUF == 1) {
+            hand_over();
+            request(Vh, n + 1, true);
+            if (decltype(multiply)::value) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) kf[j] = read_k(j, 0);
+            }
+        }
         if (decltype(multiply)::value) settle(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
     };
 
     request(Kh, 0, false);
-    request(Kh, 1, false);
+    if (BUF == 2) request(Kh, 1, false);
     request(Vh, 0, true);
     hand_over();                                       // (the Q rows have arrived as well)
     float16v sa[2], sb[2];
@@ -289,11 +301,18 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sa[t][i]);
         settle(mx);
+        if (BUF == 2) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) kf[j] = read_k(j, 1);      // (with a single tile: unused)
+            for (int j = 0; j < 4; ++j) kf[j] = read_k(j, 1);  // (with a single tile: unused)
+        }
     }
     hand_over();
-    request(Kh, 2, false);
+    request(Kh, BUF, false);
+    if (BUF == 1) {
+        hand_over();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) kf[j] = read_k(j, 0);
+    }
 
     const std::true_type yes{};
     const std::false_type no{};
@@ -311,14 +330,19 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
         if (n + 1 < mytiles) {
             step(sa, sb, n, yes, no, yes);
             sa[0] = sb[0], sa[1] = sb[1];
-            Vs += kPfTile, ++n;
+            if (BUF == 2) Vs += kPfTile;
+            ++n;
         }
         step(sa, sb, n, no, no, no);
     }
     for (int n = mytiles; n < ntiles; ++n) {           // tiles only other waves see: this one still loads its share
         hand_over();
-        request(Vh, n + 1, true);
-        request(Kh, n + 3, false);
+        if (BUF == 2) request(Vh, n + 1, true);
+        request(Kh, n + BUF + 1, false);
+        if (BUF == 1) {
+            hand_over();
+            request(Vh, n + 1, true);
+        }
     }
     if constexpr (SPLIT == 2) {
         // the second set's state goes to the first through LDS (every tile has been read, every load has landed)
@@ -541,31 +565,36 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
     // prompts, while they leave four workgroups per compute unit, that is 1-3 % (64 heads x 16384: 4.32 -> 4.25 ms), on
     // shorter ones the waves that are done wait for the others (512 heads x 257: 47 -> 59 us).  Else 128, but a launch of
     // few workgroups lasts as long as its longest row block, and that is shorter
-    //   with 64 queries shared by two sets, if there is one workgroup per compute unit (LDS holds no second one; 8 heads x
-    //   2048: 37.4 -> 27.2 us, 32 x 512 14.7 -> 11.9, 64 x 200 9.7 -> 9.2, 32 x 128 8.0 -> 7.4; but 64 x 257 10.9 -> 14.6 and
-    //   8 x 65 6.8 -> 7.3), or two and few heads: the second ones are then blocks that see a short part of the prompt
-    //   (16 x 2048 38.8 -> 34.7, 8 x 4096 69.6 -> 58.2, but 24 x 1200 25.5 -> 25.7, 32 x 1000 23.0 -> 23.8),
-    //   with 128 shared by two sets, if there are up to two per compute unit and the prompt is long (8 x 6000: 110.8 -> 98.5,
-    //   16 x 3000 59.8 -> 53.8; 32 x 2048 51.4 -> 52.5), at one per compute unit from 1024 tokens on (32 x 1024 23.0 -> 22.7).
+    //   with 64 queries shared by two sets, if there is one workgroup per compute unit (8 heads x 2048: 37.4 -> 27.2 us, 32 x
+    //   512 14.7 -> 11.9, 64 x 200 9.7 -> 9.2, 32 x 128 8.0 -> 7.4, but 8 x 65 6.8 -> 7.3), or, of few heads, not many more:
+    //   the second ones are then blocks that see a short part of the prompt (16 x 1200 24.2 -> 19.6, 8 x 3000 50.7 -> 38.3);
+    //   the same with one buffer each, if all run at once, two per compute unit (32 x 777 19.0 -> 16.9, 32 x 1000 22.9 ->
+    //   20.7, 48 x 512 14.9 -> 14.5, 16 x 2048 38.5 -> 32.2 against 34.6 with two buffers, which are better by themselves:
+    //   16 x 1200 19.6 against 20.6; 64 x 320 10.9 -> 12.3, 48 x 777, at 624 workgroups, 21.7 -> 24.7);
+    //   with 128 shared by two sets, if there are not many more than one per compute unit on long prompts of few heads (8 x
+    //   6000: 110.8 -> 98.5, 16 x 3000 59.3 -> 52.9, 32 x 1200 27.5 -> 26.4; but 24 x 2100 45.2 -> 46.1, 48 x 1000 26.2 -> 29.7).
     // In the second pass eight waves per workgroup lose (4.36 -> 4.62 ms): they wait for each other at every tile.  Two
     // waves (64 keys) are for prompts of one such block, where two of the four would have no key, once the workgroups no
     // longer all run at once (1024 heads x 48: first and second pass 26.7 -> 24.0 us).
     const int64_t heads = (int64_t)B * Hq;
     auto blocks = [&](int queries) { return heads * ((L + queries - 1) / queries); };
     constexpr int64_t kComputeUnits = 256;
-    const bool two_sets_64 = L > 96 && blocks(64) <= (heads <= 20 ? 2 : 1) * kComputeUnits;
-    const bool two_sets_128 = L >= 1024 && blocks(128) <= (L > 2048 ? 2 : 1) * kComputeUnits;
+    const bool two_buffers = L > 96 && 2 * blocks(64) <= (heads <= 20 ? 3 : 2) * kComputeUnits;
+    const bool two_sets_64 = two_buffers || (L > 384 && blocks(64) <= 2 * kComputeUnits);
+    const bool two_sets_128 = L >= 1024 && heads <= 32 && 2 * blocks(128) <= (heads <= 20 ? 4 : 3) * kComputeUnits;
     const int queries = L >= 4096 && blocks(256) >= 4 * kComputeUnits ? 256 : two_sets_64 ? 64 : 128;
     a.nblk = (int)((L + queries - 1) / queries);
     const dim3 grid((unsigned)(heads * a.nblk));
     if (queries == 256)
-        hipLaunchKernelGGL((prefill_fwd_kernel<8, 1>), grid, dim3(512), fwd_lds_bytes(1), st, a);
-    else if (queries == 64)
-        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2>), grid, dim3(256), fwd_lds_bytes(2), st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<8, 1, 2>), grid, dim3(512), fwd_lds_bytes(1, 2), st, a);
+    else if (two_sets_64 && !two_buffers)
+        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2, 1>), grid, dim3(256), fwd_lds_bytes(2, 1), st, a);
+    else if (two_sets_64)
+        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2, 2>), grid, dim3(256), fwd_lds_bytes(2, 2), st, a);
     else if (two_sets_128)
-        hipLaunchKernelGGL((prefill_fwd_kernel<4, 2>), grid, dim3(512), fwd_lds_bytes(2), st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 2, 2>), grid, dim3(512), fwd_lds_bytes(2, 2), st, a);
     else
-        hipLaunchKernelGGL((prefill_fwd_kernel<4, 1>), grid, dim3(256), fwd_lds_bytes(1), st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 1, 2>), grid, dim3(256), fwd_lds_bytes(1, 2), st, a);
     if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     if (A_cumul) {
         const int keys = L <= 64 && heads > 2 * kComputeUnits ? 64 : 128;
