@@ -104,9 +104,17 @@ __device__ __forceinline__ half4 read_transposed(const _Float16 *p)
 // BUF == 1: one K and one V buffer per set instead of two, so that a compute unit has room for two workgroups of two sets.
 // K tile n+2 is requested between the halves and V tile n+1 at the end of step n, each into the buffer that has just been
 // read, at a second barrier; what a wave then waits the other workgroup's wave of its SIMD fills.
-constexpr unsigned fwd_lds_bytes(int split, int buffers) { return split * 2 * buffers * kPfTile * sizeof(_Float16); }
+//
+// SCORES: the prompt is one row block, whose workgroup then has every row's LSE and returns the column sums as well: the
+// scores once more, as S = Q K^T with the Q rows it still holds, so that a lane adds up one key's weights; the waves' sums
+// meet in LDS.  What bounds short prompts is the launch and its two round trips to memory, and a second one repeats them:
+// 8 heads x 48 tokens 9.8 -> 6.7 us, 8 x 128 13.3 -> 10.2, 1024 x 64 26.7 -> 21.4, 2048 x 128 95.6 -> 71.7.
+constexpr unsigned fwd_lds_bytes(int split, int buffers, int scored_queries = 0)
+{
+    return split * 2 * buffers * kPfTile * sizeof(_Float16) + scored_queries * (1 + scored_queries / 32) * sizeof(float);
+}
 
-template <int WAVES, int SPLIT, int BUF>
+template <int WAVES, int SPLIT, int BUF, bool SCORES>
 __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(PrefillArgs a)
 {
     constexpr int kRows = kPfN / WAVES, kLoads = kRows / 4;     // rows of a tile one wave loads, four per instruction
@@ -364,9 +372,18 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
     }
 
     l += __shfl_xor(l, 32, 64);
-    const float inv = 1.0f / l;
+    const float inv = 1.0f / l, lse2 = m * c + log2f(l);
+    float *row_lse2 = (float *)(tiles + SPLIT * 2 * BUF * kPfTile), *part = row_lse2 + 32 * WAVES;
+    if constexpr (SCORES) {                            // the prompt's one or two K tiles again, and every row's LSE
+        static_assert(!SCORES || (WAVES == 4 && SPLIT == 1 && BUF == 2), "two tiles, one set of waves");
+        hand_over();
+        request(Kh, 0, false);
+        request(Kh, 1, false);
+        if (g == 0) row_lse2[wave * 32 + r] = lse2;
+        hand_over();
+    }
     if (query < L) {
-        if (g == 0) a.lse[bh * L + query] = (m * c + log2f(l)) * kLn2;
+        if (g == 0) a.lse[bh * L + query] = lse2 * kLn2;
         _Float16 *orow = a.XO + (bh * L + query) * kPfD;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -377,6 +394,42 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
                 for (int j = 0; j < 4; ++j) h[j] = (_Float16)(o[db][iq * 4 + j] * inv);
                 *(half4 *)(orow + db * 32 + iq * 8 + g * 4) = h;
             }
+    }
+    if constexpr (SCORES) {
+        float ls[16];
+#pragma unroll
+        for (int iq = 0; iq < 4; ++iq) {
+            const float4 v = *(const float4 *)&row_lse2[wave * 32 + iq * 8 + g * 4];
+            ls[iq * 4] = v.x, ls[iq * 4 + 1] = v.y, ls[iq * 4 + 2] = v.z, ls[iq * 4 + 3] = v.w;
+        }
+        const int end = L - q0 - 4 * g;                // rows of the wave's block that exist, this half-wave's share
+        for (int n = 0; n < mytiles; ++n) {
+            float16v s[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[t][i] = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) s[j & 1] = mfma32(qf[j >> 1], read_k(j, n), s[j & 1]);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int key = n * kPfN + t * 32 + r, first = key - q0 - 4 * g;     // first row that sees the key
+                float sum = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][i], c, -ls[i]));
+                    sum += acc_row(i, 0) >= first && acc_row(i, 0) < end ? w : 0.0f;
+                }
+                sum += __shfl_xor(sum, 32, 64);
+                if (g == 0) part[wave * (32 * WAVES) + key] = sum;
+            }
+        }
+        __syncthreads();
+        if (tid < L) {                                 // (the waves of the rows before the key have nothing to add)
+            float total = 0.0f;
+            for (int w = tid >> 5; w < WAVES; ++w) total += part[w * (32 * WAVES) + tid];
+            a.A_cumul[bh * L + tid] = total;
+        }
     }
 }
 
@@ -392,11 +445,11 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
 // they are formed: without that the weights of every other step stood after its products, in front of the next ones (32
 // heads x 16384 1.185 -> 1.156 ms, 32 x 777 12.7 -> 12.1 us, 8 x 2048 21.6 -> 20.2).  Two sets of waves on the even and the
 // odd tiles, as in the first pass, gain from 4096 tokens on only (8 x 4096 37.5 -> 35.3, but 32 x 777 12.3 -> 14.0).
-template <int kWaves>
-__global__ __launch_bounds__(64 * kWaves, 2) void prefill_colsum_kernel(PrefillArgs a)
+constexpr int kColWaves = 4, kKeyWaves = kColWaves / 2, kKeys = 64 * kKeyWaves;
+
+__global__ __launch_bounds__(64 * kColWaves, 2) void prefill_colsum_kernel(PrefillArgs a)
 {
-    constexpr int kKeyWaves = kWaves / 2, kKeys = 64 * kKeyWaves;
-    constexpr int kRows = kPfN / kWaves, kLoads = kRows / 4;    // rows of a tile one wave loads, four per instruction
+    constexpr int kRows = kPfN / kColWaves, kLoads = kRows / 4;    // rows of a tile one wave loads, four per instruction
     __shared__ __align__(16) _Float16 Qs[2 * kPfN * kPfD];
     __shared__ __align__(16) float lse2[4 * kPfN];     // LSE of a tile's queries in powers of two; read one iteration
                                                        // after the tile's rows, so kept longer
@@ -573,12 +626,15 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
     //   16 x 1200 19.6 against 20.6; 64 x 320 10.9 -> 12.3, 48 x 777, at 624 workgroups, 21.7 -> 24.7);
     //   with 128 shared by two sets, if there are not many more than one per compute unit on long prompts of few heads (8 x
     //   6000: 110.8 -> 98.5, 16 x 3000 59.3 -> 52.9, 32 x 1200 27.5 -> 26.4; but 24 x 2100 45.2 -> 46.1, 48 x 1000 26.2 -> 29.7).
-    // In the second pass eight waves per workgroup lose (4.36 -> 4.62 ms): they wait for each other at every tile.  Two
-    // waves (64 keys) are for prompts of one such block, where two of the four would have no key, once the workgroups no
-    // longer all run at once (1024 heads x 48: first and second pass 26.7 -> 24.0 us).
+    // In the second pass eight waves per workgroup lose (4.36 -> 4.62 ms): they wait for each other at every tile.
     const int64_t heads = (int64_t)B * Hq;
     auto blocks = [&](int queries) { return heads * ((L + queries - 1) / queries); };
     constexpr int64_t kComputeUnits = 256;
+    if (A_cumul && L <= 128) {                         // one row block a head: always faster in one launch (see SCORES)
+        a.nblk = 1;
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 1, 2, true>), dim3((unsigned)heads), dim3(256), fwd_lds_bytes(1, 2, 128), st, a);
+        return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
+    }
     const bool two_buffers = L > 96 && 2 * blocks(64) <= (heads <= 20 ? 3 : 2) * kComputeUnits;
     const bool two_sets_64 = two_buffers || (L > 384 && blocks(64) <= 2 * kComputeUnits);
     const bool two_sets_128 = L >= 1024 && heads <= 32 && 2 * blocks(128) <= (heads <= 20 ? 4 : 3) * kComputeUnits;
@@ -586,23 +642,19 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
     a.nblk = (int)((L + queries - 1) / queries);
     const dim3 grid((unsigned)(heads * a.nblk));
     if (queries == 256)
-        hipLaunchKernelGGL((prefill_fwd_kernel<8, 1, 2>), grid, dim3(512), fwd_lds_bytes(1, 2), st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<8, 1, 2, false>), grid, dim3(512), fwd_lds_bytes(1, 2), st, a);
     else if (two_sets_64 && !two_buffers)
-        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2, 1>), grid, dim3(256), fwd_lds_bytes(2, 1), st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2, 1, false>), grid, dim3(256), fwd_lds_bytes(2, 1), st, a);
     else if (two_sets_64)
-        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2, 2>), grid, dim3(256), fwd_lds_bytes(2, 2), st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<2, 2, 2, false>), grid, dim3(256), fwd_lds_bytes(2, 2), st, a);
     else if (two_sets_128)
-        hipLaunchKernelGGL((prefill_fwd_kernel<4, 2, 2>), grid, dim3(512), fwd_lds_bytes(2, 2), st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 2, 2, false>), grid, dim3(512), fwd_lds_bytes(2, 2), st, a);
     else
-        hipLaunchKernelGGL((prefill_fwd_kernel<4, 1, 2>), grid, dim3(256), fwd_lds_bytes(1, 2), st, a);
+        hipLaunchKernelGGL((prefill_fwd_kernel<4, 1, 2, false>), grid, dim3(256), fwd_lds_bytes(1, 2), st, a);
     if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     if (A_cumul) {
-        const int keys = L <= 64 && heads > 2 * kComputeUnits ? 64 : 128;
-        a.nblk = (int)((L + keys - 1) / keys);
-        if (keys == 64)
-            hipLaunchKernelGGL(prefill_colsum_kernel<2>, dim3((unsigned)(heads * a.nblk)), dim3(128), 0, st, a);
-        else
-            hipLaunchKernelGGL(prefill_colsum_kernel<4>, dim3((unsigned)(heads * a.nblk)), dim3(256), 0, st, a);
+        a.nblk = (int)((L + kKeys - 1) / kKeys);
+        hipLaunchKernelGGL(prefill_colsum_kernel, dim3((unsigned)(heads * a.nblk)), dim3(64 * kColWaves), 0, st, a);
         if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     }
     return MINIKV_OK;

@@ -154,6 +154,11 @@ def test_column_sums_of_64_keys_per_workgroup(g, B, Hq, Hkv, L):
     check_last(g, B, Hq, Hkv, L, 1400 + L)
 
 
+@pytest.mark.parametrize("L", [2, 32, 33, 63, 95, 96, 97, 127, 128])
+def test_one_launch_for_prompts_of_one_row_block(g, L):
+    check(g, 2, 6, 2, L, 1500 + L, gain=1.5)
+
+
 @pytest.mark.parametrize("per_tile", [-3.0, 0.02, 0.7, 3.0, 30.0])
 def test_scores_that_rise_or_fall_along_the_keys(g, per_tile):
     """Scores whose level moves by `per_tile` (in powers of e) every 64 keys, so that the running maximum is raised, and the
