@@ -133,8 +133,8 @@ def test_two_sets_of_waves_on_128_queries(g, B, Hq, Hkv, L):
     check_last(g, B, Hq, Hkv, L, 1200 + L)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,L", [(4, 32, 8, 65), (2, 32, 8, 256), (5, 32, 8, 128), (8, 1, 1, 2049), (2, 8, 2, 2048), (3, 4, 4, 2689), (11, 1, 1, 3009), (8, 1, 1, 8191),
-                                         (33, 1, 1, 449), (19, 2, 1, 385), (5, 8, 4, 512), (10, 4, 4, 513), (7, 4, 1, 640), (3, 8, 2, 1217), (2, 16, 4, 1024), (2, 16, 4, 1025)])
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(4, 32, 8, 65), (2, 32, 8, 256), (5, 32, 8, 129), (8, 1, 1, 2049), (16, 1, 1, 2048), (11, 1, 1, 2689), (11, 1, 1, 3009),
+                                         (33, 1, 1, 449), (19, 2, 1, 385), (5, 8, 4, 512), (10, 4, 4, 513), (7, 4, 1, 640), (12, 2, 1, 1217), (32, 1, 1, 1024), (16, 2, 1, 1025)])
 def test_launches_of_up_to_two_long_row_blocks_per_compute_unit(g, B, Hq, Hkv, L):
     """Either side of the lines between 64 queries and two sets of waves (two buffers or one), 128 and two sets, and 128 alone:
     an odd and an even number of tiles, ragged ends."""
