@@ -14,6 +14,7 @@
 //                          the B operand), walks the queries from the diagonal down in tiles of 64 through LDS,
 //                          recomputes S = Q K^T, normalises with the saved LSE and adds the weights of its key column
 //                          in the lane: no atomics, one exchange at the end.
+// A prompt of at most 128 tokens is one row block: its workgroup of the first kernel forms the column sums as well.
 #include "common.h"
 
 #include <type_traits>
