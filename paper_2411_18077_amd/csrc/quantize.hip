@@ -210,8 +210,9 @@ __device__ __forceinline__ void quantize_keys(const QuantArgs &a, const u32x4 (&
     // lanes of a pair share the store of their words: the even one the first eight tokens, the odd one the others
     uint32_t *words = reinterpret_cast<uint32_t *>(lds + kKGroups<G> * 1024);
     const int wd = p >> 1, odd = p & 1, at = (wd >> 2) * kKPitch + q * kKPitchQ + (wd & 3) + odd * 16;
+    const uint32_t second = 0u - (uint32_t)odd;          // (a mask: of `odd ? :` the compiler makes an index, and of w memory)
 #pragma unroll
-    for (int i = 0; i < 8; i++) words[at + (i & 1) * 2 * kKPitch + (i >> 1) * 4] = odd ? w[i + 8] : w[i];
+    for (int i = 0; i < 8; i++) words[at + (i & 1) * 2 * kKPitch + (i >> 1) * 4] = w[i] ^ ((w[i] ^ w[i + 8]) & second);
     wave_sync();
 #pragma unroll
     for (int s = 0; s < 2; s++) {                        // piece (token parity, word half, token pair): four words of a token

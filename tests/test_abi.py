@@ -193,3 +193,18 @@ def test_per_token_variant_sizes_and_host_checks(api):
     assert l.minikv_decode_attn_pt(C.byref(s), P(0x1000), C.byref(cache), 1.0, P(0x1000), P(0x1000), 16, None) == -3
     assert l.minikv_decode_attn_pt(C.byref(s), P(0x1000), C.byref(cache), float("inf"), P(0x1000), P(0x1000), 1 << 30, None) == -1
     assert l.minikv_decode_attn_pt(C.byref(s), P(0x1004), C.byref(cache), 1.0, P(0x1000), P(0x1000), 1 << 30, None) == -1
+
+
+def test_no_kernel_has_a_private_segment(api):
+    """A private segment is memory traffic that no kernel of the library means to have (an array that the compiler indexes
+    at run time, or spilled registers) and ties a launch to the runtime's scratch memory."""
+    lib = open(api.LIB_PATH, "rb").read()
+    with_one, n = [], 0
+    for m in re.finditer(rb"\xbb\.private_segment_fixed_size", lib):          # kernel metadata: MessagePack, keys in order
+        at = m.end()
+        size = lib[at] if lib[at] < 0x80 else int.from_bytes(lib[at + 1:at + 1 + (1 << (lib[at] - 0xcc))], "big")
+        name = re.match(rb"\w+", lib[lib.rfind(b"\xa5.name", 0, m.start()) + 6:].lstrip(b"\xd9\xda")[1:400])
+        n += 1
+        if size:
+            with_one.append((name and name.group().decode(), size))
+    assert n > 100 and not with_one, with_one
