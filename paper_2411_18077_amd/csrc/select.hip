@@ -2,7 +2,8 @@
 // window and, of the other prompt tokens, the n_hh with the largest cumulative attention score; write the
 // kept positions in ascending order.
 //
-// Two kernels.
+// Two ways.  One workgroup per unit (select_kernel, after score_key_kernel where that cannot add the heads itself), and, for
+// long prompts of few units, several (the sel_ kernels further down).
 //   score_key_kernel   (only when a unit has several query heads) streams the rep fp32 score rows of a
 //                      unit once, adds them in head order in fp32 and stores an order-preserving 32-bit
 //                      key per token.  Grid over (unit, 4096-token chunk): the whole chip streams.
@@ -424,15 +425,20 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
 //   sel_pick_kernel       every workgroup adds up its unit's cumulative counts -- the bin b1 of the weakest kept heavy hitter
 //                         is where the sum falls below the budget, no scan --, fetches the unit's keys inside that bin, one
 //                         contiguous piece per chunk, settles the remaining 21 bits on them in LDS, counts what precedes its
-//                         chunk, and compacts its chunk in order to the slots that follow.
+//                         chunks, and compacts those in order to the slots that follow.  (A bin of more keys than LDS holds --
+//                         ties, but also a quarter of an octave that simply is the fullest -- is read again in each of the three
+//                         passes: 16 units x 8 heads x 200000 'attention' scores 43 us with 40 % kept and 10586 keys in the bin,
+//                         48 with 70 % and 14351.)
 // A launch whose workgroups do a few dependent steps costs 4 to 9 us however small the input, so what counts is their number
 // and the round trips inside.  An earlier form (histograms, a unit sum, a candidate list, the rest: four launches of 4
-// waves per chunk) took 26.9 us on 8 units x 4 heads x 131072 where this takes 20.4.
+// waves per chunk) took 24.8 us on 8 units x 4 heads x 131072 where this takes 16.7, and 54 on 48 where this takes 47 (58.6 while
+// the second launch had a workgroup for every four chunks, of which a compute unit held one at a time).
 // Workspace, in 32-bit words: keys [units][Lp] (several heads only; Lp = L rounded up to 4), sorted keys
 // [units][nchunk][4096], cumulative counts [units][nchunk][1024] (two 16-bit counts per word), sums of those
 // [units][2048], four spare words per chunk.
 constexpr int kCh = 4096;              // tokens per chunk
 constexpr int kChThreads = 1024;       // 16 waves, four tokens each thread
+constexpr long kComputeUnits = 256;
 constexpr int kChMaxChunks = 1024;     // most chunks of one unit
 constexpr int kChList = 12288;         // keys of the cut's bin that sel_pick_kernel holds in LDS (more are read again in every pass)
 
@@ -605,35 +611,37 @@ __global__ __launch_bounds__(256) void sel_unit_hist_kernel(SelWs w, long L, con
     w.ucum[unit * kSelBins + bin] = sum;
 }
 
-// DIRECT: the unit's cumulative counts are added up here, else sel_unit_hist_kernel has done it.  A workgroup compacts NCH
-// consecutive chunks ("chunk" is the first).
-template <bool FROM_FLOAT, bool DIRECT, int NCH>
-__global__ __launch_bounds__(kChThreads) void sel_pick_kernel(const float *__restrict__ A, SelWs w, long L,
+// DIRECT: the unit's cumulative counts are added up here, else sel_unit_hist_kernel has done it.  A workgroup compacts `per`
+// consecutive chunks ("chunk" is the first; ONE: one, known at compile time).
+template <bool FROM_FLOAT, bool DIRECT, bool ONE>
+__global__ __launch_bounds__(kChThreads, ONE ? 4 : 8) void sel_pick_kernel(const float *__restrict__ A, SelWs w, long L,
                                                               const int *__restrict__ n_hh,
                                                               const int *__restrict__ n_rw,
                                                               int *__restrict__ idx, long idx_stride,
-                                                              int *__restrict__ n_tok)
+                                                              int *__restrict__ n_tok, int per_rt)
 {
     __shared__ int hist[kSelBins];                         // (first: piece ends and starts of the chunks)
     __shared__ uint32_t list[kChList];
     __shared__ int tot[16], tot2[16], found[2], acc[4];
     long unit;
     int chunk;
-    if (!sel_map(blockIdx.x, (w.nchunk + NCH - 1) / NCH, w.units, unit, chunk)) return;
-    chunk *= NCH;
+    const int per = ONE ? 1 : per_rt;
+    if (!sel_map(blockIdx.x, (w.nchunk + per - 1) / per, w.units, unit, chunk)) return;
+    chunk *= per;
     const int base = chunk * kCh;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long r_ = n_rw[unit], h_ = n_hh[unit];
-    // the chunks' keys for the compaction: tokens base + 4096 r + 4 tid .. + 3 (requested now, used last)
-    uint32_t key[NCH][4];
-#pragma unroll
-    for (int r = 0; r < NCH; ++r)
+    // a chunk's keys for the compaction: tokens base + 4096 r + 4 tid .. + 3 (the first chunk's are requested now, used last)
+    uint32_t key[4];
+    auto request = [&](int r) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const long i = min((long)base + r * kCh + 4 * tid + j, L - 1);
-            key[r][j] = FROM_FLOAT ? __float_as_uint(A[unit * L + i]) : w.keys[unit * w.Lp + i];
+            key[j] = FROM_FLOAT ? __float_as_uint(A[unit * L + i]) : w.keys[unit * w.Lp + i];
         }
+    };
+    request(0);
     const uint32_t *crow = w.cum + unit * w.nchunk * (long)(kSelBins / 2);
     int N, k, rw;
     if (!sel_budgets(r_, h_, L, idx_stride, N, k, rw)) {
@@ -641,7 +649,7 @@ __global__ __launch_bounds__(kChThreads) void sel_pick_kernel(const float *__res
         return;
     }
     int *row = idx + unit * idx_stride;
-    const int end = (int)min((long)base + NCH * kCh, L);
+    const int end = (int)min((long)base + (long)per * kCh, L);
     for (int i = max(base, N) + tid; i < end; i += kChThreads) row[k + (i - N)] = i;       // the recent window
     if (chunk == 0 && tid == 0) n_tok[unit] = k + rw;
     if (k == 0 || base >= N) return;
@@ -796,17 +804,16 @@ __global__ __launch_bounds__(kChThreads) void sel_pick_kernel(const float *__res
     __syncthreads();
     int gt_run = above_before + acc[0], eq_run = acc[1];
     // ---- ordered compaction of the chunks: 4 consecutive tokens per thread
-#pragma unroll
-    for (int r = 0; r < NCH; ++r) {
+    for (int r = 0; r < per && base + r * kCh < N; ++r) {  // (uniform)
         const int start = base + r * kCh + 4 * tid;
-        if (base + r * kCh >= N) break;                    // (uniform)
         int f[4], sum = 0;                                 // packed counts: larger | equal << 16
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const uint32_t x = FROM_FLOAT ? score_key(__uint_as_float(key[r][j])) : key[r][j];
+            const uint32_t x = FROM_FLOAT ? score_key(__uint_as_float(key[j])) : key[j];
             f[j] = start + j < N ? (int)(x > Tfull) | ((int)(x == Tfull) << 16) : 0;
             sum += f[j];
         }
+        if (!ONE && r + 1 < per) request(r + 1);
         int total;
         int excl = block_scan_incl(sum, r & 1 ? tot2 : tot, lane, wv, total) - sum;
 #pragma unroll
@@ -836,16 +843,21 @@ bool set_select_path(int path)
 
 // Several workgroups per unit pay two dependent launches and read the keys twice; they win when
 // one workgroup per unit would leave most of the chip idle.
-static bool select_chunked(int32_t units, int64_t L)
+static bool select_chunked(int32_t units, int32_t rep, int64_t L)
 {
     const long nchunk = (L + kCh - 1) / kCh;
     if (L <= 0 || nchunk > kChMaxChunks || ((long)units + 7) * nchunk > 0x7FFFFFFFL) return false;
     const int path = g_select_path.load();
     if (path) return path == 2;
-    // Prompts whose keys one workgroup cannot hold in LDS, and of those it can the long ones of few units (one workgroup against
-    // several, 4 heads: 4 units x 32768 20.4 -> 15.3 us, 32 x 32768 22.5 -> 18.5, but 64 x 32768 22.8 -> 27.0, 44 x 22289 17.1
-    // -> 22.3, 8 x 20000 12.9 -> 14.7).
-    return nchunk > 8 ? units <= 128 : nchunk > 6 && units * nchunk <= 256;
+    // Prompts whose keys one workgroup cannot hold in LDS, up to 128 units (one workgroup against several: 128 units x 32769
+    // 30.4 -> 29.9 us with one head, 42 -> 35 with four; 160 units 30.5 -> 35.9 and 46 -> 42, 160 x 65536 56.4 -> 56.8), and of
+    // those it can hold the long ones while every workgroup of the second launch has a compute unit: the units are dealt to the
+    // dies by eights (1 and 8 heads, 32 units x 24577 16.1 -> 15.0, 17.3 -> 16.8, 36 units 16.1 -> 19.6, 17.6 -> 23.3; 32 x
+    // 32768 18.7 -> 15.6, 21.4 -> 19.1).  Sums of a number of heads that select_kernel does not add itself take it a launch
+    // more: there the last die may share some (3 heads, 36 x 24577 24.1 -> 21.7).
+    if (nchunk > 8) return units <= 128;
+    const bool adds = rep == 1 || rep == 2 || rep == 4 || rep == 8;
+    return nchunk > 6 && (adds ? sel_grid_units(units) : units) * nchunk <= kComputeUnits;
 }
 
 size_t select_workspace_bytes(int32_t units, int32_t rep, int64_t L)
@@ -856,22 +868,22 @@ size_t select_workspace_bytes(int32_t units, int32_t rep, int64_t L)
     return (size_t)sel_ws_words(units, rep, L) * sizeof(uint32_t);
 }
 
-template <bool FROM_FLOAT, int NCH>
-static void launch_pick(const float *A, const SelWs &w, int32_t units, int64_t L, const int32_t *n_hh, const int32_t *n_rw,
+template <bool FROM_FLOAT, bool ONE>
+static void launch_pick(const float *A, const SelWs &w, int per, int32_t units, int64_t L, const int32_t *n_hh, const int32_t *n_rw,
                         int32_t *idx, int64_t idx_stride, int32_t *n_tok, hipStream_t st)
 {
-    const long units8 = sel_grid_units(units), parts = (w.nchunk + NCH - 1) / NCH;
+    const long units8 = sel_grid_units(units), parts = (w.nchunk + per - 1) / per;
     const dim3 grid((unsigned)(units8 * parts));
     // Every workgroup reads 4 KB of counts per chunk of its unit from its die's L2: units / 8 * parts * nchunk * 4 KB per die
     // at 2 KB a cycle.  Up to 3 us of that are less than the launch that adds them once costs.
     if (w.nchunk <= 64 && units * parts * w.nchunk <= 24576) {
-        hipLaunchKernelGGL((sel_pick_kernel<FROM_FLOAT, true, NCH>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh, n_rw, idx,
-                           (long)idx_stride, n_tok);
+        hipLaunchKernelGGL((sel_pick_kernel<FROM_FLOAT, true, ONE>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh, n_rw, idx,
+                           (long)idx_stride, n_tok, per);
     } else {
         hipLaunchKernelGGL(sel_unit_hist_kernel, dim3((unsigned)(units8 * 8)), dim3(256), 0, st, w, (long)L, n_hh, n_rw,
                            (long)idx_stride);
-        hipLaunchKernelGGL((sel_pick_kernel<FROM_FLOAT, false, NCH>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh, n_rw, idx,
-                           (long)idx_stride, n_tok);
+        hipLaunchKernelGGL((sel_pick_kernel<FROM_FLOAT, false, ONE>), grid, dim3(kChThreads), 0, st, A, w, (long)L, n_hh, n_rw, idx,
+                           (long)idx_stride, n_tok, per);
     }
 }
 
@@ -880,7 +892,7 @@ int launch_select(int32_t units, int32_t rep, int64_t L, const float *A, const i
                   hipStream_t st)
 {
     if (units == 0) return MINIKV_OK;
-    if (select_chunked(units, L)) {
+    if (select_chunked(units, rep, L)) {
         const SelWs w = sel_ws_carve(workspace, units, rep, L);
         const dim3 grid((unsigned)(sel_grid_units(units) * w.nchunk));
         auto k1 = rep == 1   ? sel_sort_kernel<1>
@@ -889,10 +901,12 @@ int launch_select(int32_t units, int32_t rep, int64_t L, const float *A, const i
                   : rep == 8 ? sel_sort_kernel<8>
                              : sel_sort_kernel<0>;
         hipLaunchKernelGGL(k1, grid, dim3(kChThreads), 0, st, A, w, rep, (long)L, n_hh, n_rw, (long)idx_stride);
-        // One chunk per workgroup while all of them run at once; beyond that every further round repeats the work on the cut.
-        const bool few = (long)units * w.nchunk <= 512;
-        const auto pick = rep == 1 ? (few ? launch_pick<true, 1> : launch_pick<true, 4>) : few ? launch_pick<false, 1> : launch_pick<false, 4>;
-        pick(A, w, units, L, n_hh, n_rw, idx, idx_stride, n_tok, st);
+        // One workgroup per compute unit, each with as many chunks as that leaves it: a second one repeats the work on the cut
+        // (4 heads: 32 units x 32769 21.5 -> 19.2 us for the call, 16 x 131072 28.7 -> 25.0, 8 x 200000 30.9 -> 25.1).
+        const int most = (int)max(kComputeUnits / sel_grid_units(units), 1L), per = (w.nchunk + most - 1) / most;
+        const auto pick = rep == 1 ? (per == 1 ? launch_pick<true, true> : launch_pick<true, false>)
+                                   : per == 1 ? launch_pick<false, true> : launch_pick<false, false>;
+        pick(A, w, per, units, L, n_hh, n_rw, idx, idx_stride, n_tok, st);
         return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
     }
     // keys stay in LDS when the whole prompt fits beside the fixed part

@@ -217,10 +217,11 @@ def test_selected_tokens_through_quantize_and_decode(g):
 
 
 @pytest.mark.parametrize("U,rep,L,kind", [(52, 1, 36865, "attention"), (64, 2, 32769, "ties"), (51, 1, 40960, "signed"), (129, 2, 13000, "attention"),
-                                          (7, 1, 36864, "ties"), (3, 4, 262145, "attention")])
-def test_four_chunks_per_workgroup_and_who_adds_the_counts(g, U, rep, L, kind):
-    """Chunk counts on both sides of where a workgroup takes four chunks (more than 512 in the launch; the last workgroup of
-    a unit has one to four), and of where a launch of its own adds the chunks' counts; windows that end inside a chunk."""
+                                          (7, 1, 36864, "ties"), (3, 4, 262145, "attention"), (33, 1, 32769, "signed"), (120, 1, 40961, "attention"),
+                                          (128, 2, 32769, "ties"), (8, 1, 262145, "attention"), (36, 1, 24577, "attention"), (32, 4, 24577, "ties"), (35, 3, 24577, "attention")])
+def test_chunks_per_workgroup_and_who_adds_the_counts(g, U, rep, L, kind):
+    """Several workgroups per unit with one to six chunks each, the last one of a unit with fewer; either side of the lines to
+    one workgroup per unit; counts that a launch of its own adds up; windows that end inside a chunk."""
     rng = np.random.default_rng(U + L)
     A = W.make_scores(U * rep, L, seed=900 + U, device="cuda", kind=kind)
     n_rw = rng.integers(0, L // 2, U)
