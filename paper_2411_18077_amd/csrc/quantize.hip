@@ -397,12 +397,18 @@ static int launch_quantize_g(const QuantArgs &a, hipStream_t st)
 {
     constexpr int NB = G == 128 ? 2 : 1;                 // blocks per workgroup
     const int units = a.units, nblk = (a.max_tok + kBlock - 1) / kBlock;
-    // Up to four blocks: one workgroup per unit, no launch of update_lengths_kernel (4 us on the device) behind this one; its
-    // waves wait for each other only for the lengths.  Against two launches, quantizing kernel alone: 1024 units x 256 rows
-    // 37.6 -> 34.5 us, 640 x 256 26.8 -> 24.9, 256 x 256 14.9 -> 12.2, 320 x 192 13.0 -> 14.8 (a fourth pair of waves for nothing).
+    // Up to four blocks: one workgroup per unit, no launch of update_lengths_kernel behind this one (2.5 us of a call); its waves
+    // wait for each other only for the lengths.  One or two blocks always (the call, against two launches, 64 units x 128 rows
+    // 12.3 -> 9.7 us, 1024 x 128 20.3 -> 18.7, 4096 x 128 60 -> 58).  Three or four take a workgroup of four, of which a compute
+    // unit holds two, the fourth with nothing to do for three: only while each has a compute unit (256 x 144 12.3 -> 10.4, x 256
+    // 13.1 -> 11.7) or most compute units have as many as the others (320 x 144 12.4 -> 14.4, x 256 15.4 -> 16.7, but 512 x 144
+    // 16.8 -> 15.3, x 256 21.2 -> 19.4, 768 x 192 23.1 -> 22.3), and, beyond two on each, while their waves have mostly full
+    // blocks (1024 x 144 23.4 -> 25.8, x 256 34.9 -> 34.4) and few rounds to go (2048 x 192 47.9 -> 49.8, 4096 x 256 114 -> 117).
     // Up to 32 tokens: two units share a block (16-token groups, 1024 units x 32 rows 11.3 -> 10.4 us: there the waves' own
     // instructions count, and half of every wave would idle).
-    if (nblk <= 4) {
+    constexpr int kComputeUnits = 256;
+    const bool even_rounds = units >= kComputeUnits * 3 / 2 && units <= (a.max_tok > 160 ? 4 : 2) * kComputeUnits;
+    if (nblk <= 2 || (nblk <= 4 && (units <= kComputeUnits || even_rounds))) {
         if (nblk > 2) {
             hipLaunchKernelGGL((quantize_pack_kernel<G, 4, true, false>), dim3(1, units), dim3(512), 0, st, a);
         } else if (nblk == 2 || G == 128) {

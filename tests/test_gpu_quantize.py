@@ -176,10 +176,11 @@ def test_short_calls_with_lengths_up_to_the_bound(g, G):
 
 
 @pytest.mark.parametrize("G,T,B", [(16, 256, 64), (16, 192, 65), (32, 256, 65), (32, 256, 16), (64, 256, 17), (64, 192, 64), (32, 128, 128), (16, 128, 129),
-                                   (64, 128, 129), (32, 64, 260), (128, 256, 8), (128, 128, 65)])
+                                   (64, 128, 129), (32, 64, 260), (128, 256, 8), (128, 128, 65), (16, 144, 95), (32, 192, 96), (16, 160, 128), (16, 160, 129),
+                                   (16, 176, 129), (64, 256, 256), (32, 192, 257)])
 def test_short_calls_of_many_units(g, G, T, B):
-    """Up to four blocks per unit at the unit counts where a unit stops being one workgroup (256 of three or four blocks, 512 of
-    two) and beyond, with lengths of every kind; the oracle takes sampled units."""
+    """Up to four blocks per unit at the unit counts where three or four of them are one workgroup or two launches (256, 384, 512
+    and 1024) and beyond, with lengths of every kind; the oracle takes sampled units."""
     w = small(G, B=B, Hkv=4, Hq=4, L=T, keep=1.0)
     inp = W.make_inputs(w, "cuda")
     n = torch.tensor([T, 0, G, T - G, T // 2 // G * G], dtype=torch.int32, device="cuda")
