@@ -147,8 +147,8 @@ __device__ inline float *slot_ptr(const DecArgs &a, int slot, int h)
 // What a small launch spends its time on is round trips -- lengths to work line, partial to ticket, ticket to merge --,
 // and this form has one of them, the unit's own two lengths: see launch_stream() for where it is taken.
 //
-// STREAM: the code words are loaded with the streaming hint.  They are read once per call; without the hint they push each
-// other through the caches, and the read rate is what suffers: see launch_stream() for where and how much.
+// STREAM: the code words are loaded with the streaming hint, where a call reads each of them once (one set of heads); without
+// the hint they push each other through the caches, and the read rate is what suffers: see launch_stream() for where and how much.
 template <int G> constexpr int kUnitWaves = G == 16 ? 4 : 8;     // (two per SIMD, one at G = 16)
 template <int G> constexpr size_t kWaveLds =                     // local memory of one wave, bytes
     (size_t)(kD / G) * kPsG * 2 > (size_t)kNH * kD * 2 + (size_t)64 * kKRowH * 2
@@ -1112,12 +1112,35 @@ static bool unit_per_workgroup(const DecArgs &a, int G)
     return items <= (units >= 192 ? 28 : units >= 96 ? 24 : 12);
 }
 
+// Single-wave workgroups of an instance that the device holds at once; 0 if the runtime does not say.
 template <int G, bool LO, bool PAIRED, bool APPEND, bool FLAT, bool STREAM>
-static int launch_stream_w(DecArgs a, long nw, int resident, size_t lds_bytes, hipStream_t st)
+static int resident_waves()
 {
+    static int resident = 0;
+    if (resident == 0) {
+        int dev = 0, cus = 0, per_cu = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT, false, STREAM>, 64,
+                                                         kWaveLds<G>) != hipSuccess ||
+            cus <= 0 || per_cu <= 0)
+            return 0;
+        resident = cus * per_cu;
+    }
+    return resident;
+}
+
+template <int G, bool LO, bool PAIRED, bool APPEND, bool FLAT, bool STREAM>
+static int launch_stream_w(DecArgs a, long cap_items, hipStream_t st)
+{
+    const int resident = resident_waves<G, LO, PAIRED, APPEND, FLAT, STREAM>();
+    if (resident == 0) return MINIKV_ELAUNCH;
+    long nw = resident < kMaxStreamWaves ? resident : kMaxStreamWaves;
+    if (nw > cap_items) nw = cap_items;
+    if (nw < 1) nw = 1;
     a.first_slot = resident / 2;
     a.skew16 = kSkew16;
-    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT, false, STREAM>), dim3((unsigned)nw), dim3(64), lds_bytes, st, a);
+    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT, false, STREAM>), dim3((unsigned)nw), dim3(64), kWaveLds<G>, st, a);
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
 
@@ -1132,36 +1155,34 @@ bool set_decode_weights(int mode)
 template <int G, bool LO, bool PAIRED, bool APPEND>
 static int launch_stream(DecArgs a, hipStream_t st)
 {
-    constexpr size_t lds_bytes = kWaveLds<G>;
-    auto kern = decode_stream_kernel<G, LO, PAIRED, APPEND, false, false, false>;
-    static int resident = 0;                               // single-wave workgroups the device holds at once
-    if (resident == 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64, lds_bytes) != hipSuccess ||
-            cus <= 0 || per_cu <= 0)
-            return MINIKV_ELAUNCH;
-        resident = cus * per_cu;
-    }
+    const int resident = resident_waves<G, LO, PAIRED, APPEND, false, false>();
+    if (resident == 0) return MINIKV_ELAUNCH;
     const long cap_items = (long)a.units * a.hsets * ((a.Tcap + kPass - 1) / kPass + (a.Rcap + 63) / 64);
-    long nw = resident < kMaxStreamWaves ? resident : kMaxStreamWaves;
-    if (nw > cap_items) nw = cap_items;
-    if (nw < 1) nw = 1;
     // (unit weights when the launch cannot hold more items than half the waves the device holds: measured on
     // shapes of 80 to 2240 items, they win up to 608 items -- 13.3 against 16.7 us -- tie at 560 and lose from
     // 1120 on -- 19.8 against 17.7 us)
     const int mode = g_decode_weights.load();
     if (mode == 0 && unit_per_workgroup(a, G)) return launch_units<G, LO, PAIRED, APPEND>(a, st);
-    if (mode == 0 ? cap_items * 2 <= (long)resident : mode == 2) return launch_stream_w<G, LO, PAIRED, APPEND, true, false>(a, nw, resident, lds_bytes, st);
-    // Streaming loads where the packed cache (by its capacity) is larger than a third of the 256 MB memory-side cache: 4.0 ->
-    // 4.3 TB/s on 169 MB (42.7 -> 39.9 us), 107 -> 98.8 us on 510 MB, 34.7 -> 31.1 on 116 MB.  A smaller one may still be
-    // there from the call before, and is then read faster with ordinary loads (three caches in turn: 74 MB 24.8 against
-    // 25.6 us, 50 MB 19.8 against 20.2; at 82 MB 28.3 against 27.8).
-    constexpr long kStreamBytes = 80L << 20;
+    if (mode == 0 ? cap_items * 2 <= (long)resident : mode == 2) return launch_stream_w<G, LO, PAIRED, APPEND, true, false>(a, cap_items, st);
+    // Streaming loads where the packed cache (by its capacity) is larger than a third of the 256 MB memory-side cache and a
+    // call reads it once.  Twice, with two sets of heads, the hint loses at every size (8 heads per KV head, G = 32, 200 MB
+    // 71.8 -> 75.1 us, 300 MB 101 -> 105; 6 heads the same, G = 16 1 % less, G = 128 3 % from 300 MB on).  Once, with three
+    // caches in turn and 90 / 120 / 300 MB (4 heads per KV head, then one; 128 units):
+    //   G = 16   31.3 -> 30.9 / 37.9 -> 35.4 / 74.3 -> 70.5        (320 units) 39.6 -> 35.2 at 120, 77.5 -> 73.3 at 300
+    //   G = 32   27.9 -> 27.7 / 33.6 -> 30.6 / 67.3 -> 62.3        33.5 -> 29.4, 65.8 -> 60.9
+    //   G = 64   26.5 -> 26.3 / 32.9 -> 31.3 / 64.9 -> 60.6        (2 heads) 26.1 -> 25.5 at 90
+    //   G = 128  26.2 -> 26.0 / 32.5 -> 31.9 / 64.2 -> 61.5        (320 units) 36.4 -> 32.6, 70.1 -> 60.2
+    // Smaller ones may still be there from the call before, and are then read faster with ordinary loads (65 MB: G = 128 24.8
+    // against 25.8, 2 heads 20.8 against 22.0, G = 64 24.3 against 25.1, G = 16 and 32 within 1 %), unless ten of them take
+    // turns (the hint gains 1-5 % from 65 MB on).  That is also what a cache sees that is allocated long and filled short:
+    // 40 MB in 160 17.7 -> 17.9 us at G = 32, 18.1 -> 18.6 at G = 64, 17.7 -> 18.5 at G = 128 if it is among the last three,
+    // and nothing otherwise.  The lengths are not known here.  Choosing in the kernel by the total of the work line costs
+    // more than that (a branch at each pair of loads: 65 MB 21.7 -> 24.2 us; a second copy of the pass loop does not fit the
+    // registers).
+    constexpr long kStreamBytes = 88L << 20;
     const long packed = (long)a.units * a.Tcap * (64 + 8 * kD / G);
-    return packed > kStreamBytes ? launch_stream_w<G, LO, PAIRED, APPEND, false, true>(a, nw, resident, lds_bytes, st)
-                                 : launch_stream_w<G, LO, PAIRED, APPEND, false, false>(a, nw, resident, lds_bytes, st);
+    return packed > kStreamBytes && a.hsets == 1 ? launch_stream_w<G, LO, PAIRED, APPEND, false, true>(a, cap_items, st)
+                                                 : launch_stream_w<G, LO, PAIRED, APPEND, false, false>(a, cap_items, st);
 }
 
 template <bool LO, bool PAIRED>

@@ -101,6 +101,37 @@ def test_ragged_units_including_empty_ones(g, variant):
 
 
 @pytest.mark.parametrize("G", [16, 32, 64, 128])
+@pytest.mark.parametrize("rep", [1, 2, 3, 4, 7])
+def test_caches_of_large_capacity(g, G, rep):
+    """A packed cache of more than 88 MiB, whose code words come with the streaming hint where each is read once (up to four
+    heads per KV head), attended to alone and as a fused step; ragged units of up to 20 passes, two of them empty."""
+    from paper_2411_18077_amd import api
+    from oracle import ref
+    w = tiny(G, B=2, Hq=12 * rep, Hkv=12, L=2560, keep=None, keep_range=(0.02, 1.0), Rcap=128)
+    inp = W.make_inputs(w, "cuda")
+    inp.n_tok[3] = 0
+    inp.n_tok[-1] = 0
+    big = (88 << 20) // (w.units * (64 + 1024 // G)) // 128 * 128 + 128
+    s, _ = g.shapes_for(w, big)
+    _, rs = g.shapes_for(w, inp.Tcap)
+    r_len = np.arange(w.units) * 5 % 128
+    r_len[3] = 0
+    gc, rc = g.gpu_build_cache(inp, s, r_len=r_len), g.ref_build_cache(inp, rs, r_len=r_len)
+    sm = g.sm_scale()
+    out = torch.full((w.B, w.Hq, w.D), float("nan"), dtype=torch.float16, device="cuda")
+    api.minikv_decode_attn(s, inp.q, gc, sm, out)
+    want, _, _ = ref.decode_attn(rc, g.to_np(inp.q), sm)
+    assert np.max(np.abs(g.to_np(out).astype(np.float64) - want)) <= TOL
+    k_new, v_new = inp.Rk[:, -1].contiguous(), inp.Rv[:, -1].contiguous()
+    step, r_next = torch.full_like(out, float("nan")), torch.full((w.units,), -1, dtype=torch.int32, device="cuda")
+    api.minikv_decode_step(s, inp.q, k_new, v_new, gc, r_next, sm, step)
+    api.kv_append_residual(s, k_new, v_new, gc)
+    api.minikv_decode_attn(s, inp.q, gc, sm, out)
+    torch.cuda.synchronize()
+    assert torch.equal(step.view(torch.int16), out.view(torch.int16)) and torch.equal(r_next, gc.r_len)
+
+
+@pytest.mark.parametrize("G", [16, 32, 64, 128])
 @pytest.mark.parametrize("Hq,Hkv,B,L,Rcap", [(4, 4, 9, 128, 128), (8, 2, 17, 1024, 128), (16, 2, 8, 1000, 384),
                                              (3, 3, 32, 2048, 256), (12, 12, 20, 300, 768), (8, 1, 1, 900, 128)])
 def test_a_workgroup_per_unit(g, G, Hq, Hkv, B, L, Rcap):
