@@ -203,7 +203,7 @@ template <int BITS> struct PtFields {
 // make operands of codes and weights; a form with one dot2 per pair of codes and head was bound by those alone.  Calls of
 // 128 units x 13088 tokens, 4 heads each, G = 128: 4 bits 79 -> 52 us (4.4 TB/s; a plain copy reaches 5.0), 2 bits
 // 82 -> 46.5, 8 bits 110 -> 83; 16 units 23 -> 16 us; G = 32, 128 units x 8192 tokens 63 -> 41 us.
-// STREAM: the code words, read once per call, are loaded with the streaming hint (see pt_streams()).
+// STREAM: code words, read once per call, are loaded with the streaming hint (see pt_streams()).
 typedef uint32_t pt_word2 __attribute__((ext_vector_type(2)));
 typedef uint32_t pt_word4 __attribute__((ext_vector_type(4)));
 template <bool STREAM, class T> __device__ __forceinline__ T pt_load(const T *p)
@@ -221,6 +221,7 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
     constexpr int NS = NG * REPT > 16 ? 2 : 1;           // column sets of a score product
     constexpr int NB = NG == 1 ? 1 : 2;                  // weight operands: the channel halves may differ in scale
     constexpr int E = TB * NG / 64 ? TB * NG / 64 : 1;   // scales of a block and array that one lane loads
+    constexpr bool HINT_K = STREAM && KW <= 4;           // (see pt_streams())
     __shared__ __align__(16) _Float16 meta[4][4][NG][TB];                  // wave; Ks, Kz, Vs, Vz; group; token
     __shared__ float part_o[4][REPT][kD], part_m[4][REPT], part_l[4][REPT], zsum[4][NG][REPT];
 
@@ -249,12 +250,12 @@ __global__ __launch_bounds__(256, 2) void decode_pt_kernel(PtDecArgs a)
             const int t = min(t0 + CPW * (col >> 2) + 4 * CPW * s + 4 * q4 + (col & 3), a.Tcap - 1);
             const uint32_t *src = Kc + (size_t)t * W + kg * KW;
             if constexpr (KW == 2) {
-                const pt_word2 v = pt_load<STREAM>(reinterpret_cast<const pt_word2 *>(src));
+                const pt_word2 v = pt_load<HINT_K>(reinterpret_cast<const pt_word2 *>(src));
                 kw[tau][0] = v.x, kw[tau][1] = v.y;
             } else {
 #pragma unroll
                 for (int i = 0; i < KW / 4; i++) {
-                    const pt_word4 v = pt_load<STREAM>(reinterpret_cast<const pt_word4 *>(src) + i);
+                    const pt_word4 v = pt_load<HINT_K>(reinterpret_cast<const pt_word4 *>(src) + i);
                     kw[tau][4 * i] = v.x, kw[tau][4 * i + 1] = v.y, kw[tau][4 * i + 2] = v.z, kw[tau][4 * i + 3] = v.w;
                 }
             }
@@ -588,7 +589,11 @@ static int pt_launch_quantize(const PtQuantArgs &a, int G, dim3 grid, int units,
 // Whether a call loads its codes with the streaming hint: where the packed cache (by its capacity) is larger than three
 // eighths of the 256 MB memory-side cache.  128 units x 13088 tokens at 4 bits (228 MB) 51.7 -> 49.9 us, 8 bits x 8192
 // (272 MB) 55.6 -> 50.7, 104 MB 28.7 -> 28.0; what is smaller may still be cached from the call before (three caches in
-// turn, 84 MB 21.8 against 22.3, 36 .. 80 MB a tie).
+// turn, 84 MB 21.8 against 22.3, 36 .. 80 MB a tie).  A cache that is larger than what it holds is judged by its capacity all
+// the same: 60 MB in 240, ten such caches in turn, 50.4 -> 49.8 us (three in turn 49.4 -> 49.5).  Not with the hint on the keys
+// at 8 bits: there a lane's 32 bytes of a key are two loads, half of every sector each, and a sector that the first has marked as
+// used up comes from memory again for the second where few waves run (120 MB in 240: 38.2 us without a hint, 42.7 with it on
+// both, 36.7 on the values only; full caches of 120 and 250 MB 28.7, 28.3, 25.8 and 51.9, 49.5, 47.7).
 static bool pt_streams(const PtDecArgs &a, int bits, int G, unsigned units)
 {
     return (long)units * a.Tcap * (2 * (kD * bits / 8 + 4 * kD / G)) > (96L << 20);

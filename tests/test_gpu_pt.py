@@ -115,6 +115,28 @@ def test_block_and_chunk_edges_with_poisoned_tails(bits, G, rep):
     assert np.all(np.abs(got - want.astype(np.float32)) <= np.maximum(TOL, np.abs(want) * 2.0 ** -10))
 
 
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("G,rep", [(32, 1), (32, 2), (32, 4), (32, 8), (64, 1), (64, 2), (64, 3), (64, 8), (128, 1), (128, 2), (128, 4), (128, 5)])
+def test_caches_of_large_capacity(bits, G, rep):
+    """A packed cache of more than 96 MiB, whose code words come with the streaming hint (at 8 bits the values' only); ragged
+    units over several chunks, one of them empty."""
+    from oracle import ref
+    from paper_2411_18077_amd import api
+    w, inp = _inputs(2, 12 * rep, 12, 4096, seed=700 + bits + G + rep, ragged=True)
+    inp.n_tok[5] = 0
+    s = api.make_pt_shape(2, 12 * rep, 12, 128, G, bits, (96 << 20) // (24 * 2 * (16 * bits + 512 // G)) // 64 * 64 + 64)
+    gc = api.PtCache(s)
+    api.kv_quantize_pack_pt(s, inp.K, inp.V, w.L, inp.idx, inp.idx.shape[1], inp.n_tok, int(inp.n_tok.max()), gc)
+    rc = ref.RefPtCache(ref.RefPtShape(2, 12 * rep, 12, 128, G, bits, 4096))
+    assert ref.quantize_pack_pt(rc, inp.K.cpu().numpy(), inp.V.cpu().numpy(), inp.n_tok.cpu().numpy(), inp.idx.cpu().numpy()) == 0
+    out = torch.full((2, 12 * rep, 128), float("nan"), dtype=torch.float16, device="cuda")
+    sm = 1.0 / math.sqrt(128)
+    api.minikv_decode_attn_pt(s, inp.q, gc, sm, out)
+    torch.cuda.synchronize()
+    want, _ = ref.decode_attn_pt(rc, inp.q.cpu().numpy(), sm)
+    assert np.max(np.abs(out.float().cpu().numpy() - want.astype(np.float32))) <= TOL
+
+
 @pytest.mark.parametrize("bits,G", [(2, 32), (8, 32), (2, 128), (8, 64)])
 @pytest.mark.parametrize("rep", [2, 8])
 def test_two_and_eight_heads_per_kv_head(rep, bits, G):
