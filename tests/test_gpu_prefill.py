@@ -149,8 +149,9 @@ def test_256_queries_per_workgroup_on_long_prompts(g, B, Hq, Hkv, L):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,L", [(33, 16, 4, 1), (33, 16, 16, 31), (33, 16, 8, 63), (33, 16, 4, 64), (33, 16, 4, 65), (32, 16, 4, 64)])
-def test_column_sums_of_64_keys_per_workgroup(g, B, Hq, Hkv, L):
-    """Prompts of up to 64 tokens on more than 512 heads, and the calls next to them."""
+def test_short_prompts_of_many_heads(g, B, Hq, Hkv, L):
+    """Prompts of one or two key tiles on 512 heads and more: the launch that forms the column sums as well, with more
+    workgroups than run at once."""
     check_last(g, B, Hq, Hkv, L, 1400 + L)
 
 
@@ -175,11 +176,18 @@ def test_scores_that_rise_or_fall_along_the_keys(g, per_tile):
     assert np.all(np.abs(g.to_np(acc) - acc64) <= RTOL_A * np.abs(acc64) + ATOL_A)
 
 
-def test_first_pass_alone(g):
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(1, 2, 1, L) for L in (1, 31, 48, 64, 65, 96, 97, 127, 128, 129, 200, 1000)] +
+                                       [(9, 32, 8, L) for L in (1, 48, 96, 97, 128, 129)] +
+                                       [(5, 8, 4, 512), (10, 4, 4, 513), (32, 1, 1, 1024), (16, 1, 1, 3000), (64, 1, 1, 4096)])
+def test_first_pass_alone(g, B, Hq, Hkv, L):
+    """Without column sums: one row block on few heads and on many (128 queries from 97 tokens on only there), a block of 64
+    shared by two sets of waves with two buffers and with one, 128 shared by two sets, 256; the last sequence against the oracle."""
     from oracle import ref
-    Q, K, V = W.make_prefill_inputs(1, 2, 1, 200, 5, device="cuda")
+    Q, K, V = W.make_prefill_inputs(B, Hq, Hkv, L, 5, device="cuda")
     xo, lse, acc = run_gpu(Q, K, V, 0.09, want_cumul=False)
-    _, xo64, lse64, _ = ref.selective_flash_attn(g.to_np(Q), g.to_np(K), g.to_np(V), 0.09)
+    assert torch.isfinite(xo).all() and torch.isfinite(lse).all()
+    xo, lse = xo[-1:], lse[-1:]
+    _, xo64, lse64, _ = ref.selective_flash_attn(g.to_np(Q[-1:]), g.to_np(K[-1:]), g.to_np(V[-1:]), 0.09)
     assert np.max(np.abs(g.to_np(xo).astype(np.float64) - xo64)) <= TOL_O
     assert np.max(np.abs(g.to_np(lse).astype(np.float64) - lse64)) <= TOL_LSE
 
