@@ -170,6 +170,12 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
     constexpr int NKW = NKR * 2;                           // words of one lane's slice of a K meta row
     typedef KData<NKW> KD;
     typedef VData<NCG> VD;
+    // The tiles that a wave's last pass requests: its own ones again are still cached, but not with the streaming hint; they
+    // then came from memory a second time (190.1 MB read per call on the 16 x 32768 workload, 177.6 without the hint).  With
+    // it every wave requests the same tile there, the first unit's first: 176.1 MB, 1024 units x 4896 98.2 -> 96.5 us, 512 x
+    // 4864 53.8 -> 51.9, 128 x 13088, two heads, 35.6 -> 34.7, four 36.6 -> 36.1.  (Not in the instance that has no register
+    // left, the fused step of three and four heads at G = 32: 37.0 -> 37.4.)
+    constexpr bool kOneTile = STREAM && !(FUSED && !PAIRED && G == 32);
 
     extern __shared__ __attribute__((aligned(16))) _Float16 lds_launch[];
     _Float16 *lds_all = lds_launch;
@@ -396,8 +402,8 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             if constexpr (STREAM) return __builtin_nontemporal_load(p);
             return *p;
         };
-        auto load_k_codes = [&](KD &d, int tp, int half) {       // half 0: words 0..3 of both tokens, 1: words 4..7
-            const u4 *ktile = reinterpret_cast<const u4 *>(Kc + (size_t)(tp >> 7) * 1024);
+        auto load_k_codes = [&](KD &d, int tp, int half, bool last = false) {   // half 0: words 0..3 of both tokens, 1: words 4..7
+            const u4 *ktile = reinterpret_cast<const u4 *>(kOneTile && last ? a.Kc : Kc + (size_t)(tp >> 7) * 1024);
             d.kw[half] = words(ktile + half * 64 + lane_u);
             d.kw[2 + half] = words(ktile + (2 + half) * 64 + lane_u);
         };
@@ -409,8 +415,8 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             d.vs = load_words<NCG>(Vs + vo);
             d.vz = load_words<NCG>(Vz + vo);
         };
-        auto load_v_codes = [&](VD &d, int tp, int tl) {         // tl: 64-token tile of the pass
-            const u4 *vtile = reinterpret_cast<const u4 *>(Vc + (size_t)(tp >> 6) * (4 * kD));
+        auto load_v_codes = [&](VD &d, int tp, int tl, bool last = false) {     // tl: 64-token tile of the pass
+            const u4 *vtile = reinterpret_cast<const u4 *>(kOneTile && last ? a.Vc : Vc + (size_t)(tp >> 6) * (4 * kD));
             d.vw[0][tl] = words(vtile + tl * kD + lane_u);
             d.vw[1][tl] = words(vtile + tl * kD + lane_u + 64);
         };
@@ -673,7 +679,7 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             float s0[kNH], s1[kNH];                        // scores of the lane's two tokens (NHQ heads)
 
             // ---------------- K phase: scores of tokens 2*lane, 2*lane+1 for the 4 heads
-            auto k_phase = [&](KD &d, int tp, int t2) {        // t2: the pass whose tiles are requested meanwhile
+            auto k_phase = [&](KD &d, int tp, int t2, bool last) {        // t2: the pass whose tiles are requested meanwhile
                 const bool valid = tp + 2 * lane < t_end;  // both tokens of the lane (t_end % 16 == 0)
                 // A operands of this lane's k-steps (exact hi + lo split of q * Ks), qz = sum_c q_c Kz[g,c]
                 h4 a_hi[NKR], a_lo[NKR];
@@ -722,12 +728,12 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
                     }
                     if (wd == 3) {                         // words 0..3 are done
                         __builtin_amdgcn_sched_barrier(0);
-                        load_k_codes(d, t2, 0);
+                        load_k_codes(d, t2, 0, last);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                load_k_codes(d, t2, 1);
+                load_k_codes(d, t2, 1, last);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (PAIRED) {
                     const float zz[2] = {quad_bcast<0>(qz) * a.c1, quad_bcast<2>(qz) * a.c1};
@@ -748,7 +754,7 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             };
 
             // ---------------- softmax update, ps table, V products
-            auto v_phase = [&](VD &d, int tp, int t2) {
+            auto v_phase = [&](VD &d, int tp, int t2, bool last) {
                 const bool valid = tp + 2 * lane < t_end;
                 float mn[kNH];
                 bool grow = false;
@@ -825,23 +831,23 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
                     }
                     if (blk == 3) {                        // the first 64-token tile is done
                         __builtin_amdgcn_sched_barrier(0);
-                        load_v_codes(d, t2, 0);
+                        load_v_codes(d, t2, 0, last);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                load_v_codes(d, t2, 1);
+                load_v_codes(d, t2, 1, last);
                 __builtin_amdgcn_wave_barrier();
             };
 
             // Every piece of a pass's tiles is requested for the next pass right after its last use and is
-            // issued on every path (the last pass requests its own tiles again), so the number in flight is
-            // always the same.
+            // issued on every path (the last pass requests tiles again, nobody uses them: see kOneTile), so the
+            // number in flight is always the same.
             for (int jj = j0; jj < j1; jj++) {
                 const int tp = jj * kPass;
                 const int t2 = (jj + 1 < j1 ? jj + 1 : jj) * kPass;
-                k_phase(kd, tp, t2);
-                v_phase(vd, tp, t2);
+                k_phase(kd, tp, t2, jj + 1 == j1);
+                v_phase(vd, tp, t2, jj + 1 == j1);
             }
         }
         residual_items(b0, b1, 1);
