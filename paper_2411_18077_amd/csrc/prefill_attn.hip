@@ -445,7 +445,8 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
 // 32 x 2048 32 -> 25 us, 32 x 777 15.6 -> 12.3 us.  Three LDS buffers instead of two: the same.  The sums are pinned where
 // they are formed: without that the weights of every other step stood after its products, in front of the next ones (32
 // heads x 16384 1.185 -> 1.156 ms, 32 x 777 12.7 -> 12.1 us, 8 x 2048 21.6 -> 20.2).  Two sets of waves on the even and the
-// odd tiles, as in the first pass, gain from 4096 tokens on only (8 x 4096 37.5 -> 35.3, but 32 x 777 12.3 -> 14.0).
+// odd tiles, as in the first pass, gain on long prompts of few heads and lose on the others (8 x 2048 20.3 -> 19.2, 8 x 4096 36.0
+// -> 33.2, but 32 x 400 9.1 -> 10.3, 32 x 777 12.2 -> 13.0, 32 x 4096 80 -> 95).
 constexpr int kColWaves = 4, kKeyWaves = kColWaves / 2, kKeys = 64 * kKeyWaves;
 
 __global__ __launch_bounds__(64 * kColWaves, 2) void prefill_colsum_kernel(PrefillArgs a)

@@ -10,12 +10,13 @@
 // memory carries only the group parameters and the finished words on their way to coalesced stores, and the waves of a
 // workgroup meet at no barrier (but one where a group of 128 tokens spans two of them).
 //
-// What bounds it: memory.  An element costs about 8.5 vector instructions (5 of them the quantizer's own roundings), 40 % of
-// the time at most.  Rows and words pass the caches once, so both carry the streaming hint: with 128 units x 13088 of 32768
-// rows, G = 32, 215 us without it, 202 with it on the loads, 183 (5.6 TB/s) on the stores as well.  An earlier form, blocks
-// in local memory and four waves on each with barriers between the passes, took 214 there (127 -> 60 us at G = 128, 32
-// units x 17664, where half its threads had no statistics to do; 76 -> 62 at G = 16, 256 units x 2048) and twice the
-// time of a short call (a flush of 8 x 128 rows 12.3 -> 5.7 us).
+// What bounds it: memory.  An element costs about 8.9 vector instructions (5 of them the quantizer's own roundings), half of
+// the time.  Rows and words pass the caches once, so both carry the streaming hint: a call on 128 units x 13088 of 32768
+// rows, G = 32, three sets of inputs in turn, takes 209 us without it, 200 with it on the loads or the stores alone, 180 (5.7
+// TB/s) with it on both (188 while the code words went through a private segment).  An earlier form, blocks in local memory
+// and four waves on each with barriers between the passes, took 214 there (129 -> 61 us at G = 128, 32 units x 17664, where
+// half its threads had no statistics to do; 151 -> 132 at G = 64, 32 x 40000; 71 -> 62 at G = 16, 256 units x 2048; a flush of
+// 256 x 128 rows at G = 16 10.9 -> 9.8).
 #include "common.h"
 
 #include <hip/hip_fp16.h>
@@ -404,8 +405,8 @@ static int launch_quantize_g(const QuantArgs &a, hipStream_t st)
     // 13.1 -> 11.7) or most compute units have as many as the others (320 x 144 12.4 -> 14.4, x 256 15.4 -> 16.7, but 512 x 144
     // 16.8 -> 15.3, x 256 21.2 -> 19.4, 768 x 192 23.1 -> 22.3), and, beyond two on each, while their waves have mostly full
     // blocks (1024 x 144 23.4 -> 25.8, x 256 34.9 -> 34.4) and few rounds to go (2048 x 192 47.9 -> 49.8, 4096 x 256 114 -> 117).
-    // Up to 32 tokens: two units share a block (16-token groups, 1024 units x 32 rows 11.3 -> 10.4 us: there the waves' own
-    // instructions count, and half of every wave would idle).
+    // Up to 32 tokens: two units share a block (16-token groups, 1024 units x 32 rows 10.4 -> 10.2 us, 2048 15.9 -> 13.0, 4096
+    // 24.9 -> 19.8; 256 units the same: there the waves' own instructions count, and half of every wave would idle).
     constexpr int kComputeUnits = 256;
     const bool even_rounds = units >= kComputeUnits * 3 / 2 && units <= (a.max_tok > 160 ? 4 : 2) * kComputeUnits;
     if (nblk <= 2 || (nblk <= 4 && (units <= kComputeUnits || even_rounds))) {

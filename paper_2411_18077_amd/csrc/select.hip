@@ -431,8 +431,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
 //                         48 with 70 % and 14351.)
 // A launch whose workgroups do a few dependent steps costs 4 to 9 us however small the input, so what counts is their number
 // and the round trips inside.  An earlier form (histograms, a unit sum, a candidate list, the rest: four launches of 4
-// waves per chunk) took 24.8 us on 8 units x 4 heads x 131072 where this takes 16.7, and 54 on 48 where this takes 47 (58.6 while
-// the second launch had a workgroup for every four chunks, of which a compute unit held one at a time).
+// waves per chunk) took 24.8 us on 8 units x 4 heads x 131072 where this takes 16.8 (the same scores every call; 27.0 and 19.3
+// with two sets in turn), and 54 on 48 where this takes 47 (58.6 while the second launch had a workgroup for every four chunks,
+// of which a compute unit held one at a time).
 // Workspace, in 32-bit words: keys [units][Lp] (several heads only; Lp = L rounded up to 4), sorted keys
 // [units][nchunk][4096], cumulative counts [units][nchunk][1024] (two 16-bit counts per word), sums of those
 // [units][2048], four spare words per chunk.
