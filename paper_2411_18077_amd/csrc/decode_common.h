@@ -15,8 +15,8 @@ struct DecArgs {
     int *cnt;                    // per-unit ticket counters of the single-launch kernel (zero between calls)
     int *cnt1;                   // ticket counters of the sub-groups, indexed by the sub-group's first slot
     int *redo;                   // counts (wave, unit) pairs redone with range-normalised operands (diagnostics)
-    int first_slot;              // workgroups that fill the first wave slot of every SIMD
-    int skew16;                  // sixteenths of a wave pair's range that its first wave takes
+    int by_die;                  // the work line is dealt to the dies in contiguous eighths
+    int wq_log, wr_log;          // weight of a quantized pass and of a residual item on the work line (log2)
     float c1;                    // sm_scale * log2(e): scores are kept in the base-2 domain
     int Hq, Hkv, rep, Tcap, Rcap, chunk, nchunk;
     int units, hsets;            // B*Hkv; sets of 4 query heads per KV head (1 or 2)

@@ -208,7 +208,6 @@ int launch_decode_parts(const minikv_shape &s, const minikv_f16 *q, const minikv
     a.out = out;
     a.append = ap.k_new != nullptr;
     a.k_new = ap.k_new; a.v_new = ap.v_new; a.r_len_out = ap.r_len_out;
-    a.first_slot = 0;
     a.cnt = cnt;
     a.cnt1 = cnt1;
     a.redo = redo;

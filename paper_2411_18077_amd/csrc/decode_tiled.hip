@@ -9,11 +9,11 @@
 //
 // so the inner products run over the raw 2-bit codes and the scales move onto the small operands.
 //
-// Work split: single-wave workgroups, as many as the chip holds.  A flat, weighted list of work items
+// Work split: one workgroup of eight waves (four at G = 16) per compute unit.  A flat, weighted list of work items
 // (items of 64 fp16 residual tokens, passes of 128 quantized tokens) over all (batch, KV head) units is cut
 // into equal ranges, one per wave; see "Work distribution" below.  Every wave keeps one online-softmax
-// state per unit it touches and the last wave to finish a unit merges the unit's partial results, all
-// inside one launch.
+// state per unit it touches, the waves of a workgroup merge theirs in local memory, and the last workgroup to finish a
+// unit merges the unit's partial results, all inside one launch.
 //
 // One pass of 128 quantized tokens, lane l of the wave:
 //   K phase: the lane owns tokens 2l and 2l+1; four 128-bit loads bring their 2 x 8 code words.  Codes
@@ -36,6 +36,7 @@
 // and V scales < 4096 with the default scalings; a wave whose sums show an overflow repeats its share of the
 // unit with range-normalised operands (see "Operand ranges" in the kernel).
 #include <atomic>
+#include <type_traits>
 
 #include "decode_wave.h"
 
@@ -45,17 +46,22 @@ namespace minikv {
 // Work distribution.  Every unit (batch, KV head, set of 4 query heads) has ceil(R/64) residual items and
 // ceil(T/128) quantized passes; its span of the weight line holds the even residual items, the passes,
 // then the odd residual items (so that the usual two items fall to two different waves).  The units'
-// spans (kWR per residual item, kWQ per pass) are laid end to end and the line is cut into NW equal
+// spans (2^wr_log per residual item, 2^wq_log per pass) are laid end to end and the line is cut into NW equal
 // ranges, one per wave; a wave owns the items that START inside its range, so ragged lengths are balanced
-// by construction.  What a wave does for one unit
-// ends in one split-K partial (running max, sum, un-normalised output); the partial that arrives last at
-// its unit (device-scope ticket counter) merges the unit's partials and writes the fp16 output, so one
+// by construction.  A workgroup has the ranges of its waves side by side.  What its waves do for one unit ends in one
+// split-K partial (running max, sum, un-normalised output), merged in local memory; where several workgroups share a unit,
+// the partial that arrives last (device-scope ticket counter) merges the unit's partials, and the fp16 output is written: one
 // kernel launch does the whole call.  (Drawing passes from a per-unit counter instead was tried: a vector
 // atomic per pass, even one whose result is needed a full pass later, slowed the pass loop by 40 %.)
+//
+// What bounds a call whose waves have a few items each is the chain behind the last pass: a partial per WAVE, merged through
+// memory in two levels of up to sixteen, cost 4 to 8 us of round trips, and a range had to hold a whole residual item (3.5
+// passes), so that 700 items ran on 128 waves one after the other.  With a partial per workgroup a unit has at most sixteen or
+// so, one level merges them, and a range can be shorter than an item (only a workgroup's range must hold one).  Fused steps, us:
+// 8 heads x 7168 tokens 18.9 -> 12.2 (G = 64), 32 x 5120 20.2 -> 13.0, 32/8 heads x 16 x 13088 39.1 -> 36.4; attention 1024 units x
+// 4896 96.5 -> 93.1, ragged 128k 43.1 -> 41.0; 1.15 times in the geometric mean over 233 shapes from 8 to 1024 units.
 struct UnitItems { int nq, nr, T, R, rn; };   // rn: residual row the fused step appends (-1: none)
 constexpr int kSkew16 = 10;             // share (in sixteenths) of a wave pair's range given to its first wave
-constexpr int kPassWeight = 2, kResidualWeight = 7;   // relative cost of a quantized pass (128 tokens, 12 KB) and a residual
-                                       // item (64 fp16 tokens, 32 KB), measured
 
 // Residual tokens a unit attends to: its stored ones, plus -- in the fused step -- the token this launch appends
 // (when the buffer has room for it, as kv_append_residual would).
@@ -86,16 +92,15 @@ __device__ inline UnitItems unit_items(bool APPEND, const DecArgs &a, int up)
 }
 // P weight units are cut into NW = 2^nw_log ranges.  Waves 2p and 2p+1 share the pair range
 // [p*2P >> nw_log, (p+1)*2P >> nw_log); the first of them takes skew16/16 of it (8 = equal halves).
-__device__ inline long range_start(int w, int P, int nw_log, int skew16)
+__device__ inline int range_start(int w, int P, int nw_log, int skew16)
 {
-    if (nw_log == 0) return w ? P : 0;
-    const long s0 = ((long)(w >> 1) * P) >> (nw_log - 1);
+    const int s0 = (int)(((long)(w >> 1) * P) >> (nw_log - 1));
     if (!(w & 1)) return s0;
-    const long s1 = ((long)((w >> 1) + 1) * P) >> (nw_log - 1);
-    return s0 + (((s1 - s0) * skew16) >> 4);
+    const int s1 = (int)(((long)((w >> 1) + 1) * P) >> (nw_log - 1));
+    return s0 + (int)(((long)(s1 - s0) * skew16) >> 4);
 }
 // wave that owns position i: binary32 estimate, then exact correction against the range bounds
-__device__ inline int wave_of(long i, int P, int nw_log, float inv_p, int skew16)
+__device__ inline int wave_of(int i, int P, int nw_log, float inv_p, int skew16)
 {
     int w = (int)((float)i * inv_p);                       // inv_p = NW / P
     w = min(max(w, 0), (1 << nw_log) - 1);
@@ -118,11 +123,6 @@ __device__ inline int wave_scan_i32(int v)
     return v;
 }
 __device__ inline int wave_sum_i32(int v) { return __builtin_amdgcn_readlane(wave_scan_i32(v), 63); }
-// Split-K partial of (slot, head): [0] running max (base-2 domain), [1] sum of weights, [4..131] output.
-__device__ inline float *slot_ptr(const DecArgs &a, int slot, int h)
-{
-    return a.ws + ((size_t)slot * kNH + h) * kPartialStride;
-}
 
 // Two waves per SIMD, except for G = 16, whose per-lane share of the K scale / zero rows and of q*Ks does not
 // fit 256 registers: one wave per SIMD with the full register file runs 1.6x faster there than two that
@@ -137,26 +137,21 @@ __device__ inline float *slot_ptr(const DecArgs &a, int slot, int h)
 // 16 x 32768 workload, the instance built with the flag as a constant ran 3 us (7 %) slower, with or without a
 // token to append -- the compiler then arranges the unit set-up and the residual item differently.
 //
-// FLAT: every item weighs 1.  A range of the work line must be at least one residual item long, so with the
-// measured weights a small workload is cut into few ranges -- one sequence of 1024 tokens and 8 heads gets 16
-// waves of 4 to 6 items each, 16 us of which 7 are items worked off one after the other.  When the whole
-// launch cannot hold more items than half the waves the device holds, balance does not matter and
-// parallelism does: with unit weights every item gets a wave of its own.
-//
-// UNIT: a workgroup of kUnitWaves waves IS one unit; they divide its items, and their partials meet in local memory.
+// UNIT: a workgroup of kGroupWaves waves IS one unit; they divide its items, and their partials meet in local memory.
 // What a small launch spends its time on is round trips -- lengths to work line, partial to ticket, ticket to merge --,
 // and this form has one of them, the unit's own two lengths: see launch_stream() for where it is taken.
 //
 // STREAM: the code words are loaded with the streaming hint, where a call reads each of them once (one set of heads); without
 // the hint they push each other through the caches, and the read rate is what suffers: see launch_stream() for where and how much.
-template <int G> constexpr int kUnitWaves = G == 16 ? 4 : 8;     // (two per SIMD, one at G = 16)
-template <int G> constexpr size_t kWaveLds =                     // local memory of one wave, bytes
-    (size_t)(kD / G) * kPsG * 2 > (size_t)kNH * kD * 2 + (size_t)64 * kKRowH * 2
-        ? (size_t)(kD / G) * kPsG * 2 : (size_t)kNH * kD * 2 + (size_t)64 * kKRowH * 2;
-template <int G, bool LO, bool PAIRED, bool FUSED, bool FLAT, bool UNIT, bool STREAM>
-__global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) void decode_stream_kernel(DecArgs a)
+template <int G> constexpr int kGroupWaves = G == 16 ? 4 : 8;     // (two per SIMD, one at G = 16)
+template <int G, bool LO, bool PAIRED, bool FUSED, bool UNIT, bool STREAM>
+__global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_stream_kernel(DecArgs a)
 {
-    constexpr int kWQ = FLAT ? 1 : kPassWeight, kWR = FLAT ? 1 : kResidualWeight;
+    constexpr int kWaves = kGroupWaves<G>, kWavesLog = ilog2(kWaves);
+    constexpr int kPrH = 72, kPrHalfs = UNIT ? kNH * kD : kNH * kPrH;        // weights of a residual item [kNH][64 + 8], in front of its rows
+    constexpr int kLdsHalfs = kPrHalfs + 64 * kKRowH;      // local memory of one wave
+    static_assert(kLdsHalfs >= (kD / G) * kPsG && kLdsHalfs * 2 >= kNH * kPartialStride * 4, "weights of a pass; a partial");
+    const int wq_log = UNIT ? 0 : a.wq_log, wr_log = UNIT ? 0 : a.wr_log, kWQ = 1 << wq_log, kWR = 1 << wr_log;
     const bool APPEND = FUSED && a.append;
     static_assert(!PAIRED || LO, "the paired rows are the hi and lo parts");
     constexpr int NHQ = PAIRED ? 2 : kNH;                  // heads the quantized passes work on
@@ -170,24 +165,30 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
     constexpr int NKW = NKR * 2;                           // words of one lane's slice of a K meta row
     typedef KData<NKW> KD;
     typedef VData<NCG> VD;
-    // The tiles that a wave's last pass requests: its own ones again are still cached, but not with the streaming hint; they
-    // then came from memory a second time (190.1 MB read per call on the 16 x 32768 workload, 177.6 without the hint).  With
-    // it every wave requests the same tile there, the first unit's first: 176.1 MB, 1024 units x 4896 98.2 -> 96.5 us, 512 x
-    // 4864 53.8 -> 51.9, 128 x 13088, two heads, 35.6 -> 34.7, four 36.6 -> 36.1.  (Not in the instance that has no register
-    // left, the fused step of three and four heads at G = 32: 37.0 -> 37.4.)
-    constexpr bool kOneTile = STREAM && !(FUSED && !PAIRED && G == 32);
+    // The tiles that a wave's last pass requests are used by nobody.  Its own ones again are still cached, but not with the
+    // streaming hint; they then came from memory a second time (190.1 MB read per call on the 16 x 32768 workload, 177.6
+    // without the hint).  So every wave of the work line requests the same tile there, the first unit's first: 176.1 MB, 1024
+    // units x 4896 98.2 -> 96.5 us, 512 x 4864 53.8 -> 51.9, 128 x 13088, two heads, 35.6 -> 34.7, four 36.6 -> 36.1.
+    constexpr bool kOneTile = !UNIT;
 
-    extern __shared__ __attribute__((aligned(16))) _Float16 lds_launch[];
-    _Float16 *lds_all = lds_launch;
-    if constexpr (UNIT) {                                  // (the size is known here: no launch attribute to set)
-        __shared__ __attribute__((aligned(16))) _Float16 lds_unit[kUnitWaves<G> * kWaveLds<G> / 2];
-        lds_all = lds_unit;
+    __shared__ __attribute__((aligned(16))) _Float16 lds_all[kWaves * kLdsHalfs];
+    // A wave's partials of the unit its range begins with and of the one it ends with are entries 2 * pos and 2 * pos + 1
+    // (pos: the wave's place in the workgroup's range): which unit, its first and last workgroup, the row appended to it
+    struct Entry { int up, wf, wl, rn; };
+    Entry *entries = nullptr;
+    float *first_part = nullptr;
+    if constexpr (!UNIT) {
+        __shared__ __attribute__((aligned(16))) float lds_first[kWaves * kNH * kPartialStride];
+        __shared__ __attribute__((aligned(16))) Entry lds_entries[2 * kWaves];
+        first_part = lds_first, entries = lds_entries;
     }
-    const int wave = UNIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
-    _Float16 *lds = lds_all + wave * (kWaveLds<G> / 2);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // (the older wave of a SIMD first: waves i and i + 4 are neighbours in the range)
+    const int pos = !UNIT && kWaves == 8 ? (wave < 4 ? 2 * wave : 2 * wave - 7) : wave;
+    _Float16 *lds = lds_all + wave * kLdsHalfs;
     _Float16 *ps = lds;                                    // [NCG][kNH][kPsH] halfs (quantized passes)
 
-    const int lane = UNIT ? threadIdx.x & 63 : threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int NU = a.units * a.hsets;
 
     // ---------------- the work list: total weight P, this wave's range, the unit that holds its start.
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
     };
     auto weight_of = [&](int T, int R) -> int {
         if (APPEND) R &= (1 << kAppBit) - 1;
-        return kWQ * ((T + kPass - 1) / kPass) + kWR * ((R + 63) >> 6);
+        return (((T + kPass - 1) / kPass) << wq_log) + (((R + 63) >> 6) << wr_log);
     };
     const bool small = NU <= 256;
     int Tl[4], Rl[4], wl4[4], incl4[4];
@@ -237,7 +238,7 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
     int new_row = -1;
     const int file_unit = UNIT ? (int)blockIdx.x >> a.hs_shift : (int)blockIdx.x;
     const bool files_new = UNIT ? APPEND && wave == 0 && ((int)blockIdx.x & (a.hsets - 1)) == 0 && lane < 32
-                                : APPEND && (int)blockIdx.x < a.units && lane < 32;
+                                : APPEND && wave == 0 && (int)blockIdx.x < a.units && lane < 32;
     auto new_src = [&](int u) { return reinterpret_cast<const uint4 *>((lane < 16 ? a.k_new : a.v_new) + (size_t)u * kD) + (lane & 15); };
     auto new_dst = [&](int u, int r) { return reinterpret_cast<uint4 *>(const_cast<uint16_t *>(lane < 16 ? a.Rk : a.Rv) + ((size_t)u * a.Rcap + r) * kD) + (lane & 15); };
     if (files_new) {
@@ -275,40 +276,38 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             if (r >= 0 && r < a.Rcap) *new_dst(u, r) = *new_src(u);
         }
     }
-    if (!UNIT && __ballot(empties)) {                               // rare: look again, one unit at a time
+    if (!UNIT && wave == 0 && __ballot(empties)) {                               // rare: look again, one unit at a time
         for (int uu = blockIdx.x; uu < NU; uu += gridDim.x) {
             const UnitItems it = unit_items(APPEND, a, uu);
             if (it.nq + it.nr == 0) zero_fill(uu);
         }
     }
-    // The weight line is cut into NW ranges, each at least one residual item long.  NW is a power of two so
-    // that the cuts need no division.
+    // The weight line is cut into NW ranges, those of a workgroup together at least one residual item long (so that every
+    // workgroup between the first and the last of a unit owns an item of it).  NW is a power of two so that the cuts need no
+    // division.
     if (!UNIT && P == 0) return;
-    const int nw_cap = max(1, min((int)gridDim.x, P / kWR));
-    const int nw_log = 31 - __builtin_clz(nw_cap), NW = 1 << nw_log;
-    if (!UNIT && (int)blockIdx.x >= NW) return;
-    // Wave numbers.  The hardware serves the older of the two waves on a SIMD first, so the workgroups
-    // that were dispatched first (they fill the first wave slot of every SIMD, a.first_slot of them) get
-    // through their passes measurably faster than the rest.  When the launch fills both slots, workgroup b
-    // and workgroup b + a.first_slot take the neighbouring numbers 2b and 2b + 1, so that every unit is
-    // served by both kinds in equal parts and all units finish together.
-    const bool paired = NW == 2 * a.first_slot;
-    const int w = !paired ? (int)blockIdx.x
-                : (int)blockIdx.x < a.first_slot ? 2 * (int)blockIdx.x : 2 * ((int)blockIdx.x - a.first_slot) + 1;
-    // (the wave in the first slot of a SIMD runs faster; both parts of a pair range must stay longer than one
-    // item, so that every wave between the first and the last of a unit owns an item of it)
-    const int want16 = min(max(a.skew16, 4), 12);
-    const int skew16 = paired && ((((2L * P) >> nw_log) * min(want16, 16 - want16)) >> 4) >= kWR ? want16 : 8;
-    const long start = UNIT ? 0 : range_start(w, P, nw_log, skew16), end = UNIT ? 1 : range_start(w + 1, P, nw_log, skew16);
+    const int nw_cap = max(1, min((int)gridDim.x, P >> wr_log));
+    const int nw_log = 31 - __builtin_clz(nw_cap) + kWavesLog, NW = 1 << nw_log;
+    if (!UNIT && (int)blockIdx.x >= NW >> kWavesLog) return;
+    if (!UNIT && lane < 2) entries[2 * pos + lane].up = -1;
+    // This workgroup's place on the line: its number, or, workgroups being dealt to the eight dies in turn, a numbering that
+    // gives every die a contiguous eighth of the line (see by_die in launch_stream).
+    const int groups_log = nw_log - kWavesLog;
+    const int group = groups_log < 3 || !a.by_die ? (int)blockIdx.x : (((int)blockIdx.x & 7) << (groups_log - 3)) + ((int)blockIdx.x >> 3);
+    const int w = group * kWaves + pos;
+    // Waves i and i + 4 of a workgroup share a SIMD, which serves the older one first, so that one gets through its passes
+    // measurably faster: it takes skew16 sixteenths of the pair's range.
+    const int skew16 = kWaves == 8 && ((((2L * P) >> nw_log) * min(kSkew16, 16 - kSkew16)) >> 4) >= kWR ? kSkew16 : 8;
+    const int start = UNIT ? 0 : range_start(w, P, nw_log, skew16), end = UNIT ? 1 : range_start(w + 1, P, nw_log, skew16);
     // (NW / P as a wave-uniform value in a scalar register)
     const float inv_p = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)NW / (float)P)));
 
     // ---------------- the unit whose weight span holds position `start`
     int up = UNIT ? (int)blockIdx.x : -1;
-    long ib = 0;                                           // position of the unit's first item
+    int ib = 0;                                            // position of the unit's first item
     int T_first = unit_T, R_first = unit_R;                // its lengths
     if (!UNIT) {
-        long running = 0;
+        int running = 0;
         for (int base = 0; base < NU && up < 0; base += 256) {
             if (!small) {
                 lengths4(base, Tl, Rl);
@@ -320,7 +319,7 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             }
 #pragma unroll
             for (int k = 0; k < 4; k++) {
-                const long excl = running + incl4[k] - wl4[k];
+                const int excl = running + incl4[k] - wl4[k];
                 const bool hit = up < 0 && wl4[k] > 0 && start >= excl && start < excl + wl4[k];
                 const unsigned long long mask = __ballot(hit);
                 if (mask) {
@@ -352,33 +351,30 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
     for (; up < NU && ib < end; up++) {
         // (the lengths of the first unit are already known)
         const UnitItems it = up == up_first ? make_items(APPEND, T_first, R_first) : unit_items(APPEND, a, up);
-        const int wt = kWR * it.nr + kWQ * it.nq;
+        const int wt = (it.nr << wr_log) + (it.nq << wq_log);
         if (wt == 0) continue;
-        const long ib_next = ib + wt;
+        const int ib_next = ib + wt;
         // this wave's items of the unit (the offsets are clamped to the unit's span first, so 32-bit
         // arithmetic suffices): front residual items f0..f1-1, passes j0..j1-1, back residual items b0..b1-1
         const int nf = (it.nr + 1) >> 1, nb = it.nr >> 1;
         const int span = wt + kWR;
-        const int ds = (int)min((long)span, max(0L, start - ib)), de = (int)min((long)span, max(0L, end - ib));
-        const int dq = kWR * nf, db = dq + kWQ * it.nq;
+        const int ds = min(span, max(0, start - ib)), de = min(span, max(0, end - ib));
+        const int dq = nf << wr_log, db = dq + (it.nq << wq_log);
         // (UNIT: passes from the first wave on, residual items -- even ones in front, odd ones at the back -- from the last)
-        constexpr int NWV = kUnitWaves<G>, HW = NWV / 2;
+        constexpr int NWV = kWaves, HW = NWV / 2;
         auto share = [](int n, int k, int of) { return (n * k + of - 1) / of; };
         const int from_last = NWV - 1 - wave, kf = UNIT && !(from_last & 1) ? from_last >> 1 : 0, kb = UNIT && (from_last & 1) ? from_last >> 1 : 0;
         const int on_f = UNIT && !(from_last & 1), on_b = UNIT && (from_last & 1);
-        const int f0 = UNIT ? share(nf, kf, HW) : min(nf, (ds + kWR - 1) / kWR), f1 = UNIT ? (on_f ? share(nf, kf + 1, HW) : 0) : min(nf, (de + kWR - 1) / kWR);
-        const int j0 = UNIT ? share(it.nq, wave, NWV) : min(it.nq, (max(0, ds - dq) + kWQ - 1) / kWQ), j1 = UNIT ? share(it.nq, wave + 1, NWV) : min(it.nq, (max(0, de - dq) + kWQ - 1) / kWQ);
-        const int b0 = UNIT ? share(nb, kb, HW) : min(nb, (max(0, ds - db) + kWR - 1) / kWR), b1 = UNIT ? (on_b ? share(nb, kb + 1, HW) : 0) : min(nb, (max(0, de - db) + kWR - 1) / kWR);
+        const int f0 = UNIT ? share(nf, kf, HW) : min(nf, (ds + kWR - 1) >> wr_log), f1 = UNIT ? (on_f ? share(nf, kf + 1, HW) : 0) : min(nf, (de + kWR - 1) >> wr_log);
+        const int j0 = UNIT ? share(it.nq, wave, NWV) : min(it.nq, (max(0, ds - dq) + kWQ - 1) >> wq_log), j1 = UNIT ? share(it.nq, wave + 1, NWV) : min(it.nq, (max(0, de - dq) + kWQ - 1) >> wq_log);
+        const int b0 = UNIT ? share(nb, kb, HW) : min(nb, (max(0, ds - db) + kWR - 1) >> wr_log), b1 = UNIT ? (on_b ? share(nb, kb + 1, HW) : 0) : min(nb, (max(0, de - db) + kWR - 1) >> wr_log);
         if (!UNIT && f0 >= f1 && j0 >= j1 && b0 >= b1) { ib = ib_next; continue; }
         const int u = up >> a.hs_shift, hs = up & (a.hsets - 1);
         const int bi = (int)fast_div((uint32_t)u, a.hkv_magic, a.hkv_shift);
         const int bq0 = bi * a.Hq + (u - bi * a.Hkv) * a.rep + hs * kNH;
         const int nheads = min(kNH, a.rep - hs * kNH);
         const int t_end = it.T;
-        // the waves that own items of this unit: from the owner of the first item to the owner of the last
-        const int wf = UNIT ? 0 : wave_of(ib, P, nw_log, inv_p, skew16);
-        const int wl = UNIT ? 0 : wave_of(ib_next - (nb ? kWR : it.nq ? kWQ : kWR), P, nw_log, inv_p, skew16);
-        const int expected = wl - wf + 1;
+        const bool ends_here = ib_next >= end;             // (the wave's last unit)
         const uint32_t *Kc = a.Kc + (size_t)u * kc_words(a.Tcap);
         const uint32_t *Vc = a.Vc + (size_t)u * vc_words(a.Tcap);
         const uint16_t *Ks = a.Ks + (size_t)u * (a.Tcap / G) * kD;
@@ -503,9 +499,8 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
         for (int fi = lo; fi < hi; fi++) {
             const int ri = 2 * fi + odd;
             const int R = it.R;
-            _Float16 *pr = lds;                            // [kNH][64 + 8] halfs: weights of the item's tokens
-            _Float16 *rows = lds + kNH * kD;               // [64][kKRowH] halfs: key rows, then value rows
-            constexpr int kPrH = 72;
+            _Float16 *pr = lds;                            // [kNH][kPrH] halfs: weights of the item's tokens
+            _Float16 *rows = lds + kPrHalfs;               // [64][kKRowH] halfs: key rows, then value rows
             const uint16_t *Rk = a.Rk + (size_t)u * a.Rcap * kD;
             const uint16_t *Rv = a.Rv + (size_t)u * a.Rcap * kD;
             int lane_r = lane;                             // (opaque copy: keeps the address terms below out of
@@ -892,6 +887,9 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
         // =============================== publish this wave's partial of the unit
         int lane_p = lane;
         asm volatile("" : "+v"(lane_p));                   // (opaque copy: address terms computed here, not hoisted)
+        // the waves that own items of this unit: from the owner of the first item to the owner of the last
+        const int wf = UNIT ? 0 : wave_of(ib, P, nw_log, inv_p, skew16);
+        const int wl = UNIT ? 0 : wave_of(ib_next - (nb ? kWR : it.nq ? kWQ : kWR), P, nw_log, inv_p, skew16);
         // (fused step: the unit's residual length after the append, for the next call -- into an array of its own,
         // because every wave of THIS launch still reads the old lengths when it starts; written by the wave that
         // writes the unit's output)
@@ -901,7 +899,7 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
         if constexpr (UNIT) {
             // every wave's state goes to its own part of the local memory; then a thread per (head, channel) merges them
             // in wave order (a wave without items left m = -1e30, weight 0)
-            constexpr int NWV = kUnitWaves<G>;
+            constexpr int NWV = kWaves;
             float *mine = reinterpret_cast<float *>(lds);
             asm volatile("" ::: "memory");                 // (the same bytes held weights and rows, as other types)
 #pragma unroll
@@ -915,7 +913,7 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
             for (int i = wave * 64 + lane_p; i < nheads * kD; i += 64 * NWV) {
                 const int h = i / kD, c = i % kD;
                 const float *part = reinterpret_cast<const float *>(lds_all) + h * kPartialStride;
-                constexpr size_t step = kWaveLds<G> / 4;
+                constexpr size_t step = kLdsHalfs / 2;
                 float M = part[0];
 #pragma unroll
                 for (int k = 1; k < NWV; k++) M = fmaxf(M, part[k * step]);
@@ -928,7 +926,18 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
                 }
                 a.out[(size_t)(bq0 + h) * kD + c] = __half_as_ushort(__float2half_rn(L > 0.f ? O / L : 0.f));
             }
-        } else if (expected == 1) {
+        } else if (wf != wl) {
+            // (the last one into the memory the wave worked in, the first one must outlive the wave's next unit)
+            float *part = ends_here ? reinterpret_cast<float *>(lds) : first_part + wave * (kNH * kPartialStride);
+            asm volatile("" ::: "memory");                 // (the same bytes held weights and rows, as other types)
+#pragma unroll
+            for (int h = 0; h < NHQ; h++) {
+                part[h * kPartialStride + 4 + lane_p] = oa[h];
+                part[h * kPartialStride + 4 + lane_p + 64] = ob[h];
+                if (lane == 0) part[h * kPartialStride] = m[h], part[h * kPartialStride + 1] = lsum[h];
+            }
+            if (lane == 0) entries[2 * pos + ends_here] = Entry{up, wf >> kWavesLog, wl >> kWavesLog, it.rn};
+        } else {
             // the only partial of its unit: normalise and write the result directly
             write_next_len();
 #pragma unroll
@@ -939,169 +948,211 @@ __global__ __launch_bounds__(UNIT ? 64 * kUnitWaves<G> : 64, G == 16 ? 1 : 2) vo
                     a.out[(size_t)(bq0 + h) * kD + lane_p + 64] = __half_as_ushort(__float2half_rn(ob[h] * inv));
                 }
             }
-        } else {
-            // Two-level merge.  The waves of the unit form sub-groups of 16 (by their place in the group);
-            // the last partial to arrive in a sub-group merges it -- the slots are consecutive, every
-            // address is a wave-uniform base plus constants, one round trip -- and, when the unit has more
-            // than one sub-group, writes the result over the sub-group's first slot and takes a ticket at
-            // the unit; the last sub-group to arrive merges those (slots 16 apart).  So a unit served by
-            // hundreds of waves still ends with two short merges, and the first level runs while other
-            // waves are still at work.
-            constexpr int kSlotB = kNH * kPartialStride * 4, kHeadB = kPartialStride * 4;
-            // The merging wave holds, per lane, 4 consecutive channels of two heads: lanes 0..31 of heads 0 and 2,
-            // lanes 32..63 of heads 1 and 3.  One 128-bit load per lane then fetches a partial's outputs of two heads,
-            // so the 16 partials of a sub-group are 32 + 4 loads: a wave can have 63 memory instructions outstanding,
-            // and with 64-bit loads (68 of them) the last ones went out only after the first had returned -- two
-            // round trips where this is one.
-            const int half_p = lane_p >> 5, c4 = lane_p & 31;
-            const unsigned lane_off = (unsigned)(half_p * kHeadB + 16 + c4 * 16);
+        }
+        ib = ib_next;
+    }
+    if constexpr (!UNIT) {
+        // =============================== the workgroup's partials: a wave per unit merges the entries of the unit in local
+        // memory, and, if other workgroups have items of the unit as well, publishes the result and takes a ticket
+        // (the arguments once more from memory: held over the passes they would not fit the scalar registers)
+        auto b = (const __attribute__((address_space(4))) DecArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(b));
+        // split-K partial of (slot, head): [0] running max (base-2 domain), [1] sum of weights, [4..131] output
+        auto slot_of = [&](int slot, int h) -> float * { return b->ws + ((size_t)slot * kNH + h) * kPartialStride; };
+        __syncthreads();
+        constexpr int NE = 2 * kWaves, NJ = NHQ / 2;       // (NJ: pairs of heads in use)
+        constexpr int kSlotB = kNH * kPartialStride * 4, kHeadB = kPartialStride * 4, kSc1 = 16;  // (cache policy: device scope)
+        typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+        const int half_p = lane >> 5, c4 = lane & 31;      // a lane holds channels 4 c4 .. 4 c4 + 3 of heads half_p and 2 + half_p
+        const unsigned lane_off = (unsigned)(half_p * kHeadB + 16 + c4 * 16);
+        const Entry mine = entries[min(lane, NE - 1)];
+        const int up_e = lane < NE ? mine.up : -1;
+        auto part_of = [&](int e) -> const float * {
+            const int p = e >> 1, wv = kWaves == 8 ? (p >> 1) + (p & 1) * 4 : p;
+            return e & 1 ? reinterpret_cast<const float *>(lds_all + wv * kLdsHalfs) : first_part + wv * (kNH * kPartialStride);
+        };
+        unsigned long long left = __ballot(up_e >= 0);
+        for (int seg = 0; left != 0; seg++) {
+            const int head = __ffsll((long long)left) - 1, up = __builtin_amdgcn_readlane(up_e, head);
+            unsigned long long same = __ballot(up_e == up);
+            left &= ~same;
+            if ((seg & (kWaves - 1)) != wave) continue;
+            const int gf = __builtin_amdgcn_readlane(mine.wf, head), gl = __builtin_amdgcn_readlane(mine.wl, head);
+            const int rn = __builtin_amdgcn_readlane(mine.rn, head);
+            const int u = up >> b->hs_shift, hs = up & (b->hsets - 1);
+            const int bi = (int)fast_div((uint32_t)u, b->hkv_magic, b->hkv_shift);
+            const int bq0 = bi * b->Hq + (u - bi * b->Hkv) * b->rep + hs * kNH;
+            const int nheads = min(kNH, b->rep - hs * kNH);
+
             float M[kNH], L[kNH];
-            f4 Oq[2];                                      // Oq[j]: channels 4*c4 .. 4*c4+3 of head 2*j + half_p
-            // merges `count` partials, `stride` slots apart from slot `first`, into (M, L, Oq): lane s fetches
-            // (max, sum) of partial s, which gives every partial's weight; the output vectors of up to 16
-            // partials are requested in the same round trip (device-scope loads: sc1)
-            auto merge = [&](int first, int stride, int count) {
-                const char *const sbase = reinterpret_cast<const char *>(slot_ptr(a, first, 0));
-                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(sbase), 0, 0x7fffffff, 0x00020000);
-                const unsigned step = (unsigned)stride * kSlotB;
+            f4 Oq[NJ];
 #pragma unroll
-                for (int h = 0; h < kNH; h++) { M[h] = -1e30f; L[h] = 0.f; }
-                Oq[0] = f4{0.f, 0.f, 0.f, 0.f}; Oq[1] = Oq[0];
-                constexpr int MB = 16;
-                constexpr int kSc1 = 16;                   // cache policy of the buffer load: device scope
-#pragma unroll 1
-                for (int base = 0; base < count; base += MB) {
-                    const int cnt = min(MB, count - base);
-                    const bool has = lane < cnt;
-                    const char *const mine_p = sbase + (size_t)(base + (has ? lane : 0)) * step;
-                    float ms[kNH], ls[kNH], cm[kNH];
+            for (int h = 0; h < kNH; h++) { M[h] = -1e30f; L[h] = 0.f; }
 #pragma unroll
-                    for (int h = 0; h < kNH; h++) {
-                        const float2 ml = ld_agent2(reinterpret_cast<const float *>(mine_p + h * kHeadB));
-                        const bool on = has && h < nheads;
-                        ms[h] = on ? ml.x : -1e30f;        // partials that do not exist get weight 0 below
-                        ls[h] = on ? ml.y : 0.f;
-                    }
-                    f4 x[MB][2];
+            for (int j = 0; j < NJ; j++) Oq[j] = f4{0.f, 0.f, 0.f, 0.f};
+            // adds `n` partials to (M, L, Oq): lane k holds (max, sum) of partial k, x their outputs
+            auto fold = [&](float (&ms)[kNH], float (&ls)[kNH], auto &x, auto n) __attribute__((always_inline)) {
+                float cm[kNH], wgt[kNH], lw[kNH], so2[2] = {0.f, 0.f};
 #pragma unroll
-                    for (int k = 0; k < MB; k++) {
-                        const unsigned pk = (unsigned)(base + min(k, cnt - 1)) * step;   // uniform
+                for (int h = 0; h < kNH; h++) cm[h] = ms[h];
+                if constexpr (PAIRED) wave_max64x2(cm); else wave_max64x4(cm);
 #pragma unroll
-                        for (int j = 0; j < 2; j++) {
-                            typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-                            const u4v v = __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, pk + (unsigned)(2 * j * kHeadB), kSc1);
-                            x[k][j] = __builtin_bit_cast(f4, v);
-                        }
-                    }
-#pragma unroll
-                    for (int h = 0; h < kNH; h++) cm[h] = ms[h];
-                    wave_max64x4(cm);
-                    float wgt[kNH], lw[kNH];
-                    float so2[2];
-#pragma unroll
-                    for (int h = 0; h < kNH; h++) {
-                        const float Mn = fmaxf(M[h], cm[h]);
-                        const float so = fast_exp2(M[h] - Mn);
-                        wgt[h] = fast_exp2(ms[h] - Mn);    // exactly 0 for ms = -1e30
-                        lw[h] = ls[h] * wgt[h];
-                        L[h] *= so;
-                        if ((h & 1) == 0) so2[h >> 1] = so; else so2[h >> 1] = half_p ? so : so2[h >> 1];
-                        M[h] = Mn;
-                    }
-                    Oq[0] *= so2[0]; Oq[1] *= so2[1];
-                    wave_sum64x4(lw);
-#pragma unroll
-                    for (int h = 0; h < kNH; h++) L[h] += lw[h];
-#pragma unroll
-                    for (int k = 0; k < MB; k++)
-#pragma unroll
-                        for (int j = 0; j < 2; j++) {
-                            const float w0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt[2 * j]), k));
-                            const float w1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt[2 * j + 1]), k));
-                            const float wl = half_p ? w1 : w0;
-                            Oq[j] += x[k][j] * wl;
-                        }
+                for (int h = 0; h < NHQ; h++) {
+                    const float Mn = fmaxf(M[h], cm[h]), so = fast_exp2(M[h] - Mn);
+                    wgt[h] = fast_exp2(ms[h] - Mn);        // exactly 0 for ms = -1e30
+                    lw[h] = ls[h] * wgt[h];
+                    L[h] *= so;
+                    if ((h & 1) == 0) so2[h >> 1] = so; else so2[h >> 1] = half_p ? so : so2[h >> 1];
+                    M[h] = Mn;
                 }
-            };
-            auto write_out = [&]() {
-                write_next_len();
+                if constexpr (PAIRED) lw[2] = lw[3] = 0.f;
+                wave_sum64x4(lw);
 #pragma unroll
-                for (int j = 0; j < 2; j++) {
+                for (int h = 0; h < NHQ; h++) L[h] += lw[h];
+#pragma unroll
+                for (int j = 0; j < NJ; j++) Oq[j] *= so2[j];
+#pragma unroll
+                for (int k = 0; k < decltype(n)::value; k++)
+#pragma unroll
+                    for (int j = 0; j < NJ; j++) {
+                        const float w0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt[2 * j]), k));
+                        const float w1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt[2 * j + 1]), k));
+                        Oq[j] += x[k][j] * (half_p ? w1 : w0);
+                    }
+            };
+            {
+                // (partial k of the unit: the k-th entry; past the last one the last again, with weight 0)
+                float ms[kNH], ls[kNH];
+                f4 x[kWaves][NJ];
+                const int count = __builtin_popcountll(same);
+                int place = 0;
+#pragma unroll
+                for (int k = 0; k < kWaves; k++) {
+                    const int e = __ffsll((long long)same) - 1;
+                    if (same & (same - 1)) same &= same - 1;
+                    place = lane == k ? e : place;
+                    const float *p = part_of(e);
+#pragma unroll
+                    for (int j = 0; j < NJ; j++) x[k][j] = *reinterpret_cast<const f4 *>(p + (2 * j + half_p) * kPartialStride + 4 + 4 * c4);
+                }
+                const float *p = part_of(lane < kWaves ? place : head);
+#pragma unroll
+                for (int h = 0; h < kNH; h++) {
+                    const bool on = lane < count && h < nheads;
+                    const float2 ml = *reinterpret_cast<const float2 *>(p + (h < NHQ ? h : 0) * kPartialStride);
+                    ms[h] = on ? ml.x : -1e30f;
+                    ls[h] = on ? ml.y : 0.f;
+                }
+                fold(ms, ls, x, std::integral_constant<int, kWaves>{});
+            }
+            auto write_out = [&]() {
+                if (FUSED && b->append && lane == 0) b->r_len_out[u] = rn >= 0 ? rn + 1 : b->r_len[u];
+#pragma unroll
+                for (int j = 0; j < NJ; j++) {
                     const int h = 2 * j + half_p;
                     if (h >= nheads) continue;
-                    const float Lh = half_p ? L[2 * j + 1] : L[2 * j];
-                    const float inv = Lh > 0.f ? 1.0f / Lh : 0.f;
+                    const float Lh = half_p ? L[2 * j + 1] : L[2 * j], inv = Lh > 0.f ? 1.0f / Lh : 0.f;
                     const h2 r0 = {(_Float16)(Oq[j][0] * inv), (_Float16)(Oq[j][1] * inv)};
                     const h2 r1 = {(_Float16)(Oq[j][2] * inv), (_Float16)(Oq[j][3] * inv)};
-                    *reinterpret_cast<uint2 *>(a.out + (size_t)(bq0 + h) * kD + 4 * c4) = uint2{as_u32(r0), as_u32(r1)};
+                    *reinterpret_cast<uint2 *>(b->out + (size_t)(bq0 + h) * kD + 4 * c4) = uint2{as_u32(r0), as_u32(r1)};
                 }
             };
-            auto take_ticket = [&](int *counter) -> int {           // after this wave's stores are acknowledged
+            if (gf == gl) { write_out(); continue; }
+
+            auto slots = [&](int first) {
+                return __builtin_amdgcn_make_buffer_rsrc(slot_of(first, 0), 0, 0x7fffffff, 0x00020000);
+            };
+            // (device scope throughout: the workgroups of a unit run on different dies, see take_ticket)
+            auto publish = [&](int slot) {
+                const __amdgpu_buffer_rsrc_t rs = slots(slot);
+#pragma unroll
+                for (int j = 0; j < NJ; j++)
+                    if (2 * j + half_p < nheads)
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, Oq[j]), rs, lane_off, 2 * j * kHeadB, kSc1);
+#pragma unroll
+                for (int h = 0; h < NHQ; h++)
+                    if (h < nheads && lane == 0) { float *pp = slot_of(slot, h); st_agent(pp, M[h]); st_agent(pp + 1, L[h]); }
+            };
+            auto take_ticket = [&](int *counter) -> int {  // after this wave's stores are acknowledged
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 int old = 0;
                 if (lane == 0) old = atomicAdd(counter, 1);
                 return __builtin_amdgcn_readfirstlane(old);
             };
-
-            const int me = w - wf, sg = me >> 4;
-            const int n1 = min(16, expected - 16 * sg), nsg = (expected + 15) >> 4;
-            const int slot1 = wf + 16 * sg + 2 * up;               // first slot of the sub-group
-            const int slot = w + 2 * up;
+            // merges `count` partials, `stride` slots apart from slot `first`, MB of them a round trip
+            auto merge = [&](int first, int stride, int count, auto mb) __attribute__((always_inline)) {
+                constexpr int MB = decltype(mb)::value;
+                const char *const sbase = reinterpret_cast<const char *>(slot_of(first, 0));
+                const __amdgpu_buffer_rsrc_t rs = slots(first);
+                const unsigned step = (unsigned)stride * kSlotB;
 #pragma unroll
-            for (int h = 0; h < kNH; h++) {
-                if (h < nheads) {
-                    float *pp = slot_ptr(a, slot, h);
-                    st_agent(pp + 4 + lane, oa[h]);
-                    st_agent(pp + 4 + lane + 64, ob[h]);
-                    if (lane == 0) { st_agent(pp, m[h]); st_agent(pp + 1, lsum[h]); }
-                }
-            }
-            const int old1 = take_ticket(a.cnt1 + slot1);
-            if (old1 == n1 - 1) {
-                merge(slot1, 1, n1);
-                if (lane == 0) st_agent_i32(a.cnt1 + slot1, 0);   // ready for the next call
-                if (nsg == 1) {
-                    write_out();
-                } else {
+                for (int h = 0; h < kNH; h++) { M[h] = -1e30f; L[h] = 0.f; }
 #pragma unroll
-                    for (int j = 0; j < 2; j++) {
-                        const int h = 2 * j + half_p;
-                        if (h < nheads) {
-                            float *pp = slot_ptr(a, slot1, h) + 4 + 4 * c4;
+                for (int j = 0; j < NJ; j++) Oq[j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int base = 0; base < count; base += MB) {
+                    const int cnt = min(MB, count - base);
+                    const bool has = lane < cnt;
+                    const char *const mine_p = sbase + (size_t)(base + (has ? lane : 0)) * step;
+                    float ms[kNH], ls[kNH];
 #pragma unroll
-                            for (int e = 0; e < 4; e++) st_agent(pp + e, Oq[j][e]);
-                        }
+                    for (int h = 0; h < kNH; h++) {
+                        const bool on = has && h < nheads;
+                        const float2 ml = h < NHQ ? ld_agent2(reinterpret_cast<const float *>(mine_p + h * kHeadB)) : float2{0.f, 0.f};
+                        ms[h] = on ? ml.x : -1e30f;        // partials that do not exist get weight 0
+                        ls[h] = on ? ml.y : 0.f;
                     }
+                    f4 x[MB][NJ];
 #pragma unroll
-                    for (int h = 0; h < kNH; h++)
-                        if (h < nheads && lane == 0) { float *pp = slot_ptr(a, slot1, h); st_agent(pp, M[h]); st_agent(pp + 1, L[h]); }
-                    const int old2 = take_ticket(a.cnt + up);
-                    if (old2 == nsg - 1) {
-                        merge(wf + 2 * up, 16, nsg);
-                        write_out();
-                        if (lane == 0) st_agent_i32(a.cnt + up, 0);
+                    for (int k = 0; k < MB; k++) {
+                        const unsigned pk = (unsigned)(base + min(k, cnt - 1)) * step;   // uniform
+#pragma unroll
+                        for (int j = 0; j < NJ; j++)
+                            x[k][j] = __builtin_bit_cast(f4, (u4v)__builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, pk + (unsigned)(2 * j * kHeadB), kSc1));
                     }
+                    fold(ms, ls, x, mb);
                 }
+            };
+            // Up to kOneLevel workgroups merge at once; more in sets of 16, whose results take the place of the set's first slot
+            constexpr int kOneLevel = 32;
+            const int expected = gl - gf + 1, me = group - gf;
+            const int per = expected <= kOneLevel ? kOneLevel : 16, sg = expected <= kOneLevel ? 0 : me >> 4;
+            const int n1 = min(per, expected - per * sg), nsg = expected <= kOneLevel ? 1 : (expected + 15) >> 4;
+            const int slot1 = gf + per * sg + 2 * up;
+            int into = group + 2 * up, from = slot1, stride = 1, count = n1;
+            int *counter = b->cnt1 + slot1;
+#pragma unroll 1
+            for (bool last = nsg == 1;; last = true) {
+                publish(into);
+                if (take_ticket(counter) != count - 1) break;
+                if (count <= 4) merge(from, stride, count, std::integral_constant<int, 4>{});
+                else if (count <= 8) merge(from, stride, count, std::integral_constant<int, 8>{});
+                else merge(from, stride, count, std::integral_constant<int, 16>{});
+                if (lane == 0) st_agent_i32(counter, 0);   // ready for the next call
+                if (last) { write_out(); break; }
+                into = slot1, from = gf + 2 * up, stride = 16, count = nsg, counter = b->cnt + up;
             }
         }
-        ib = ib_next;
     }
 }
 
-template <int G, bool LO, bool PAIRED, bool APPEND>
-static int launch_units(const DecArgs &a, hipStream_t st)
+template <int G, bool LO, bool PAIRED, bool APPEND, bool UNIT, bool STREAM>
+static int launch_form(const DecArgs &a, long groups, hipStream_t st)
 {
-    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, true, true, false>), dim3((unsigned)(a.units * a.hsets)),
-                       dim3(64 * kUnitWaves<G>), 0, st, a);
+    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, UNIT, STREAM>), dim3((unsigned)groups),
+                       dim3(64 * kGroupWaves<G>), 0, st, a);
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
+
+constexpr long kComputeUnits = 256;
 
 // Whether a workgroup per unit serves the call, from the capacities (the lengths are on the device).  It needs a compute
 // unit per unit, and few enough items that the eight waves of a unit (four at G = 16) are done before the work line, which
 // spreads the items over the whole device, has paid for its round trips -- also when the lengths are ragged and the line
-// has the better balance.  The limits lie on the safe side of that: inside them the line never won (1.0-2.9 times over 564
-// shapes), a little outside the unit form often still does (with one head per KV head 256 units x 35 items 1.2 times).
-// Measured with all lengths at the capacity / ragged (5 .. 100 % of it), line against unit, us:
+// has the better balance.  Line against unit at the limits, us: 8 units x 10 items 11.5 against 10.9, 13 items 11.2 against
+// 11.5; 128 units x 12 items 13.9 against 13.0, 21 items 16.9 against 15.8, 22 items (a second residual item) 16.9 against
+// 18.8; 160 x 14 at G = 16 19.3 against 17.7; 256 x 22, ragged, 17.1 against 12.6.
+// With a line of single waves, which had the longer chain behind it, lengths at the capacity / ragged (5 .. 100 % of it):
 //   32/8 heads, G = 32:    8 units x 11 items 12.1 / 11.5 against 11.5, 15 items 12.0 against 14.1
 //                         64 units x 11 items 13.3 against 12.0 / 16.3 against 11.8, 15 items 13.5 against 14.9
 //                        128 units x 19 items 19.9 against 15.2, 27 items 17.9 against 17.9, 35 items 19.6 against 20.8
@@ -1113,41 +1164,9 @@ static bool unit_per_workgroup(const DecArgs &a, int G)
 {
     const long units = (long)a.units * a.hsets;
     const int items = (a.Tcap + kPass - 1) / kPass + (a.Rcap + 63) / 64;
-    if (units > 256) return false;                         // compute units of the device
+    if (units > kComputeUnits) return false;
     if (G == 16) return items <= (units >= 96 ? 20 : units >= 32 ? 12 : 0);
     return items <= (units >= 192 ? 28 : units >= 96 ? 24 : 12);
-}
-
-// Single-wave workgroups of an instance that the device holds at once; 0 if the runtime does not say.
-template <int G, bool LO, bool PAIRED, bool APPEND, bool FLAT, bool STREAM>
-static int resident_waves()
-{
-    static int resident = 0;
-    if (resident == 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT, false, STREAM>, 64,
-                                                         kWaveLds<G>) != hipSuccess ||
-            cus <= 0 || per_cu <= 0)
-            return 0;
-        resident = cus * per_cu;
-    }
-    return resident;
-}
-
-template <int G, bool LO, bool PAIRED, bool APPEND, bool FLAT, bool STREAM>
-static int launch_stream_w(DecArgs a, long cap_items, hipStream_t st)
-{
-    const int resident = resident_waves<G, LO, PAIRED, APPEND, FLAT, STREAM>();
-    if (resident == 0) return MINIKV_ELAUNCH;
-    long nw = resident < kMaxStreamWaves ? resident : kMaxStreamWaves;
-    if (nw > cap_items) nw = cap_items;
-    if (nw < 1) nw = 1;
-    a.first_slot = resident / 2;
-    a.skew16 = kSkew16;
-    hipLaunchKernelGGL((decode_stream_kernel<G, LO, PAIRED, APPEND, FLAT, false, STREAM>), dim3((unsigned)nw), dim3(64), kWaveLds<G>, st, a);
-    return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
 
 static std::atomic<int> g_decode_weights{0};
@@ -1161,15 +1180,25 @@ bool set_decode_weights(int mode)
 template <int G, bool LO, bool PAIRED, bool APPEND>
 static int launch_stream(DecArgs a, hipStream_t st)
 {
-    const int resident = resident_waves<G, LO, PAIRED, APPEND, false, false>();
-    if (resident == 0) return MINIKV_ELAUNCH;
     const long cap_items = (long)a.units * a.hsets * ((a.Tcap + kPass - 1) / kPass + (a.Rcap + 63) / 64);
-    // (unit weights when the launch cannot hold more items than half the waves the device holds: measured on
-    // shapes of 80 to 2240 items, they win up to 608 items -- 13.3 against 16.7 us -- tie at 560 and lose from
-    // 1120 on -- 19.8 against 17.7 us)
     const int mode = g_decode_weights.load();
-    if (mode == 0 && unit_per_workgroup(a, G)) return launch_units<G, LO, PAIRED, APPEND>(a, st);
-    if (mode == 0 ? cap_items * 2 <= (long)resident : mode == 2) return launch_stream_w<G, LO, PAIRED, APPEND, true, false>(a, cap_items, st);
+    if (mode == 0 && unit_per_workgroup(a, G)) return launch_form<G, LO, PAIRED, APPEND, true, false>(a, (long)a.units * a.hsets, st);
+    // Weight of a residual item against a pass: 8 : 2 where every wave has several items (1344 items, G = 128, 11.7 us against
+    // 12.5 with 4 : 2; 512 units x 12 items 22.5 against 23.3).  4 : 2 where the ranges would be too few for the compute units (64
+    // units x 8 items 13.8 -> 11.8; 8 units x 42, G = 16, 17.9 -> 15.1), and where a wave has one or two items, so that one
+    // with a residual item should hold nothing else (2816 items 18.8 -> 16.9, 3072 items 18.7 -> 17.2, but 5376 19.7 -> 20.2).
+    const long units = (long)a.units * a.hsets;
+    const long weight = units * (2 * ((a.Tcap + kPass - 1) / kPass) + 8 * ((a.Rcap + 63) / 64));
+    const bool light = weight < 8 * kComputeUnits || (cap_items > 2048 && cap_items <= 3584);
+    a.wq_log = mode == 2 ? 0 : 1, a.wr_log = mode == 2 ? 0 : mode == 0 && light ? 2 : 3;
+    // Two sets of heads read the same words: their workgroups on one die find them in its L2 (128 units x 102 items 35.1 ->
+    // 32.0 us, x 42 22.0 -> 20.6), if a die's eighth holds both; small calls lose (8 units x 22 items 13.8 -> 14.4).
+    a.by_die = a.hsets > 1 && cap_items > 2048 && units >= 16;
+    // More than 16 workgroups a unit (a merge of two loops) only where each has eight items (8 units x 102 items, G = 128, 15.1
+    // us with 32 workgroups a unit, 13.6 with 16; but 8 x 784 28.3 against 31.0).
+    long groups = cap_items < kComputeUnits ? cap_items : kComputeUnits;
+    const long few = 16 * units > cap_items / 8 ? 16 * units : cap_items / 8;
+    groups = groups < few ? groups : few;
     // Streaming loads where the packed cache (by its capacity) is larger than a third of the 256 MB memory-side cache and a
     // call reads it once.  Twice, with two sets of heads, the hint loses at every size (8 heads per KV head, G = 32, 200 MB
     // 71.8 -> 75.1 us, 300 MB 101 -> 105; 6 heads the same, G = 16 1 % less, G = 128 3 % from 300 MB on).  Once, with three
@@ -1187,8 +1216,8 @@ static int launch_stream(DecArgs a, hipStream_t st)
     // registers).
     constexpr long kStreamBytes = 88L << 20;
     const long packed = (long)a.units * a.Tcap * (64 + 8 * kD / G);
-    return packed > kStreamBytes && a.hsets == 1 ? launch_stream_w<G, LO, PAIRED, APPEND, false, true>(a, cap_items, st)
-                                                 : launch_stream_w<G, LO, PAIRED, APPEND, false, false>(a, cap_items, st);
+    return packed > kStreamBytes && a.hsets == 1 ? launch_form<G, LO, PAIRED, APPEND, false, true>(a, groups, st)
+                                                 : launch_form<G, LO, PAIRED, APPEND, false, false>(a, groups, st);
 }
 
 template <bool LO, bool PAIRED>

@@ -151,6 +151,35 @@ def test_a_workgroup_per_unit(g, G, Hq, Hkv, B, L, Rcap):
     assert w.units <= 2 or not got.reshape(w.units, -1)[0].any()
 
 
+def one_unit(B, Hkv):
+    return B * Hkv == 1
+
+
+@pytest.mark.parametrize("variant", [3, 31, 32])
+@pytest.mark.parametrize("G,Hq,Hkv,B,L,Tcap", [
+    (32, 4, 1, 1, 100000, None),        # one unit over so many workgroups that they merge in two levels
+    (16, 2, 1, 1, 40000, None),         # over one to two dozen: one level, in two rounds
+    (64, 6, 3, 3, 3000, None),          # a few workgroups a unit, ranges that begin and end inside units
+    (32, 1, 1, 700, 96, None),          # several whole units a wave
+    (128, 16, 16, 24, 900, None),       # about one unit a workgroup, the units' ends anywhere in it
+    (32, 16, 2, 9, 1300, 16384),        # two sets of heads, the line dealt to the dies
+])
+def test_work_line_of_workgroups(g, variant, G, Hq, Hkv, B, L, Tcap):
+    """Units of 1 to 391 passes, ragged, every third without residual tokens and two of many empty, on the work line."""
+    w = tiny(G, B=B, Hq=Hq, Hkv=Hkv, L=L, keep=None, keep_range=(0.5, 1.0) if one_unit(B, Hkv) else (0.02, 1.0), Rcap=128)
+
+    def mutate(inp):
+        if not one_unit(B, Hkv):
+            inp.n_tok[1] = 0
+            inp.n_tok[-1] = 0
+
+    r_len = (np.arange(w.units) * 37 + 90) % 129 * (np.arange(w.units) % 3 != 1)
+    got, want = run_both(g, w, r_len=r_len, variant=variant, mutate=mutate, Tcap=Tcap)
+    assert np.max(np.abs(got - want)) <= TOL
+    if not one_unit(B, Hkv):
+        assert not got.reshape(w.units, -1)[1].any()
+
+
 @pytest.mark.parametrize("variant", VARIANTS)
 def test_peaked_attention_with_outlier_channels(g, variant):
     """Few tokens, the query aligned with one key, x10 outlier channels: the case that stresses 2e-3."""
