@@ -10,8 +10,8 @@
 //                          multiply, and the fp32 scores, once turned into fp16 weights, ARE the B operand of
 //                          O^T = V^T P^T without any shuffle (the key order inside a 16-key step is whatever the
 //                          accumulator layout gives; the V^T operand is read in the same order).
-//   prefill_colsum_kernel  column blocks in parallel.  A workgroup owns 128 keys (their K rows held in registers as
-//                          the B operand), walks the queries from the diagonal down in tiles of 64 through LDS,
+//   prefill_colsum_kernel  column blocks in parallel.  A workgroup owns 128 or 64 keys (their K rows held in registers as
+//                          the B operand), walks the queries from the diagonal down in tiles of 64 or 128 through LDS,
 //                          recomputes S = Q K^T, normalises with the saved LSE and adds the weights of its key column
 //                          in the lane: no atomics, one exchange at the end.
 // A prompt of at most 128 tokens is one row block: its workgroup of the first kernel forms the column sums as well.
@@ -434,9 +434,9 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
     }
 }
 
-// A workgroup owns 128 keys and walks the queries from the diagonal down in tiles of 64 through LDS.  Wave (kw, qw)
-// holds the K rows of 64 of the keys as B operands and takes 32 of a tile's queries, so that every Q fragment read
-// from LDS feeds two products.  The products of tile n+1 and the exponentials of tile n stand side by side in one
+// A workgroup of four waves owns 64 KW keys and walks the queries from the diagonal down in tiles of 128 / KW through LDS.
+// Wave (kw, qw) holds the K rows of 64 of the keys as B operands and takes 32 of a tile's queries, so that every Q fragment
+// read from LDS feeds two products.  The products of tile n+1 and the exponentials of tile n stand side by side in one
 // instruction stream (one 32x32x16 product, then the two weights whose exponent is ready): 43 cycles per product and
 // two weights with two waves on a SIMD, where products and weights in separate phases took their sum.
 // What bounds it: on N(0,1) data the clock falls to 1.8 GHz under this load (2.4 GHz on zeros, same cycles), so what
@@ -447,19 +447,21 @@ __global__ __launch_bounds__(64 * WAVES * SPLIT, 2) void prefill_fwd_kernel(Pref
 // heads x 16384 1.185 -> 1.156 ms, 32 x 777 12.7 -> 12.1 us, 8 x 2048 21.6 -> 20.2).  Two sets of waves on the even and the
 // odd tiles, as in the first pass, gain on long prompts of few heads and lose on the others (8 x 2048 20.3 -> 19.2, 8 x 4096 36.0
 // -> 33.2, but 32 x 400 9.1 -> 10.3, 32 x 777 12.2 -> 13.0, 32 x 4096 80 -> 95).
-constexpr int kColWaves = 4, kKeyWaves = kColWaves / 2, kKeys = 64 * kKeyWaves;
+constexpr int kColWaves = 4;
 
+template <int KW>
 __global__ __launch_bounds__(64 * kColWaves, 2) void prefill_colsum_kernel(PrefillArgs a)
 {
-    constexpr int kRows = kPfN / kColWaves, kLoads = kRows / 4;    // rows of a tile one wave loads, four per instruction
-    __shared__ __align__(16) _Float16 Qs[2 * kPfN * kPfD];
-    __shared__ __align__(16) float lse2[4 * kPfN];     // LSE of a tile's queries in powers of two; read one iteration
+    constexpr int kKeys = 64 * KW, QW = kColWaves / KW, kTile = 32 * QW;   // keys of the workgroup, queries of a tile
+    constexpr int kRows = kTile / kColWaves, kLoads = kRows / 4;   // rows of a tile one wave loads, four per instruction
+    __shared__ __align__(16) _Float16 Qs[2 * kTile * kPfD];
+    __shared__ __align__(16) float lse2[4 * kTile];    // LSE of a tile's queries in powers of two; read one iteration
                                                        // after the tile's rows, so kept longer
-    __shared__ float half_sum[kKeys];
+    __shared__ float part_sum[(QW - 1) * kKeys];
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kw = wave % kKeyWaves, qw = wave / kKeyWaves;
+    const int kw = wave % KW, qw = wave / KW;
     // column blocks in natural order: block 0 is seen by every query and is the heaviest
     const int nbh = (int)gridDim.x / a.nblk, kb = (int)blockIdx.x / nbh, head = (int)blockIdx.x % nbh;
     const long bh = head, kvh = (head / a.Hq) * (a.Hq / a.rep) + (head % a.Hq) / a.rep;
@@ -477,22 +479,23 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void prefill_colsum_kernel(Prefi
     }
 
     const float c = a.scale_log2;
-    const int tile0 = kb * kKeyWaves, ntiles = (L + kPfN - 1) / kPfN;
+    const int tile0 = kb * kKeys / kTile, ntiles = (L + kTile - 1) / kTile;
     // A wave loads kRows consecutive rows of a tile; lanes whose row lies past the prompt load the last chunk of its last
     // row (their weights are masked), and for a tile past the last every lane loads the same bytes: nearly nothing moves.
     const unsigned q_lds = lds_offset(Qs) + wave * (kRows * 256u);
     const unsigned q_off = (wave * kRows + (lane >> 4)) * 256u + (((lane & 15) ^ (lane >> 4)) << 4);    // of the first load
-    auto request = [&](int n) -> float {               // returns the LSE of query `lane` of the tile
-        const unsigned tile = (unsigned)min(n, ntiles - 1) * (kPfN * 256u);
+    const int lse0 = wave % (kTile / 64) * 64;   // (uniform)
+    auto request = [&](int n) -> float {               // returns the LSE of query lse0 + lane of the tile
+        const unsigned tile = (unsigned)min(n, ntiles - 1) * (kTile * 256u);
         const unsigned end = n < ntiles ? (unsigned)(L - 1) * 256u + 240u : 0u;
 #pragma unroll
         for (int i = 0; i < kLoads; ++i)
-            load_to_lds(Qh, min((q_off ^ ((i & 3) << 6)) + i * 1024u + tile, end), q_lds + (n & 1) * (kPfN * 256u) + i * 1024u);
-        return lseh[min(n * kPfN + lane, L - 1)];      // (each wave the same 64: no branch in the stream)
+            load_to_lds(Qh, min((q_off ^ ((i & 3) << 6)) + i * 1024u + tile, end), q_lds + (n & 1) * (kTile * 256u) + i * 1024u);
+        return lseh[min((n * kTile + lse0) + lane, L - 1)];  // (some waves the same 64: no branch in the stream)
     };
     float lr = 0.0f;
     auto settle = [&](int n) {                         // tile n is in LDS (this wave's share): then a barrier
-        lse2[(n & 3) * kPfN + lane] = lr * kLog2e;
+        lse2[(n & 3) * kTile + lse0 + lane] = lr * kLog2e;
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
     };
     const int frag_row = qw * 32 + r;
@@ -501,14 +504,14 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void prefill_colsum_kernel(Prefi
     int q_place[8];
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) q_place[ks] = tile_place(frag_row, 2 * ks + g);
-    auto read_q = [&](int ks, int n) { qf[ks] = *(const half8 *)(Qs + (n & 1) * (kPfN * kPfD) + q_place[ks]); };
+    auto read_q = [&](int ks, int n) { qf[ks] = *(const half8 *)(Qs + (n & 1) * (kTile * kPfD) + q_place[ks]); };
     auto read_lse = [&](int iq, int n) {
-        const float4 v = *(const float4 *)&lse2[(n & 3) * kPfN + qw * 32 + iq * 8 + g * 4];
+        const float4 v = *(const float4 *)&lse2[(n & 3) * kTile + qw * 32 + iq * 8 + g * 4];
         ls[iq * 4] = v.x, ls[iq * 4 + 1] = v.y, ls[iq * 4 + 2] = v.z, ls[iq * 4 + 3] = v.w;
     };
     // scores that do not count (query before the key, or past the prompt) become -inf: weight 0.  Few tiles have any.
     auto mask = [&](float16v (&s)[2], int n) {
-        const int row0 = n * kPfN + qw * 32;
+        const int row0 = n * kTile + qw * 32;
         if (row0 >= k0 + 63 && row0 + 32 <= L) return;
         const int hi = L - row0 - 4 * g;               // rows of the block that exist, this half-wave's share
 #pragma unroll
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void prefill_colsum_kernel(Prefi
 
     lr = request(tile0);
     const float lr1 = request(tile0 + 1);
-    lse2[((tile0 + 1) & 3) * kPfN + lane] = lr1 * kLog2e;
+    lse2[((tile0 + 1) & 3) * kTile + lse0 + lane] = lr1 * kLog2e;
     settle(tile0);                                     // (the second tile and the K rows have arrived as well)
     __syncthreads();
     float16v sa[2], sb[2];
@@ -604,9 +607,13 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void prefill_colsum_kernel(Prefi
 #pragma unroll
     for (int t = 0; t < 2; ++t) cs[t] += __shfl_xor(cs[t], 32, 64);
     const float sum = g ? cs[1] : cs[0];               // lane (r, g) stores key k0 + 32 g + r = k0 + lane
-    if (qw) half_sum[kw * 64 + lane] = sum;
+    if (qw) part_sum[(qw - 1) * kKeys + kw * 64 + lane] = sum;
     __syncthreads();
-    if (!qw && k0 + lane < L) a.A_cumul[bh * L + k0 + lane] = sum + half_sum[kw * 64 + lane];
+    if (qw || k0 + lane >= L) return;
+    float total = sum;
+#pragma unroll
+    for (int w = 0; w < QW - 1; ++w) total += part_sum[w * kKeys + kw * 64 + lane];
+    a.A_cumul[bh * L + k0 + lane] = total;
 }
 
 int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f16 *Q, const minikv_f16 *K,
@@ -655,8 +662,18 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
         hipLaunchKernelGGL((prefill_fwd_kernel<4, 1, 2, false>), grid, dim3(256), fwd_lds_bytes(1, 2), st, a);
     if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     if (A_cumul) {
-        a.nblk = (int)((L + kKeys - 1) / kKeys);
-        hipLaunchKernelGGL(prefill_colsum_kernel, dim3((unsigned)(heads * a.nblk)), dim3(64 * kColWaves), 0, st, a);
+        // 64 keys per workgroup, its four waves side by side on 128 queries, while the launch lasts as long as its longest walk:
+        // one workgroup per compute unit, or two of few heads, where the second ones walk a short part of the prompt.
+        // Whole call, 128 keys -> 64 keys, us: 8 heads x 160 14.9 -> 14.2, x 777 25.4 -> 23.3, x 2048 45.1 -> 39.9, x 4096 (512
+        // workgroups) 89.6 -> 84.0; 16 x 2048 51.6 -> 49.4, 32 x 512 20.3 -> 19.0; beyond, the second read of Q by twice the
+        // workgroups loses: 32 x 777 (416) the same, 64 x 384 (384) 20.9 -> 21.7, 16 x 3000 83.8 -> 86.7, 32 x 1500 53.5 -> 57.5.  (Eight waves on 256 queries lose to four everywhere: 8 x 384 16.9 -> 19.5, 8 x 2048 39.9 -> 40.7.)
+        if (blocks(64) <= (heads <= 20 ? 2 : 1) * kComputeUnits) {
+            a.nblk = (int)((L + 63) / 64);
+            hipLaunchKernelGGL((prefill_colsum_kernel<1>), dim3((unsigned)(heads * a.nblk)), dim3(64 * kColWaves), 0, st, a);
+        } else {
+            a.nblk = (int)((L + 127) / 128);
+            hipLaunchKernelGGL((prefill_colsum_kernel<2>), dim3((unsigned)(heads * a.nblk)), dim3(64 * kColWaves), 0, st, a);
+        }
         if (hipGetLastError() != hipSuccess) return MINIKV_ELAUNCH;
     }
     return MINIKV_OK;

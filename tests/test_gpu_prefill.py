@@ -160,6 +160,14 @@ def test_one_launch_for_prompts_of_one_row_block(g, L):
     check(g, 2, 6, 2, L, 1500 + L, gain=1.5)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(1, 2, 1, 191), (1, 2, 1, 193), (1, 1, 1, 255), (1, 1, 1, 257), (16, 1, 1, 1025), (20, 1, 1, 1601),
+                                         (20, 1, 1, 1599), (64, 1, 1, 256), (64, 1, 1, 257), (21, 1, 1, 767), (21, 1, 1, 769)])
+def test_column_sums_of_64_keys_per_workgroup(g, B, Hq, Hkv, L):
+    """Either side of the lines between 64 and 128 keys per workgroup, key blocks that begin in the second half of a tile of 128
+    queries, ragged last tiles."""
+    check_last(g, B, Hq, Hkv, L, 1600 + L)
+
+
 @pytest.mark.parametrize("per_tile", [-3.0, 0.02, 0.7, 3.0, 30.0])
 def test_scores_that_rise_or_fall_along_the_keys(g, per_tile):
     """Scores whose level moves by `per_tile` (in powers of e) every 64 keys, so that the running maximum is raised, and the
