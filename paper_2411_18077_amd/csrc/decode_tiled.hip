@@ -139,7 +139,11 @@ __device__ inline int wave_sum_i32(int v) { return __builtin_amdgcn_readlane(wav
 //
 // UNIT: a workgroup of kGroupWaves waves IS one unit; they divide its items, and their partials meet in local memory.
 // What a small launch spends its time on is round trips -- lengths to work line, partial to ticket, ticket to merge --,
-// and this form has one of them, the unit's own two lengths: see launch_stream() for where it is taken.
+// and this form has one of them, the unit's own two lengths: see unit_per_workgroup() for where it is taken.  It has no loop
+// over units (the compiler is told: while it allowed for a second one, half of the instances kept 20 to 80 scalar registers in
+// vector ones), its residual items stand in one place, behind the passes, on waves that have a pass less.  us, before -> now: fused
+// step, 8 heads x 1024 10.5 -> 8.9, 32/8 heads x 512, two residual items 11.5 -> 8.2, 240 units x 1024 13.3 -> 11.2, G = 16 x 2048, 256
+// units 18.9 -> 17.6; behind only without residual tokens on 192 units and more of ragged lengths, by 0.1-0.3 (0.96-0.99 times).
 //
 // STREAM: the code words are loaded with the streaming hint, where a call reads each of them once (one set of heads); without
 // the hint they push each other through the caches, and the read rate is what suffers: see launch_stream() for where and how much.
@@ -249,7 +253,28 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
     // statement, not enclosed, so that the line instances are compiled from unchanged code: other arrangements of the same
     // statements ran up to 3 % slower there.)
     int unit_T = 0, unit_R = 0;
+    const bool early = UNIT && gridDim.x <= 64;
+    KD kd_first = {};
+    VD vd_first = {};
     if constexpr (UNIT) {
+        // Passes go to the waves in turn, so a wave's first one is known before the lengths: its tiles are requested together
+        // with them (what lies past the unit's end inside the buffers is masked as it is in any pass), a round trip less.  On up
+        // to 64 units: what the lengths then leave unused was read for nothing, which many units of a cache allocated long and
+        // filled short would wait for (256 units x 512 of 2688 tokens 7.7 -> 9.9 us, 128 x 512 6.5 -> 7.2).
+        const int tp = wave * kPass;
+        if (early && tp < a.Tcap) {
+            const u4 *kt = reinterpret_cast<const u4 *>(a.Kc + (size_t)file_unit * kc_words(a.Tcap) + (size_t)(tp >> 7) * 1024) + lane;
+            const u4 *vt = reinterpret_cast<const u4 *>(a.Vc + (size_t)file_unit * vc_words(a.Tcap) + (size_t)(tp >> 6) * (4 * kD)) + lane;
+            const size_t vo = ((size_t)file_unit * a.Tcap + tp + 2 * lane) * NCG;
+            const size_t go = (size_t)file_unit * (a.Tcap / G) * kD + (size_t)(tp / G + (lane >> 2) / BGK) * kD + (lane >> 2) % BGK * (NKR * 4);
+#pragma unroll
+            for (int i = 0; i < 4; i++) kd_first.kw[i] = kt[i * 64];
+            kd_first.ks = load_words<NKW>(a.Ks + go), kd_first.kz = load_words<NKW>(a.Kz + go);
+#pragma unroll
+            for (int tl = 0; tl < 2; tl++) vd_first.vw[0][tl] = vt[tl * kD], vd_first.vw[1][tl] = vt[tl * kD + 64];
+            vd_first.vs = load_words<NCG>(a.Vs + vo), vd_first.vz = load_words<NCG>(a.Vz + vo);
+        }
+        asm volatile("" ::: "memory");                     // (the requests stay in front)
         unit_T = clampi(load_const_i32(a.q_len + file_unit), 0, a.Tcap);
         unit_R = res_len(APPEND, a, load_const_i32(a.r_len + file_unit));
         if (files_new && new_row >= 0 && new_row < a.Rcap) *new_dst(file_unit, new_row) = new_piece;
@@ -352,7 +377,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
         // (the lengths of the first unit are already known)
         const UnitItems it = up == up_first ? make_items(APPEND, T_first, R_first) : unit_items(APPEND, a, up);
         const int wt = (it.nr << wr_log) + (it.nq << wq_log);
-        if (wt == 0) continue;
+        if (!UNIT && wt == 0) continue;
         const int ib_next = ib + wt;
         // this wave's items of the unit (the offsets are clamped to the unit's span first, so 32-bit
         // arithmetic suffices): front residual items f0..f1-1, passes j0..j1-1, back residual items b0..b1-1
@@ -360,14 +385,13 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
         const int span = wt + kWR;
         const int ds = min(span, max(0, start - ib)), de = min(span, max(0, end - ib));
         const int dq = nf << wr_log, db = dq + (it.nq << wq_log);
-        // (UNIT: passes from the first wave on, residual items -- even ones in front, odd ones at the back -- from the last)
-        constexpr int NWV = kWaves, HW = NWV / 2;
-        auto share = [](int n, int k, int of) { return (n * k + of - 1) / of; };
-        const int from_last = NWV - 1 - wave, kf = UNIT && !(from_last & 1) ? from_last >> 1 : 0, kb = UNIT && (from_last & 1) ? from_last >> 1 : 0;
-        const int on_f = UNIT && !(from_last & 1), on_b = UNIT && (from_last & 1);
-        const int f0 = UNIT ? share(nf, kf, HW) : min(nf, (ds + kWR - 1) >> wr_log), f1 = UNIT ? (on_f ? share(nf, kf + 1, HW) : 0) : min(nf, (de + kWR - 1) >> wr_log);
-        const int j0 = UNIT ? share(it.nq, wave, NWV) : min(it.nq, (max(0, ds - dq) + kWQ - 1) >> wq_log), j1 = UNIT ? share(it.nq, wave + 1, NWV) : min(it.nq, (max(0, de - dq) + kWQ - 1) >> wq_log);
-        const int b0 = UNIT ? share(nb, kb, HW) : min(nb, (max(0, ds - db) + kWR - 1) >> wr_log), b1 = UNIT ? (on_b ? share(nb, kb + 1, HW) : 0) : min(nb, (max(0, de - db) + kWR - 1) >> wr_log);
+        // UNIT: a wave at the end of the row for each residual item (half of the waves at most), which therefore has no part in
+        // the first round of passes; the later rounds go to all.
+        const int with_res = UNIT ? min(it.nr, kWaves / 2) : 0, np = kWaves - with_res;
+        const int f0 = min(nf, (ds + kWR - 1) >> wr_log), f1 = min(nf, (de + kWR - 1) >> wr_log);
+        const int j0 = UNIT ? (wave < np ? wave : np + wave) : min(it.nq, (max(0, ds - dq) + kWQ - 1) >> wq_log);
+        const int j1 = UNIT ? it.nq : min(it.nq, (max(0, de - dq) + kWQ - 1) >> wq_log);
+        const int b0 = min(nb, (max(0, ds - db) + kWR - 1) >> wr_log), b1 = min(nb, (max(0, de - db) + kWR - 1) >> wr_log);
         if (!UNIT && f0 >= f1 && j0 >= j1 && b0 >= b1) { ib = ib_next; continue; }
         const int u = up >> a.hs_shift, hs = up & (a.hsets - 1);
         const int bi = (int)fast_div((uint32_t)u, a.hkv_magic, a.hkv_shift);
@@ -443,6 +467,8 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
         // bits of the small weights.
         float m[kNH], lsum[kNH];                           // running max; sum of weights (wave-uniform at the end)
         float oa[kNH], ob[kNH];                            // un-normalised output of channels lane, lane+64
+        KD kd = kd_first;
+        VD vd = vd_first;
 #pragma nounroll
         for (int attempt = 0; attempt < 2; attempt++) {
         const bool safe = attempt != 0;
@@ -467,13 +493,14 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
         // The tiles of the first pass are requested before anything else is waited for; without residual items
         // in front the query values go first (they are needed first, and a wait for them then does not wait
         // for the tiles), with residual items they are fetched afterwards (fewer registers live in between).
-        KD kd = {};
-        VD vd = {};
-        const bool front = f0 < f1;
+        const bool front = !UNIT && f0 < f1;               // (UNIT: all residual items after the passes)
         if (!front) load_q();
-        if (j0 < j1) {
-            kd = load_k(j0 * kPass);
-            vd = load_v(j0 * kPass);
+        if (!UNIT || safe || !early || wave >= np) {       // (not requested yet, or another pass)
+            kd = KD{}, vd = VD{};
+            if (j0 < j1) {
+                kd = load_k(j0 * kPass);
+                vd = load_v(j0 * kPass);
+            }
         }
         // the wave's online-softmax state for this unit
         float l_lane[kNH];
@@ -494,10 +521,9 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
         // read back as the B operand, q as the A operand broadcast to all 16 blocks.  Values: lane =
         // channels lane, lane+64, the B operand gathered token by token from the staged rows, the weights
         // p (fp16, through LDS) as the broadcast A operand.  The result is folded into the wave's state.
-        auto residual_items = [&](int lo, int hi, int odd) {   // even items sit before the passes, odd ones after
+        auto residual_items = [&](int first, int end_item, int step) {
 #pragma unroll 1
-        for (int fi = lo; fi < hi; fi++) {
-            const int ri = 2 * fi + odd;
+        for (int ri = first; ri < end_item; ri += step) {
             const int R = it.R;
             _Float16 *pr = lds;                            // [kNH][kPrH] halfs: weights of the item's tokens
             _Float16 *rows = lds + kPrHalfs;               // [64][kKRowH] halfs: key rows, then value rows
@@ -514,11 +540,29 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
             // this launch)
             const int r_new = it.rn;                       // (a full or invalid buffer takes no token)
             const uint16_t *kn = APPEND ? a.k_new + (size_t)u * kD : nullptr, *vn = APPEND ? a.v_new + (size_t)u * kD : nullptr;
-            // (the rows are loaded as in the plain call; the item that holds the new row then loads it once more,
-            // from the caller's array, into the registers of the four-row step it belongs to: one wave-uniform branch
-            // per step instead of a select per row)
+            // (the rows are loaded as in the plain call; the item that holds the new row then loads it once more, from the
+            // caller's array.  UNIT: 16 bytes a lane, put over the row the buffer gave once the rows are in local memory, 12 to 45
+            // registers less.  The work line, whose tiles are in flight meanwhile, has none for it: into the registers of the
+            // four-row step the row belongs to, one wave-uniform branch per step instead of a select per row.)
             const bool has_new = APPEND && r_new >= t0 && r_new < t0 + 64;     // (uniform)
             const int new_step = (r_new - t0) >> 2, new_sub = (r_new - t0) & 3;
+            uint4 fresh = {0u, 0u, 0u, 0u};
+            auto request_new = [&](Words<64> &g, const uint16_t *row) __attribute__((always_inline)) {
+                if (!has_new) return;
+                if (UNIT) {
+                    fresh = reinterpret_cast<const uint4 *>(row)[piece];
+                    return;
+                }
+#pragma unroll
+                for (int i = 0; i < 16; i++)
+                    if (i == new_step && rsub == new_sub) {
+                        const uint4 x = reinterpret_cast<const uint4 *>(row)[piece];
+                        g.v[4 * i] = x.x; g.v[4 * i + 1] = x.y; g.v[4 * i + 2] = x.z; g.v[4 * i + 3] = x.w;
+                    }
+            };
+            auto put_new = [&]() {
+                if (UNIT && has_new && lane_r < 16) *reinterpret_cast<uint4 *>(rows + (r_new - t0) * kKRowH + piece * 8) = fresh;
+            };
             Words<64> g;
 #pragma unroll
             for (int i = 0; i < 16; i++) {
@@ -527,14 +571,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
                 const uint4 x = reinterpret_cast<const uint4 *>(src)[piece];
                 g.v[4 * i] = x.x; g.v[4 * i + 1] = x.y; g.v[4 * i + 2] = x.z; g.v[4 * i + 3] = x.w;
             }
-            if (has_new) {
-#pragma unroll
-                for (int i = 0; i < 16; i++)
-                    if (i == new_step && rsub == new_sub) {
-                        const uint4 x = reinterpret_cast<const uint4 *>(kn)[piece];
-                        g.v[4 * i] = x.x; g.v[4 * i + 1] = x.y; g.v[4 * i + 2] = x.z; g.v[4 * i + 3] = x.w;
-                    }
-            }
+            request_new(g, kn);
             // A operands of the scores: block b supplies k-steps b and b+16 (channels 4b.., 64+4b..) of head `row`
             h4 qa[2];
 #pragma unroll
@@ -548,6 +585,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
             for (int i = 0; i < 16; i++)
                 *reinterpret_cast<uint4 *>(rows + (4 * i + rsub) * kKRowH + piece * 8) =
                     uint4{g.v[4 * i], g.v[4 * i + 1], g.v[4 * i + 2], g.v[4 * i + 3]};
+            put_new();
             // the value rows are requested now and travel while the scores are computed
 #pragma unroll
             for (int i = 0; i < 16; i++) {
@@ -556,14 +594,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
                 const uint4 x = reinterpret_cast<const uint4 *>(src)[piece];
                 g.v[4 * i] = x.x; g.v[4 * i + 1] = x.y; g.v[4 * i + 2] = x.z; g.v[4 * i + 3] = x.w;
             }
-            if (has_new) {
-#pragma unroll
-                for (int i = 0; i < 16; i++)
-                    if (i == new_step && rsub == new_sub) {
-                        const uint4 x = reinterpret_cast<const uint4 *>(vn)[piece];
-                        g.v[4 * i] = x.x; g.v[4 * i + 1] = x.y; g.v[4 * i + 2] = x.z; g.v[4 * i + 3] = x.w;
-                    }
-            }
+            request_new(g, vn);
             __builtin_amdgcn_wave_barrier();
 
             f4 sc = {0.f, 0.f, 0.f, 0.f};                  // scores of token t0 + lane for the 4 heads
@@ -579,6 +610,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
             for (int i = 0; i < 16; i++)
                 *reinterpret_cast<uint4 *>(rows + (4 * i + rsub) * kKRowH + piece * 8) =
                     uint4{g.v[4 * i], g.v[4 * i + 1], g.v[4 * i + 2], g.v[4 * i + 3]};
+            put_new();
 
             // softmax update against the wave's state
             float s[kNH], mn[kNH];
@@ -634,7 +666,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
         }
         };
         if (front) {
-            residual_items(f0, f1, 0);
+            residual_items(2 * f0, 2 * f1, 2);             // (even items sit before the passes, odd ones after)
             load_q();
         }
         {
@@ -838,14 +870,17 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
             // Every piece of a pass's tiles is requested for the next pass right after its last use and is
             // issued on every path (the last pass requests tiles again, nobody uses them: see kOneTile), so the
             // number in flight is always the same.
-            for (int jj = j0; jj < j1; jj++) {
+            for (int jj = j0, next; jj < j1; jj = next) {
+                next = UNIT ? jj + (jj < np ? np : kWaves) : jj + 1;
                 const int tp = jj * kPass;
-                const int t2 = (jj + 1 < j1 ? jj + 1 : jj) * kPass;
-                k_phase(kd, tp, t2, jj + 1 == j1);
-                v_phase(vd, tp, t2, jj + 1 == j1);
+                const bool last = next >= j1;
+                const int t2 = (last ? jj : next) * kPass;
+                k_phase(kd, tp, t2, last);
+                v_phase(vd, tp, t2, last);
             }
         }
-        residual_items(b0, b1, 1);
+        if (UNIT) residual_items(kWaves - 1 - wave, wave >= np ? it.nr : 0, kWaves / 2);
+        else residual_items(2 * b0 + 1, 2 * b1 + 1, 2);
 
         {
             // finish: undo operand scalings, add the zero-point term
@@ -881,6 +916,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
 #pragma unroll
             for (int h = 0; h < NHQ; h++) chk += (O0[h] + O1[h]) + l_lane[h];
             if (__ballot(!(chk - chk == 0.f)) == 0) break;
+            if (UNIT) kd = KD{}, vd = VD{};                // (nothing of the first attempt's tiles lives on)
         }
         }   // attempt
 
@@ -949,6 +985,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
                 }
             }
         }
+        if constexpr (UNIT) break;
         ib = ib_next;
     }
     if constexpr (!UNIT) {

@@ -180,6 +180,32 @@ def test_work_line_of_workgroups(g, variant, G, Hq, Hkv, B, L, Tcap):
         assert not got.reshape(w.units, -1)[1].any()
 
 
+@pytest.mark.parametrize("G", [16, 32, 128])
+@pytest.mark.parametrize("Hq,Hkv,B", [(2, 2, 32), (8, 2, 33), (16, 2, 16), (16, 2, 17)])
+def test_units_shorter_than_their_capacity(g, G, Hq, Hkv, B):
+    """64 units and a few more, the line up to which a wave's first tiles are requested before the lengths are known: 0 to 8 passes in
+    a capacity of 11, 0 to 4 residual items, units without tokens, with residual tokens only and without any of those."""
+    from paper_2411_18077_amd import api
+    from oracle import ref
+    w = tiny(G, B=B, Hq=Hq, Hkv=Hkv, L=1024, keep=None, keep_range=(0.02, 1.0), Rcap=256)
+    inp = W.make_inputs(w, "cuda")
+    inp.n_tok[2::5] = 0
+    s, _ = g.shapes_for(w, 1408 - 256)
+    _, rs = g.shapes_for(w, inp.Tcap)
+    r_len = np.arange(w.units) * 53 % 257 * (np.arange(w.units) % 4 != 2)
+    gc, rc = g.gpu_build_cache(inp, s, r_len=r_len), g.ref_build_cache(inp, rs, r_len=r_len)
+    n = inp.n_tok.tolist()
+    for name, value in (("Ks", float("nan")), ("Kz", float("nan")), ("Vs", float("inf")), ("Vz", float("nan"))):
+        rows = gc.t[name].view(w.units, -1)                # what lies past the lengths may hold anything
+        per = rows.shape[1] // s.Tcap if name[0] == "V" else 0
+        for u in range(w.units):
+            rows[u, (n[u] * per if per else n[u] // G * w.D):] = value
+    out = torch.full((w.B, w.Hq, w.D), float("nan"), dtype=torch.float16, device="cuda")
+    api.minikv_decode_attn(s, inp.q, gc, g.sm_scale(), out)
+    want, _, _ = ref.decode_attn(rc, g.to_np(inp.q), g.sm_scale())
+    assert np.max(np.abs(g.to_np(out).astype(np.float64) - want.astype(np.float64))) <= TOL
+
+
 @pytest.mark.parametrize("variant", VARIANTS)
 def test_peaked_attention_with_outlier_channels(g, variant):
     """Few tokens, the query aligned with one key, x10 outlier channels: the case that stresses 2e-3."""
