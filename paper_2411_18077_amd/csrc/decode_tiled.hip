@@ -173,7 +173,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
     // streaming hint; they then came from memory a second time (190.1 MB read per call on the 16 x 32768 workload, 177.6
     // without the hint).  So every wave of the work line requests the same tile there, the first unit's first: 176.1 MB, 1024
     // units x 4896 98.2 -> 96.5 us, 512 x 4864 53.8 -> 51.9, 128 x 13088, two heads, 35.6 -> 34.7, four 36.6 -> 36.1.
-    constexpr bool kOneTile = !UNIT;
+    constexpr bool kOneTile = !UNIT || STREAM;
 
     __shared__ __attribute__((aligned(16))) _Float16 lds_all[kWaves * kLdsHalfs];
     // A wave's partials of the unit its range begins with and of the one it ends with are entries 2 * pos and 2 * pos + 1
@@ -1185,25 +1185,34 @@ constexpr long kComputeUnits = 256;
 
 // Whether a workgroup per unit serves the call, from the capacities (the lengths are on the device).  It needs a compute
 // unit per unit, and few enough items that the eight waves of a unit (four at G = 16) are done before the work line, which
-// spreads the items over the whole device, has paid for its round trips -- also when the lengths are ragged and the line
-// has the better balance.  Line against unit at the limits, us: 8 units x 10 items 11.5 against 10.9, 13 items 11.2 against
-// 11.5; 128 units x 12 items 13.9 against 13.0, 21 items 16.9 against 15.8, 22 items (a second residual item) 16.9 against
-// 18.8; 160 x 14 at G = 16 19.3 against 17.7; 256 x 22, ragged, 17.1 against 12.6.
-// With a line of single waves, which had the longer chain behind it, lengths at the capacity / ragged (5 .. 100 % of it):
-//   32/8 heads, G = 32:    8 units x 11 items 12.1 / 11.5 against 11.5, 15 items 12.0 against 14.1
-//                         64 units x 11 items 13.3 against 12.0 / 16.3 against 11.8, 15 items 13.5 against 14.9
-//                        128 units x 19 items 19.9 against 15.2, 27 items 17.9 against 17.9, 35 items 19.6 against 20.8
-//                        256 units x 11 items 17.6 against 13.5 / 21.6 against 12.8, 27 items 25.9 against 21.4 / 22.1
-//                            against 18.7, 50 items 40.2 against 34.8 / 27.8 against 28.4
-//   32/8 heads, G = 16:   16 units x 11 items 13.9 against 14.6; 128 units x 19 items 24.6 against 20.0, 27 items 22.7
-//                            against 24.2; 256 units x 19 items 28.8 against 21.2
-static bool unit_per_workgroup(const DecArgs &a, int G)
+// spreads the items over the whole device and balances ragged lengths, has paid for its round trips.  More items where the line
+// cannot give a unit two workgroups (beyond 128 units), where a pass is short (G = 128), where one wave has a SIMD for itself (G =
+// 16) fewer.  Time of the line over that of the unit form, fused step, one / four heads per KV head, all lengths alike -- ragged
+// (5 .. 100 % of the capacity), at the limit and behind it:
+//   units     G    at                                   behind
+//   8 .. 48   32   14 items 1.14-1.20 / 1.05-1.11 -- 1.3   18 items 1.06 / 0.94-1.02 -- 1.03-1.20, 22 items 0.92 / 0.81
+//             64   18 items 1.14 / 1.04 -- 1.12-1.32       22 items 1.01-1.12 / 0.91-1.05 -- 1.03-1.23
+//             128  18 items 1.20 / 1.10 -- 1.25-1.54       22 items 1.09-1.22 / 0.98-1.12 -- 1.11-1.39
+//             16   8 items 1.22 / 1.13 -- 1.19-1.39        11 items 1.10 / 0.94 -- 0.98-1.19
+//   96, 128   64   26 items 1.13 / 1.04-1.11 -- 1.02-1.13  30 items 1.07 / 0.95-1.08 -- 0.94-1.24   (G = 32 26 items 0.92-1.08)
+//             128  30 items 1.09 / 0.99-1.11 -- 1.07-1.33  (G = 16 22 items 1.03 / 0.91 -- 1.08-1.19)
+//   136, 160  32   42 items 1.14 / 1.03-1.07 -- 1.00-1.10  52 items 1.05 / 0.97-1.06 -- 0.93-1.05
+//             128  42 items 1.21 / 1.07-1.12 -- 1.10-1.24  66 items 1.11 / 1.00 -- 0.91-0.99        (G = 16 30 items 1.09, 35 0.92-1.00)
+//   200 .. 256 32  52 items 1.01-1.18 / 1.06-1.09 -- 1.03-1.16   66 items 0.94-1.08 / 0.93-1.03 -- 0.96-1.03
+//             128  66 items 1.09-1.31 / 1.05-1.23 -- 1.02-1.15   86 items 1.04-1.15 -- 0.95-1.10
+//             16   35 items 1.09-1.20 / 1.06-1.15 -- 0.99-1.15   42 items 0.98-1.16 / 0.96-1.04 -- 0.95-1.14
+// (Above 88 MiB of packed cache these were with the line's streaming hint and without one on the unit form, which now has it as
+// well.)  With two sets of heads, 136 to 208 units of ragged lengths, 40 items: 0.91-0.98.
+static bool unit_per_workgroup(const DecArgs &a, int G, bool paired)
 {
     const long units = (long)a.units * a.hsets;
     const int items = (a.Tcap + kPass - 1) / kPass + (a.Rcap + 63) / 64;
     if (units > kComputeUnits) return false;
-    if (G == 16) return items <= (units >= 96 ? 20 : units >= 32 ? 12 : 0);
-    return items <= (units >= 192 ? 28 : units >= 96 ? 24 : 12);
+    if (G == 16) return items <= (units > 192 ? 35 : units >= 96 ? 20 : units >= 32 ? 12 : paired ? 11 : 8);
+    if (units > 192) return items <= (G == 128 ? 66 : 52);
+    if (units > 128) return items <= 42;
+    if (units >= 96) return items <= (G == 128 ? 30 : G == 64 ? 26 : 24);
+    return items <= (G == 128 ? 20 : G == 64 || paired ? 18 : 14);
 }
 
 static std::atomic<int> g_decode_weights{0};
@@ -1219,7 +1228,6 @@ static int launch_stream(DecArgs a, hipStream_t st)
 {
     const long cap_items = (long)a.units * a.hsets * ((a.Tcap + kPass - 1) / kPass + (a.Rcap + 63) / 64);
     const int mode = g_decode_weights.load();
-    if (mode == 0 && unit_per_workgroup(a, G)) return launch_form<G, LO, PAIRED, APPEND, true, false>(a, (long)a.units * a.hsets, st);
     // Weight of a residual item against a pass: 8 : 2 where every wave has several items (1344 items, G = 128, 11.7 us against
     // 12.5 with 4 : 2; 512 units x 12 items 22.5 against 23.3).  4 : 2 where the ranges would be too few for the compute units (64
     // units x 8 items 13.8 -> 11.8; 8 units x 42, G = 16, 17.9 -> 15.1), and where a wave has one or two items, so that one
@@ -1252,9 +1260,10 @@ static int launch_stream(DecArgs a, hipStream_t st)
     // more than that (a branch at each pair of loads: 65 MB 21.7 -> 24.2 us; a second copy of the pass loop does not fit the
     // registers).
     constexpr long kStreamBytes = 88L << 20;
-    const long packed = (long)a.units * a.Tcap * (64 + 8 * kD / G);
-    return packed > kStreamBytes && a.hsets == 1 ? launch_form<G, LO, PAIRED, APPEND, false, true>(a, groups, st)
-                                                 : launch_form<G, LO, PAIRED, APPEND, false, false>(a, groups, st);
+    const bool streams = (long)a.units * a.Tcap * (64 + 8 * kD / G) > kStreamBytes && a.hsets == 1;
+    if (mode == 0 && unit_per_workgroup(a, G, PAIRED))
+        return streams ? launch_form<G, LO, PAIRED, APPEND, true, true>(a, units, st) : launch_form<G, LO, PAIRED, APPEND, true, false>(a, units, st);
+    return streams ? launch_form<G, LO, PAIRED, APPEND, false, true>(a, groups, st) : launch_form<G, LO, PAIRED, APPEND, false, false>(a, groups, st);
 }
 
 template <bool LO, bool PAIRED>
