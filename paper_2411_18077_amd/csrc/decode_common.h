@@ -13,7 +13,7 @@ struct DecArgs {
     uint16_t *out;               // [B][Hq][D] fp16
     float *ws;                   // split-K partials (layout depends on the variant)
     int *cnt;                    // per-unit ticket counters of the single-launch kernel (zero between calls)
-    int *cnt1;                   // ticket counters of the sub-groups, indexed by the sub-group's first slot
+    int *cnt1;                   // ticket counters of the sets of workgroups that merge, indexed by the set's first slot
     int *redo;                   // counts (wave, unit) pairs redone with range-normalised operands (diagnostics)
     int by_die;                  // the work line is dealt to the dies in contiguous eighths
     int wq_log, wr_log;          // weight of a quantized pass and of a residual item on the work line (log2)
