@@ -564,12 +564,19 @@ static int pt_ws_chunks(const minikv_pt_shape &s)
 // launch -- the two per compute unit that the registers allow, so that all run at once and each sets up its query operands
 // once (1024: 49.7 instead of 44.7 us on 128 units x 13088 tokens, 38 instead of 32 on 16 x 65536) -- and never more
 // chunks than the workspace holds (a unit's share of 1024 workgroups).
+// One chunk a unit, and with it no merge launch, where splitting saves less than that costs: up to 512 tokens (at 2 bits one round
+// of the four waves' blocks: 24 units 10.4 -> 8.3 us, 192 units 12.3 -> 8.1, 1024 tokens 10.4 against 12.6; at 4 bits two, G = 128
+// 7.9 -> 7.3, but G = 32 8.5 against 8.6 and with 8 units 8.0 against 8.3; at 8 bits four, 9.2 against 9.6), and up to 1536 on
+// more than 170 units, which could have two (192 units, G = 32, 1024 tokens: 2 bits 15.0 -> 13.6, 4 bits 15.9 -> 14.5, 8 bits 18.8 ->
+// 15.9; 1536 tokens 21.2 -> 18.2, 20.2 -> 19.1, 21.8 -> 21.4; 2048 21.4 against 22.5, 23.5 against 23.6, 26.5 against 27.2).
 constexpr int kPtTargetWgs = 512;
 static int pt_chunk(const minikv_pt_shape &s)
 {
     const long units = (long)s.B * s.Hkv;
     const long most = kPtTargetWgs / units > 1 ? kPtTargetWgs / units : 1;
     const long blocks = ((long)s.Tcap + kPtMinChunk - 1) / kPtMinChunk;
+    const int whole = most <= 2 ? 1536 : s.bits == 2 || (s.bits == 4 && s.G == kD) ? 512 : 0;     // most tokens in one chunk
+    if (s.Tcap <= whole) return (int)blocks * kPtMinChunk;
     return (int)((blocks + most - 1) / most) * kPtMinChunk;
 }
 

@@ -137,6 +137,26 @@ def test_caches_of_large_capacity(bits, G, rep):
     assert np.max(np.abs(out.float().cpu().numpy() - want.astype(np.float32))) <= TOL
 
 
+@pytest.mark.parametrize("bits,G", [(2, 32), (4, 32), (4, 128), (8, 64)])
+@pytest.mark.parametrize("units,Tcap", [(3, 512), (3, 576), (170, 1536), (171, 1536), (171, 1600)])
+def test_either_side_of_one_chunk_a_unit(units, Tcap, bits, G):
+    """512 tokens of few units and 1536 of more than 170: one chunk a unit and no merge, or several; the workspace poisoned."""
+    from oracle import ref
+    from paper_2411_18077_amd import api
+    w, inp = _inputs(1, 2 * units, units, Tcap, seed=900 + Tcap + bits + G, keep=1.0, ragged=True)
+    inp.n_tok[1], inp.n_tok[2] = 0, 16
+    s, gc, rc = _both_caches(api, ref, w, inp, G, bits, Tcap=Tcap)
+    gc.workspace.fill_(0xFF)
+    out = torch.full((1, 2 * units, 128), float("nan"), dtype=torch.float16, device="cuda")
+    sm = 1.0 / math.sqrt(128)
+    api.minikv_decode_attn_pt(s, inp.q, gc, sm, out)
+    torch.cuda.synchronize()
+    want, _ = ref.decode_attn_pt(rc, inp.q.cpu().numpy(), sm)
+    got = out.float().cpu().numpy()
+    # one fp16 step of a result above 2 is more than the bar (16 tokens give such results)
+    assert np.all(np.abs(got - want.astype(np.float32)) <= np.maximum(TOL, np.abs(want) * 2.0 ** -10))
+
+
 @pytest.mark.parametrize("bits,G", [(2, 32), (8, 32), (2, 128), (8, 64)])
 @pytest.mark.parametrize("rep", [2, 8])
 def test_two_and_eight_heads_per_kv_head(rep, bits, G):
