@@ -173,7 +173,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
     // streaming hint; they then came from memory a second time (190.1 MB read per call on the 16 x 32768 workload, 177.6
     // without the hint).  So every wave of the work line requests the same tile there, the first unit's first: 176.1 MB, 1024
     // units x 4896 98.2 -> 96.5 us, 512 x 4864 53.8 -> 51.9, 128 x 13088, two heads, 35.6 -> 34.7, four 36.6 -> 36.1.
-    constexpr bool kOneTile = !UNIT || STREAM;
+    constexpr bool kOneTile = !UNIT || (STREAM && !(FUSED && !PAIRED && G == 32));   // (that instance has no register left)
 
     __shared__ __attribute__((aligned(16))) _Float16 lds_all[kWaves * kLdsHalfs];
     // A wave's partials of the unit its range begins with and of the one it ends with are entries 2 * pos and 2 * pos + 1

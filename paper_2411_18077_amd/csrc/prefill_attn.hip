@@ -488,9 +488,11 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void prefill_colsum_kernel(Prefi
     auto request = [&](int n) -> float {               // returns the LSE of query lse0 + lane of the tile
         const unsigned tile = (unsigned)min(n, ntiles - 1) * (kTile * 256u);
         const unsigned end = n < ntiles ? (unsigned)(L - 1) * 256u + 240u : 0u;
+        unsigned off = q_off;
+        if (KW == 1) asm volatile("" : "+v"(off));     // (opaque: its four forms are not kept over the loop, which has no register for them)
 #pragma unroll
         for (int i = 0; i < kLoads; ++i)
-            load_to_lds(Qh, min((q_off ^ ((i & 3) << 6)) + i * 1024u + tile, end), q_lds + (n & 1) * (kTile * 256u) + i * 1024u);
+            load_to_lds(Qh, min((off ^ ((i & 3) << 6)) + i * 1024u + tile, end), q_lds + (n & 1) * (kTile * 256u) + i * 1024u);
         return lseh[min((n * kTile + lse0) + lane, L - 1)];  // (some waves the same 64: no branch in the stream)
     };
     float lr = 0.0f;
