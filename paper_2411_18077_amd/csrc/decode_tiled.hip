@@ -142,8 +142,11 @@ __device__ inline int wave_sum_i32(int v) { return __builtin_amdgcn_readlane(wav
 // and this form has one of them, the unit's own two lengths: see unit_per_workgroup() for where it is taken.  It has no loop
 // over units (the compiler is told: while it allowed for a second one, half of the instances kept 20 to 80 scalar registers in
 // vector ones), its residual items stand in one place, behind the passes, on waves that have a pass less.  us, before -> now: fused
-// step, 8 heads x 1024 10.5 -> 8.9, 32/8 heads x 512, two residual items 11.5 -> 8.2, 240 units x 1024 13.3 -> 11.2, G = 16 x 2048, 256
-// units 18.9 -> 17.6; behind only without residual tokens on 192 units and more of ragged lengths, by 0.1-0.3 (0.96-0.99 times).
+// step, 8 heads x 1024 10.7 -> 8.0, 32/8 heads x 512, two residual items 11.5 -> 7.6, 240 units x 1024 13.6 -> 10.8, attention, G = 16 x
+// 2048, 256 units 16.4 -> 15.7, with two residual items 19.2 -> 17.7.  Requesting a wave's first tiles together with the lengths, a
+// round trip less, was tried on up to 64 units and lost: the tiles' registers were then written on two paths, and every instance
+// paid for it, also where the branch was not taken (8 heads x 1024 8.0 -> 8.7, 216 units x 896 5.7 -> 6.1, 1.05 times in the
+// geometric mean over 880 shapes; only 64 units x 12 passes, four heads, gained, 10.2 -> 9.7).
 //
 // STREAM: the code words are loaded with the streaming hint, where a call reads each of them once (one set of heads); without
 // the hint they push each other through the caches, and the read rate is what suffers: see launch_stream() for where and how much.
@@ -253,28 +256,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
     // statement, not enclosed, so that the line instances are compiled from unchanged code: other arrangements of the same
     // statements ran up to 3 % slower there.)
     int unit_T = 0, unit_R = 0;
-    const bool early = UNIT && gridDim.x <= 64;
-    KD kd_first = {};
-    VD vd_first = {};
     if constexpr (UNIT) {
-        // Passes go to the waves in turn, so a wave's first one is known before the lengths: its tiles are requested together
-        // with them (what lies past the unit's end inside the buffers is masked as it is in any pass), a round trip less.  On up
-        // to 64 units: what the lengths then leave unused was read for nothing, which many units of a cache allocated long and
-        // filled short would wait for (256 units x 512 of 2688 tokens 7.7 -> 9.9 us, 128 x 512 6.5 -> 7.2).
-        const int tp = wave * kPass;
-        if (early && tp < a.Tcap) {
-            const u4 *kt = reinterpret_cast<const u4 *>(a.Kc + (size_t)file_unit * kc_words(a.Tcap) + (size_t)(tp >> 7) * 1024) + lane;
-            const u4 *vt = reinterpret_cast<const u4 *>(a.Vc + (size_t)file_unit * vc_words(a.Tcap) + (size_t)(tp >> 6) * (4 * kD)) + lane;
-            const size_t vo = ((size_t)file_unit * a.Tcap + tp + 2 * lane) * NCG;
-            const size_t go = (size_t)file_unit * (a.Tcap / G) * kD + (size_t)(tp / G + (lane >> 2) / BGK) * kD + (lane >> 2) % BGK * (NKR * 4);
-#pragma unroll
-            for (int i = 0; i < 4; i++) kd_first.kw[i] = kt[i * 64];
-            kd_first.ks = load_words<NKW>(a.Ks + go), kd_first.kz = load_words<NKW>(a.Kz + go);
-#pragma unroll
-            for (int tl = 0; tl < 2; tl++) vd_first.vw[0][tl] = vt[tl * kD], vd_first.vw[1][tl] = vt[tl * kD + 64];
-            vd_first.vs = load_words<NCG>(a.Vs + vo), vd_first.vz = load_words<NCG>(a.Vz + vo);
-        }
-        asm volatile("" ::: "memory");                     // (the requests stay in front)
         unit_T = clampi(load_const_i32(a.q_len + file_unit), 0, a.Tcap);
         unit_R = res_len(APPEND, a, load_const_i32(a.r_len + file_unit));
         if (files_new && new_row >= 0 && new_row < a.Rcap) *new_dst(file_unit, new_row) = new_piece;
@@ -467,8 +449,6 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
         // bits of the small weights.
         float m[kNH], lsum[kNH];                           // running max; sum of weights (wave-uniform at the end)
         float oa[kNH], ob[kNH];                            // un-normalised output of channels lane, lane+64
-        KD kd = kd_first;
-        VD vd = vd_first;
 #pragma nounroll
         for (int attempt = 0; attempt < 2; attempt++) {
         const bool safe = attempt != 0;
@@ -494,13 +474,12 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
         // in front the query values go first (they are needed first, and a wait for them then does not wait
         // for the tiles), with residual items they are fetched afterwards (fewer registers live in between).
         const bool front = !UNIT && f0 < f1;               // (UNIT: all residual items after the passes)
+        KD kd = {};
+        VD vd = {};
         if (!front) load_q();
-        if (!UNIT || safe || !early || wave >= np) {       // (not requested yet, or another pass)
-            kd = KD{}, vd = VD{};
-            if (j0 < j1) {
-                kd = load_k(j0 * kPass);
-                vd = load_v(j0 * kPass);
-            }
+        if (j0 < j1) {
+            kd = load_k(j0 * kPass);
+            vd = load_v(j0 * kPass);
         }
         // the wave's online-softmax state for this unit
         float l_lane[kNH];
@@ -916,7 +895,6 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
 #pragma unroll
             for (int h = 0; h < NHQ; h++) chk += (O0[h] + O1[h]) + l_lane[h];
             if (__ballot(!(chk - chk == 0.f)) == 0) break;
-            if (UNIT) kd = KD{}, vd = VD{};                // (nothing of the first attempt's tiles lives on)
         }
         }   // attempt
 

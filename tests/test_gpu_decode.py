@@ -183,8 +183,8 @@ def test_work_line_of_workgroups(g, variant, G, Hq, Hkv, B, L, Tcap):
 @pytest.mark.parametrize("G", [16, 32, 128])
 @pytest.mark.parametrize("Hq,Hkv,B", [(2, 2, 32), (8, 2, 33), (16, 2, 16), (16, 2, 17)])
 def test_units_shorter_than_their_capacity(g, G, Hq, Hkv, B):
-    """64 units and a few more, the line up to which a wave's first tiles are requested before the lengths are known: 0 to 8 passes in
-    a capacity of 11, 0 to 4 residual items, units without tokens, with residual tokens only and without any of those."""
+    """Around 64 units whose cache holds anything past their lengths: 0 to 8 passes in a capacity of 9, 0 to 4 residual items, units
+    without tokens, with residual tokens only and without any of those."""
     from paper_2411_18077_amd import api
     from oracle import ref
     w = tiny(G, B=B, Hq=Hq, Hkv=Hkv, L=1024, keep=None, keep_range=(0.02, 1.0), Rcap=256)
