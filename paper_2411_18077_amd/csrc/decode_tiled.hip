@@ -1165,30 +1165,39 @@ constexpr long kComputeUnits = 256;
 // unit per unit, and few enough items that the eight waves of a unit (four at G = 16) are done before the work line, which
 // spreads the items over the whole device and balances ragged lengths, has paid for its round trips.  More items where the line
 // cannot give a unit two workgroups (beyond 128 units), where a pass is short (G = 128), where one wave has a SIMD for itself (G =
-// 16) fewer.  Time of the line over that of the unit form, fused step, one / four heads per KV head, all lengths alike -- ragged
-// (5 .. 100 % of the capacity), at the limit and behind it:
-//   units     G    at                                   behind
-//   8 .. 48   32   14 items 1.14-1.20 / 1.05-1.11 -- 1.3   18 items 1.06 / 0.94-1.02 -- 1.03-1.20, 22 items 0.92 / 0.81
-//             64   18 items 1.14 / 1.04 -- 1.12-1.32       22 items 1.01-1.12 / 0.91-1.05 -- 1.03-1.23
-//             128  18 items 1.20 / 1.10 -- 1.25-1.54       22 items 1.09-1.22 / 0.98-1.12 -- 1.11-1.39
-//             16   8 items 1.22 / 1.13 -- 1.19-1.39        11 items 1.10 / 0.94 -- 0.98-1.19
-//   96, 128   64   26 items 1.13 / 1.04-1.11 -- 1.02-1.13  30 items 1.07 / 0.95-1.08 -- 0.94-1.24   (G = 32 26 items 0.92-1.08)
-//             128  30 items 1.09 / 0.99-1.11 -- 1.07-1.33  (G = 16 22 items 1.03 / 0.91 -- 1.08-1.19)
-//   136, 160  32   42 items 1.14 / 1.03-1.07 -- 1.00-1.10  52 items 1.05 / 0.97-1.06 -- 0.93-1.05
-//             128  42 items 1.21 / 1.07-1.12 -- 1.10-1.24  66 items 1.11 / 1.00 -- 0.91-0.99        (G = 16 30 items 1.09, 35 0.92-1.00)
-//   200 .. 256 32  52 items 1.01-1.18 / 1.06-1.09 -- 1.03-1.16   66 items 0.94-1.08 / 0.93-1.03 -- 0.96-1.03
-//             128  66 items 1.09-1.31 / 1.05-1.23 -- 1.02-1.15   86 items 1.04-1.15 -- 0.95-1.10
-//             16   35 items 1.09-1.20 / 1.06-1.15 -- 0.99-1.15   42 items 0.98-1.16 / 0.96-1.04 -- 0.95-1.14
-// (Above 88 MiB of packed cache these were with the line's streaming hint and without one on the unit form, which now has it as
-// well.)  With two sets of heads, 136 to 208 units of ragged lengths, 40 items: 0.91-0.98.
+// 16) fewer.  Time of the line over that of the unit form, mean (least) of attention and fused steps, one and two heads / three
+// to eight heads per KV head, all lengths alike -- ragged (5 .. 100 % of the capacity):
+//   units       G    at the limit                                               behind it
+//   8 .. 48     16   10 items 1.20 (1.14) / 1.06 (0.97) -- 1.19 (1.08) / 1.04 (0.94)  12 items 1.10 / 0.98 -- 1.10 / 0.99
+//               32   14 items / 1.11 (1.07) -- / 1.11 (1.04)                    18 items 1.12 / 0.98 -- 1.15 / 0.98 (0.90)
+//               64   18 items 1.21 (1.12) / 1.09 (1.05) -- 1.22 (1.14) / 1.09 (1.00)
+//               128  20 items 1.17 (1.10) / 1.12 (1.03) -- 1.28 (1.19) / 1.20 (1.10)
+//   96 .. 128   16   20 items 1.15 (1.10) / 1.06 (0.99) -- 1.14 (0.97) / 1.04 (0.89)
+//               32   22 items 1.26 (1.19) / 1.11 (1.04) -- 1.11 (1.05) / 0.98 (0.92)  26 items 1.18 / 1.06 -- 1.09 / 0.96 (0.86)
+//               64   26 items 1.21 (1.20) / 1.10 (1.04) -- 1.10 (0.99) / 1.00 (0.88)
+//               128  30 items 1.23 (1.17) / 1.11 (0.98) -- 1.11 (0.96) / 1.02 (0.88)
+//   136 .. 192  16   26 items 1.21 (1.13) / 1.13 (1.06) -- 1.12 (0.98) / 1.02 (0.89)      28 items 1.19 / 1.13 -- 1.08 / 1.00
+//                    two sets of heads: 20 items 1.19 (1.09) -- 1.10 (0.94)      24 items 1.17 (1.14) -- 1.04 (0.91)
+//   193 .. 224  16   35 items 1.18 (1.11) -- 1.00 (0.90), four heads and more;  225 .. 256  1.11 (1.08) -- 1.09 (1.00)
+//   225 .. 256  32   52 items 1.13 (1.10) / 1.09 (0.99) -- 1.08 (1.03) / 1.03 (0.98)   56 items 1.13 / 1.09 -- 1.06 / 1.00 (0.96)
+//               128  60 items 1.18 (1.18) / 1.16 (1.12) -- 1.08 (1.03) / 1.02 (0.96)   66 items 1.12 / 1.07 -- 1.05 / 0.99 (0.94)
+// Beyond 128 units the longest unit's compute unit decides, and with three heads and more the line wins back on ragged lengths the
+// sooner the fewer units there are, hence units / 5; sooner with two sets of heads, whose words the line reads once (by_die).
+// Three to eight heads, all lengths alike -- ragged, G = 32 / 64:
+//   136 .. 159 units x 34 items 1.13 (1.12) / 1.18 (1.17) -- 1.04 (0.92) / 1.07 (0.94)   x 38 1.09 (1.07) -- 0.98 (0.89), G = 32
+//                    x 42 items 1.09 (1.07) / 1.13 (1.11) -- 0.95 (0.89) / 0.98 (0.90)
+//   160 .. 192 units x 38 items 1.17 (1.12) / 1.22 (1.15) -- 1.04 (0.93) / 1.07 (0.95)   x 42 1.14 (1.08) -- 1.00 (0.91), G = 32
+//   193 .. 224 units x 44 items 1.19 (1.15) / 1.24 (1.20) -- 1.03 (0.97) / 1.05 (0.97)   x 52 1.12 (1.10) -- 0.97 (0.91), G = 32
 static bool unit_per_workgroup(const DecArgs &a, int G, bool paired)
 {
     const long units = (long)a.units * a.hsets;
-    const int items = (a.Tcap + kPass - 1) / kPass + (a.Rcap + 63) / 64;
+    const long items = ((long)a.Tcap + kPass - 1) / kPass + ((long)a.Rcap + 63) / 64;
     if (units > kComputeUnits) return false;
-    if (G == 16) return items <= (units > 192 ? 35 : units >= 96 ? 20 : units >= 32 ? 12 : paired ? 11 : 8);
-    if (units > 192) return items <= (G == 128 ? 66 : 52);
-    if (units > 128) return items <= 42;
+    if (G == 16) return items <= (units > 192 ? 35 : units > 128 && a.hsets == 1 ? 26 : units >= 96 ? 20 : units >= 32 ? 12 : paired ? 11 : 10);
+    if (units > 128) {
+        const long most = units <= 192 ? 42 : G == 128 ? 66 : 52;
+        return items <= most && (paired || items <= units / 5 + (G == 128 ? 12 : G == 64 ? 8 : 4) + (a.hsets > 1 ? 0 : G == 128 ? 66 : 4));
+    }
     if (units >= 96) return items <= (G == 128 ? 30 : G == 64 ? 26 : 24);
     return items <= (G == 128 ? 20 : G == 64 || paired ? 18 : 14);
 }

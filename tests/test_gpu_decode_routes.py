@@ -1,0 +1,84 @@
+"""The forms of the decode kernel -- a workgroup per unit, or the work line -- by the calls that each is chosen for, seen by
+whether partials went through the workspace (a workgroup per unit leaves it as it was): attention against the oracle, the fused
+step against append + attend, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2411_18077_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-3
+
+
+@pytest.fixture(scope="module")
+def g():
+    import gpu_common
+    assert torch.cuda.is_available()
+    return gpu_common
+
+
+def bar(want):
+    """2e-3, or one fp16 step of a larger result (two correctly rounded results of nearly equal sums)."""
+    return np.maximum(TOL, 2.0 ** (np.floor(np.log2(np.maximum(np.abs(want), 2.0 ** -14))) - 10))
+
+
+def cache_and_oracle(g, w, Tcap, r_len, lengths=None):
+    """The cache of capacity Tcap, and the oracle's answer for it."""
+    from oracle import ref
+    inp = W.make_inputs(w, "cuda")
+    if lengths is not None:
+        inp.n_tok.copy_(torch.minimum(inp.n_tok.cpu(), torch.as_tensor(lengths, dtype=torch.int32)))
+    s, _ = g.shapes_for(w, Tcap)
+    _, rs = g.shapes_for(w, inp.Tcap)
+    cache, rc = g.gpu_build_cache(inp, s, r_len=r_len), g.ref_build_cache(inp, rs, r_len=r_len)
+    want, _, _ = ref.decode_attn(rc, g.to_np(inp.q), g.sm_scale())
+    return inp, s, cache, want.astype(np.float64)
+
+
+def attend(g, w, inp, s, cache, want):
+    """Attention on a zeroed workspace; returns whether it took the work line."""
+    from paper_2411_18077_amd import api
+    assert not cache.workspace.any()
+    out = torch.full((w.B, w.Hq, w.D), float("nan"), dtype=torch.float16, device="cuda")
+    api.minikv_decode_attn(s, inp.q, cache, g.sm_scale(), out)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(g.to_np(out).astype(np.float64) - want) <= bar(want))
+    return bool(cache.workspace.any())
+
+
+def step(g, w, inp, s, cache):
+    """The fused step, then append + attend on the same cache: the same bits and the same lengths."""
+    from paper_2411_18077_amd import api
+    k_new, v_new = inp.Rk[:, -1].contiguous(), inp.Rv[:, 0].contiguous()
+    one = torch.full((w.B, w.Hq, w.D), float("nan"), dtype=torch.float16, device="cuda")
+    two, r_next = torch.full_like(one, float("nan")), torch.full((w.units,), -1, dtype=torch.int32, device="cuda")
+    api.minikv_decode_step(s, inp.q, k_new, v_new, cache, r_next, g.sm_scale(), one)
+    api.kv_append_residual(s, k_new, v_new, cache)
+    api.minikv_decode_attn(s, inp.q, cache, g.sm_scale(), two)
+    torch.cuda.synchronize()
+    assert torch.equal(one.view(torch.int16), two.view(torch.int16)) and torch.equal(r_next, cache.r_len)
+    assert torch.isfinite(one).all()
+
+
+@pytest.mark.parametrize("behind", [0, 1])
+@pytest.mark.parametrize("G,rep,units,items", [
+    (32, 8, 144, 32), (32, 4, 144, 36), (32, 2, 144, 42), (32, 4, 256, 52), (64, 8, 176, 42), (64, 3, 136, 39), (64, 1, 200, 52),
+    (128, 4, 208, 66), (128, 8, 208, 53), (128, 1, 132, 42), (32, 4, 96, 24), (64, 2, 128, 26), (128, 4, 100, 30),
+    (16, 4, 24, 10), (16, 2, 24, 11), (16, 1, 64, 12), (16, 4, 120, 20), (16, 4, 136, 26), (16, 8, 192, 20), (16, 1, 196, 35),
+])
+def test_either_side_of_a_workgroup_per_unit(g, G, rep, units, items, behind):
+    """Capacities at each limit and an item behind it: a workgroup per unit, then the work line.  Units of all lengths up to the
+    capacity, one of them without any token, 0 to 2 residual items."""
+    kv = units // (2 if rep > 4 else 1)                    # (five heads and more are two units)
+    Tcap = (items + behind - 2) * 128
+    w = W.Workload(name="t", B=kv // 4, Hq=4 * rep, Hkv=4, L=Tcap, keep=None, keep_range=(0.02, 1.0), G=G, Rcap=128, seed=2000 + items,
+                   n_outlier=3, outlier_scale=8.0)
+    r_len = np.arange(kv) * 37 % 129
+    r_len[1] = 0
+    lengths = np.full(kv, Tcap)
+    lengths[1] = 0
+    inp, s, cache, want = cache_and_oracle(g, w, Tcap, r_len, lengths)
+    assert attend(g, w, inp, s, cache, want) == bool(behind)
+    cache.r_len.clamp_(max=127)                            # (there is room for the token)
+    step(g, w, inp, s, cache)
