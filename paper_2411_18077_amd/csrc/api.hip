@@ -115,9 +115,9 @@ size_t minikv_workspace_bytes(const minikv_shape *s)
     // cross-check kernel: one partial per (query row, chunk) for the smallest chunk, plus the residual chunk
     const size_t nch = (size_t)(s->Tcap + kMinChunk - 1) / kMinChunk + 1;
     const size_t scalar = (size_t)s->B * s->Hq * nch * kPartialStride * sizeof(float);
-    // single-launch kernel: one slot of 4 heads per (wave, unit it serves): slot = wave + 2 * unit
+    // single-launch kernel: one slot of 4 heads per (workgroup, unit it shares with others): slot = workgroup + 2 * unit
     const size_t nu = ws_units(*s);
-    const size_t stream = ((size_t)kMaxStreamWaves + 2 * nu) * 4 * kPartialStride * sizeof(float);
+    const size_t stream = ((size_t)kWorkspaceSlots + 2 * nu) * 4 * kPartialStride * sizeof(float);
     return ws_counter_bytes(*s) + (scalar > stream ? scalar : stream);
 }
 
@@ -250,7 +250,7 @@ int minikv_stream_read_probe(const void *src, size_t bytes, uint32_t *sums, void
 int minikv_diag_redo_count(const minikv_shape *s, const void *workspace, int32_t *count)
 {
     if (validate_shape(s) != MINIKV_OK || !workspace || !count) return MINIKV_EINVAL;
-    const int *p = reinterpret_cast<const int *>(workspace) + 3 * ws_units(*s) + kMaxStreamWaves;
+    const int *p = reinterpret_cast<const int *>(workspace) + 3 * ws_units(*s) + kWorkspaceSlots;
     return hipMemcpy(count, p, sizeof(int32_t), hipMemcpyDeviceToHost) == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
 

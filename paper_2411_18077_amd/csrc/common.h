@@ -14,11 +14,16 @@ constexpr int kVTile = 64;         // tokens per V code tile (4*D words)
 constexpr int kPartialStride = 132;  // floats per split-K partial: m, l, 2 pad, o[128]
 constexpr int kMinChunk = 512;     // smallest token chunk one workgroup of the decode kernel takes
 constexpr int kMaxRep = 8;         // most query heads per KV head
-constexpr int kMaxStreamWaves = 4096;  // partial slots of the decode workspace beside two a unit (its work line uses one a workgroup)
+constexpr long kComputeUnits = 256;  // of the device
+// Partial slots of the decode workspace beside two a unit.  The work line uses one a workgroup, kComputeUnits of them at most;
+// the size that callers were told stays, and with it the place of the partials: where shapes take turns on one workspace, those
+// of a small one begin behind the counters that a larger one uses (up to 1280 units).
+constexpr int kWorkspaceSlots = 4096;
+static_assert(kComputeUnits <= kWorkspaceSlots, "a slot per workgroup of the work line");
 
 // Workspace layout of the single-launch decode kernel: ticket counters (zero between calls) -- one per
 // (unit, set of 4 query heads) and one per partial slot for sets of up to 32 workgroups -- then the split-K
-// partials (slot = workgroup + 2 * unit, fewer than kMaxStreamWaves + 2 * units of them).  One more word behind the
+// partials (slot = workgroup + 2 * unit, fewer than kComputeUnits + 2 * units of them in use).  One more word behind the
 // ticket counters counts the units that had to be redone with range-normalised operands (never reset by the
 // kernels; read by minikv_diag_redo_count).
 __host__ __device__ inline size_t ws_units(const minikv_shape &s)
@@ -27,7 +32,7 @@ __host__ __device__ inline size_t ws_units(const minikv_shape &s)
 }
 __host__ __device__ inline size_t ws_counter_bytes(const minikv_shape &s)
 {
-    return ((3 * ws_units(s) + kMaxStreamWaves + 1) * sizeof(int) + 255) / 256 * 256;
+    return ((3 * ws_units(s) + kWorkspaceSlots + 1) * sizeof(int) + 255) / 256 * 256;
 }
 
 // per-unit element counts
@@ -85,7 +90,7 @@ int launch_decode(const minikv_shape &s, const minikv_f16 *q, const minikv_cache
                   minikv_f16 *out, void *workspace, int variant, hipStream_t st, const AppendArgs *ap = nullptr);
 
 // the same with the three parts of the workspace given one by one: per-unit ticket counters (ws_units ints),
-// ticket counters of the partial slots (2 * ws_units + kMaxStreamWaves ints), the redo counter (one int), split-K partials
+// ticket counters of the partial slots (2 * ws_units + kWorkspaceSlots ints), the redo counter (one int), split-K partials
 int launch_decode_parts(const minikv_shape &s, const minikv_f16 *q, const minikv_cache &c, float sm_scale,
                         minikv_f16 *out, int *cnt, int *cnt1, int *redo, float *partials, int variant, hipStream_t st,
                         const AppendArgs &ap = AppendArgs());

@@ -192,7 +192,7 @@ int launch_decode(const minikv_shape &s, const minikv_f16 *q, const minikv_cache
                   minikv_f16 *out, void *workspace, int variant, hipStream_t st, const AppendArgs *ap)
 {
     int *cnt = reinterpret_cast<int *>(workspace);
-    return launch_decode_parts(s, q, c, sm_scale, out, cnt, cnt + ws_units(s), cnt + 3 * ws_units(s) + kMaxStreamWaves,
+    return launch_decode_parts(s, q, c, sm_scale, out, cnt, cnt + ws_units(s), cnt + 3 * ws_units(s) + kWorkspaceSlots,
                                reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + ws_counter_bytes(s)),
                                variant, st, ap ? *ap : AppendArgs());
 }

@@ -13,9 +13,9 @@ constexpr size_t kStaticUnits = 2048;
 // ticket counters of the largest case first (they are zero between calls: the kernel returns every counter it
 // used to zero), then the split-K partial slots (no initial state).
 constexpr size_t kStaticCnt = kStaticUnits;                                   // per-unit counters
-constexpr size_t kStaticCnt1 = 2 * kStaticUnits + kMaxStreamWaves;            // counters of the partial slots
+constexpr size_t kStaticCnt1 = 2 * kStaticUnits + kWorkspaceSlots;            // counters of the partial slots
 constexpr size_t kStaticCounterBytes = ((kStaticCnt + kStaticCnt1 + 1) * sizeof(int) + 255) / 256 * 256;   // + the redo counter
-constexpr size_t kStaticPartialBytes = ((size_t)kMaxStreamWaves + 2 * kStaticUnits) * 4 * kPartialStride * sizeof(float);
+constexpr size_t kStaticPartialBytes = ((size_t)kWorkspaceSlots + 2 * kStaticUnits) * 4 * kPartialStride * sizeof(float);
 constexpr size_t kStaticBytes = kStaticCounterBytes + kStaticPartialBytes;    // about 17.3 MB per GPU
 
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];

@@ -1159,8 +1159,6 @@ static int launch_form(const DecArgs &a, long groups, hipStream_t st)
     return hipGetLastError() == hipSuccess ? MINIKV_OK : MINIKV_ELAUNCH;
 }
 
-constexpr long kComputeUnits = 256;
-
 // Whether a workgroup per unit serves the call, from the capacities (the lengths are on the device).  It needs a compute
 // unit per unit, and few enough items that the eight waves of a unit (four at G = 16) are done before the work line, which
 // spreads the items over the whole device and balances ragged lengths, has paid for its round trips.  More items where the line

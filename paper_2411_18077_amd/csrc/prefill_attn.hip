@@ -640,7 +640,6 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
     // In the second pass eight waves per workgroup lose (4.36 -> 4.62 ms): they wait for each other at every tile.
     const int64_t heads = (int64_t)B * Hq;
     auto blocks = [&](int queries) { return heads * ((L + queries - 1) / queries); };
-    constexpr int64_t kComputeUnits = 256;
     if (A_cumul && L <= 128) {                         // one row block a head: always faster in one launch (see SCORES)
         a.nblk = 1;
         hipLaunchKernelGGL((prefill_fwd_kernel<4, 1, 2, true>), dim3((unsigned)heads), dim3(256), fwd_lds_bytes(1, 2, 128), st, a);

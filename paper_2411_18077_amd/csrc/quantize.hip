@@ -407,7 +407,6 @@ static int launch_quantize_g(const QuantArgs &a, hipStream_t st)
     // blocks (1024 x 144 23.4 -> 25.8, x 256 34.9 -> 34.4) and few rounds to go (2048 x 192 47.9 -> 49.8, 4096 x 256 114 -> 117).
     // Up to 32 tokens: two units share a block (16-token groups, 1024 units x 32 rows 10.4 -> 10.2 us, 2048 15.9 -> 13.0, 4096
     // 24.9 -> 19.8; 256 units the same: there the waves' own instructions count, and half of every wave would idle).
-    constexpr int kComputeUnits = 256;
     const bool even_rounds = units >= kComputeUnits * 3 / 2 && units <= (a.max_tok > 160 ? 4 : 2) * kComputeUnits;
     if (nblk <= 2 || (nblk <= 4 && (units <= kComputeUnits || even_rounds))) {
         if (nblk > 2) {

@@ -439,7 +439,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
 // [units][2048], four spare words per chunk.
 constexpr int kCh = 4096;              // tokens per chunk
 constexpr int kChThreads = 1024;       // 16 waves, four tokens each thread
-constexpr long kComputeUnits = 256;
 constexpr int kChMaxChunks = 1024;     // most chunks of one unit
 constexpr int kChList = 12288;         // keys of the cut's bin that sel_pick_kernel holds in LDS (more are read again in every pass)
 

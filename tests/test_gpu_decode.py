@@ -11,9 +11,9 @@ TOL = 2e-3
 
 import os
 
-# 1 = the plain scalar-loop kernel, 3 = the product kernel; 31 / 32 = the product kernel with its work cut by
-# measured / by unit item weights whatever the shape (by itself it picks by the number of items)
-VARIANTS = [pytest.param(int(v), id={31: "3-measured-weights", 32: "3-unit-weights"}.get(int(v), v))
+# 1 = the plain scalar-loop kernel, 3 = the product kernel; 31 / 32 = the product kernel on its work line whatever the shape
+# (by itself it gives calls of few items a workgroup per unit), with its own item weights / with equal ones
+VARIANTS = [pytest.param(int(v), id={31: "3-work-line", 32: "3-work-line-equal-weights"}.get(int(v), v))
             for v in os.environ.get("MINIKV_TEST_VARIANTS", "1,3,31,32").split(",")]
 
 

@@ -19,7 +19,7 @@ def g():
     return gpu_common
 
 
-@pytest.fixture(params=[0, 1, 2], ids=["by-shape", "measured-weights", "unit-weights"])
+@pytest.fixture(params=[0, 1, 2], ids=["by-shape", "work-line", "work-line-equal-weights"])
 def weights(request):
     """The work cut as the library chooses (a workgroup per unit at most of these sizes), then along the work line with
     either weights, as larger calls have it."""
