@@ -506,8 +506,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
             const int R = it.R;
             _Float16 *pr = lds;                            // [kNH][kPrH] halfs: weights of the item's tokens
             _Float16 *rows = lds + kPrHalfs;               // [64][kKRowH] halfs: key rows, then value rows
-            const uint16_t *Rk = a.Rk + (size_t)u * a.Rcap * kD;
-            const uint16_t *Rv = a.Rv + (size_t)u * a.Rcap * kD;
+            const uint16_t *Rk = a.Rk + (size_t)u * a.Rcap * kD, *Rv = a.Rv + (size_t)u * a.Rcap * kD;
             int lane_r = lane;                             // (opaque copy: keeps the address terms below out of
             asm volatile("" : "+v"(lane_r));               //  the registers that live across the pass loop)
             const int rsub = lane_r >> 4, piece = lane_r & 15;  // row within a group of 4, 16-byte piece of the row
@@ -519,6 +518,9 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
             // this launch)
             const int r_new = it.rn;                       // (a full or invalid buffer takes no token)
             const uint16_t *kn = APPEND ? a.k_new + (size_t)u * kD : nullptr, *vn = APPEND ? a.v_new + (size_t)u * kD : nullptr;
+            // (an empty buffer: its row 0, which stands in for the rows past the end, may hold anything, NaN included, and is being
+            // written by the wave that files the new token; the new token's row stands in for them)
+            if (APPEND && r_new == 0) Rk = kn, Rv = vn;
             // (the rows are loaded as in the plain call; the item that holds the new row then loads it once more, from the
             // caller's array.  UNIT: 16 bytes a lane, put over the row the buffer gave once the rows are in local memory, 12 to 45
             // registers less.  The work line, whose tiles are in flight meanwhile, has none for it: into the registers of the

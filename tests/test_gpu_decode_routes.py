@@ -82,3 +82,33 @@ def test_either_side_of_a_workgroup_per_unit(g, G, rep, units, items, behind):
     assert attend(g, w, inp, s, cache, want) == bool(behind)
     cache.r_len.clamp_(max=127)                            # (there is room for the token)
     step(g, w, inp, s, cache)
+
+
+@pytest.mark.parametrize("line", [0, 1])
+@pytest.mark.parametrize("G,Tcap", [(16, 1024), (32, 1152), (64, 1152), (128, 1152)])
+@pytest.mark.parametrize("Hq,Hkv,B", [(2, 2, 32), (8, 2, 33), (16, 2, 17)])
+def test_anything_behind_the_lengths(g, G, Tcap, Hq, Hkv, B, line):
+    """What the cache holds past the lengths -- infinities and NaN in the scales, the zero-points and the residual rows, those of an
+    empty residual included -- reaches no output of either form, alone and as a fused step."""
+    from paper_2411_18077_amd import api
+    w = W.Workload(name="t", B=B, Hq=Hq, Hkv=Hkv, L=Tcap - 128, keep=None, keep_range=(0.02, 1.0), G=G, Rcap=256, seed=2200 + G,
+                   n_outlier=3, outlier_scale=8.0)
+    r_len = np.arange(w.units) * 53 % 256 * (np.arange(w.units) % 4 != 2)
+    lengths = np.full(w.units, w.L)
+    lengths[2::5] = 0
+    inp, s, cache, want = cache_and_oracle(g, w, Tcap, r_len, lengths)
+    n, r = inp.n_tok.tolist(), r_len.tolist()
+    for name, value in (("Ks", float("nan")), ("Kz", float("nan")), ("Vs", float("inf")), ("Vz", float("nan"))):
+        rows = cache.t[name].view(w.units, -1)
+        per = rows.shape[1] // Tcap if name[0] == "V" else 0
+        for u in range(w.units):
+            rows[u, (n[u] * per if per else n[u] // G * w.D):] = value
+    for rows in (cache.Rk.view(w.units, w.Rcap, w.D), cache.Rv.view(w.units, w.Rcap, w.D)):
+        for u in range(w.units):
+            rows[u, r[u]:] = float("nan")
+    api.minikv_diag_decode_weights(line)
+    try:
+        assert attend(g, w, inp, s, cache, want) == bool(line)
+        step(g, w, inp, s, cache)
+    finally:
+        api.minikv_diag_decode_weights(0)
