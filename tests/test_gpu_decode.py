@@ -158,7 +158,7 @@ def one_unit(B, Hkv):
 @pytest.mark.parametrize("variant", [3, 31, 32])
 @pytest.mark.parametrize("G,Hq,Hkv,B,L,Tcap", [
     (32, 4, 1, 1, 100000, None),        # one unit over so many workgroups that they merge in two levels
-    (16, 2, 1, 1, 40000, None),         # over one to two dozen: one level, in two rounds
+    (16, 2, 1, 1, 40000, None),         # over sixteen: one level, one round trip
     (64, 6, 3, 3, 3000, None),          # a few workgroups a unit, ranges that begin and end inside units
     (32, 1, 1, 700, 96, None),          # several whole units a wave
     (128, 16, 16, 24, 900, None),       # about one unit a workgroup, the units' ends anywhere in it
