@@ -58,8 +58,11 @@ namespace minikv {
 // memory in two levels of up to sixteen, cost 4 to 8 us of round trips, and a range had to hold a whole residual item (3.5
 // passes), so that 700 items ran on 128 waves one after the other.  With a partial per workgroup a unit has at most sixteen or
 // so, one level merges them, and a range can be shorter than an item (only a workgroup's range must hold one).  Fused steps, us:
-// 8 heads x 7168 tokens 18.9 -> 12.2 (G = 64), 32 x 5120 20.2 -> 13.0, 32/8 heads x 16 x 13088 39.1 -> 36.4; attention 1024 units x
-// 4896 96.5 -> 93.1, ragged 128k 43.1 -> 41.0; 1.15 times in the geometric mean over 233 shapes from 8 to 1024 units.
+// 8 heads x 7168 tokens 18.9 -> 12.2 (G = 64), 32 x 5120 20.2 -> 13.0, 32/8 heads x 16 x 13088 39.4 -> 37.2; attention 1024 units x
+// 4896 96.7 -> 93.1, ragged 128k 42.5 -> 40.7 (41.0 -> 40.3 on another box, inside its noise); 1.15 times in the geometric mean
+// over 233 shapes from 8 to 1024 units.  Behind (0.93-0.97) where a call does not wait for the chain: 512 units and more of at most
+// four passes each and no residual token, or of one pass and the new token only (1024 units x 512, one head, G = 32 18.4 -> 19.9);
+// with residual tokens the same units gain 1.05 to 1.5 times.
 struct UnitItems { int nq, nr, T, R, rn; };   // rn: residual row the fused step appends (-1: none)
 constexpr int kSkew16 = 10;             // share (in sixteenths) of a wave pair's range given to its first wave
 
@@ -174,7 +177,8 @@ __global__ __launch_bounds__(64 * kGroupWaves<G>, G == 16 ? 1 : 2) void decode_s
     typedef VData<NCG> VD;
     // The tiles that a wave's last pass requests are used by nobody.  Its own ones again are still cached, but not with the
     // streaming hint; they then came from memory a second time (190.1 MB read per call on the 16 x 32768 workload, 177.6
-    // without the hint).  So every wave of the work line requests the same tile there, the first unit's first: 176.1 MB, 1024
+    // without the hint).  So every wave of the work line requests the same tile there, the first unit's first: 176.1 MB (171.6 since a
+    // workgroup has one partial), 1024
     // units x 4896 98.2 -> 96.5 us, 512 x 4864 53.8 -> 51.9, 128 x 13088, two heads, 35.6 -> 34.7, four 36.6 -> 36.1.
     constexpr bool kOneTile = !UNIT || (STREAM && !(FUSED && !PAIRED && G == 32));   // (that instance has no register left)
 
@@ -1219,6 +1223,11 @@ static int launch_stream(DecArgs a, hipStream_t st)
     // 12.5 with 4 : 2; 512 units x 12 items 22.5 against 23.3).  4 : 2 where the ranges would be too few for the compute units (64
     // units x 8 items 13.8 -> 11.8; 8 units x 42, G = 16, 17.9 -> 15.1), and where a wave has one or two items, so that one
     // with a residual item should hold nothing else (2816 items 18.8 -> 16.9, 3072 items 18.7 -> 17.2, but 5376 19.7 -> 20.2).
+    // Time with 8 : 2 over that with 4 : 2, 880 calls of 32 to 768 units with residual tokens, mean (least .. most):
+    //   items      1500 .. 2048       2049 .. 3584       3585 .. 4600       4601 .. 7000
+    //   G = 16     1.02 (0.89..1.15)  1.01 (0.90..1.15)  0.98 (0.93..1.05)  1.00 (0.87..1.11)
+    //   G > 16     1.04 (0.92..1.16)  1.04 (0.94..1.16)  1.02 (0.94..1.12)  1.02 (0.91..1.17)
+    // so the window is where 4 : 2 gains most for what it can lose; outside it single calls gain as much and lose more.
     const long units = (long)a.units * a.hsets;
     const long weight = units * (2 * ((a.Tcap + kPass - 1) / kPass) + 8 * ((a.Rcap + 63) / 64));
     const bool light = weight < 8 * kComputeUnits || (cap_items > 2048 && cap_items <= 3584);

@@ -667,7 +667,10 @@ int launch_prefill(int32_t B, int32_t Hq, int32_t Hkv, int64_t L, const minikv_f
         // one workgroup per compute unit, or two of few heads, where the second ones walk a short part of the prompt.
         // Whole call, 128 keys -> 64 keys, us: 8 heads x 160 14.9 -> 14.2, x 777 25.4 -> 23.3, x 2048 45.1 -> 39.9, x 4096 (512
         // workgroups) 89.6 -> 84.0; 16 x 2048 51.6 -> 49.4, 32 x 512 20.3 -> 19.0; beyond, the second read of Q by twice the
-        // workgroups loses: 32 x 777 (416) the same, 64 x 384 (384) 20.9 -> 21.7, 16 x 3000 83.8 -> 86.7, 32 x 1500 53.5 -> 57.5.  (Eight waves on 256 queries lose to four everywhere: 8 x 384 16.9 -> 19.5, 8 x 2048 39.9 -> 40.7.)
+        // workgroups loses: 32 x 777 (416) the same, 64 x 384 (384) 20.9 -> 21.7, 16 x 3000 83.8 -> 86.7, 32 x 1500 53.5 -> 57.5.
+        // At the lines: 17 x 1868 (510 workgroups) 54.2 -> 54.2, 18 x 1778 49.9 -> 49.3, 19 x 1605 49.7 -> 50.8, 20 x 1575 46.1 -> 45.2
+        // (each side varies by 2-4 % there), 20 x 1369 (440) 39.7 -> 37.7; 21 x 747 (252) 28.5 -> 27.1, 32 x 493 (256) 21.5 -> 19.9, 64 x 209
+        // 16.9 -> 15.9.  (Eight waves on 256 queries lose to four everywhere: 8 x 384 16.9 -> 19.5, 8 x 2048 39.9 -> 40.7.)
         if (blocks(64) <= (heads <= 20 ? 2 : 1) * kComputeUnits) {
             a.nblk = (int)((L + 63) / 64);
             hipLaunchKernelGGL((prefill_colsum_kernel<1>), dim3((unsigned)(heads * a.nblk)), dim3(64 * kColWaves), 0, st, a);
