@@ -1176,6 +1176,10 @@ static int launch_form(const DecArgs &a, long groups, hipStream_t st)
 //               32   14 items / 1.11 (1.07) -- / 1.11 (1.04)                    18 items 1.12 / 0.98 -- 1.15 / 0.98 (0.90)
 //               64   18 items 1.21 (1.12) / 1.09 (1.05) -- 1.22 (1.14) / 1.09 (1.00)
 //               128  20 items 1.17 (1.10) / 1.12 (1.03) -- 1.28 (1.19) / 1.20 (1.10)
+//   49 .. 95    16   12 items 1.26 (1.22) / 1.32 (1.24) -- 1.46 (1.24) / 1.36 (1.18)
+//               32   14 items / 1.27 (1.21) -- / 1.27 (1.20)                    18 items 1.16 / 1.08 (1.07) -- 1.20 / 1.08 (1.03)
+//               64   18 items 1.25 (1.22) / 1.18 (1.16) -- 1.30 (1.21) / 1.17 (1.10)
+//               128  20 items 1.26 (1.21) / 1.22 (1.19) -- 1.34 (1.26) / 1.25 (1.18)
 //   96 .. 128   16   20 items 1.15 (1.10) / 1.06 (0.99) -- 1.14 (0.97) / 1.04 (0.89)
 //               32   22 items 1.26 (1.19) / 1.11 (1.04) -- 1.11 (1.05) / 0.98 (0.92)  26 items 1.18 / 1.06 -- 1.09 / 0.96 (0.86)
 //               64   26 items 1.21 (1.20) / 1.10 (1.04) -- 1.10 (0.99) / 1.00 (0.88)
